@@ -1,143 +1,187 @@
-// Block-sparse attention, generic path: any head_dim <= 256, any tile shape, f32 or bf16
-// storage, plain FMA arithmetic in float.  Used where the matrix-core kernel's shape
-// constraints do not hold (e.g. the 16-token / d = 32 / f32 toy configuration).
+// Block-sparse attention, general path: any head_dim <= 256, any block shape, f32 or bf16 storage, float products on the
+// matrix cores (lcsa_fp32_mma.h).  Used where the shape constraints of the bf16 / d = 128 kernel do not hold.
 //
-// One workgroup per (head, query block), four wavefronts, each owning one query token at a
-// time.  Keys of a selected block are taken 64 at a time: lane-per-key dot products against
-// the query held in LDS, wavefront max/sum for the online softmax (eq. 1), probabilities
-// through LDS, then lane-per-channel accumulation of P*V with coalesced V reads.
-#include "lcsa_kernels.h"
+// One workgroup per (head, query block), four wavefronts.  A wavefront owns 16 QS query rows (columns of S^T = K Q^T, so
+// that a query's statistics live in four lanes and S^T is the operand of O^T += V^T P^T as it stands) and walks the
+// 16-key groups of the selected blocks, GI groups at a time.  Blocks with fewer query rows than four wavefronts take
+// split the key groups instead: each wavefront keeps a softmax of its own over every (4 / ways)-th stretch of GI groups,
+// and the partial results meet in LDS at the end.  No LDS and no barrier otherwise.
+//
+// What bounds it: at 8 heads, d = 64, bf16, 32-token blocks, k = 16 on a 24 x 44 grid 33 us, of which the float P V products
+// are 9 us of matrix time and the rest is load latency (two wavefronts per SIMD).  A wavefront per query token with
+// lane-per-key dot products in vector FMA took 1429 us there (every query re-read all its keys) and 49 us where this
+// takes 7 us on the smallest case (1 head, d = 32, f32, 16-token blocks, k = 4).
+#include "lcsa_fp32_mma.h"
 
 namespace lcsa {
 namespace {
 
-constexpr int kWaves = 4;
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
+using namespace fp32mma;
 
-template <typename T> struct Elt;
-template <> struct Elt<float> {
-    static constexpr int VEC = 4;
-    static __device__ float load(const float *p) { return *p; }
-    static __device__ void store(float *p, float x) { *p = x; }
-    static __device__ void load_vec(const float *p, float *f) {
-        const float4 u = *(const float4 *)p;
-        f[0] = u.x; f[1] = u.y; f[2] = u.z; f[3] = u.w;
-    }
-};
-template <> struct Elt<__bf16> {
-    static constexpr int VEC = 8;
-    static __device__ float load(const __bf16 *p) { return (float)*p; }
-    static __device__ void store(__bf16 *p, float x) { *p = (__bf16)x; }
-    static __device__ void load_vec(const __bf16 *p, float *f) {
-        const uint4 u = *(const uint4 *)p;
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            f[2 * i] = __uint_as_float(w[i] << 16);
-            f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-};
+constexpr int kThreads = 256;
 
-__device__ inline float wave_max(float x) {
-    for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-    return x;
-}
-__device__ inline float wave_sum(float x) {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
-template <typename T>
-__global__ __launch_bounds__(64 * kWaves) void attn_generic_kernel(
+template <typename T, int NT, int QS>
+__global__ __launch_bounds__(kThreads) void attn_generic_kernel(
     KGeom g, KCache c, const T *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
-    T *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse, float scale_log2) {
-    __shared__ float qs[kWaves][256];
-    __shared__ float ps[kWaves][64];
-    constexpr int VEC = Elt<T>::VEC;
-    constexpr int DPL = 4;                                  // channels per lane: e = lane + 64*jj
-    const int qb = blockIdx.x, head = blockIdx.y;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    T *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse, float scale_log2, int per_xcd) {
+    constexpr int GI = NT <= 4 ? 4 : NT <= 8 ? 2 : 1;
+    __shared__ float part_ml[4][QS][2][16];                  // [wavefront][piece][max, sum][query]
+    __shared__ f32x4 part_o[4][QS][NT][64];
+    // XCD-aware order: an XCD (workgroup id mod 8) gets a contiguous run of (head, query block) items
     const int n_qb = g.q_groups * g.nb;
+    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (item >= n_qb * g.heads) return;
+    const int head = item / n_qb, qb = item - head * n_qb;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = lane & 15, g4 = lane >> 4;
     const int fq = qb / g.nb, tile = qb - fq * g.nb, by = tile / g.tx, bx = tile - by * g.tx;
-    const int qvh = min(g.th, g.H - by * g.th), qvw = min(g.tw, g.W - bx * g.tw);
+    const BlockTokens qt(g, min(g.th, g.H - by * g.th), min(g.tw, g.W - bx * g.tw));
+    const int ways = row_ways(qt.n_valid, 16 * QS), splits = 4 / ways;
+    const int qw = wave / splits, ks = wave - qw * splits;
+
     const int64_t row = (int64_t)head * n_qb + qb;
     const int cnt = min(max(sel_cnt[row], 0), g.topk);       // a row holds at most topk ids
     const int32_t *sel = sel_idx + row * g.topk;
-    const T *kc = (const T *)c.k, *vc = (const T *)c.v;
     const int start = ring_start(c, g);
+    const int per_block = (g.bt + 15) >> 4, total = cnt * per_block;      // 16-key groups
+    const T *k_head = (const T *)c.k + (int64_t)head * g.cap * g.nb * g.bt * g.d;
+    const T *v_head = (const T *)c.v + (int64_t)head * g.cap * g.nb * g.bt * g.d;
 
-    // every wavefront walks the same loop structure so that workgroup barriers line up;
-    // wavefronts whose token is padding compute on a clamped token and store nothing
-    for (int t0 = 0; t0 < g.bt; t0 += kWaves) {
-        const int tq = t0 + wave;
-        int qft, r, cc;
-        const bool q_valid = block_token(g, tq, qvh, qvw, qft, r, cc);
-        const int64_t token = q_valid ? raster_token(g, fq, qft, by * g.th + r, bx * g.tw + cc)
-                                      : raster_token(g, fq, 0, by * g.th, bx * g.tw);
-        __syncthreads();                                     // previous token's readers of qs are done
-        for (int e = lane; e < g.d; e += 64) qs[wave][e] = Elt<T>::load(q + token * q_st + (int64_t)head * q_sh + e);
-        __syncthreads();
-        float m = -__builtin_inff(), l = 0.f, acc[DPL] = {0.f, 0.f, 0.f, 0.f};
-        for (int b = 0; b < cnt; ++b) {
-            const int kb = min(max(sel[b], 0), c.valid * g.nb - 1);   // ids outside the cache must not become wild addresses
-            const int f = kb / g.nb, kt = kb - f * g.nb, kby = kt / g.tx, kbx = kt - kby * g.tx;
-            const int vh = min(g.th, g.H - kby * g.th), vw = min(g.tw, g.W - kbx * g.tw);
-            const int slot = cache_slot(c, g, start, head, f);
-            const int64_t tbase = (((int64_t)head * g.cap + slot) * g.nb + kt) * g.bt * g.d;
-            for (int base = 0; base < g.bt; base += 64) {
-                const int key = base + lane;
-                int kft, kr, kcc;
-                const bool k_valid = block_token(g, key, vh, vw, kft, kr, kcc);
-                float s = -__builtin_inff();
-                if (k_valid) {
-                    const T *kp = kc + tbase + (int64_t)key * g.d;
-                    float dot = 0.f;
-                    for (int e = 0; e < g.d; e += VEC) {
-                        float kv[VEC];
-                        Elt<T>::load_vec(kp + e, kv);
+    // more than one round only where four wavefronts do not cover the block, and then splits == 1
+    for (int q0 = qw * 16 * QS; q0 < qt.n_valid || splits > 1; q0 += ways * 16 * QS) {
+        RowFrag<T, NT> qf[QS];
+        int64_t token[QS];
+        bool q_valid[QS];
 #pragma unroll
-                        for (int i = 0; i < VEC; ++i) dot = fmaf(qs[wave][e + i], kv[i], dot);
+        for (int s = 0; s < QS; ++s) {
+            int ft, r, cc;
+            q_valid[s] = qt.at(q0 + 16 * s + m, ft, r, cc);
+            if (!q_valid[s]) ft = r = cc = 0;                // padding rows compute on the block's first token and store nothing
+            token[s] = raster_token(g, fq, ft, by * g.th + r, bx * g.tw + cc);
+            qf[s].load(q + token[s] * q_st + (int64_t)head * q_sh, g.d, g4);
+        }
+        f32x4 oacc[QS][NT];
+        float mx[QS], l[QS];
+#pragma unroll
+        for (int s = 0; s < QS; ++s) {
+            mx[s] = -__builtin_inff();
+            l[s] = 0.f;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) oacc[s][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int i0 = ks * GI; i0 < total; i0 += splits * GI) {
+            RowFrag<T, NT> kf[GI];
+            ColFrag<T, NT> vf[GI];
+            int left[GI];                                    // valid keys of the group, <= 0: none
+#pragma unroll
+            for (int i = 0; i < GI; ++i) {
+                const int f = min(i0 + i, total - 1), b = f / per_block, first = (f - b * per_block) * 16;
+                const int kb = min(max(sel[b], 0), c.valid * g.nb - 1);   // ids outside the cache must not become wild addresses
+                const int grp = kb / g.nb, kt = kb - grp * g.nb, kby = kt / g.tx, kbx = kt - kby * g.tx;
+                const int n = g.tt * min(g.th, g.H - kby * g.th) * min(g.tw, g.W - kbx * g.tw);
+                left[i] = i0 + i < total ? n - first : 0;
+                const int64_t base = ((int64_t)cache_slot(c, g, start, head, grp) * g.nb + kt) * g.bt;
+                // rows beyond the block's bt (bt not a multiple of 16) repeat its last one; they are masked
+                kf[i].load(k_head + (base + min(first + m, g.bt - 1)) * g.d, g.d, g4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) vf[i].load(r, v_head + (base + min(first + 4 * g4 + r, g.bt - 1)) * g.d, g.d, m);
+            }
+#pragma unroll
+            for (int s = 0; s < QS; ++s) {
+                f32x4 sc[GI];
+                float mnew = mx[s];
+#pragma unroll
+                for (int i = 0; i < GI; ++i) {
+                    sc[i] = RowFrag<T, NT>::mma(kf[i], qf[s], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        sc[i][r] = 4 * g4 + r < left[i] ? sc[i][r] * scale_log2 : -__builtin_inff();
+                        mnew = fmaxf(mnew, sc[i][r]);
                     }
-                    s = dot * scale_log2;
                 }
-                const float cmax = wave_max(s);
-                // a 64-key group made only of padding is skipped by all wavefronts alike
-                if (cmax == -__builtin_inff()) continue;
-                const float m_new = fmaxf(m, cmax);
-                const float p = k_valid ? __builtin_amdgcn_exp2f(s - m_new) : 0.f;
-                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-                l = l * alpha + wave_sum(p);
-                m = m_new;
-                __syncthreads();                             // previous group's readers of ps are done
-                ps[wave][lane] = p;
-                __syncthreads();
-                const int nk = min(64, g.bt - base);
+                mnew = column_max(mnew);
+                const float ref = mnew == -__builtin_inff() ? 0.f : mnew;     // nothing but padding so far
+                const float alpha = __builtin_amdgcn_exp2f(mx[s] - ref);
+                mx[s] = mnew;
+                l[s] *= alpha;
 #pragma unroll
-                for (int jj = 0; jj < DPL; ++jj) {
-                    const int e = lane + 64 * jj;
-                    if (e < g.d) {
-                        float a = acc[jj] * alpha;
-                        const T *vp = vc + tbase + (int64_t)base * g.d + e;
-                        for (int j = 0; j < nk; ++j) a = fmaf(ps[wave][j], Elt<T>::load(vp + (int64_t)j * g.d), a);
-                        acc[jj] = a;
+                for (int t = 0; t < NT; ++t) oacc[s][t] *= alpha;
+#pragma unroll
+                for (int i = 0; i < GI; ++i) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        sc[i][r] = __builtin_amdgcn_exp2f(sc[i][r] - ref);
+                        l[s] += sc[i][r];
                     }
+                    ColFrag<T, NT>::mma(vf[i], sc[i], oacc[s]);
                 }
             }
         }
-        if (q_valid) {
-            const float inv = l > 0.f ? 1.f / l : 0.f;
 #pragma unroll
-            for (int jj = 0; jj < DPL; ++jj) {
-                const int e = lane + 64 * jj;
-                if (e < g.d) Elt<T>::store(o + token * o_st + (int64_t)head * o_sh + e, acc[jj] * inv);
+        for (int s = 0; s < QS; ++s) l[s] = column_sum(l[s]);
+
+        if (splits > 1) {                                    // uniform over the workgroup
+#pragma unroll
+            for (int s = 0; s < QS; ++s) {
+                if (g4 == 0) { part_ml[wave][s][0][m] = mx[s]; part_ml[wave][s][1][m] = l[s]; }
+#pragma unroll
+                for (int t = 0; t < NT; ++t) part_o[wave][s][t][lane] = oacc[s][t];
             }
-            if (lse && lane == 0)
-                lse[token * g.heads + head] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -__builtin_inff();
+            __syncthreads();
+            if (ks != 0) return;
+#pragma unroll
+            for (int s = 0; s < QS; ++s) {
+                float all = mx[s];
+                for (int w = 1; w < splits; ++w) all = fmaxf(all, part_ml[wave + w][s][0][m]);
+                const float ref = all == -__builtin_inff() ? 0.f : all;
+                const float own = __builtin_amdgcn_exp2f(mx[s] - ref);
+                l[s] *= own;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) oacc[s][t] *= own;
+                for (int w = 1; w < splits; ++w) {
+                    const float theirs = __builtin_amdgcn_exp2f(part_ml[wave + w][s][0][m] - ref);
+                    l[s] = fmaf(part_ml[wave + w][s][1][m], theirs, l[s]);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) oacc[s][t] += part_o[wave + w][s][t][lane] * theirs;
+                }
+                mx[s] = all;
+            }
         }
+#pragma unroll
+        for (int s = 0; s < QS; ++s) {
+            if (!q_valid[s]) continue;
+            const float inv = l[s] > 0.f ? 1.f / l[s] : 0.f;
+#pragma unroll
+            for (int p = 0; p < NT / 2; ++p) {
+                float x[8];
+                channels_of(oacc[s], p, x);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] *= inv;
+                store8(o + token[s] * o_st + (int64_t)head * o_sh, 32 * p + 8 * g4, g.d, x);
+            }
+            if (lse && g4 == 0) lse[token[s] * g.heads + head] = l[s] > 0.f ? (mx[s] + __builtin_amdgcn_logf(l[s])) * kLn2 : -__builtin_inff();
+        }
+        if (splits > 1) return;
     }
+}
+
+template <typename T>
+void launch(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh, const int32_t *sel_idx, const int32_t *sel_cnt,
+            void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
+    const int per_xcd = (g.q_groups * g.nb * g.heads + 7) / 8;
+#define LCSA_CALL(NT)                                                                                                       \
+    {                                                                                                                       \
+        constexpr int QS = NT <= 8 ? 2 : 1;      /* 32 query rows per wavefront share each operand fragment */             \
+        if (QS == 2 && g.bt > 16)                                                                                           \
+            attn_generic_kernel<T, NT, QS><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(                                     \
+                g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);        \
+        else                                                                                                                \
+            attn_generic_kernel<T, NT, 1><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(                                      \
+                g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);        \
+    }
+    LCSA_FOR_HEAD_DIM(g.d, LCSA_CALL)
+#undef LCSA_CALL
 }
 
 } // namespace
@@ -145,14 +189,8 @@ __global__ __launch_bounds__(64 * kWaves) void attn_generic_kernel(
 hipError_t launch_attn_generic(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh,
                                const int32_t *sel_idx, const int32_t *sel_cnt,
                                void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
-    dim3 grid(g.q_groups * g.nb, g.heads);
-    const float scale_log2 = scale * kLog2e;
-    if (g.bf16)
-        attn_generic_kernel<__bf16><<<grid, 64 * kWaves, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,
-                                                                      (__bf16 *)o, o_st, o_sh, lse, scale_log2);
-    else
-        attn_generic_kernel<float><<<grid, 64 * kWaves, 0, stream>>>(g, c, (const float *)q, q_st, q_sh, sel_idx, sel_cnt,
-                                                                     (float *)o, o_st, o_sh, lse, scale_log2);
+    if (g.bf16) launch<__bf16>(g, c, q, q_st, q_sh, sel_idx, sel_cnt, o, o_st, o_sh, lse, scale, stream);
+    else launch<float>(g, c, q, q_st, q_sh, sel_idx, sel_cnt, o, o_st, o_sh, lse, scale, stream);
     return hipGetLastError();
 }
 

@@ -1,0 +1,120 @@
+// Building blocks of the general attention kernels (any head_dim <= 256, any block shape, f32 or bf16 storage):
+// 16 x 16 products on the matrix cores with float operands (v_mfma_f32_16x16x4_f32: float products and accumulation;
+// 157 TFLOP/s, 154 of them reached by a large float matrix product).
+//
+// A first-level product C[m][n] = sum_c A[m][c] B[n][c] sums over channels; both operands are rows of d channels
+// ("row fragments").  bf16 rows need no conversion: v_mfma_f32_16x16x32_bf16 forms the same exact products and
+// accumulates them in float.  C has its column n in lane & 15 and its rows 4 g + r, g = lane >> 4, in register r.
+// That is the B-operand layout of v_mfma_f32_16x16x4_f32 with the summed index m = 4 g + r in step r: a second-level
+// product sum_m X[m][ch] C[m][n] takes the accumulator as it is, and its A operand is the channels of rows 4 g + r
+// ("column fragment").  Which channel a matrix row stands for is free: tile t = 2 p + e of a column fragment holds
+// the channels 32 p + 2 m + e, so that a lane loads two neighbouring channels of a row at a time and owns, of the
+// result, the eight consecutive channels 32 p + 8 g .. + 7 (register r of tiles 2 p, 2 p + 1: channels + 2 r, + 2 r + 1).
+//
+// Fragments are loaded from global memory straight into registers: a float operand serves 32 cycles of matrix work per
+// 256 bytes, which the caches feed without a detour through LDS (and without barriers between wavefronts).
+#pragma once
+#include "lcsa_kernels.h"
+
+namespace lcsa {
+namespace fp32mma {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+
+// A row of up to 16 NT channels, spread over the four lanes (m, g = 0..3); channels from d on are zero.
+template <typename T, int NT> struct RowFrag;
+template <int NT> struct RowFrag<float, NT> {
+    f32x4 v[NT];                                             // chunk j: channels 16 j + 4 g .. + 3
+    __device__ void load(const float *row, int d, int g) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int c = 16 * j + 4 * g;
+            v[j] = c < d ? *(const f32x4 *)(row + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    __device__ static f32x4 mma(const RowFrag &a, const RowFrag &b, f32x4 acc) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j][e], b.v[j][e], acc, 0, 0, 0);
+        return acc;
+    }
+};
+template <int NT> struct RowFrag<__bf16, NT> {
+    bf16x8 v[NT / 2];                                        // chunk j: channels 32 j + 8 g .. + 7
+    __device__ void load(const __bf16 *row, int d, int g) {
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j) {
+            const int c = 32 * j + 8 * g;
+            const uint4 u = c < d ? *(const uint4 *)(row + c) : make_uint4(0, 0, 0, 0);
+            v[j] = __builtin_bit_cast(bf16x8, u);
+        }
+    }
+    __device__ static f32x4 mma(const RowFrag &a, const RowFrag &b, f32x4 acc) {
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[j], b.v[j], acc, 0, 0, 0);
+        return acc;
+    }
+};
+
+// Channels of four rows: what a lane feeds the second-level products of one 16-row group.
+template <typename T, int NT> struct ColFrag {
+    T v[4][NT / 2][2];                                       // [row 4 g + r][p]: channels 32 p + 2 m, + 1
+    __device__ void load(int r, const T *row, int d, int m) {
+        typedef __attribute__((ext_vector_type(2))) T T2;
+#pragma unroll
+        for (int p = 0; p < NT / 2; ++p) {
+            const int c = 32 * p + 2 * m;
+            const T2 u = c < d ? *(const T2 *)(row + c) : T2{(T)0.f, (T)0.f};
+            v[r][p][0] = u[0];
+            v[r][p][1] = u[1];
+        }
+    }
+    // acc[t] += X^T w: w = this lane's column of the first-level result
+    __device__ static void mma(const ColFrag &x, const f32x4 &w, f32x4 (&acc)[NT]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)x.v[r][t >> 1][t & 1], w[r], acc[t], 0, 0, 0);
+    }
+};
+
+// The lane's eight consecutive channels 32 p + 8 g .. + 7 of a second-level result.
+template <int NT> __device__ inline void channels_of(const f32x4 (&acc)[NT], int p, float (&out)[8]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) { out[2 * r] = acc[2 * p][r]; out[2 * r + 1] = acc[2 * p + 1][r]; }
+}
+// Stores those of them that exist (d is a multiple of 4, of 8 for bf16); row and its stride are 16-byte aligned.
+__device__ inline void store8(float *row, int c, int d, const float (&x)[8]) {
+    if (c < d) *(f32x4 *)(row + c) = f32x4{x[0], x[1], x[2], x[3]};
+    if (c + 4 < d) *(f32x4 *)(row + c + 4) = f32x4{x[4], x[5], x[6], x[7]};
+}
+__device__ inline void store8(__bf16 *row, int c, int d, const float (&x)[8]) {
+    if (c >= d) return;
+    bf16x8 w;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = (__bf16)x[i];
+    *(bf16x8 *)(row + c) = w;
+}
+
+// over the four lanes (m, 0..3) that share a column
+__device__ inline float column_sum(float x) { x += __shfl_xor(x, 16); return x + __shfl_xor(x, 32); }
+__device__ inline float column_max(float x) { x = fmaxf(x, __shfl_xor(x, 16)); return fmaxf(x, __shfl_xor(x, 32)); }
+
+// How the four wavefronts of a workgroup share a block of n rows (n > 0) against a list of row groups: `ways` of them
+// take 16-row pieces (16 * S rows each) of the block, and 4 / ways share each piece's list.
+__device__ inline int row_ways(int n, int rows_per_wave) { return n > 2 * rows_per_wave ? 4 : n > rows_per_wave ? 2 : 1; }
+
+// head_dim -> number of 16-channel tiles the kernels are built for
+#define LCSA_FOR_HEAD_DIM(d, call)                                                                                    \
+    if ((d) <= 32) { call(2) } else if ((d) <= 64) { call(4) } else if ((d) <= 96) { call(6) }                          \
+    else if ((d) <= 128) { call(8) } else { call(16) }
+
+} // namespace fp32mma
+} // namespace lcsa

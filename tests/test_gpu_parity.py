@@ -171,6 +171,29 @@ def test_f32_ragged_window_bites():
     run_primed(w, window_mode=1)
 
 
+@pytest.mark.parametrize("dtype,d,tile_t,tile_h,tile_w", [
+    ("fp32", 4, 1, 3, 5),          # fewer channels than a matrix tile; 15-token blocks (one row short of a 16-row group)
+    ("fp32", 40, 1, 4, 5),         # 20 tokens: a second, mostly empty group; channels that end inside a tile pair
+    ("fp32", 64, 1, 4, 8),         # 32 tokens: one wavefront's two query pieces, keys shared out over four wavefronts
+    ("bf16", 72, 2, 4, 6),         # 48 tokens
+    ("bf16", 96, 1, 9, 8),         # 72 tokens: three pieces, one wavefront without queries
+    ("fp32", 128, 1, 8, 16),       # 128 tokens in fp32
+    ("bf16", 200, 1, 4, 4),
+    ("fp32", 256, 1, 10, 30),      # 300 tokens: more pieces than wavefronts
+])
+def test_general_path_head_dims_and_block_edges(dtype, d, tile_t, tile_h, tile_w):
+    """General kernels where a head size or a block does not fill the 16-row, 16-channel matrix tiles, and on either side
+    of the splits of a block over wavefronts; clipped blocks on both axes; every row."""
+    w = wl.with_overrides(wl.WORKLOADS["tiny"], name=f"general-{dtype}-d{d}", dtype=dtype, heads=2, head_dim=d, grid_h=2 * tile_h + 1,
+                          grid_w=2 * tile_w + 3, tile_h=tile_h, tile_w=tile_w, radius=2 * tile_h, topk=5)
+    p = Pipeline(w, tile_t=tile_t)
+    for _ in range(w.prime_chunks + 1):
+        q, qd = p.feed()
+    tol = dict(max_abs=F32_MAX, mean_abs=F32_MEAN) if dtype == "fp32" else dict(bf16_relative=True)
+    r = p.step(q, qd, check_lse=True, **tol)
+    say(f"{w.name}: max-abs {r.max_abs:.2e}, mean-abs {r.mean_abs:.2e}")
+
+
 def test_uneven_appends_wrap_the_ring():
     """Appends of 1, 2, 3 frames against a capacity of 4: a chunk straddles the eviction point."""
     w = wl.with_overrides(SMALL_MFMA, cache_frames=4, q_frames=1, heads=2)
