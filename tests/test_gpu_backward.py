@@ -119,6 +119,24 @@ def test_backward_generic_bf16_d64():
     run_backward(w)
 
 
+@pytest.mark.parametrize("dtype,d,tile_t,tile_h,tile_w", [
+    ("fp32", 4, 1, 3, 5),          # fewer channels than a matrix tile; 15-token blocks
+    ("fp32", 40, 1, 4, 5),         # 20 tokens: two pieces, two wavefronts each; channels that end inside a tile pair
+    ("bf16", 72, 2, 4, 6),         # 48 tokens: three pieces, one wavefront without rows
+    ("bf16", 128, 1, 9, 8),        # 72 tokens: a second round over the block's rows
+    ("fp32", 200, 1, 4, 4),
+])
+def test_backward_general_head_dims_and_block_edges(dtype, d, tile_t, tile_h, tile_w):
+    run_backward(wl.with_overrides(wl.WORKLOADS["tiny"], name=f"bwd-general-{dtype}-d{d}", dtype=dtype, heads=2, head_dim=d,
+                                   grid_h=2 * tile_h + 1, grid_w=2 * tile_w + 3, tile_h=tile_h, tile_w=tile_w, radius=2 * tile_h,
+                                   topk=4), tile_t=tile_t)
+
+
+def test_backward_more_query_blocks_than_one_list_holds():
+    """2 x 33 x 32 = 2112 query blocks: the key-side kernel makes its list of them in two parts."""
+    run_backward(wl.with_overrides(wl.WORKLOADS["tiny"], name="bwd-many-blocks", head_dim=4, grid_h=132, grid_w=128, topk=2))
+
+
 def test_backward_is_deterministic_and_rejects_bad_arguments():
     w = wl.with_overrides(wl.WORKLOADS["small"], name="bwd-det", heads=2, grid_h=16, grid_w=32, topk=4)
     a = run_backward(w)
