@@ -145,23 +145,24 @@ __device__ inline uint32_t pack_block(const KGeom &g, const KCache &c, int start
 }
 __device__ inline int block_keys(uint32_t blk) { return (int)(blk >> 24) + 1; }
 
-// SINGLE: one work item per workgroup (group 1 only keeps the barriers company).  A lone group is faster than
-// a group that shares its SIMDs, so a launch with no more work items than compute units spreads over twice as
-// many units this way.
-template <bool SINGLE>
+// SPLIT: one work item per workgroup, its selected blocks dealt out to the two groups in turn (group g takes blocks
+// g, g + 2, ...), each group with a softmax of its own; at the end the groups exchange halves of their accumulators
+// through LDS and each finishes 64 of the 128 channels.
+template <bool SPLIT>
 __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     KGeom g, KCache c, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     __bf16 *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse,
     float scale_log2, int total_items, int pairs_per_xcd) {
     __shared__ __attribute__((aligned(16))) unsigned char lds_all[2][2][kTileBytes];   // [group][K, V]
+    __shared__ float2 softmax_all[SPLIT ? 2 : 1][128];                                 // SPLIT: [group][query] reference and sum
     LCSA_STAMP(0)
 
     // Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous run of work
     // items (same head, neighbouring tiles, both query frames) so that K/V tiles shared by
     // neighbouring windows are found in that XCD's L2.
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-    const int total_pairs = SINGLE ? total_items : (total_items + 1) >> 1;
+    const int total_pairs = SPLIT ? total_items : (total_items + 1) >> 1;
     const int pair = xcd * pairs_per_xcd + idx;
     if (pair >= total_pairs) return;
 
@@ -179,8 +180,10 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
         const int tile = rem / g.q_groups, fq = rem - tile * g.q_groups;   // items ordered (head, tile, group)
         qb = fq * g.nb + tile;
     };
-    const int item = SINGLE ? (grp8 == 0 ? pair : total_items) : 2 * pair + grp8;
-    const int other = SINGLE ? (grp8 == 0 ? total_items : pair) : 2 * pair + (grp8 ^ 1);
+    const int item = SPLIT ? pair : 2 * pair + grp8;
+    const int other = SPLIT ? pair : 2 * pair + (grp8 ^ 1);
+    // entry of the row's id list that is this group's block number i
+    auto listed = [&](int i) { return SPLIT ? 2 * i + grp8 : i; };
     const bool active = item < total_items;
     int head = 0, qb = 0, cnt = 0, other_cnt = 0;
     const int start = ring_start(c, g);    // requested together with the counts and ids below
@@ -188,9 +191,9 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     if (active) {
         item_row(item, head, qb);
         cnt = sel_cnt[(int64_t)head * n_qb + qb];
-        if (lane < g.topk) first_ids = sel_idx[((int64_t)head * n_qb + qb) * g.topk + lane];
+        if (listed(lane) < g.topk) first_ids = sel_idx[((int64_t)head * n_qb + qb) * g.topk + listed(lane)];
     }
-    if (other < total_items) { int h2, q2; item_row(other, h2, q2); other_cnt = sel_cnt[(int64_t)h2 * n_qb + q2]; }
+    if (!SPLIT && other < total_items) { int h2, q2; item_row(other, h2, q2); other_cnt = sel_cnt[(int64_t)h2 * n_qb + q2]; }
     const int fq = qb / g.nb, tile = qb - fq * g.nb;
     const int by = tile / g.tx, bx = tile - by * g.tx;
     const int qvh = min(g.th, g.H - by * g.th), qvw = min(g.tw, g.W - bx * g.tw);
@@ -213,6 +216,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
 
     cnt = min(max(__builtin_amdgcn_readfirstlane(cnt), 0), g.topk);            // a row holds at most topk ids
     other_cnt = min(max(__builtin_amdgcn_readfirstlane(other_cnt), 0), g.topk);
+    if (SPLIT) { other_cnt = (cnt + grp8) >> 1; cnt = (cnt + 1 - grp8) >> 1; }
     const int n_iter = max(cnt, other_cnt);
     const int64_t row = (int64_t)head * n_qb + qb;
     const int32_t *sel = sel_idx + row * g.topk;
@@ -358,7 +362,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
             has_next = it + 1 < cnt;
             if (has_next) {
                 if (((it + 1) & 63) == 0) {
-                    blk_chunk = (it + 1 + lane) < cnt ? pack_block(g, c, start, head, sel[it + 1 + lane], ph, pw) : 0u;
+                    blk_chunk = (it + 1 + lane) < cnt ? pack_block(g, c, start, head, sel[listed(it + 1 + lane)], ph, pw) : 0u;
                     blk_next = __builtin_amdgcn_readlane(blk_chunk, 0);
                 } else {
                     blk_next = __builtin_amdgcn_readlane(blk_chunk, (it + 1) & 63);
@@ -452,36 +456,78 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     if (grp8 == 0) { stage_barrier(); stage_barrier(); }   // matches group 1's two extra barriers at the start
     LCSA_STAMP(2)
 
-    // ---- epilogue: normalise, transpose through this wavefront's own 8 KB of LDS, store 256-byte rows.
+    // ---- epilogue: normalise, transpose through this wavefront's own quarter of its group's K buffer, store.
     // No LDS reads of other wavefronts are outstanding: the last stage ended in a barrier.
     if (!active) return;
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    float l_tot = l_run + __shfl_xor(l_run, 32);
+    constexpr int kOut = SPLIT ? 2 : 4;                    // channel groups of 32 that this group finishes: first_dt ..
+    const int first_dt = SPLIT ? 2 * grp8 : 0;
+    f32x16 out[kOut];
+    if constexpr (SPLIT) {
+        // Each group passes the 64 channels it does not finish to the other one, through its own V and K buffers: a
+        // wavefront's 8 KB of either, register quad by register quad, 16 bytes per lane.
+        unsigned char *mine = v_lds + wave * 8192, *theirs = lds_all[grp8 ^ 1][1] + wave * 8192;
+        f32x16 give[2];
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+            out[dt] = grp8 ? oacc[2 + dt] : oacc[dt];
+            give[dt] = grp8 ? oacc[dt] : oacc[2 + dt];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            typedef __attribute__((ext_vector_type(4))) float f32x4;
+            const f32x16 &from = give[i >> 2];
+            const int r = (i & 3) * 4;
+            *(f32x4 *)(mine + i * 1024 + lane * 16) = f32x4{from[r], from[r + 1], from[r + 2], from[r + 3]};
+        }
+        if (half == 0) softmax_all[grp8][tq] = make_float2(m_run, l_tot);
+        stage_barrier();
+        const float2 o_ml = softmax_all[grp8 ^ 1][tq];
+        const float m_all = fmaxf(m_run, o_ml.x), ref = m_all == -__builtin_inff() ? 0.f : m_all;   // a group without blocks: reference -inf, sum 0
+        const float a_own = __builtin_amdgcn_exp2f(m_run - ref), a_other = __builtin_amdgcn_exp2f(o_ml.x - ref);
+        l_tot = l_tot * a_own + o_ml.y * a_other;
+        m_run = m_all;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            typedef __attribute__((ext_vector_type(4))) float f32x4;
+            const f32x4 x = *(const f32x4 *)(theirs + i * 1024 + lane * 16);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float &y = ((float *)&out[i >> 2])[(i & 3) * 4 + j];
+                y = y * a_own + x[j] * a_other;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) out[dt] = oacc[dt];
+    }
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     // lane owns query row tq; accumulator register i of channel group dt is channel
     // dt*32 + (i>>2)*8 + half*4 + (i&3): 4 consecutive channels = 8 bytes
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < kOut; ++dt)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
             bf16x4 w;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = (__bf16)(oacc[dt][i4 * 4 + j] * inv);
+            for (int j = 0; j < 4; ++j) w[j] = (__bf16)(out[dt][i4 * 4 + j] * inv);
             const int chunk = dt * 4 + i4;
             *(bf16x4 *)(k_lds + tq * 256 + ((chunk ^ (tq & 15)) << 4) + half * 8) = w;
         }
-    if (lse && half == 0 && q_valid)
+    if (lse && half == 0 && q_valid && (!SPLIT || grp8 == 0))
         lse[token * g.heads + head] = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // rows written by this wavefront are read by it only
     {
-        const int rg = lane >> 4, j = lane & 15;            // 4 rows per pass, 16 lanes x 16 bytes per row
+        constexpr int kLanes = kOut * 4, kRows = 64 / kLanes;     // lanes x 16 bytes per row, rows per pass
+        const int rg = lane / kLanes, j = lane % kLanes;
 #pragma unroll
-        for (int itr = 0; itr < 8; ++itr) {
-            const int t = wave * 32 + rg + 4 * itr;
+        for (int itr = 0; itr < 32 / kRows; ++itr) {
+            const int t = wave * 32 + rg + kRows * itr;
             int ft, r, cc;
             if (block_token(g, t, qvh, qvw, ft, r, cc)) {
                 const int64_t tok = raster_token(g, fq, ft, by * g.th + r, bx * g.tw + cc);
                 const uint4 u = *(const uint4 *)(k_lds + t * 256 + ((j ^ (t & 15)) << 4));
-                *(uint4 *)(o + tok * o_st + (int64_t)head * o_sh + j * 8) = u;
+                *(uint4 *)(o + tok * o_st + (int64_t)head * o_sh + first_dt * 32 + j * 8) = u;
             }
         }
     }
@@ -497,7 +543,13 @@ hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int6
     int n_cu = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
-    if (total <= n_cu) {
+    // A workgroup holds a compute unit to itself, so a launch takes as many rounds as it has workgroups per unit, each as
+    // long as the blocks of two items (pairs) or of half of that (split).  Split where its rounds end earlier: always up to
+    // one item per unit, then for total in (2, 3] x units, (4, 5] x units and so on.  Measured on 48 x 96 tokens, k = 32,
+    // 256 units: 216 items 82 us as one idle group per workgroup, 65 split; 576 items 207 us in pairs, 173 split; 1080 items
+    // 328 and 298; in between (504, 864, 1008 items) the rounds are equally long and pairs set up and finish once less.
+    const int rounds_split = (total + n_cu - 1) / n_cu, rounds_pairs = ((total + 1) / 2 + n_cu - 1) / n_cu;
+    if (rounds_split < 2 * rounds_pairs) {
         const int per_xcd = (total + 7) / 8;
         attn_mfma_kernel<true><<<dim3(per_xcd * 8), 512, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,
                                                                       (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e,

@@ -349,6 +349,19 @@ def test_more_than_64_selected_blocks_refills_the_id_chunk():
     assert r.rows_checked == 30
 
 
+@pytest.mark.parametrize("heads,topk,grid", [
+    (2, 1, (24, 44)),          # one group of the workgroup has no block
+    (2, 3, (21, 37)),          # two blocks against one; clipped query blocks leave wavefronts without rows
+    (1, 192, (64, 64)),        # 96 blocks per group: each refills its id chunk
+    (29, 7, (24, 44)),         # 522 items on 256 compute units: several rounds of split items
+    (15, 7, (24, 44)),         # 270 items: two items per workgroup again
+])
+def test_an_item_split_over_the_two_groups_of_a_workgroup(heads, topk, grid):
+    w = wl.with_overrides(wl.WORKLOADS["small"], name=f"split-{heads}-{topk}", heads=heads, grid_h=grid[0], grid_w=grid[1], radius=-1, topk=topk)
+    _, og = geoms(w)
+    run_primed(w, rows=None if heads < 3 else sample_rows(og, 40), check_lse=True)
+
+
 # ---- the paper's own block shape: (2, 8, 8) = two frames x 8 x 8 tokens (Sec. 3.2) ----------------------
 
 def test_paper_block_shape_2x8x8_small_grid_all_rows():
