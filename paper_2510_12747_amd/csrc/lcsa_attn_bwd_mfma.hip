@@ -9,8 +9,8 @@
 // Tiles.  A 128-token x 128-channel bf16 tile lives in LDS as 128 rows of 256 bytes, the 16-byte chunk j of row r
 // at chunk position j ^ sw(r), sw(r) = the low four bits of r rotated left by one.  It is copied there straight
 // from the raster tensor by direct-to-LDS loads (a wavefront instruction moves 4 rows: lane t lands at byte 16 t of
-// them and fetches the chunk that belongs there; rows beyond the block's valid tokens fetch zeros), two tiles per
-// step into one of two buffers, so that the next block's tiles arrive while the current block is computed.
+// them and fetches the chunk that belongs there), ahead of the computation: the query-side kernel copies a block's K and
+// V tiles into one of two buffers, the key-side kernel streams units of 32 rows of Q and dO through a ring.
 // All products have the form C[m][n] = sum_k A[m][k] B[n][k].  Where the summed index runs along the rows of the
 // tile (first level: over channels), an operand fragment is one ds_read_b128 of a row; where it runs down the
 // columns (second level: over keys or queries), the fragment comes from two transposing reads (ds_read_b64_tr_b16:
@@ -24,18 +24,17 @@
 // hold 8 consecutive indices of the summed dimension of the second-level product: the accumulator, rounded to
 // bf16, IS the A operand of that product.
 //
-//   bwd_delta_mfma_kernel workgroup = (head, query block): D_i = sum_j p_ij t_ij over the kept key blocks (stored in
-//                         `delta`), formed from unrounded p and t in float.
-//   bwd_dq_mfma_kernel    workgroup = (head, query block), wavefront w owns queries 32w..32w+31 (their Q and dO
-//                         fragments stay in registers as B operands): u from D, dQ += u K.
-//   bwd_dkv_mfma_kernel   workgroup = (head, key block), wavefront w owns keys 32w..32w+31 (K and V fragments in
-//                         registers).  Walks the query blocks that kept this block (ascending), per query block
-//                         the Q and dO tiles: dV += P^T dO, dK += U^T Q.
+//   bwd_dq_mfma_kernel    workgroup = (head, query block), two passes over the kept key blocks: D_i = sum_j p_ij t_ij (stored
+//                         in `delta`), formed from unrounded p and t in float; then u from D and dQ += u K.
+//   bwd_dkv_mfma_kernel   workgroup = (head, key block).  Walks the query blocks that kept this block (ascending):
+//                         dV += P^T dO, dK += U^T Q.
 // Every matrix instruction takes one 1 KB operand fragment from LDS (the 64-bit transposing reads at less than half
-// the rate of the 128-bit row reads), and every kernel fetches 64 KB of tiles per block pair from L2.
+// the rate of the 128-bit row reads), and 64 KB of tiles per block pair come from L2 for each of the three passes.
+//
+// Paper scale (12 heads, 48 x 88 tokens, k = 32): 618 us + 640 us.  As three kernels, D and dQ apart and dK, dV with four
+// wavefronts, one per SIMD, they took 312 + 506 + 761 us: with one wavefront per SIMD nothing ran beside the exponentials,
+// and every copied row cost a 64-bit address computation.
 #include "lcsa_kernels.h"
-
-#include <type_traits>
 
 namespace lcsa {
 namespace {
@@ -44,15 +43,12 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-constexpr int kThreads = 256;
 constexpr int kTileBytes = 128 * 256;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxQueryBlocks = 8192;        // flags of the key-block kernel
+constexpr int kMaxQueryBlocks = 8192;        // limit of these kernels; more query blocks go to the float kernels
+constexpr int kListed = 512;                 // query blocks whose kept flags are turned into a list at a time
 
 #define LCSA_LDS __attribute__((address_space(3)))
-
-// what padding rows of a tile are copied from
-__device__ __attribute__((aligned(256))) const unsigned char zero_row[256] = {};
 
 struct BlockRef { int group, by, bx, vh, vw, n_valid; };
 __device__ inline BlockRef block_ref(const KGeom &g, int block) {
@@ -69,12 +65,11 @@ __device__ inline BlockRef block_ref(const KGeom &g, int block) {
 // raster token of the first token of a block; token i of the block lies rel_token(i) further on
 __device__ inline int64_t block_origin(const KGeom &g, const BlockRef &b) { return raster_token(g, b.group, 0, b.by * g.th, b.bx * g.tw); }
 // distance, in raster tokens, from a block's first token to its i-th valid token (valid tokens first, in
-// (frame, row, column) order over the block's clipped extent vh x vw); -1 beyond the valid tokens
-__device__ inline int rel_token(const KGeom &g, int vh, int vw, int i) {
+// (frame, row, column) order over the block's clipped extent); 0 beyond the valid tokens
+__device__ inline int rel_token(const KGeom &g, const BlockTokens &bt, int i) {
     int ft, r, c;
-    return block_token(g, i, vh, vw, ft, r, c) ? (ft * g.H + r) * g.W + c : -1;
+    return bt.at(i, ft, r, c) ? (ft * g.H + r) * g.W + c : 0;
 }
-__device__ inline int64_t token_of(const KGeom &g, const BlockRef &b, int i) { return block_origin(g, b) + rel_token(g, b.vh, b.vw, i); }
 
 // chunk position swizzle of a tile image and the byte offset of 16-byte chunk `chunk` of row `row`
 __device__ inline int sw(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
@@ -82,22 +77,32 @@ __device__ inline int img_off(int row, int chunk) { return row * 256 + ((chunk ^
 // matrix row m of a first-level product reads tile row swap23(m)
 __device__ inline int swap23(int m) { return (m & 0x13) | ((m & 4) << 1) | ((m & 8) >> 1); }
 
-// operand fragment along a row: elements 8 chunk .. 8 chunk + 7 of row `row`
-__device__ inline bf16x8 frag(const unsigned char *img, int row, int chunk) { return *(const bf16x8 *)(img + img_off(row, chunk)); }
-
-// Operand fragment down a column.  Lane (n = lane & 31, half = lane >> 5) receives column col0 + n, rows
-// row0 + 8 half .. + 7.  A transposing read serves 16 lanes at a time: lane i of the 16 points at 4 elements of row
-// (first + i / 4), columns (c16 + 4 (i % 4) ..), and receives rows first .. first + 3 of column c16 + i.
-__device__ inline bf16x8 frag_down(const unsigned char *img, int row0, int col0, int lane) {
-    const int i = lane & 15, c16 = col0 + (lane & 16), half = lane >> 5;
-    const int chunk = (c16 >> 3) + ((i >> 1) & 1), sub = (i & 1) * 8;
-    const int ra = row0 + 8 * half + (i >> 2), rb = ra + 4;
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(img + img_off(ra, chunk) + sub));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(img + img_off(rb, chunk) + sub));
+// Operand fragments of a 32-row unit of a tile (`unit` = the tile's address in LDS + 8192 * the unit; tiles are 256-byte
+// aligned, so every address is one XOR away from a per-lane base).
+//
+// Along a row: lane (n = lane & 31, half = lane >> 5) receives elements 16 ks + 8 half .. + 7 of row swap23(n).
+__device__ inline int row_base(int lane) {
+    const int row = swap23(lane & 31);
+    return img_off(row, lane >> 5);
+}
+__device__ inline bf16x8 frag(const unsigned char *unit, int base, int ks) { return *(const bf16x8 *)(unit + (base ^ (ks << 5))); }
+// Down a column: lane (n, half) receives column 32 nt + n, rows 16 kk + 8 half .. + 7.  A transposing read serves 16 lanes
+// at a time: lane i of the 16 points at 4 elements of row (first + i / 4), columns (c16 + 4 (i % 4) ..), and receives rows
+// first .. first + 3 of column c16 + i.
+__device__ inline int column_base(int lane) {
+    const int i = lane & 15, row = 8 * (lane >> 5) + (i >> 2), chunk = 2 * ((lane >> 4) & 1) + ((i >> 1) & 1);
+    return img_off(row, chunk) + (i & 1) * 8;
+}
+__device__ inline bf16x8 frag_down(const unsigned char *unit, int base, int nt, int kk) {
+    const unsigned char *a = unit + 4096 * kk;               // rows + 4: four rows further, and bit 3 of sw() flips
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + (base ^ (nt << 6))));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + 1024 + (base ^ (nt << 6) ^ 128)));
     typedef __attribute__((ext_vector_type(8))) short i16x8;
     const i16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, both);
 }
+// Hides where a base came from, so that the XORs are formed where they are used instead of kept in registers.
+__device__ inline int fresh(int base) { asm volatile("" : "+v"(base)); return base; }
 
 // B-operand fragments of the 32 rows a wavefront owns, straight from the raster tensor: lane (n, half) holds
 // x[token(first + n)][16 ks + 8 half .. + 8] for ks = 0..7; rows beyond the block's valid tokens are zeros
@@ -105,7 +110,7 @@ __device__ inline void load_own_rows(const KGeom &g, const BlockRef &b, const __
                                      int first, int lane, bf16x8 (&f)[8]) {
     const int n = lane & 31, half = lane >> 5;
     const bool ok = first + n < b.n_valid;
-    const __bf16 *p = x + (ok ? token_of(g, b, first + n) : 0) * st + (int64_t)head * sh + half * 8;
+    const __bf16 *p = x + (block_origin(g, b) + rel_token(g, BlockTokens(g, b.vh, b.vw), first + n)) * st + (int64_t)head * sh + half * 8;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
         const uint4 u = ok ? *(const uint4 *)(p + ks * 16) : make_uint4(0, 0, 0, 0);
@@ -114,16 +119,21 @@ __device__ inline void load_own_rows(const KGeom &g, const BlockRef &b, const __
 }
 
 // ---- tile copies -------------------------------------------------------------------------------------------------
-// A wavefront copies rows 32 wave .. 32 wave + 31 of a tile with 8 instructions; instruction i moves rows
-// 32 wave + 4 i .. + 3, lane t supplying row (t >> 4), chunk position (t & 15).  RowPlan holds, for the 8 rows of a
-// lane, the distance of the row's token from the block's first token (-1: padding row) for one block extent; the
-// plan of the unclipped extent is made once, clipped blocks make their own.
-template <int WAVES> struct RowPlan { int rel[32 / WAVES]; };
-template <int WAVES>
-__device__ inline RowPlan<WAVES> plan_rows(const KGeom &g, int vh, int vw, int wave, int lane) {
-    RowPlan<WAVES> p;
+// A wavefront copies 16 rows of a tile with 4 instructions; instruction i moves rows 16 wave + 4 i .. + 3, lane t
+// supplying row (t >> 4), chunk position (t & 15).  A CopyPlan holds, for the 4 rows of a lane, the byte distance of the
+// lane's 16 bytes from the block's first token: made once for the unclipped extent, so that a block costs one 64-bit
+// addition per row; clipped blocks make their own.  Rows beyond the block's valid tokens repeat its first one: their
+// probabilities are set to zero, so what they hold never reaches a result.
+constexpr int kWaves = 8;
+struct CopyPlan { int64_t at[4]; };
+__device__ inline CopyPlan copy_plan(const KGeom &g, int vh, int vw, int64_t st, int wave, int lane) {
+    CopyPlan p;
+    const BlockTokens bt(g, vh, vw);
 #pragma unroll
-    for (int i = 0; i < 32 / WAVES; ++i) p.rel[i] = rel_token(g, vh, vw, (128 / WAVES) * wave + 4 * i + (lane >> 4));
+    for (int i = 0; i < 4; ++i) {
+        const int row = 4 * i + (lane >> 4);
+        p.at[i] = (rel_token(g, bt, 16 * wave + row) * st + ((lane & 15) ^ sw(row)) * 8) * 2;   // 16 wave does not enter sw()
+    }
     return p;
 }
 // One copy instruction: 64 lanes x 16 bytes from per-lane addresses to LDS bytes lds_rows + 16 lane.  The load
@@ -132,36 +142,40 @@ __device__ inline void copy_rows_to_lds(const void *src, uint32_t lds_rows) {
     lds_rows = __builtin_amdgcn_readfirstlane(lds_rows);     // wavefront-uniform already; this pins it to a scalar register
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(lds_rows) : "memory", "m0");
 }
-// Copies this wavefront's rows (128 / WAVES of them) of the tiles of block `b` of two tensors (K and V, or Q and dO);
-// x1 = the second tensor moved so that the first tensor's strides reach its elements too when the two share
-// strides (`same`, the usual case: one address computation serves both), else its own base with strides st1, sh1.
-template <int WAVES>
-__device__ inline void copy_tiles(const KGeom &g, const BlockRef &b, const RowPlan<WAVES> &full, int wave, int lane,
-                                  const __bf16 *__restrict__ x0, const __bf16 *__restrict__ x1, int64_t st, int64_t sh, int head,
-                                  uint32_t lds0, uint32_t lds1, bool same = true, int64_t st1 = 0, int64_t sh1 = 0) {
-    RowPlan<WAVES> plan = full;
-    if (b.vh != g.th || b.vw != g.tw) plan = plan_rows<WAVES>(g, b.vh, b.vw, wave, lane);     // workgroup-uniform
-    const int64_t origin = block_origin(g, b);
-    const int slot = lane & 15, q4 = lane >> 4;
-    const int first = (128 / WAVES) * wave;                  // a multiple of 16: its low bits do not enter sw()
+__device__ inline uint32_t lds_address(const unsigned char *p) { return (uint32_t)(uintptr_t)((LCSA_LDS unsigned char *)p); }
+
+// A block as the loops want it: raster token of its first token, and its clipped extent.
+struct Located { int origin, extent; };                      // extent = vh | vw << 16
+__device__ inline Located locate(const KGeom &g, int block) {
+    const BlockRef b = block_ref(g, block);
+    return {(int)block_origin(g, b), b.vh | b.vw << 16};
+}
+__device__ inline int valid_tokens(const KGeom &g, const Located &b) { return g.tt * (b.extent & 0xffff) * (b.extent >> 16); }
+
+// This wavefront's rows of the tiles of block `b` of two tensors (K and V, or Q and dO), each with its plan.
+__device__ inline void copy_tiles(const KGeom &g, const Located &b, const CopyPlan &full0, const CopyPlan &full1, int wave, int lane,
+                                  const __bf16 *__restrict__ x0, int64_t st0, const __bf16 *__restrict__ x1, int64_t st1, uint32_t lds0) {
+    CopyPlan p0 = full0, p1 = full1;
+    if (b.extent != (g.th | g.tw << 16)) {                   // workgroup-uniform
+        p0 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st0, wave, lane);
+        p1 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st1, wave, lane);
+    }
+    const char *b0 = (const char *)(x0 + b.origin * st0), *b1 = (const char *)(x1 + b.origin * st1);
 #pragma unroll
-    for (int i = 0; i < 32 / WAVES; ++i) {
-        const int chunk = slot ^ sw(4 * i + q4);
-        const int64_t at = ((origin + plan.rel[i]) * st + (int64_t)head * sh + chunk * 8) * 2;
-        const int64_t at1 = same ? at : ((origin + plan.rel[i]) * st1 + (int64_t)head * sh1 + chunk * 8) * 2;      // `same` is workgroup-uniform
-        const bool ok = plan.rel[i] >= 0;
-        const void *s0 = ok ? (const void *)((const char *)x0 + at) : (const void *)(zero_row + chunk * 16);
-        const void *s1 = ok ? (const void *)((const char *)x1 + at1) : (const void *)(zero_row + chunk * 16);
-        const uint32_t rows = (uint32_t)(first + 4 * i) * 256;
-        copy_rows_to_lds(s0, lds0 + rows);
-        copy_rows_to_lds(s1, lds1 + rows);
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t rows = (uint32_t)(16 * wave + 4 * i) * 256;
+        copy_rows_to_lds(b0 + p0.at[i], lds0 + rows);
+        copy_rows_to_lds(b1 + p1.at[i], lds0 + kTileBytes + rows);
     }
 }
-__device__ inline uint32_t lds_address(const unsigned char *p) { return (uint32_t)(uintptr_t)((LCSA_LDS unsigned char *)p); }
 
 // all of this wavefront's tile copies have landed; then a workgroup barrier: everybody's have, and everybody is
 // done with the buffer that the next copies will overwrite
 __device__ inline void tiles_ready() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// this wavefront's LDS writes so far are done
+__device__ inline void lds_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// a barrier for LDS traffic only: tile copies stay in flight
+__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Launch order.  Workgroups are dealt to the 8 XCDs round-robin, each with an L2 of its own; workgroup ids are
 // mapped so that an XCD walks a contiguous run of (head, tile, frame group) items: neighbouring tiles of a head keep
@@ -181,18 +195,71 @@ __device__ inline void zero(f32x16 &a) {
     for (int i = 0; i < 16; ++i) a[i] = 0.f;
 }
 
+// First-level products of the 32 rows mt of two tiles with two sets of register operands, operand fragments read kAhead
+// pairs ahead of the matrix instructions that use them.
+constexpr int kAhead = 3, kRing = kAhead + 1;
+__device__ inline void first_level(const unsigned char *x_unit, const unsigned char *y_unit, int base,
+                                   const bf16x8 (&xf)[8], const bf16x8 (&yf)[8], f32x16 &xs, f32x16 &ys) {
+    bf16x8 xa[kRing], ya[kRing];
+    base = fresh(base);
+#pragma unroll
+    for (int n = 0; n < kAhead; ++n) { xa[n] = frag(x_unit, base, n); ya[n] = frag(y_unit, base, n); }
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAhead, 0);
+    zero(xs); zero(ys);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+        if (ks + kAhead < 8) {
+            xa[(ks + kAhead) % kRing] = frag(x_unit, base, ks + kAhead);
+            ya[(ks + kAhead) % kRing] = frag(y_unit, base, ks + kAhead);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        xs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[ks % kRing], xf[ks], xs, 0, 0, 0);
+        ys = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ya[ks % kRing], yf[ks], ys, 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    }
+}
+// Keeps the work that formed a value from moving past this point.
+__device__ inline void pin(bf16x8 (&v)[2]) { asm volatile("" : "+v"(v[0]), "+v"(v[1])); }
+// Row fragments of a unit
+__device__ inline void read_rows(const unsigned char *unit, int base, bf16x8 (&a)[8]) {
+    base = fresh(base);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) a[ks] = frag(unit, base, ks);
+}
+__device__ inline void first_level(const unsigned char *x_unit, int base, const bf16x8 (&xf)[8], f32x16 &xs) {
+    bf16x8 xa[8];
+    read_rows(x_unit, base, xa);
+    zero(xs);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) xs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[ks], xf[ks], xs, 0, 0, 0);
+}
+// Values of a unit's rows in the order of the accumulator registers: registers 4 r .. 4 r + 3
+__device__ inline float4 row_quad(const float *values, int half, int r) { return *(const float4 *)(values + 16 * (r >> 1) + 8 * half + 4 * (r & 1)); }
+// Column fragments of a unit (B operands of a second-level product: 4 channel groups x 2 k-steps)
+__device__ inline void read_columns(const unsigned char *unit, int base, bf16x8 (&b)[8]) {
+    base = fresh(base);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = frag_down(unit, base, i >> 1, i & 1);
+}
+__device__ inline void second_level(const bf16x8 (&a)[2], const bf16x8 (&b)[8], f32x16 (&acc)[4]) {
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk], b[nt * 2 + kk], acc[nt], 0, 0, 0);
+}
+
 // ---------------------------------------------------------------------------------------------------------------
-// D_i = sum_j p_ij t_ij.  Eight wavefronts, two per SIMD, so that one wavefront's matrix products run beside the
-// other's LDS reads and exponentials: wavefront w owns queries 32 (w & 3) .. + 31 and, of every kept key block, the
-// 32-key units 2 (w >> 2) and 2 (w >> 2) + 1; the two partial sums of a query meet in LDS at the end.
-__global__ __launch_bounds__(512) void bwd_delta_mfma_kernel(
+// D_i = sum_j p_ij t_ij over the kept key blocks, then once more over them for dQ += u K.  Eight wavefronts, two per SIMD:
+// wavefront w owns queries 32 (w & 3) .. + 31 and, of every kept key block, the 32-key units w >> 2 and (w >> 2) + 2; the
+// two partial results of a query meet in LDS.
+__global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
     KGeom g, int kv_groups, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
     const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse,
-    float *__restrict__ delta, float scale, int per_xcd) {
-    __shared__ __attribute__((aligned(16))) unsigned char img[2][2][kTileBytes];      // [buffer][K, V]
-    __shared__ float part[128];
+    float *__restrict__ d_q, float *__restrict__ delta, float scale, int per_xcd) {
+    __shared__ __attribute__((aligned(256))) unsigned char img[2][2][kTileBytes];      // [buffer][K, V]
+    __shared__ float part[2][128];
     int qb, head;
     if (!work_item(g, g.q_groups, per_xcd, head, qb)) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -205,360 +272,393 @@ __global__ __launch_bounds__(512) void bwd_delta_mfma_kernel(
     const int32_t *sel = sel_idx + row * g.topk;
     const float scale_log2 = scale * kLog2e;
     const uint32_t lds_img = lds_address(&img[0][0][0]);
-    const RowPlan<8> full = plan_rows<8>(g, g.th, g.tw, wave, lane);
+    k += (int64_t)head * kv_sh;
+    v += (int64_t)head * kv_sh;
+    const CopyPlan plan = copy_plan(g, g.th, g.tw, kv_st, wave, lane);
 
+    // kept blocks of this row, 64 at a time, one per lane
+    Located chunk = {0, 0};
+    auto refill = [&](int b0) {
+        // ids outside the visible blocks must not become wild addresses
+        if (b0 + lane < cnt) chunk = locate(g, min(max(sel[b0 + lane], 0), kv_groups * g.nb - 1));
+    };
+    auto request = [&](int b, int buf) {
+        if ((b & 63) == 0 && cnt > 64) refill(b);
+        const Located kr = {__builtin_amdgcn_readlane(chunk.origin, b & 63), __builtin_amdgcn_readlane(chunk.extent, b & 63)};
+        copy_tiles(g, kr, plan, plan, wave, lane, k, kv_st, v, kv_st, lds_img + buf * 2 * kTileBytes);
+        return valid_tokens(g, kr);
+    };
+    refill(0);
+    int n_next = cnt > 0 ? request(0, 0) : 0;
+
+    // this wavefront's queries: Q and dO fragments (B operands), lse and the token to write to
     bf16x8 qf[8], gf[8];
     load_own_rows(g, qr, q, q_st, q_sh, head, 32 * qg, lane, qf);
     load_own_rows(g, qr, d_o, o_st, o_sh, head, 32 * qg, lane, gf);
     const bool q_ok = 32 * qg + ql < qr.n_valid;
-    const int64_t q_token = token_of(g, qr, q_ok ? 32 * qg + ql : 0);
-    const float l2 = q_ok ? lse[q_token * g.heads + head] * kLog2e : __builtin_inff();   // padding queries: probability zero
-    auto key_block = [&](int b) { return block_ref(g, min(max(sel[b], 0), kv_groups * g.nb - 1)); };
-    auto copy_block = [&](const BlockRef &kr, int buf) {
-        copy_tiles<8>(g, kr, full, wave, lane, k, v, kv_st, kv_sh, head, lds_img + buf * 2 * kTileBytes, lds_img + (buf * 2 + 1) * kTileBytes);
-    };
-    __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), where the compiler sees it: no wait of its own inside the loop
-
-    float dsum = 0.f;
-    BlockRef kr = key_block(0);
-    if (cnt > 0) copy_block(kr, 0);
-    for (int b = 0; b < cnt; ++b) {
-        tiles_ready();
-        const int n_keys = kr.n_valid;
-        if (b + 1 < cnt) { kr = key_block(b + 1); copy_block(kr, (b + 1) & 1); }
-        const unsigned char *k_img = img[b & 1][0], *v_img = img[b & 1][1];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int mt = 2 * kh + u;
-            if (mt * 32 < n_keys) {
-                const int arow = mt * 32 + swap23(ql);
-                bf16x8 ka[8], va[8];
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks) { ka[ks] = frag(k_img, arow, 2 * ks + half); va[ks] = frag(v_img, arow, 2 * ks + half); }
-                __builtin_amdgcn_sched_barrier(0);
-                f32x16 st_, dpt;
-                zero(st_); zero(dpt);
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    st_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qf[ks], st_, 0, 0, 0);
-                    dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ks], gf[ks], dpt, 0, 0, 0);
-                }
-                // register 8 kk + j = key mt*32 + 16 kk + 8 half + j; keys beyond the valid ones get probability zero
-                const int left = n_keys - (mt * 32 + 8 * half);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(st_[r], scale_log2, -l2));
-                    dsum = fmaf((r >> 3) * 16 + (r & 7) < left ? p : 0.f, dpt[r], dsum);
-                }
-            }
-        }
-    }
-    const float d = dsum + __shfl_xor(dsum, 32);             // the two half-waves hold the two halves of a unit's keys
-    if (kh == 1 && half == 0) part[32 * qg + ql] = d;
-    __syncthreads();
-    if (kh == 0 && half == 0 && q_ok) delta[q_token * g.heads + head] = d + part[32 * qg + ql];
-}
-
-// ---------------------------------------------------------------------------------------------------------------
-// dQ += u K over the kept key blocks, with D_i read from `delta`.  Four wavefronts, one per SIMD (the accumulators
-// and both operand sets of a unit do not fit twice), software-pipelined instead.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_dq_mfma_kernel(
-    KGeom g, int kv_groups, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
-    const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
-    const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
-    const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse,
-    float *__restrict__ d_q, const float *__restrict__ delta, float scale, int per_xcd) {
-    __shared__ __attribute__((aligned(16))) unsigned char img[2][2][kTileBytes];      // [buffer][K, V]
-    int qb, head;
-    if (!work_item(g, g.q_groups, per_xcd, head, qb)) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ql = lane & 31, half = lane >> 5;
-    const int n_qb = g.q_groups * g.nb;
-    const BlockRef qr = block_ref(g, qb);
-    const int64_t row = (int64_t)head * n_qb + qb;
-    const int cnt = min(max(sel_cnt[row], 0), g.topk);
-    const int32_t *sel = sel_idx + row * g.topk;
-    const float scale_log2 = scale * kLog2e;
-    const uint32_t lds_img = lds_address(&img[0][0][0]);
-    const RowPlan<4> full = plan_rows<4>(g, g.th, g.tw, wave, lane);
-
-    // this wavefront's queries: Q and dO fragments (B operands), lse and the token to write to
-    bf16x8 qf[8], gf[8];
-    load_own_rows(g, qr, q, q_st, q_sh, head, 32 * wave, lane, qf);
-    load_own_rows(g, qr, d_o, o_st, o_sh, head, 32 * wave, lane, gf);
-    const bool q_ok = 32 * wave + ql < qr.n_valid;
-    const int64_t q_token = token_of(g, qr, q_ok ? 32 * wave + ql : 0);
+    const BlockTokens qt(g, qr.vh, qr.vw);
+    const int64_t q_token = block_origin(g, qr) + rel_token(g, qt, 32 * qg + ql);
     // padding queries: an infinite reference makes every probability zero
     const float l2 = q_ok ? lse[q_token * g.heads + head] * kLog2e : __builtin_inff();
-
-    auto key_block = [&](int b) {
-        return block_ref(g, min(max(sel[b], 0), kv_groups * g.nb - 1));   // ids outside the visible blocks must not become wild addresses
-    };
-    auto copy_block = [&](const BlockRef &kr, int buf) {
-        copy_tiles<4>(g, kr, full, wave, lane, k, v, kv_st, kv_sh, head, lds_img + buf * 2 * kTileBytes, lds_img + (buf * 2 + 1) * kTileBytes);
-    };
-    const float D = q_ok ? delta[q_token * g.heads + head] : 0.f;
+    const bool wave_on = 32 * qg < qr.n_valid;               // else only copies and barriers
     // All loads so far are waited for here, where the compiler sees it: left to itself it would wait at their first
     // use inside the loop, on every trip, and each such wait also drains the tile copies in flight (they share the counter).
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0)
+    const int rows = row_base(lane), columns = column_base(lane);
+
+    // Lane = query ql; register 8 kk + j = key mt*32 + 16 kk + 8 half + j.  Keys beyond the block's valid ones must get
+    // probability zero; only a block's last unit can hold any.
+    auto mask_keys = [&](f32x16 &s, int left) {
+        if (left < 32) {                                     // uniform
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if ((r >> 3) * 16 + (r & 7) + 8 * half >= left) s[r] = -__builtin_inff();
+        }
+    };
+    auto prob = [&](float s) { return __builtin_amdgcn_exp2f(fmaf(s, scale_log2, -l2)); };
+
+    int step = 0;                                            // tile buffers alternate over both passes
+    auto for_each_unit = [&](bool last_pass, auto &&work) {
+        for (int b = 0; b < cnt; ++b, ++step) {
+            tiles_ready();                                   // block b is in buffer step & 1; nobody reads the other buffer any more
+            const int n_keys = n_next;
+            if (b + 1 < cnt) n_next = request(b + 1, (step + 1) & 1);
+            else if (!last_pass) n_next = request(0, (step + 1) & 1);
+            if (wave_on) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int mt = kh + 2 * u;
+                    if (mt * 32 < n_keys) work(img[step & 1][0] + mt * 8192, img[step & 1][1] + mt * 8192, n_keys - mt * 32);
+                }
+            }
+        }
+    };
+
+    float dsum = 0.f;
+    for_each_unit(false, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left) {
+        f32x16 s, t;
+        first_level(k_unit, v_unit, rows, qf, gf, s, t);
+        mask_keys(s, left);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dsum = fmaf(prob(s[r]), t[r], dsum);
+    });
+    const float d_own = dsum + __shfl_xor(dsum, 32);         // the two half-waves hold the two halves of a unit's keys
+    if (half == 0) part[kh][32 * qg + ql] = d_own;
+    lds_barrier();
+    const float D = part[0][32 * qg + ql] + part[1][32 * qg + ql];
+    if (kh == 0 && half == 0 && q_ok) delta[q_token * g.heads + head] = D;
+
     f32x16 dq[4];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) zero(dq[nt]);
+    const float d_scaled = D * scale;
+    for_each_unit(true, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left) {
+        f32x16 s, t;
+        bf16x8 kc[8], u[2];
+        first_level(k_unit, v_unit, rows, qf, gf, s, t);
+        read_columns(k_unit, columns, kc);                   // arrives under the element-wise part
+        mask_keys(s, left);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) u[r >> 3][r & 7] = (__bf16)(prob(s[r]) * fmaf(t[r], scale, -d_scaled));
+        second_level(u, kc, dq);
+    });
 
-    // Operand reads of the 32-key unit mt of the tiles in `k_img`, `v_img`.
-    auto read_a = [&](const unsigned char *k_img, const unsigned char *v_img, int mt, bf16x8 (&ka)[8], bf16x8 (&va)[8]) {
-        const int arow = mt * 32 + swap23(ql);
+    // The two wavefronts of a query group exchange halves: wavefront kh finishes channel groups 2 kh, 2 kh + 1.
+    tiles_ready();                                           // nobody reads the tiles any more
+    float *x = (float *)&img[0][0][0] + wave * 2048;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) { ka[ks] = frag(k_img, arow, 2 * ks + half); va[ks] = frag(v_img, arow, 2 * ks + half); }
-    };
-    auto read_b = [&](const unsigned char *k_img, int mt, bf16x8 (&kb_)[8]) {
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) kb_[i] = frag_down(k_img, mt * 32 + 16 * (i & 1), (i >> 1) * 32, lane);
-    };
-    // first level: S^T = K Q^T and (dO V^T)^T = V dO^T for 32 keys x this wavefront's 32 queries
-    auto first_level = [&](const bf16x8 (&ka)[8], const bf16x8 (&va)[8], f32x16 &st_, f32x16 &dpt) {
-        zero(st_); zero(dpt);
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            st_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qf[ks], st_, 0, 0, 0);
-            dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ks], gf[ks], dpt, 0, 0, 0);
-        }
-    };
-    // lane = query ql; register 8 kk + j = key mt*32 + 16 kk + 8 half + j.  Keys beyond the block's valid ones (zero
-    // rows of the tiles) must get probability zero; only a block's last unit can hold any (MASK): `left` = valid keys
-    // from this lane's first one on.
-    auto prob = [&](float s_, bool mask, int idx, int left) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s_, scale_log2, -l2));
-        return mask && idx >= left ? 0.f : p;
-    };
-
-    // A block is walked in 32-key units, software-pipelined so that the matrix pipe, the vector pipe and the LDS reads
-    // of neighbouring units run side by side:
-    //     first level(mt), reads A(mt+1) | element-wise(mt) || second level(mt-1) | reads B(mt)
-    auto block_units = [&](auto n_tag, const unsigned char *k_img, const unsigned char *v_img, int n_keys) {
-        constexpr int N = decltype(n_tag)::value;
-        bf16x8 ka[8], va[8], kb_[8], ua[2];
-        f32x16 st_, dpt;
-        const float d_scaled = D * scale;
-        read_a(k_img, v_img, 0, ka, va);
-#pragma unroll
-        for (int mt = 0; mt <= N; ++mt) {
-            if (mt < N) {
-                __builtin_amdgcn_sched_barrier(0);
-                first_level(ka, va, st_, dpt);
-                __builtin_amdgcn_sched_barrier(0);
-                if (mt + 1 < N) read_a(k_img, v_img, mt + 1, ka, va);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            bf16x8 un[2];
-            if (mt < N) {
-                const int left = n_keys - (mt * 32 + 8 * half);
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int r = kk * 8 + j;
-                        un[kk][j] = (__bf16)(prob(st_[r], mt == N - 1, 16 * kk + j, left) * fmaf(dpt[r], scale, -d_scaled));
-                    }
-            }
-            if (mt > 0) {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk)
-                        dq[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua[kk], kb_[nt * 2 + kk], dq[nt], 0, 0, 0);
-            }
-            if (mt > 0 && mt < N) {
-#pragma unroll
-                for (int n = 0; n < 8; ++n) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (mt < N) { read_b(k_img, mt, kb_); ua[0] = un[0]; ua[1] = un[1]; }
-        }
-    };
-
-    BlockRef kr = key_block(0);
-    if (cnt > 0) copy_block(kr, 0);
-    for (int b = 0; b < cnt; ++b) {
-        tiles_ready();                                       // block b is in buffer b & 1; nobody reads the other buffer any more
-        const int n_keys = kr.n_valid;
-        if (b + 1 < cnt) { kr = key_block(b + 1); copy_block(kr, (b + 1) & 1); }
-        const unsigned char *k_img = img[b & 1][0], *v_img = img[b & 1][1];
-        auto units = [&](auto n_tag) { block_units(n_tag, k_img, v_img, n_keys); };
-        switch ((n_keys + 31) >> 5) {                        // 32-key units that hold valid keys
-        case 4: units(std::integral_constant<int, 4>()); break;
-        case 3: units(std::integral_constant<int, 3>()); break;
-        case 2: units(std::integral_constant<int, 2>()); break;
-        default: units(std::integral_constant<int, 1>()); break;
-        }
-    }
+        for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 64 + lane] = kh ? dq[i][r] : dq[2 + i][r];
+    lds_barrier();
+    const float *y = (const float *)&img[0][0][0] + (wave ^ 4) * 2048;
     // dq tile nt: lane = channel nt*32 + ql, register r = query row 8 (r >> 2) + 4 half + (r & 3) of this wavefront
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int qi = 32 * wave + 8 * (r >> 2) + 4 * half + (r & 3);
+        const int qi = 32 * qg + 8 * (r >> 2) + 4 * half + (r & 3);
         if (qi < qr.n_valid) {
-            float *out = d_q + (token_of(g, qr, qi) * g.heads + head) * 128 + ql;
+            float *out = d_q + ((block_origin(g, qr) + rel_token(g, qt, qi)) * g.heads + head) * 128 + kh * 64 + ql;
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) out[nt * 32] = dq[nt][r];
+            for (int i = 0; i < 2; ++i) out[i * 32] = (kh ? dq[2 + i][r] : dq[i][r]) + y[(i * 16 + r) * 64 + lane];
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// SAME_STRIDES: Q and dO share their strides (the usual case: one address computation per copied row serves both).
-template <bool SAME_STRIDES>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_dkv_mfma_kernel(
+// Eight wavefronts, two per SIMD, in two roles: wavefront w < 4 forms S and P of its 32 keys and dV += P^T dO, wavefront
+// w + 4 forms T = dO V^T of the same keys, U from T and from the P that wavefront w leaves in LDS, and dK += U^T Q.  Each
+// role needs half of the register operands and accumulators, so two wavefronts fit a SIMD.
+// The query rows stream through LDS in units of 32 (Q and dO rows: 16 KB), kStages of them at a time, one unit per slot and
+// one barrier per slot; a role's element-wise work stands beside matrix work of its own that does not depend on it:
+//     slot t   w < 4:  exponentials of S(t), P(t) -> LDS  beside  dV += P(t - 1)^T dO;   then S(t + 1)
+//              w >= 4: U(t - 1) from T(t - 1), P(t - 1)   beside  dK += U(t - 2)^T Q;    then T(t)
+// Slot t reads units t - 2 .. t + 1, and unit t + 4 is requested into the place of unit t - 3.
+constexpr int kStages = 7, kLead = kStages - 3, kStatLead = 3;
+constexpr int kUnitBytes = 32 * 256;
+
+__global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
     KGeom g, int kv_groups, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
     const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse, const float *__restrict__ delta,
     float *__restrict__ d_k, float *__restrict__ d_v, float scale, int per_xcd) {
-    __shared__ __attribute__((aligned(16))) unsigned char img[2][2][kTileBytes];      // [buffer][Q, dO]
-    __shared__ float l2_s[2][128], D_s[2][128];
-    __shared__ unsigned char kept_by[kMaxQueryBlocks];
+    __shared__ __attribute__((aligned(256))) unsigned char img[kStages][2][kUnitBytes];      // [stage][Q, dO]
+    __shared__ float4 p_lds[2][4][4][64];                    // [slot parity][key group][register quad][lane]
+    __shared__ __attribute__((aligned(16))) float row_lds[kStages][2][32];       // [stage][-lse log2(e), -scale D][query of the unit]
+    __shared__ unsigned char kept_by[kListed];
+    __shared__ uint16_t list[4 * kListed];                   // units: 4 * query block + unit of the block
+    __shared__ int n_listed;
     int kb, head;
     if (!work_item(g, kv_groups, per_xcd, head, kb)) return;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave & 3;
+    const bool p_role = wave < 4;
     const int ql = lane & 31, half = lane >> 5;
     const int n_qb = g.q_groups * g.nb;
     const BlockRef kr = block_ref(g, kb);
     const float scale_log2 = scale * kLog2e;
     const uint32_t lds_img = lds_address(&img[0][0][0]);
-    const RowPlan<4> full = plan_rows<4>(g, g.th, g.tw, wave, lane);
+    q += (int64_t)head * q_sh;
+    d_o += (int64_t)head * o_sh;
 
-    // which query blocks kept this key block?  (ascending id lists: binary search)
-    for (int qb = tid; qb < n_qb; qb += kThreads) {
-        const int64_t row = (int64_t)head * n_qb + qb;
-        const int32_t *sel = sel_idx + row * g.topk;
-        const int c = min(max(sel_cnt[row], 0), g.topk);
-        int lo = 0, hi = c;
-        while (lo < hi) { const int mid = (lo + hi) >> 1; if (sel[mid] < kb) lo = mid + 1; else hi = mid; }
-        kept_by[qb] = lo < c && sel[lo] == kb;
-    }
-    // this wavefront's keys: K and V fragments (B operands of the first-level products)
-    bf16x8 kf[8], vf[8];
-    load_own_rows(g, kr, k, kv_st, kv_sh, head, 32 * wave, lane, kf);
-    load_own_rows(g, kr, v, kv_st, kv_sh, head, 32 * wave, lane, vf);
-    const bool key_ok = 32 * wave + ql < kr.n_valid;
-    f32x16 dk[4], dv[4];
+    // this wavefront's keys: K or V fragments (B operands of the first-level products)
+    bf16x8 own[8];
+    load_own_rows(g, kr, p_role ? k : v, kv_st, kv_sh, head, 32 * kg, lane, own);
+    f32x16 acc[4];                                           // dV or dK
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) { zero(dk[nt]); zero(dv[nt]); }
-    __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), where the compiler sees it (see the query-side kernel)
-    __syncthreads();
+    for (int nt = 0; nt < 4; ++nt) zero(acc[nt]);
+    const bool wave_on = 32 * kg < kr.n_valid;               // else only copies and barriers
+    const int rows = row_base(lane), columns = column_base(lane);
 
-    auto next_kept = [&](int from) { while (from < n_qb && !kept_by[from]) ++from; return from; };   // uniform
-    int qb = next_kept(0);
-    float l2_next = 0.f, D_next = 0.f;
-    auto request = [&](int qb_, int buf) {                   // a query block's tiles, lse and D
-        const BlockRef qr = block_ref(g, qb_);
-        copy_tiles<4>(g, qr, full, wave, lane, q, d_o, q_st, q_sh, head, lds_img + buf * 2 * kTileBytes, lds_img + (buf * 2 + 1) * kTileBytes,
-                      SAME_STRIDES, o_st, o_sh);
-        if (tid < 128) {
-            const bool ok = tid < qr.n_valid;
-            const int64_t token = token_of(g, qr, ok ? tid : 0);
-            l2_next = ok ? lse[token * g.heads + head] * kLog2e : __builtin_inff();   // padding queries: probability zero
-            D_next = ok ? delta[token * g.heads + head] : 0.f;
+    for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
+        // which query blocks kept this key block?  (ascending id lists)
+        const int n_here = min(kListed, n_qb - qb0);
+        __syncthreads();                                     // the previous list and its units are no longer read
+        if (g.topk <= 64) {                                  // 16 lanes look at a row's ids at once
+            for (int i = 4 * wave + (lane >> 4); i < ((n_here + 3) & ~3); i += 4 * kWaves) {
+                bool hit = false;
+                if (i < n_here) {
+                    const int64_t row = (int64_t)head * n_qb + qb0 + i;
+                    const int c = min(max(sel_cnt[row], 0), g.topk);
+                    int ids[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ids[e] = (lane & 15) + 16 * e < g.topk ? sel_idx[row * g.topk + (lane & 15) + 16 * e] : -1;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) hit |= (lane & 15) + 16 * e < c && ids[e] == kb;
+                }
+                const uint64_t hits = __ballot(hit);
+                if ((lane & 15) == 0 && i < n_here) kept_by[i] = (hits >> (lane & 48) & 0xffff) != 0;
+            }
+        } else {                                             // a binary search per row
+            for (int i = tid; i < n_here; i += 64 * kWaves) {
+                const int64_t row = (int64_t)head * n_qb + qb0 + i;
+                const int32_t *sel = sel_idx + row * g.topk;
+                const int c = min(max(sel_cnt[row], 0), g.topk);
+                int lo = 0, hi = c;
+                while (lo < hi) { const int mid = (lo + hi) >> 1; if (sel[mid] < kb) lo = mid + 1; else hi = mid; }
+                kept_by[i] = lo < c && sel[lo] == kb;
+            }
         }
-    };
-    int buf = 0;
-    if (qb < n_qb) request(qb, 0);
-    while (qb < n_qb) {
-        const int n_queries = block_ref(g, qb).n_valid;
-        // buffer `buf` of the per-query values was last read two blocks ago, before the previous barrier
-        if (tid < 128) { l2_s[buf][tid] = l2_next; D_s[buf][tid] = D_next; }
-        tiles_ready();
-        qb = next_kept(qb + 1);
-        if (qb < n_qb) request(qb, buf ^ 1);                 // lands while this block is computed
-        const unsigned char *q_img = img[buf][0], *g_img = img[buf][1];
-        const float *l2_b = l2_s[buf], *D_b = D_s[buf];
-        const int n_units = (n_queries + 31) >> 5;           // 32-query units that hold valid queries
-        // Software pipeline over the units (a wavefront has its SIMD to itself): the element-wise work of unit mt
-        // runs beside the second-level products of unit mt - 1:
-        //     first level(mt), reads A(mt+1) | element-wise(mt) || second level(mt-1) | reads B(mt)
-        bf16x8 qa[8], ga[8], gb[8], qb_[8], pa[2], ua[2];
-        auto read_a = [&](int mt) {
-            const int arow = mt * 32 + swap23(ql);
+        __syncthreads();
+        if (wave == 0) {                                     // the kept blocks' units that hold valid queries, in order
+            int n = 0;
+            for (int i0 = 0; i0 < n_here; i0 += 64) {
+                const int i = i0 + lane;
+                const bool kept = i < n_here && kept_by[i];
+                const int units = kept ? (block_ref(g, qb0 + i).n_valid + 31) >> 5 : 0;
+                int before = units;                          // inclusive prefix sum
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) { qa[ks] = frag(q_img, arow, 2 * ks + half); ga[ks] = frag(g_img, arow, 2 * ks + half); }
-        };
-        // lane = key ql of this wavefront; register 8 kk + j = query mt*32 + 16 kk + 8 half + j
-        auto element_wise = [&](int mt, const f32x16 &s, const f32x16 &dp, bf16x8 (&pn)[2], bf16x8 (&un)[2]) {
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                const int q0 = mt * 32 + 16 * kk + 8 * half;
-                const float4 la = *(const float4 *)(l2_b + q0), lb = *(const float4 *)(l2_b + q0 + 4);
-                const float4 da = *(const float4 *)(D_b + q0), db = *(const float4 *)(D_b + q0 + 4);
-                const float l8[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
-                const float d8[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int r = kk * 8 + j;
-                    float p = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -l8[j]));
-                    p = key_ok ? p : 0.f;
-                    pn[kk][j] = (__bf16)p;
-                    un[kk][j] = (__bf16)(p * ((dp[r] - d8[j]) * scale));
-                }
+                for (int off = 1; off < 64; off <<= 1) { const int x = __shfl_up(before, off); before += lane >= off ? x : 0; }
+                for (int u = 0; u < units; ++u) list[n + before - units + u] = (uint16_t)(4 * i + u);
+                n += __shfl(before, 63);
             }
-        };
-        auto second_level = [&]() {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
-                    dv[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[kk], gb[nt * 2 + kk], dv[nt], 0, 0, 0);
-                    dk[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua[kk], qb_[nt * 2 + kk], dk[nt], 0, 0, 0);
-                }
-        };
-        read_a(0);
-        for (int mt = 0; mt < n_units; ++mt) {
-            __builtin_amdgcn_sched_barrier(0);
-            f32x16 s, dp;
-            zero(s); zero(dp);
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[ks], kf[ks], s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga[ks], vf[ks], dp, 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (mt + 1 < n_units) read_a(mt + 1);            // arrives under the element-wise part and the second-level products
-            __builtin_amdgcn_sched_barrier(0);
-            bf16x8 pn[2], un[2];
-            if (mt > 0) {
-                element_wise(mt, s, dp, pn, un);
-                second_level();
-#pragma unroll
-                for (int n = 0; n < 16; ++n) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-                }
-            } else {
-                element_wise(mt, s, dp, pn, un);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                gb[i] = frag_down(g_img, mt * 32 + 16 * (i & 1), (i >> 1) * 32, lane);
-                qb_[i] = frag_down(q_img, mt * 32 + 16 * (i & 1), (i >> 1) * 32, lane);
-            }
-            pa[0] = pn[0]; pa[1] = pn[1]; ua[0] = un[0]; ua[1] = un[1];
+            if (lane == 0) n_listed = n;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        second_level();                                      // of the block's last unit
-        buf ^= 1;
+        __syncthreads();
+        const int n_units = __builtin_amdgcn_readfirstlane(n_listed);
+        __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0), where the compiler sees it (see the query-side kernel)
+        if (n_units == 0) continue;
+
+        // Units 64 at a time, one per lane: raster token of the block's first token, vh | vw << 8 | unit of the block << 16,
+        // and the reciprocals that turn a token number into (frame, row, column).
+        int unit_origin = 0, unit_shape = 0, unit_mf = 0, unit_mr = 0;
+        auto refill = [&](int t) {
+            if ((t & 63) == 0 && t + lane < n_units) {
+                const int e = list[t + lane];
+                const BlockRef b = block_ref(g, qb0 + (e >> 2));
+                const BlockTokens bt(g, b.vh, b.vw);
+                unit_origin = (int)block_origin(g, b);
+                unit_shape = b.vh | b.vw << 8 | (e & 3) << 16;
+                unit_mf = (int)bt.m_frame;
+                unit_mr = (int)bt.m_row;
+            }
+        };
+        auto unit_tokens = [&](int t, int &origin, int &first) {
+            const int shape = __builtin_amdgcn_readlane(unit_shape, t & 63);
+            origin = __builtin_amdgcn_readlane(unit_origin, t & 63);
+            first = (shape >> 16) * 32;
+            return BlockTokens(shape & 0xff, shape >> 8 & 0xff, g.tt, __builtin_amdgcn_readlane(unit_mf, t & 63), __builtin_amdgcn_readlane(unit_mr, t & 63));
+        };
+        // Unit t on its way into stage `stage`: 8 rows of Q and of dO per wavefront of the second role (lane t supplies row
+        // t >> 4 of four).  Rows beyond the block's valid queries repeat its first one.
+        auto request_rows = [&](int t, int stage) {
+            if (t >= n_units) return;
+            refill(t);
+            int origin, first;
+            const BlockTokens bt = unit_tokens(t, origin, first);
+            const __bf16 *q_row = q + origin * q_st, *o_row = d_o + origin * o_st;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int l = fresh(lane), row = 8 * kg + 4 * i + (l >> 4);
+                const uint32_t chunk = ((l & 15) ^ sw(row)) * 16;
+                const uint32_t rel = rel_token(g, bt, first + row);
+                const uint32_t dst = lds_img + stage * 2 * kUnitBytes + (8 * kg + 4 * i) * 256;
+                copy_rows_to_lds((const char *)(q_row + rel * (uint64_t)q_st) + chunk, dst);
+                copy_rows_to_lds((const char *)(o_row + rel * (uint64_t)o_st) + chunk, dst + kUnitBytes);
+            }
+        };
+        // lse (lanes 0..7) and D (lanes 8..15) of 8 rows per wavefront of the first role: an ordinary load, stored to the
+        // stage when it has arrived.  (As direct-to-LDS loads of single dwords these made every slot twice as long.)
+        // Stored as the kernel uses them, -lse log2(e) and -scale D; padding queries get an infinite lse: probability zero.
+        float stat = 0.f;
+        auto request_stats = [&](int t) {
+            if (t >= n_units) return;
+            refill(t);
+            int origin, first;
+            const BlockTokens bt = unit_tokens(t, origin, first);
+            const int i = first + 8 * kg + (lane & 7);
+            const int64_t tok = (int64_t)(origin + rel_token(g, bt, i)) * g.heads + head;
+            if (lane < 16) stat = (lane < 8 ? lse : delta)[tok] * (lane < 8 ? -kLog2e : -scale);
+            if (lane < 8 && i >= bt.n_valid) stat = -__builtin_inff();
+        };
+        auto store_stats = [&](int stage) {
+            if (lane < 16) row_lds[stage][lane >> 3][8 * kg + (lane & 7)] = stat;
+        };
+        // The second role's copies of all units but the two requested last have landed, and every wavefront is done with the slot.
+        auto end_of_slot = [&](bool draining) {
+            if (p_role) asm volatile("s_barrier" ::: "memory");
+            else if (draining) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+        };
+        auto wrap = [](int stage) { return stage >= kStages ? stage - kStages : stage; };
+
+        if (p_role)
+            { for (int t = 0; t < kStatLead; ++t) { request_stats(t); store_stats(t); } lds_done(); }
+        else
+            for (int t = 0; t < kLead; ++t) request_rows(t, t);
+        end_of_slot(n_units < kLead);                        // units 0 and 1 are in LDS
+
+        // The slots are alike; what a first or last one would take from a unit that does not exist is either multiplied by
+        // the zeros p and u start with (tile rows: of unit 0 instead) or never used.
+        // Lane = key ql of this wavefront; register 8 kk + j = query 16 kk + 8 half + j of the unit.
+        bf16x8 w[2];                                         // P(t - 1) or U(t - 2)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[i][j] = (__bf16)0.f;
+        f32x16 x;                                            // S(t) or T(t - 1)
+        zero(x);
+        if (!wave_on) {
+#pragma unroll 1
+            for (int t = 0, now = 0; t < n_units + 2; ++t, now = wrap(now + 1)) {
+                if (p_role) { request_stats(t + kStatLead); store_stats(wrap(now + kStatLead)); lds_done(); }
+                else request_rows(t + kLead, wrap(now + kLead));
+                end_of_slot(t + kLead >= n_units);
+            }
+        } else if (p_role) {
+            first_level(img[0][0], rows, own, x);
+            bf16x8 cols[8];                                  // of unit t - 1
+            float4 l4[4];                                    // of unit t, quads 0 and 1 read ahead
+            read_columns(img[0][1], columns, cols);
+            l4[0] = row_quad(row_lds[0][0], half, 0);
+            l4[1] = row_quad(row_lds[0][0], half, 1);
+#pragma unroll 1
+            for (int t = 0, now = 0; t <= n_units; ++t, now = wrap(now + 1)) {
+                request_stats(t + kStatLead);
+                bf16x8 xa[8], wn[2];
+                const unsigned char *next = img[wrap(now + 1)][0];
+                const int base = fresh(rows);
+                l4[2] = row_quad(row_lds[now][0], half, 2);
+                l4[3] = row_quad(row_lds[now][0], half, 3);
+#pragma unroll
+                for (int n = 0; n < 8; ++n) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
+                    xa[n] = frag(next, base, n);
+#pragma unroll
+                    for (int e = 2 * n; e < 2 * n + 2; ++e) {
+                        x[e] = __builtin_amdgcn_exp2f(fmaf(x[e], scale_log2, (&l4[e >> 2].x)[e & 3]));
+                        wn[e >> 3][e & 7] = (__bf16)x[e];
+                    }
+                    if (n & 1) p_lds[t & 1][kg][n >> 1][lane] = make_float4(x[2 * n - 2], x[2 * n - 1], x[2 * n], x[2 * n + 1]);
+                }
+                pin(wn);
+                store_stats(wrap(now + kStatLead));
+                const int col_base = fresh(columns);
+                zero(x);
+#pragma unroll
+                for (int n = 0; n < 8; ++n) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[n], own[n], x, 0, 0, 0);
+                    cols[n] = frag_down(img[now][1], col_base, n >> 1, n & 1);      // for the next slot: these need not wait for the barrier
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                w[0] = wn[0]; w[1] = wn[1];
+                // P(t) and the stored row values are in LDS once all but the 15 LDS operations issued last are done
+                asm volatile("s_waitcnt lgkmcnt(15)" ::: "memory");
+                l4[0] = row_quad(row_lds[wrap(now + 1)][0], half, 0);
+                l4[1] = row_quad(row_lds[wrap(now + 1)][0], half, 1);
+                end_of_slot(t + kLead >= n_units);
+            }
+            end_of_slot(true);
+        } else {
+            bf16x8 cols[8];                                  // of unit t - 2
+            read_columns(img[0][0], columns, cols);
+#pragma unroll 1
+            for (int t = 0, now = 0; t < n_units + 2; ++t, now = wrap(now + 1)) {
+                bf16x8 xa[8], wn[2];
+                float4 p4[4], d4[4];
+                const float *d_rows = row_lds[wrap(now + kStages - 1)][1];
+                const int base = fresh(rows);
+#pragma unroll
+                for (int r4 = 0; r4 < 2; ++r4) { p4[r4] = p_lds[(t & 1) ^ 1][kg][r4][lane]; d4[r4] = row_quad(d_rows, half, r4); }
+                request_rows(t + kLead, wrap(now + kLead));
+#pragma unroll
+                for (int n = 0; n < 8; ++n) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
+                    xa[n] = frag(img[now][1], base, n);
+                    if (n < 2) { p4[n + 2] = p_lds[(t & 1) ^ 1][kg][n + 2][lane]; d4[n + 2] = row_quad(d_rows, half, n + 2); }
+#pragma unroll
+                    for (int e = 2 * n; e < 2 * n + 2; ++e)
+                        wn[e >> 3][e & 7] = (__bf16)((&p4[e >> 2].x)[e & 3] * fmaf(x[e], scale, (&d4[e >> 2].x)[e & 3]));
+                }
+                pin(wn);
+                const unsigned char *before = img[t == 0 ? 0 : wrap(now + kStages - 1)][0];
+                const int col_base = fresh(columns);
+                zero(x);
+#pragma unroll
+                for (int n = 0; n < 8; ++n) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[n], own[n], x, 0, 0, 0);
+                    cols[n] = frag_down(before, col_base, n >> 1, n & 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (t > 0) { w[0] = wn[0]; w[1] = wn[1]; }
+                end_of_slot(t + kLead >= n_units);
+            }
+        }
     }
     // tile nt: lane = channel nt*32 + ql, register r = key row 8 (r >> 2) + 4 half + (r & 3) of this wavefront
+    float *out = p_role ? d_v : d_k;
+    const BlockTokens kt(g, kr.vh, kr.vw);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int ki = 32 * wave + 8 * (r >> 2) + 4 * half + (r & 3);
+        const int ki = 32 * kg + 8 * (r >> 2) + 4 * half + (r & 3);
         if (ki < kr.n_valid) {
-            const int64_t o = (token_of(g, kr, ki) * g.heads + head) * 128 + ql;
+            const int64_t o = ((block_origin(g, kr) + rel_token(g, kt, ki)) * g.heads + head) * 128 + ql;
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) { d_k[o + nt * 32] = dk[nt][r]; d_v[o + nt * 32] = dv[nt][r]; }
+            for (int nt = 0; nt < 4; ++nt) out[o + nt * 32] = acc[nt][r];
         }
     }
 }
@@ -575,23 +675,13 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
                                 const void *d_o, int64_t o_st, int64_t o_sh, const float *lse,
                                 float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream) {
     const int q_per_xcd = (g.q_groups * g.nb * g.heads + 7) / 8, k_per_xcd = (kv_groups * g.nb * g.heads + 7) / 8;
-    const dim3 grid_q(q_per_xcd * 8), grid_k(k_per_xcd * 8);
-    bwd_delta_mfma_kernel<<<grid_q, 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
-                                                      kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, delta, scale, q_per_xcd);
-    hipError_t e = hipGetLastError();
+    bwd_dq_mfma_kernel<<<dim3(q_per_xcd * 8), 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
+                                                                kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, d_q, delta, scale, q_per_xcd);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    bwd_dq_mfma_kernel<<<grid_q, kThreads, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
-                                                           kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, d_q, delta, scale, q_per_xcd);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (q_st == o_st && q_sh == o_sh)
-        bwd_dkv_mfma_kernel<true><<<grid_k, kThreads, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
-                                                                   kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, delta,
-                                                                   d_k, d_v, scale, k_per_xcd);
-    else
-        bwd_dkv_mfma_kernel<false><<<grid_k, kThreads, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
-                                                                    kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, delta,
-                                                                    d_k, d_v, scale, k_per_xcd);
+    bwd_dkv_mfma_kernel<<<dim3(k_per_xcd * 8), 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
+                                                                 kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, delta,
+                                                                 d_k, d_v, scale, k_per_xcd);
     return hipGetLastError();
 }
 
