@@ -42,7 +42,8 @@ __device__ inline BlockRef block_ref(const KGeom &g, int block) {
     b.n_valid = g.tt * b.vh * b.vw;
     return b;
 }
-// raster token of block token i; rows beyond the valid ones repeat the block's first token (they are masked)
+// raster token of block token i; rows beyond the valid ones repeat the block's first token (their probability is zero; what
+// it multiplies is read from zero_row)
 __device__ inline int64_t token_of(const KGeom &g, const BlockRef &b, const BlockTokens &bt, int i) {
     int ft, r, c;
     if (!bt.at(i, ft, r, c)) ft = r = c = 0;
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(
             const int64_t at = token_of(g, kr, kt, first + m) * kv_st;
             RowFrag<T, NT> kf, vf;
             kf.load(k + at, g.d, g4);
-            vf.load(v + at, g.d, g4);
+            vf.load(first + m < kr.n_valid ? v + at : (const T *)zero_row, g.d, g4);
             also(kr, kt, first);
             p = RowFrag<T, NT>::mma(kf, qf, f32x4{0.f, 0.f, 0.f, 0.f});
             t = RowFrag<T, NT>::mma(vf, gf, f32x4{0.f, 0.f, 0.f, 0.f});
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_kernel(
                 for (int r = 0; r < 4; ++r) {
                     const int64_t tok = token_of(g, qr, qt, first + 4 * g4 + r);
                     qc.load(r, q + tok * q_st, g.d, m);
-                    gc.load(r, d_o + tok * o_st, g.d, m);
+                    gc.load(r, first + 4 * g4 + r < qr.n_valid ? d_o + tok * o_st : (const T *)zero_row, g.d, m);
                     l2[r] = lse[tok * g.heads + head] * kLog2e;
                     D[r] = delta[tok * g.heads + head];      // written by bwd_dq_kernel, earlier on the stream
                 }

@@ -122,9 +122,10 @@ __device__ inline void load_own_rows(const KGeom &g, const BlockRef &b, const __
 // A wavefront copies 16 rows of a tile with 4 instructions; instruction i moves rows 16 wave + 4 i .. + 3, lane t
 // supplying row (t >> 4), chunk position (t & 15).  A CopyPlan holds, for the 4 rows of a lane, the byte distance of the
 // lane's 16 bytes from the block's first token: made once for the unclipped extent, so that a block costs one 64-bit
-// addition per row; clipped blocks make their own.  Rows beyond the block's valid tokens repeat its first one: their
-// probabilities are set to zero, so what they hold never reaches a result.
+// addition per row; clipped blocks make their own.  Rows beyond the block's valid tokens are copied from zero_row: their
+// probabilities are zero, and zero times an infinity of another row would not be.
 constexpr int kWaves = 8;
+__device__ __attribute__((aligned(256))) const unsigned char zero_row[256] = {};
 struct CopyPlan { int64_t at[4]; };
 __device__ inline CopyPlan copy_plan(const KGeom &g, int vh, int vw, int64_t st, int wave, int lane) {
     CopyPlan p;
@@ -155,17 +156,27 @@ __device__ inline int valid_tokens(const KGeom &g, const Located &b) { return g.
 // This wavefront's rows of the tiles of block `b` of two tensors (K and V, or Q and dO), each with its plan.
 __device__ inline void copy_tiles(const KGeom &g, const Located &b, const CopyPlan &full0, const CopyPlan &full1, int wave, int lane,
                                   const __bf16 *__restrict__ x0, int64_t st0, const __bf16 *__restrict__ x1, int64_t st1, uint32_t lds0) {
-    CopyPlan p0 = full0, p1 = full1;
-    if (b.extent != (g.th | g.tw << 16)) {                   // workgroup-uniform
-        p0 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st0, wave, lane);
-        p1 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st1, wave, lane);
-    }
     const char *b0 = (const char *)(x0 + b.origin * st0), *b1 = (const char *)(x1 + b.origin * st1);
+    const char *s0[4], *s1[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { s0[i] = b0 + full0.at[i]; s1[i] = b1 + full1.at[i]; }
+    if (b.extent != (g.th | g.tw << 16)) {                   // workgroup-uniform
+        const CopyPlan p0 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st0, wave, lane);
+        const CopyPlan p1 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st1, wave, lane);
+        const int n = valid_tokens(g, b);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool ok = 16 * wave + 4 * i + (lane >> 4) < n;
+            const char *none = (const char *)zero_row + (lane & 15) * 16;
+            s0[i] = ok ? b0 + p0.at[i] : none;
+            s1[i] = ok ? b1 + p1.at[i] : none;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t rows = (uint32_t)(16 * wave + 4 * i) * 256;
-        copy_rows_to_lds(b0 + p0.at[i], lds0 + rows);
-        copy_rows_to_lds(b1 + p1.at[i], lds0 + kTileBytes + rows);
+        copy_rows_to_lds(s0[i], lds0 + rows);
+        copy_rows_to_lds(s1[i], lds0 + kTileBytes + rows);
     }
 }
 
@@ -500,7 +511,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
             return BlockTokens(shape & 0xff, shape >> 8 & 0xff, g.tt, __builtin_amdgcn_readlane(unit_mf, t & 63), __builtin_amdgcn_readlane(unit_mr, t & 63));
         };
         // Unit t on its way into stage `stage`: 8 rows of Q and of dO per wavefront of the second role (lane t supplies row
-        // t >> 4 of four).  Rows beyond the block's valid queries repeat its first one.
+        // t >> 4 of four).  Rows beyond the block's valid queries repeat its first one in Q (an infinity there makes the
+        // gradients of the same keys NaN in any case) and are zeros in dO.
         auto request_rows = [&](int t, int stage) {
             if (t >= n_units) return;
             refill(t);
@@ -514,7 +526,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
                 const uint32_t rel = rel_token(g, bt, first + row);
                 const uint32_t dst = lds_img + stage * 2 * kUnitBytes + (8 * kg + 4 * i) * 256;
                 copy_rows_to_lds((const char *)(q_row + rel * (uint64_t)q_st) + chunk, dst);
-                copy_rows_to_lds((const char *)(o_row + rel * (uint64_t)o_st) + chunk, dst + kUnitBytes);
+                copy_rows_to_lds((first + row < bt.n_valid ? (const char *)(o_row + rel * (uint64_t)o_st) : (const char *)zero_row) + chunk, dst + kUnitBytes);
             }
         };
         // lse (lanes 0..7) and D (lanes 8..15) of 8 rows per wavefront of the first role: an ordinary load, stored to the
@@ -549,7 +561,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
         end_of_slot(n_units < kLead);                        // units 0 and 1 are in LDS
 
         // The slots are alike; what a first or last one would take from a unit that does not exist is either multiplied by
-        // the zeros p and u start with (tile rows: of unit 0 instead) or never used.
+        // the zeros p and u start with (dO rows: zeros too; Q rows: of unit 0 instead) or never used.
         // Lane = key ql of this wavefront; register 8 kk + j = query 16 kk + 8 half + j of the unit.
         bf16x8 w[2];                                         // P(t - 1) or U(t - 2)
 #pragma unroll
@@ -569,7 +581,10 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
             first_level(img[0][0], rows, own, x);
             bf16x8 cols[8];                                  // of unit t - 1
             float4 l4[4];                                    // of unit t, quads 0 and 1 read ahead
-            read_columns(img[0][1], columns, cols);
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cols[n][j] = (__bf16)0.f;
             l4[0] = row_quad(row_lds[0][0], half, 0);
             l4[1] = row_quad(row_lds[0][0], half, 1);
 #pragma unroll 1

@@ -82,10 +82,13 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
                 const int n = g.tt * min(g.th, g.H - kby * g.th) * min(g.tw, g.W - kbx * g.tw);
                 left[i] = i0 + i < total ? n - first : 0;
                 const int64_t base = ((int64_t)cache_slot(c, g, start, head, grp) * g.nb + kt) * g.bt;
-                // rows beyond the block's bt (bt not a multiple of 16) repeat its last one; they are masked
+                // rows beyond the block's bt (bt not a multiple of 16) repeat its last key, which is masked, and have no value
                 kf[i].load(k_head + (base + min(first + m, g.bt - 1)) * g.d, g.d, g4);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) vf[i].load(r, v_head + (base + min(first + 4 * g4 + r, g.bt - 1)) * g.d, g.d, m);
+                for (int r = 0; r < 4; ++r) {
+                    const int j = first + 4 * g4 + r;
+                    vf[i].load(r, j < g.bt && i0 + i < total ? v_head + (base + j) * g.d : (const T *)zero_row, g.d, m);
+                }
             }
 #pragma unroll
             for (int s = 0; s < QS; ++s) {

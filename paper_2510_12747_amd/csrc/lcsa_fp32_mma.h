@@ -26,6 +26,10 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// A row of zeros.  A row that is not there enters a second-level product with weight zero; it is loaded from here and not
+// from a neighbour, whose infinities would turn into NaN.
+static __device__ __attribute__((aligned(16))) float zero_row[256];      // not const: a select between two address spaces would load flat
+
 // A row of up to 16 NT channels, spread over the four lanes (m, g = 0..3); channels from d on are zero.
 template <typename T, int NT> struct RowFrag;
 template <int NT> struct RowFrag<float, NT> {

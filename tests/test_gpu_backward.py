@@ -153,3 +153,26 @@ def test_backward_is_deterministic_and_rejects_bad_arguments():
         B.lcsa_sparse_attn_bwd(g, t, kv, kv, 1, si, sc, t, lse)      # fewer key frames than the chunk has
     dq, dk, dv, _ = B.lcsa_sparse_attn_bwd(g, t, kv, kv, 6, si, sc, t, lse)   # nothing kept anywhere: all zeros
     assert not dq.any() and not dk.any() and not dv.any()
+
+
+@pytest.mark.parametrize("dtype,d,tile", [("fp32", 32, (4, 5)), ("bf16", 128, (8, 16))])
+def test_an_infinite_output_gradient_stays_in_its_channel(dtype, d, tile):
+    """Every block's first token has +inf in dO's channel 0, on a grid whose last blocks are clipped: dV is +inf there for
+    every key (all blocks kept, every probability positive), never NaN from a row that weighs nothing, and unchanged elsewhere."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    h, w, frames, dt = tile[0] + 3, tile[1] + 2, 2, torch.float32 if dtype == "fp32" else torch.bfloat16
+    g = B.Geom(2, d, h, w, tile[0], tile[1], 1, frames, -1, -1, 8, dtype=B.LCSA_F32 if dtype == "fp32" else B.LCSA_BF16)
+    q, k, v, d_o = (torch.randn(n * h * w, 2, d, generator=gen, device="cuda").to(dt) for n in (1, frames, frames, 1))
+    cache = B.lcsa_cache_init(g)
+    B.lcsa_kv_cache_append(cache, k, v, frames)
+    _, sel_idx, sel_cnt, _ = B.lcsa_pool_select_blocks(g, q, cache)
+    assert (sel_cnt == 8).all()
+    lse = torch.empty(h * w, 2, device="cuda")
+    B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
+    d_vs = []
+    for planted in (False, True):
+        if planted:
+            d_o.view(h, w, 2, d)[::tile[0], ::tile[1], :, 0] = float("inf")
+        d_vs.append(B.lcsa_sparse_attn_bwd(g, q, k, v, frames, sel_idx, sel_cnt, d_o, lse)[2])
+    assert (d_vs[1][..., 0] == float("inf")).all()
+    assert torch.equal(d_vs[0][..., 1:], d_vs[1][..., 1:])

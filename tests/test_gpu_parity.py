@@ -677,3 +677,23 @@ def test_v_beyond_half_range_is_clamped_and_counted():
     assert int(B.lcsa_cache_v_clamped(cache).sum()) == sum(planted) > 0       # all three chunks are still visible
     mx, mean = check_outputs(o, q, K, np.clip(V, -65504.0, 65504.0), og, 6, s_idx, s_cnt, None, bf16_relative=True, large_v=True)
     say(f"V clamped: {sum(planted)} values, max-abs {mx:.3e}")
+
+
+@pytest.mark.parametrize("dtype,tile,topk", [("fp32", (3, 5), 5), ("bf16", (3, 5), 4), ("fp32", (4, 8), 3)])
+def test_general_path_an_infinite_value_stays_in_its_channel(dtype, tile, topk):
+    """Every block's last token has +inf in V's channel 0: with every probability positive the output is +inf there (matrix
+    rows beyond a block or a selection weigh nothing and must not turn it into NaN) and unchanged elsewhere."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    h, w, frames, dt = 3 * tile[0], 3 * tile[1], 4, torch.float32 if dtype == "fp32" else torch.bfloat16
+    g = B.Geom(2, 32, h, w, tile[0], tile[1], 2, frames, -1, -1, topk, dtype=B.LCSA_F32 if dtype == "fp32" else B.LCSA_BF16)
+    q, k, v = (torch.randn(n * h * w, 2, 32, generator=gen, device="cuda").to(dt) for n in (2, frames, frames))
+    outs = []
+    for planted in (False, True):
+        if planted:
+            v.view(frames, 3, tile[0], 3, tile[1], 2, 32)[:, :, -1, :, -1, :, 0] = float("inf")
+        cache = B.lcsa_cache_init(g)
+        B.lcsa_kv_cache_append(cache, k, v, frames)
+        _, sel_idx, sel_cnt, _ = B.lcsa_pool_select_blocks(g, q, cache)
+        outs.append(B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt).float())
+    assert (outs[1][..., 0] == float("inf")).all()
+    assert torch.equal(outs[0][..., 1:], outs[1][..., 1:])
