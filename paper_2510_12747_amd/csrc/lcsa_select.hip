@@ -6,6 +6,7 @@
 // in ascending order with ballot prefix counts.  No sort, no atomics, fully deterministic.
 #include "lcsa_kernels.h"
 #include "lcsa_pool.h"
+#include <type_traits>
 
 namespace lcsa {
 namespace {
@@ -130,48 +131,56 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
         }
         written = n;
     } else {
-        // T = k-th largest key: the largest value with at least k keys >= it (32-step bitwise search)
-        uint32_t T = 0;
-        if (n <= 128) {
-            // the common case (a window of at most 21 tiles over 6 frames): two keys per lane in registers
-            const uint32_t k0 = lane < n ? keys[lane] : 0u, k1 = lane + 64 < n ? keys[lane + 64] : 0u;   // finite floats map to keys > 0
-            for (int bit = 31; bit >= 0; --bit) {
-                const uint32_t trial = T | (1u << bit);
-                if (wave_count(k0 >= trial) + wave_count(k1 >= trial) >= k) T = trial;
+        // Keys of the row, PER_LANE in registers of each lane; PER_LANE = 0: read from LDS each time.  The search looks at every
+        // key 32 times, one look waiting for the other: from LDS that is a round trip per 64 keys each time (a layer
+        // call with 504 candidates a row: 329 us, 313 with 8 keys per lane; up to 128 candidates were in registers before).
+        // 512 candidates cover the windows in use; a row with more takes the LDS loop.
+        uint32_t T = 0, below = 0;                       // k-th largest key; largest key < T (0 if none; keys of finite floats are > 0)
+        int n_ge = 0;
+        auto search = [&](auto per_lane) {
+            constexpr int PER_LANE = decltype(per_lane)::value;
+            uint32_t held[PER_LANE ? PER_LANE : 1];
+            auto each = [&](auto &&look) {               // look(candidate, key), 64 ascending candidates at a time
+                if constexpr (PER_LANE > 0) {
+#pragma unroll
+                    for (int i = 0; i < PER_LANE; ++i) look(i * 64 + lane, held[i]);
+                } else {
+                    for (int ci = lane; ci - lane < n; ci += 64) look(ci, ci < n ? keys[ci] : 0u);
+                }
+            };
+            if constexpr (PER_LANE > 0) {
+#pragma unroll
+                for (int i = 0; i < PER_LANE; ++i) held[i] = i * 64 + lane < n ? keys[i * 64 + lane] : 0u;
             }
-        } else {
+            // the largest value with at least k keys >= it (32-step bitwise search; trial > 0, so the zeros beyond n never count)
             for (int bit = 31; bit >= 0; --bit) {
                 const uint32_t trial = T | (1u << bit);
                 int cnt = 0;
-                for (int base = 0; base < n; base += 64) {
-                    const int ci = base + lane;
-                    cnt += wave_count(ci < n && keys[ci] >= trial);
-                }
+                each([&](int, uint32_t key) { cnt += wave_count(key >= trial); });
                 if (cnt >= k) T = trial;
             }
-        }
-        int n_gt = 0, n_ge = 0;
-        uint32_t below = 0;                              // largest key < T (0 if none; keys of finite floats are > 0)
-        for (int base = 0; base < n; base += 64) {
-            const int ci = base + lane;
-            const uint32_t key = ci < n ? keys[ci] : 0u;
-            n_gt += wave_count(ci < n && key > T);
-            n_ge += wave_count(ci < n && key >= T);
-            if (ci < n && key < T && key > below) below = key;
-        }
-        const int need = k - n_gt;                       // how many of the blocks tied at T are kept (>= 1)
-        int eq_seen = 0;
-        for (int base = 0; base < n; base += 64) {
-            const int ci = base + lane;
-            const uint32_t key = ci < n ? keys[ci] : 0u;
-            const bool gt = ci < n && key > T, eq = ci < n && key == T;
-            const uint64_t eq_mask = __ballot(eq);
-            const bool keep = gt || (eq && eq_seen + __popcll(eq_mask & lt_mask) < need);
-            const uint64_t keep_mask = __ballot(keep);
-            if (keep) { int f; const int t = tile_of(ci, f); out[written + __popcll(keep_mask & lt_mask)] = f * g.nb + t; }
-            written += __popcll(keep_mask);
-            eq_seen += __popcll(eq_mask);
-        }
+            int n_gt = 0;
+            each([&](int ci, uint32_t key) {
+                n_gt += wave_count(ci < n && key > T);
+                n_ge += wave_count(ci < n && key >= T);
+                if (ci < n && key < T && key > below) below = key;
+            });
+            const int need = k - n_gt;                   // how many of the blocks tied at T are kept (>= 1)
+            int eq_seen = 0;
+            each([&](int ci, uint32_t key) {
+                const bool gt = ci < n && key > T, eq = ci < n && key == T;
+                const uint64_t eq_mask = __ballot(eq);
+                const bool keep = gt || (eq && eq_seen + __popcll(eq_mask & lt_mask) < need);
+                const uint64_t keep_mask = __ballot(keep);
+                if (keep) { int f; const int t = tile_of(ci, f); out[written + __popcll(keep_mask & lt_mask)] = f * g.nb + t; }
+                written += __popcll(keep_mask);
+                eq_seen += __popcll(eq_mask);
+            });
+        };
+        if (n <= 128) search(std::integral_constant<int, 2>{});
+        else if (n <= 256) search(std::integral_constant<int, 4>{});
+        else if (n <= 512) search(std::integral_constant<int, 8>{});
+        else search(std::integral_constant<int, 0>{});
         if (gap) {
             if (n_ge > k) row_gap = 0.f;
             else {

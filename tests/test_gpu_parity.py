@@ -697,3 +697,25 @@ def test_general_path_an_infinite_value_stays_in_its_channel(dtype, tile, topk):
         outs.append(B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt).float())
     assert (outs[1][..., 0] == float("inf")).all()
     assert torch.equal(outs[0][..., 1:], outs[1][..., 1:])
+
+
+@pytest.mark.parametrize("rows,cols", [(4, 8), (3, 11), (8, 8), (5, 13), (8, 16), (3, 43)])
+def test_selection_at_the_numbers_of_candidates_where_its_search_changes(rows, cols):
+    """4 frames of 32, 33, 64, 65, 128, 129 blocks without a window: rows of 128 to 516 candidates, on either side of the
+    numbers of keys a lane holds.  Every row against a stable sort of its scores, and rows whose scores are all tied."""
+    h, w = 4 * rows, 4 * cols
+    g = B.Geom(2, 32, h, w, 4, 4, 2, 4, -1, -1, 7, dtype=B.LCSA_F32)
+    gen = torch.Generator(device="cuda").manual_seed(rows * cols)
+    cache = B.lcsa_cache_init(g)
+    # whole numbers, small enough for exact sums in any order: scores repeat, and ties must go to the lower id
+    pk = torch.randint(-2, 3, (4, rows, cols, 2, 32), generator=gen, device="cuda").float()
+    k = pk.repeat_interleave(4, 1).repeat_interleave(4, 2).reshape(-1, 2, 32).contiguous()
+    B.lcsa_kv_cache_append(cache, k, k, 4)
+    pq = torch.randint(-2, 3, (2, g.n_qb, 32), generator=gen, device="cuda").float()
+    pq[0] = 0.0
+    sel_idx, sel_cnt, gap = B.lcsa_select_blocks(g, pq, cache)
+    scores = (pq.cpu() @ pk.reshape(-1, 2, 32).permute(1, 2, 0).cpu().contiguous())
+    order = torch.sort(scores, dim=-1, descending=True, stable=True)
+    assert (sel_cnt == 7).all()
+    assert torch.equal(sel_idx.cpu().long(), order.indices[..., :7].sort(dim=-1).values)
+    assert torch.equal(gap.cpu(), order.values[..., 6] - order.values[..., 7])
