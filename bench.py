@@ -442,7 +442,7 @@ def trivial_loops(torch, aids):
 
 def extensions(torch, B, wl):
     """The calls beside the forward path, timed briefly: the backward of the attention (matrix-core kernels at
-    small-video and paper scale, the float FMA kernels at small-video scale) and the fused rotary embedding +
+    small-video and paper scale, the float kernels at small-video scale) and the fused rotary embedding +
     pooling of a paper-scale chunk's queries (bound by HBM)."""
     out = {}
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]

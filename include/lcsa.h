@@ -61,7 +61,7 @@ enum { LCSA_F32 = 0, LCSA_BF16 = 1 };
 enum { LCSA_WINDOW_TRUNCATED = 0, LCSA_WINDOW_PRESERVED = 1 };
 /* KV-cache eviction (appendix on KV-cache eviction): sliding window (the paper's default), or by
  * importance, decided per head or once for all heads of the layer */
-/* arithmetic of lcsa_sparse_attn_bwd: matrix cores where a kernel exists for the shape, or float FMA everywhere */
+/* arithmetic of lcsa_sparse_attn_bwd: matrix cores where a kernel exists for the shape, or float products everywhere */
 enum { LCSA_BWD_AUTO = 0, LCSA_BWD_FLOAT = 1 };
 enum { LCSA_EVICT_SLIDING = 0, LCSA_EVICT_IMPORTANCE_HEADWISE = 1, LCSA_EVICT_IMPORTANCE_UNIFORM = 2 };
 
@@ -274,11 +274,11 @@ int32_t lcsa_sparse_attn_fwd(const lcsa_geom *geom,
  * All results are written in full (zeros where no kept pair reaches).  scale <= 0 selects 1/sqrt(head_dim).
  * arithmetic = LCSA_BWD_AUTO: for bf16, head_dim 128 and 128-token blocks the products run on the matrix cores (bf16
  * operands, float accumulation; probabilities and their gradients are rounded to bf16 between the two levels of
- * products: results within a few 1e-3 of the largest gradient), every other shape in float FMA arithmetic.
- * LCSA_BWD_FLOAT: float FMA arithmetic for every shape (results within 2e-5 of the largest gradient; slow).
+ * products: results within a few 1e-3 of the largest gradient), every other shape in float products.
+ * LCSA_BWD_FLOAT: float products for every shape (results within 2e-5 of the largest gradient; slower).
  * Either way the summation orders are fixed: results are reproducible bit for bit.
  * The float kernels return LCSA_EUNSUPPORTED if 2 * (tokens per block) * head_dim floats (a key block's
- * accumulators) exceed the LDS.
+ * gradients) exceed 160 KB.
  */
 int32_t lcsa_sparse_attn_bwd(const lcsa_geom *geom,
                              const void *q, int64_t q_stride_tok, int64_t q_stride_head,
