@@ -49,6 +49,17 @@ class Geom:
     window_mode: int = WINDOW_TRUNCATED
     tile_t: int = 1          # frames per block; (tile_t, tile_h, tile_w) = (2, 8, 8) is the paper's partition
 
+    def _ref(self):
+        """The geometry as the library's calls take it.  Its fields cannot change, so the struct is made once: building it
+        anew was 1.5 us of each call."""
+        c = self.__dict__.get("_c")
+        if c is None:
+            c = self.__dict__["_c"] = self.c()
+        return ctypes.byref(c)
+
+    def __getstate__(self):
+        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+
     def c(self) -> lcsa_geom:
         return lcsa_geom(self.heads, self.head_dim, self.grid_h, self.grid_w, self.tile_h, self.tile_w, self.tile_t,
                          self.q_frames, self.cache_frames, self.radius_h, self.radius_w, self.window_mode,
@@ -135,7 +146,8 @@ def _check(status: int, what: str) -> None:
 
 def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without the Stream object around it (1.5 us of each call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -209,8 +221,7 @@ def lcsa_block_importance(geom: Geom, pooled_q: torch.Tensor, cache: Cache, scal
     """Scores the visible groups for the next append; returns the view lcsa_cache_importance gives."""
     assert pooled_q.is_contiguous() and pooled_q.dtype == torch.float32
     assert pooled_q.shape == (geom.heads, geom.n_qb, geom.head_dim)
-    g = geom.c()
-    _check(lib().lcsa_block_importance(ctypes.byref(g), pooled_q.data_ptr(), cache.handle, scale, _stream(stream)),
+    _check(lib().lcsa_block_importance(geom._ref(), pooled_q.data_ptr(), cache.handle, scale, _stream(stream)),
            "lcsa_block_importance")
     return lcsa_cache_importance(cache)
 
@@ -219,8 +230,7 @@ def lcsa_block_importance_static(geom: Geom, pooled_q: torch.Tensor, cache: Cach
     """lcsa_block_importance with the library's static scratch array (allocates nothing)."""
     assert pooled_q.is_contiguous() and pooled_q.dtype == torch.float32
     assert pooled_q.shape == (geom.heads, geom.n_qb, geom.head_dim)
-    g = geom.c()
-    _check(lib().lcsa_block_importance_static(ctypes.byref(g), pooled_q.data_ptr(), cache.handle, scale, _stream(stream)),
+    _check(lib().lcsa_block_importance_static(geom._ref(), pooled_q.data_ptr(), cache.handle, scale, _stream(stream)),
            "lcsa_block_importance_static")
     return lcsa_cache_importance(cache)
 
@@ -281,8 +291,7 @@ def lcsa_pool_blocks(geom: Geom, x: torch.Tensor, n_frames: int, pooled: torch.T
     if pooled is None:
         pooled = torch.empty(geom.heads, n_blocks, geom.head_dim, dtype=torch.float32, device=x.device)
     assert pooled.is_contiguous() and pooled.dtype == torch.float32 and pooled.numel() == geom.heads * n_blocks * geom.head_dim
-    g = geom.c()
-    _check(lib().lcsa_pool_blocks(ctypes.byref(g), xp, st, sh, n_frames, pooled.data_ptr(), _stream(stream)), "lcsa_pool_blocks")
+    _check(lib().lcsa_pool_blocks(geom._ref(), xp, st, sh, n_frames, pooled.data_ptr(), _stream(stream)), "lcsa_pool_blocks")
     return pooled
 
 
@@ -300,8 +309,7 @@ def lcsa_rope_pool_blocks(geom: Geom, x: torch.Tensor, n_frames: int, pairs, bas
     if pooled is None:
         pooled = torch.empty(geom.heads, n_blocks, geom.head_dim, dtype=torch.float32, device=x.device)
     assert pooled.is_contiguous() and pooled.dtype == torch.float32 and pooled.numel() == geom.heads * n_blocks * geom.head_dim
-    g = geom.c()
-    _check(lib().lcsa_rope_pool_blocks(ctypes.byref(g), xp, st, sh, n_frames, pairs[0], pairs[1], pairs[2], base, first_frame,
+    _check(lib().lcsa_rope_pool_blocks(geom._ref(), xp, st, sh, n_frames, pairs[0], pairs[1], pairs[2], base, first_frame,
                                        rp, rst, rsh, pooled.data_ptr(), _stream(stream)), "lcsa_rope_pool_blocks")
     return x_rot, pooled
 
@@ -319,8 +327,7 @@ def lcsa_select_blocks(geom: Geom, pooled_q: torch.Tensor, cache: Cache, sel_idx
         gap = torch.empty(geom.heads, n_qb, dtype=torch.float32, device=dev)
     assert sel_idx.is_contiguous() and sel_cnt.is_contiguous() and sel_idx.dtype == torch.int32 and sel_cnt.dtype == torch.int32
     assert sel_idx.numel() == geom.heads * n_qb * geom.topk and sel_cnt.numel() == geom.heads * n_qb
-    g = geom.c()
-    _check(lib().lcsa_select_blocks(ctypes.byref(g), pooled_q.data_ptr(), cache.handle, sel_idx.data_ptr(),
+    _check(lib().lcsa_select_blocks(geom._ref(), pooled_q.data_ptr(), cache.handle, sel_idx.data_ptr(),
                                     sel_cnt.data_ptr(), gap.data_ptr() if gap is not None else None,
                                     _stream(stream)), "lcsa_select_blocks")
     return sel_idx, sel_cnt, gap
@@ -345,8 +352,7 @@ def lcsa_pool_select_blocks(geom: Geom, q: torch.Tensor, cache: Cache, pooled_q=
     assert pooled_q.is_contiguous() and pooled_q.dtype == torch.float32 and pooled_q.numel() == geom.heads * n_qb * geom.head_dim
     assert sel_idx.is_contiguous() and sel_cnt.is_contiguous() and sel_idx.dtype == torch.int32 and sel_cnt.dtype == torch.int32
     assert sel_idx.numel() == geom.heads * n_qb * geom.topk and sel_cnt.numel() == geom.heads * n_qb
-    g = geom.c()
-    _check(lib().lcsa_pool_select_blocks(ctypes.byref(g), qp, qst, qsh, cache.handle, pooled_q.data_ptr(), sel_idx.data_ptr(),
+    _check(lib().lcsa_pool_select_blocks(geom._ref(), qp, qst, qsh, cache.handle, pooled_q.data_ptr(), sel_idx.data_ptr(),
                                          sel_cnt.data_ptr(), gap.data_ptr() if gap is not None else None,
                                          _stream(stream)), "lcsa_pool_select_blocks")
     return pooled_q, sel_idx, sel_cnt, gap
@@ -366,8 +372,7 @@ def lcsa_sparse_attn_fwd(geom: Geom, q: torch.Tensor, cache: Cache, sel_idx: tor
     assert sel_idx.numel() == geom.heads * geom.n_qb * geom.topk
     if lse is not None:
         assert lse.is_contiguous() and lse.dtype == torch.float32 and lse.shape == (q.shape[0], geom.heads)
-    g = geom.c()
-    _check(lib().lcsa_sparse_attn_fwd(ctypes.byref(g), qp, qst, qsh, cache.handle, sel_idx.data_ptr(), sel_cnt.data_ptr(),
+    _check(lib().lcsa_sparse_attn_fwd(geom._ref(), qp, qst, qsh, cache.handle, sel_idx.data_ptr(), sel_cnt.data_ptr(),
                                       op, ost, osh, lse.data_ptr() if lse is not None else None, scale,
                                       _stream(stream)), "lcsa_sparse_attn_fwd")
     return o
@@ -377,7 +382,7 @@ def lcsa_sparse_attn_bwd(geom: Geom, q: torch.Tensor, k: torch.Tensor, v: torch.
                          sel_idx: torch.Tensor, sel_cnt: torch.Tensor, d_o: torch.Tensor,
                          lse: torch.Tensor, scale: float = 0.0, float_path: bool = False, stream=None):
     """Gradients (d_q, d_k, d_v), float32 [tokens][heads][d], of the attention on the kept pairs, and delta [tokens][heads].
-    float_path: float FMA kernels for every shape (LCSA_BWD_FLOAT) instead of the matrix cores where they apply."""
+    float_path: kernels with float products for every shape (LCSA_BWD_FLOAT) instead of the matrix cores where they apply."""
     qp, qst, qsh = _tok(q)
     kp, kst, ksh = _tok(k)
     vp, vst, vsh = _tok(v)
@@ -396,8 +401,7 @@ def lcsa_sparse_attn_bwd(geom: Geom, q: torch.Tensor, k: torch.Tensor, v: torch.
     d_k = torch.empty(k.shape, dtype=torch.float32, device=q.device)
     d_v = torch.empty(k.shape, dtype=torch.float32, device=q.device)
     delta = torch.empty(q.shape[0], geom.heads, dtype=torch.float32, device=q.device)
-    g = geom.c()
-    _check(lib().lcsa_sparse_attn_bwd(ctypes.byref(g), qp, qst, qsh, kp, vp, kst, ksh, kv_frames, sel_idx.data_ptr(),
+    _check(lib().lcsa_sparse_attn_bwd(geom._ref(), qp, qst, qsh, kp, vp, kst, ksh, kv_frames, sel_idx.data_ptr(),
                                       sel_cnt.data_ptr(), gp, gst, gsh, lse.data_ptr(), d_q.data_ptr(), d_k.data_ptr(),
                                       d_v.data_ptr(), delta.data_ptr(), scale, 1 if float_path else 0, _stream(stream)),
            "lcsa_sparse_attn_bwd")
