@@ -397,8 +397,9 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
             // the final normalisation; it only has to keep 2^(score - reference) inside half's range.
             // The first block sets it to its exact row maximum; later blocks reuse it without looking
             // for their maximum (which would cost a pass over all scores) and are checked afterwards:
-            // see the end of P4.
-            if (it == 0) m_run = block_row_max(sacc, nf) * scale_log2;
+            // see the end of P4.  It is kept finite: a first block whose scores are all -inf (masked keys) weighs nothing,
+            // and the check moves the reference to the first block that does.
+            if (it == 0) m_run = fmaxf(block_row_max(sacc, nf) * scale_log2, -__FLT_MAX__);
         }
         if (k_copy) { copy_piece_to_lds(ksrc, copy_voff, kdst, 2); copy_piece_to_lds(ksrc, copy_voff, kdst, 3); }
         if (on && wave_on) {

@@ -362,6 +362,35 @@ def test_an_item_split_over_the_two_groups_of_a_workgroup(heads, topk, grid):
     run_primed(w, rows=None if heads < 3 else sample_rows(og, 40), check_lse=True)
 
 
+@pytest.mark.parametrize("masked", [(0,), (1,), (1, 2), (0, 1, 2, 3, 4, 5)])
+def test_blocks_whose_scores_are_all_minus_infinity_weigh_nothing(masked):
+    """Keys of whole blocks masked with -inf in a channel where every query is positive: such a block weighs nothing wherever it
+    stands in a row's list (first of the row, first of the list's second half, all of them), and no NaN comes of it."""
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    h, w, frames, heads = 16, 48, 1, 2
+    g = B.Geom(heads, 128, h, w, 8, 16, 1, frames, -1, -1, 6, dtype=B.LCSA_BF16)
+    q, k, v = (torch.randn(h * w, heads, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    q[..., 0] = 1.0
+    rows, cols = torch.arange(h, device="cuda")[:, None] // 8, torch.arange(w, device="cuda")[None, :] // 16
+    block = (rows * 3 + cols).reshape(-1)
+    hit = torch.isin(block, torch.tensor(masked, device="cuda"))
+    k[hit, :, 0] = float("-inf")
+    cache = B.lcsa_cache_init(g)
+    B.lcsa_kv_cache_append(cache, k, v, frames)
+    sel_idx = torch.arange(6, dtype=torch.int32, device="cuda").repeat(heads, g.n_qb, 1)
+    sel_cnt = torch.full((heads, g.n_qb), 6, dtype=torch.int32, device="cuda")
+    lse = torch.empty(h * w, heads, device="cuda")
+    o = B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
+    if hit.all():
+        assert not o.any() and (lse == float("-inf")).all()
+        return
+    s = torch.einsum("qhd,khd->hqk", q.cpu().double(), k[~hit].cpu().double()) / 128 ** 0.5
+    want = torch.einsum("hqk,khd->qhd", torch.softmax(s, -1), v[~hit].cpu().double())
+    err = (o.cpu().double() - want).abs()
+    assert (err <= 2.0 ** -8 * want.abs() + 2e-3).all()          # half an ulp of the result and the kernel's own budget
+    torch.testing.assert_close(lse.cpu().double(), torch.logsumexp(s, -1).T, rtol=0, atol=1e-5)
+
+
 # ---- the paper's own block shape: (2, 8, 8) = two frames x 8 x 8 tokens (Sec. 3.2) ----------------------
 
 def test_paper_block_shape_2x8x8_small_grid_all_rows():
