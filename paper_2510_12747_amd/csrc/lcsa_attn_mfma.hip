@@ -34,6 +34,7 @@
 // chunk j of row r at chunk position j ^ (r & 15): conflict-free ds_read_b128 operand reads)
 // and are streamed in with direct-to-LDS loads that stay in flight across barriers:
 // V(i) arrives during QK(i)+SM(i), K(i+1) during SM(i)+PV(i).
+#include "lcsa_attn_form.h"
 #include "lcsa_kernels.h"
 
 namespace lcsa {
@@ -145,16 +146,17 @@ __device__ inline uint32_t pack_block(const KGeom &g, const KCache &c, int start
 }
 __device__ inline int block_keys(uint32_t blk) { return (int)(blk >> 24) + 1; }
 
-// SPLIT: one work item per workgroup, its selected blocks dealt out to the two groups in turn (group g takes blocks
-// g, g + 2, ...), each group with a softmax of its own; at the end the groups exchange halves of their accumulators
-// through LDS and each finishes 64 of the 128 channels.
-template <bool SPLIT>
+// FORM: kAttnPairs, or one work item per workgroup.  Split: the item's selected blocks are dealt out to the two groups in turn
+// (group g takes blocks g, g + 2, ...), each group with a softmax of its own; at the end the groups exchange halves of their
+// accumulators through LDS and each finishes 64 of the 128 channels.  Alone: group 1 only keeps the barriers company.
+template <AttnForm FORM>
 __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     KGeom g, KCache c, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     __bf16 *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse,
-    float scale_log2, int total_items, int pairs_per_xcd) {
+    float scale_log2, int total_items, int wg_per_xcd) {
     __shared__ __attribute__((aligned(16))) unsigned char lds_all[2][2][kTileBytes];   // [group][K, V]
+    constexpr bool SPLIT = FORM == kAttnSplit, ALONE = FORM == kAttnAlone;
     __shared__ float2 softmax_all[SPLIT ? 2 : 1][128];                                 // SPLIT: [group][query] reference and sum
     LCSA_STAMP(0)
 
@@ -162,9 +164,9 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     // items (same head, neighbouring tiles, both query frames) so that K/V tiles shared by
     // neighbouring windows are found in that XCD's L2.
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-    const int total_pairs = SPLIT ? total_items : (total_items + 1) >> 1;
-    const int pair = xcd * pairs_per_xcd + idx;
-    if (pair >= total_pairs) return;
+    const int work = FORM == kAttnPairs ? (total_items + 1) >> 1 : total_items;        // workgroups with work
+    const int wg = xcd * wg_per_xcd + idx;
+    if (wg >= work) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int grp8 = __builtin_amdgcn_readfirstlane(tid >> 8);        // which group of 4 wavefronts
@@ -180,8 +182,8 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
         const int tile = rem / g.q_groups, fq = rem - tile * g.q_groups;   // items ordered (head, tile, group)
         qb = fq * g.nb + tile;
     };
-    const int item = SPLIT ? pair : 2 * pair + grp8;
-    const int other = SPLIT ? pair : 2 * pair + (grp8 ^ 1);
+    const int item = SPLIT ? wg : ALONE ? (grp8 == 0 ? wg : total_items) : 2 * wg + grp8;
+    const int other = SPLIT ? wg : ALONE ? (grp8 == 0 ? total_items : wg) : 2 * wg + (grp8 ^ 1);
     // entry of the row's id list that is this group's block number i
     auto listed = [&](int i) { return SPLIT ? 2 * i + grp8 : i; };
     const bool active = item < total_items;
@@ -544,24 +546,16 @@ hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int6
     int n_cu = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
-    // A workgroup holds a compute unit to itself, so a launch takes as many rounds as it has workgroups per unit, each as
-    // long as the blocks of two items (pairs) or of half of that (split).  Split where its rounds end earlier: always up to
-    // one item per unit, then for total in (2, 3] x units, (4, 5] x units and so on.  Measured on 48 x 96 tokens, k = 32,
-    // 256 units: 216 items 82 us as one idle group per workgroup, 65 split; 576 items 207 us in pairs, 173 split; 1080 items
-    // 328 and 298; in between (504, 864, 1008 items) the rounds are equally long and pairs set up and finish once less.
-    const int rounds_split = (total + n_cu - 1) / n_cu, rounds_pairs = ((total + 1) / 2 + n_cu - 1) / n_cu;
-    if (rounds_split < 2 * rounds_pairs) {
-        const int per_xcd = (total + 7) / 8;
-        attn_mfma_kernel<true><<<dim3(per_xcd * 8), 512, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,
-                                                                      (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e,
-                                                                      total, per_xcd);
-    } else {
-        const int pairs = (total + 1) / 2;
-        const int per_xcd = (pairs + 7) / 8;
-        attn_mfma_kernel<false><<<dim3(per_xcd * 8), 512, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,
-                                                                       (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e,
-                                                                       total, per_xcd);
-    }
+    const int admissible = max_candidates(g, c.valid);
+    const AttnForm form = attn_form(total, n_cu, g.topk < admissible ? g.topk : admissible);
+    const int per_xcd = (attn_workgroups(form, total) + 7) / 8;
+#define LCSA_CALL(FORM)                                                                                                    \
+    attn_mfma_kernel<FORM><<<dim3(per_xcd * 8), 512, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,     \
+                                                                  (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e, total, per_xcd)
+    if (form == kAttnPairs) LCSA_CALL(kAttnPairs);
+    else if (form == kAttnSplit) LCSA_CALL(kAttnSplit);
+    else LCSA_CALL(kAttnAlone);
+#undef LCSA_CALL
     return hipGetLastError();
 }
 

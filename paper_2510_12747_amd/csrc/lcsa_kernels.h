@@ -175,9 +175,6 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
                                 const void *d_o, int64_t o_st, int64_t o_sh, const float *lse,
                                 float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream);
 
-// Largest number of admissible key blocks of any query block (host arithmetic).
-int max_candidates(const KGeom &g, int valid_groups);
-
 // Window of tile index b along one axis: [*lo, *hi).
 __host__ __device__ inline void axis_window(int b, int tile, int n, int radius, int mode, int *lo, int *hi) {
     if (radius < 0) { *lo = 0; *hi = n; return; }
@@ -193,6 +190,14 @@ __host__ __device__ inline void axis_window(int b, int tile, int n, int radius, 
         if (s > n - size) s = n - size;
         *lo = s; *hi = s + size;
     }
+}
+
+// Largest number of admissible key blocks of any query block (host arithmetic).
+inline int max_candidates(const KGeom &g, int valid_groups) {
+    int my = 0, mx = 0;
+    for (int b = 0; b < g.ty; ++b) { int lo, hi; axis_window(b, g.th, g.ty, g.rh, g.wmode, &lo, &hi); if (hi - lo > my) my = hi - lo; }
+    for (int b = 0; b < g.tx; ++b) { int lo, hi; axis_window(b, g.tw, g.tx, g.rw, g.wmode, &lo, &hi); if (hi - lo > mx) mx = hi - lo; }
+    return my * mx * valid_groups;
 }
 
 } // namespace lcsa

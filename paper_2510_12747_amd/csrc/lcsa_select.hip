@@ -201,13 +201,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
 
 } // namespace
 
-int max_candidates(const KGeom &g, int valid_groups) {
-    int my = 0, mx = 0;
-    for (int b = 0; b < g.ty; ++b) { int lo, hi; axis_window(b, g.th, g.ty, g.rh, g.wmode, &lo, &hi); if (hi - lo > my) my = hi - lo; }
-    for (int b = 0; b < g.tx; ++b) { int lo, hi; axis_window(b, g.tw, g.tx, g.rw, g.wmode, &lo, &hi); if (hi - lo > mx) mx = hi - lo; }
-    return my * mx * valid_groups;
-}
-
 hipError_t launch_select(const KGeom &g, const KCache &c, const float *pooled_q,
                          int32_t *sel_idx, int32_t *sel_cnt, float *gap, int max_cand, hipStream_t stream) {
     dim3 grid(g.q_groups * g.nb * g.heads);

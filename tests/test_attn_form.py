@@ -1,0 +1,55 @@
+"""CPU check of the rule that deals a launch's work items out to workgroups (csrc/lcsa_attn_form.h), against the measured
+times of the launch forms in profiles/: where the rule says so, the other form is not faster by more than the runs differ."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PAIRS, SPLIT, ALONE = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("form")
+    src, lib = tmp / "form.cpp", tmp / "form.so"
+    src.write_text('#include "lcsa_attn_form.h"\n'
+                   'extern "C" int form(int items, int units, int k) { return lcsa::attn_form(items, units, k); }\n'
+                   'extern "C" int workgroups(int form, int items) { return lcsa::attn_workgroups((lcsa::AttnForm)form, items); }\n')
+    subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2510_12747_amd", "csrc"),
+                    "-o", str(lib), str(src)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+def measured():
+    """(items, k, {form: us}) of every row of the two tables"""
+    forms = None
+    for line in open(os.path.join(ROOT, "profiles", "attn_mfma_kernel_split_and_paired_items.txt")):
+        f = line.split()
+        if f[:1] == ["items"]:
+            forms = [c for c in f if c in ("alone", "pairs", "split")]
+            at = {c: f.index(c) for c in forms + ["k"]}
+        elif forms and f:
+            if f[0].isdigit():
+                yield int(f[0]), int(f[at["k"]]), {c: float(f[at[c]]) for c in forms}
+
+
+def test_the_rule_never_picks_a_form_that_was_measured_slower(rule):
+    names = {PAIRS: "pairs", SPLIT: "split", ALONE: "alone"}
+    rows = list(measured())
+    assert len(rows) > 150
+    for items, k, us in rows:
+        form = names[rule.form(items, 256, k)]
+        assert us[form] <= 1.025 * min(us.values()), (items, k, form, us)
+
+
+def test_edges_of_the_rule(rule):
+    for units in (1, 32, 256, 304):
+        for k in (1, 2, 3, 64, 1 << 24):
+            assert rule.form(1, units, k) == rule.form(units, units, k) == (SPLIT if k > 2 else ALONE)
+            assert rule.form(units + 1, units, k) == rule.form(2 * units, units, k) == PAIRS      # one round of pairs
+            assert rule.form(4 * units, units, k) == PAIRS                                        # 4 rounds against 2
+            assert rule.form(1 << 30, units, k) == PAIRS
+    assert rule.form(3 * 256, 256, 1 << 30) == SPLIT                      # no overflow
+    assert [rule.workgroups(f, 7) for f in (PAIRS, SPLIT, ALONE)] == [4, 7, 7]

@@ -350,16 +350,50 @@ def test_more_than_64_selected_blocks_refills_the_id_chunk():
 
 
 @pytest.mark.parametrize("heads,topk,grid", [
-    (2, 1, (24, 44)),          # one group of the workgroup has no block
+    (2, 1, (24, 44)),          # one block: an item on one group, the other idle
+    (2, 2, (24, 44)),          # two: the same
     (2, 3, (21, 37)),          # two blocks against one; clipped query blocks leave wavefronts without rows
     (1, 192, (64, 64)),        # 96 blocks per group: each refills its id chunk
-    (29, 7, (24, 44)),         # 522 items on 256 compute units: several rounds of split items
+    (29, 7, (24, 44)),         # 522 items on 256 compute units, rows too short to split: two items per workgroup
+    (29, 8, (24, 44)),         # three rounds of split items
     (15, 7, (24, 44)),         # 270 items: two items per workgroup again
 ])
 def test_an_item_split_over_the_two_groups_of_a_workgroup(heads, topk, grid):
     w = wl.with_overrides(wl.WORKLOADS["small"], name=f"split-{heads}-{topk}", heads=heads, grid_h=grid[0], grid_w=grid[1], radius=-1, topk=topk)
     _, og = geoms(w)
     run_primed(w, rows=None if heads < 3 else sample_rows(og, 40), check_lse=True)
+
+
+def masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse):
+    """Checks o and lse of one frame against float64 on the blocks sel_idx[..., :sel_cnt]; keys of -inf weigh nothing."""
+    for head in range(q.shape[1]):
+        for b in range(int(block.max()) + 1):
+            ids = sel_idx[head, b, :int(sel_cnt[head, b])].long()
+            rows, keys = block == b, torch.isin(block, ids) & (k[:, head, 0] != float("-inf"))
+            s = q[rows, head].double() @ k[keys, head].double().T.contiguous() / q.shape[-1] ** 0.5
+            if not keys.any():
+                assert not o[rows, head].any() and (lse[rows, head] == float("-inf")).all()
+                continue
+            want = torch.softmax(s, -1) @ v[keys, head].double()
+            # half an ulp of the result and the kernel's own budget
+            assert ((o[rows, head].double() - want).abs() <= 2.0 ** -8 * want.abs() + 2e-3).all()
+            torch.testing.assert_close(lse[rows, head].double(), torch.logsumexp(s, -1), rtol=0, atol=1e-5)
+
+
+def test_rows_that_keep_fewer_blocks_than_a_split_launch_shares_out():
+    """Row counts 0 to 6 in a launch laid out for 6: none, one (the second group has nothing), odd and even shares."""
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    h, w, heads = 16, 48, 3
+    g = B.Geom(heads, 128, h, w, 8, 16, 1, 1, -1, -1, 6, dtype=B.LCSA_BF16)
+    q, k, v = (torch.randn(h * w, heads, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    block = (torch.arange(h, device="cuda")[:, None] // 8 * 3 + torch.arange(w, device="cuda")[None, :] // 16).reshape(-1)
+    cache = B.lcsa_cache_init(g)
+    B.lcsa_kv_cache_append(cache, k, v, 1)
+    sel_idx = torch.arange(6, dtype=torch.int32, device="cuda").repeat(heads, g.n_qb, 1)
+    sel_cnt = (torch.arange(heads * g.n_qb, device="cuda", dtype=torch.int32) % 7).reshape(heads, g.n_qb).contiguous()
+    lse = torch.empty(h * w, heads, device="cuda")
+    o = B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
+    masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse)
 
 
 @pytest.mark.parametrize("masked", [(0,), (1,), (1, 2), (0, 1, 2, 3, 4, 5)])
@@ -371,8 +405,7 @@ def test_blocks_whose_scores_are_all_minus_infinity_weigh_nothing(masked):
     g = B.Geom(heads, 128, h, w, 8, 16, 1, frames, -1, -1, 6, dtype=B.LCSA_BF16)
     q, k, v = (torch.randn(h * w, heads, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
     q[..., 0] = 1.0
-    rows, cols = torch.arange(h, device="cuda")[:, None] // 8, torch.arange(w, device="cuda")[None, :] // 16
-    block = (rows * 3 + cols).reshape(-1)
+    block = (torch.arange(h, device="cuda")[:, None] // 8 * 3 + torch.arange(w, device="cuda")[None, :] // 16).reshape(-1)
     hit = torch.isin(block, torch.tensor(masked, device="cuda"))
     k[hit, :, 0] = float("-inf")
     cache = B.lcsa_cache_init(g)
@@ -381,14 +414,7 @@ def test_blocks_whose_scores_are_all_minus_infinity_weigh_nothing(masked):
     sel_cnt = torch.full((heads, g.n_qb), 6, dtype=torch.int32, device="cuda")
     lse = torch.empty(h * w, heads, device="cuda")
     o = B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
-    if hit.all():
-        assert not o.any() and (lse == float("-inf")).all()
-        return
-    s = torch.einsum("qhd,khd->hqk", q.cpu().double(), k[~hit].cpu().double()) / 128 ** 0.5
-    want = torch.einsum("hqk,khd->qhd", torch.softmax(s, -1), v[~hit].cpu().double())
-    err = (o.cpu().double() - want).abs()
-    assert (err <= 2.0 ** -8 * want.abs() + 2e-3).all()          # half an ulp of the result and the kernel's own budget
-    torch.testing.assert_close(lse.cpu().double(), torch.logsumexp(s, -1).T, rtol=0, atol=1e-5)
+    masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse)
 
 
 # ---- the paper's own block shape: (2, 8, 8) = two frames x 8 x 8 tokens (Sec. 3.2) ----------------------
