@@ -70,8 +70,10 @@ class Aids:
             vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
             self.lib.bench_probe_mfma_bf16.argtypes = [vp, i32, i32, vp]
             self.lib.bench_mock_loop.argtypes = [i32, vp, vp, i32, i32, vp]
-            self.lib.bench_attn_timed.argtypes = [vp, vp, i64, i64, vp, vp, vp, vp, i64, i64, f32, vp, vp]
-            for f in (self.lib.bench_probe_mfma_bf16, self.lib.bench_mock_loop, self.lib.bench_attn_timed):
+            self.lib.bench_attn_timed.argtypes = [vp, vp, i64, i64, vp, vp, vp, vp, i64, i64, f32, vp, i32, vp]
+            self.lib.bench_attn_workgroups.argtypes = [vp, vp, ctypes.POINTER(i32)]
+            for f in (self.lib.bench_probe_mfma_bf16, self.lib.bench_mock_loop, self.lib.bench_attn_timed,
+                      self.lib.bench_attn_workgroups):
                 f.restype = i32
 
 
@@ -342,16 +344,17 @@ def attn_timers(torch, B, aids, live):
     main loop, -DLCSA_TIMERS=1) slow its loop by 16 %, so the aid is built with entry and exit stamps only."""
     g, L = live["g"], live["layers"][0]
     q = L["chunks"][(L["turn"] - 1) % len(L["chunks"])][0]
-    total = g.heads * g.n_qb
-    n_wg = 8 * -(-((total + 1) // 2) // 8)
+    gc, form = g.c(), ctypes.c_int32()
+    n_wg = aids.lib.bench_attn_workgroups(ctypes.byref(gc), L["cache"].handle, ctypes.byref(form))
+    if n_wg < 0:
+        return None
     stamps = torch.zeros(n_wg, 10, dtype=torch.int64, device="cuda")
-    gc = g.c()
     cnt = L["sel_cnt"].cpu().numpy()
     for _ in range(3):                                   # the last of three launches is read (the first ones warm up)
         stamps.zero_()
         rc = aids.lib.bench_attn_timed(ctypes.byref(gc), q.data_ptr(), q.stride(0), q.stride(1), L["cache"].handle,
                                        L["sel_idx"].data_ptr(), L["sel_cnt"].data_ptr(), L["o"].data_ptr(),
-                                       L["o"].stride(0), L["o"].stride(1), 0.0, stamps.data_ptr(),
+                                       L["o"].stride(0), L["o"].stride(1), 0.0, stamps.data_ptr(), n_wg,
                                        torch.cuda.current_stream().cuda_stream)
         if rc != 0:
             return None
@@ -362,7 +365,8 @@ def attn_timers(torch, B, aids, live):
         return None
     clk = lambda a, b: (t[:, 2 * b] - t[:, 2 * a])                    # shader cycles between stamps a and b
     wall = lambda a, b: (t[:, 2 * b + 1] - t[:, 2 * a + 1]) * 10.0     # ns (100 MHz counter)
-    steps = int(cnt.max()) + 1                                         # loop iterations of a full workgroup
+    form = ("pairs", "split", "alone")[form.value]
+    steps = -(-int(cnt.max()) // (2 if form == "split" else 1)) + 1    # loop iterations of a full workgroup
     start_ns = (t[:, 1] - t[:, 1].min()) * 10.0
     first = start_ns < 0.25 * wall(0, 3).mean()                        # workgroups that started with the launch
 
@@ -377,8 +381,9 @@ def attn_timers(torch, B, aids, live):
 
     span = (t[:, 7].max() - t[:, 1].min()) * 10.0
     return {"kernel": "attn_mfma_kernel built with -DLCSA_TIMERS=2 (libbench_probe.so): stamps at entry and exit of every workgroup",
+            "items_per_workgroup": {"pairs": "two, one per group", "split": "one, shared by both groups", "alone": "one, on one group"}[form],
             "workgroups_that_ran": int(len(t)), "loop_steps_per_workgroup": steps,
-            "matrix_cycles_per_loop_step_per_simd": 4096,
+            "matrix_cycles_per_loop_step_per_simd": 2048 if form == "alone" else 4096,
             "first_stamp_to_last_stamp_us": round(float(span) / 1e3, 2),
             "started_with_the_launch": rnd(first), "started_later": rnd(~first)}
 

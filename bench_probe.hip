@@ -147,16 +147,37 @@ extern "C" int32_t bench_mock_loop(int32_t variant, float *out, const void *src,
 }
 
 // ---- 3. the attention kernel with per-workgroup time stamps -------------------------------------------------------
-// Arguments as lcsa_sparse_attn_fwd (matrix-core configurations only, else -2); timers: device uint64
-// [workgroups][10] (workgroups = 8 * ceil(ceil(heads*n_qb/2)/8)), per workgroup: shader-clock and 100 MHz counter
+namespace {
+lcsa::KGeom launch_geometry(const lcsa_geom *geom, const lcsa_cache *cache) {      // window and top-k are the call's own
+    lcsa::KGeom kg = cache->kg;
+    kg.topk = geom->topk;
+    kg.rh = geom->radius_h; kg.rw = geom->radius_w; kg.wmode = geom->window_mode;
+    return kg;
+}
+} // namespace
+
+// Number of workgroups of the launch (every one of them stamps its row, those without work too); *form: how items are dealt
+// out to them (AttnForm in lcsa_attn_form.h).  -1 on bad arguments, -2 where the matrix-core kernel does not run.
+extern "C" int32_t bench_attn_workgroups(const lcsa_geom *geom, const lcsa_cache *cache, int32_t *form) {
+    if (!geom || !cache || !form || cache->kc.valid * cache->kg.tt < geom->q_frames) return -1;
+    if (!cache->kc.mfma_layout) return -2;
+    const lcsa::AttnLaunch l = lcsa::attn_mfma_launch(launch_geometry(geom, cache), cache->kc);
+    *form = l.form;
+    return 8 * l.per_xcd;
+}
+
+// Arguments as lcsa_sparse_attn_fwd (matrix-core configurations only, else -2); timers: device uint64 [n_timers][10] with
+// n_timers >= bench_attn_workgroups (else -1 and no launch), per workgroup: shader-clock and 100 MHz counter
 // at entry, before the main loop, after it, at exit, then HW_ID | XCC_ID << 32, then unused.
 extern "C" int32_t bench_attn_timed(const lcsa_geom *geom, const void *q, int64_t q_st, int64_t q_sh, const lcsa_cache *cache,
                                     const int32_t *sel_idx, const int32_t *sel_cnt, void *o, int64_t o_st, int64_t o_sh,
-                                    float scale, uint64_t *timers, void *stream) {
+                                    float scale, uint64_t *timers, int32_t n_timers, void *stream) {
     if (!geom || !cache || !q || !o || !sel_idx || !sel_cnt || !timers) return -1;
-    if (!cache->kc.mfma_layout) return -2;
-    lcsa::KGeom kg = cache->kg;
-    kg.topk = geom->topk;
+    int32_t form;
+    const int32_t n_wg = bench_attn_workgroups(geom, cache, &form);
+    if (n_wg < 0) return n_wg;
+    if (n_timers < n_wg) return -1;
+    const lcsa::KGeom kg = launch_geometry(geom, cache);
     if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)kg.d);
     if (lcsa::set_attn_timers(timers) != hipSuccess) return -3;      // a synchronous copy to a device variable: fine for a measurement aid
     const hipError_t e = lcsa::launch_attn_mfma(kg, cache->kc, q, q_st, q_sh, sel_idx, sel_cnt, o, o_st, o_sh, nullptr, scale,

@@ -34,7 +34,6 @@
 // chunk j of row r at chunk position j ^ (r & 15): conflict-free ds_read_b128 operand reads)
 // and are streamed in with direct-to-LDS loads that stay in flight across barriers:
 // V(i) arrives during QK(i)+SM(i), K(i+1) during SM(i)+PV(i).
-#include "lcsa_attn_form.h"
 #include "lcsa_kernels.h"
 
 namespace lcsa {
@@ -539,16 +538,19 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
 
 } // namespace
 
-hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh,
-                            const int32_t *sel_idx, const int32_t *sel_cnt,
-                            void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
-    const int total = g.heads * g.nb * g.q_groups;
+AttnLaunch attn_mfma_launch(const KGeom &g, const KCache &c) {
     int n_cu = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
-    const int admissible = max_candidates(g, c.valid);
+    const int total = g.heads * g.nb * g.q_groups, admissible = max_candidates(g, c.valid);
     const AttnForm form = attn_form(total, n_cu, g.topk < admissible ? g.topk : admissible);
-    const int per_xcd = (attn_workgroups(form, total) + 7) / 8;
+    return {form, total, (attn_workgroups(form, total) + 7) / 8};
+}
+
+hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh,
+                            const int32_t *sel_idx, const int32_t *sel_cnt,
+                            void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
+    const auto [form, total, per_xcd] = attn_mfma_launch(g, c);
 #define LCSA_CALL(FORM)                                                                                                    \
     attn_mfma_kernel<FORM><<<dim3(per_xcd * 8), 512, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,     \
                                                                   (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e, total, per_xcd)

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "lcsa_attn_form.h"
 
 namespace lcsa {
 
@@ -151,6 +152,9 @@ hipError_t launch_attn_generic(const KGeom &g, const KCache &c, const void *q, i
                                void *o, int64_t o_st, int64_t o_sh, float *lse, float scale,
                                hipStream_t stream);
 
+// How launch_attn_mfma launches: 8 * per_xcd workgroups, on the current device.
+struct AttnLaunch { AttnForm form; int items, per_xcd; };
+AttnLaunch attn_mfma_launch(const KGeom &g, const KCache &c);
 hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh,
                             const int32_t *sel_idx, const int32_t *sel_cnt,
                             void *o, int64_t o_st, int64_t o_sh, float *lse, float scale,
