@@ -609,6 +609,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
                 }
                 pin(wn);
                 store_stats(wrap(now + kStatLead));
+                asm volatile("" ::: "memory");               // P(t) and the row values are written before the column reads below
                 const int col_base = fresh(columns);
                 zero(x);
 #pragma unroll
@@ -619,8 +620,9 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 w[0] = wn[0]; w[1] = wn[1];
-                // P(t) and the stored row values are in LDS once all but the 15 LDS operations issued last are done
-                asm volatile("s_waitcnt lgkmcnt(15)" ::: "memory");
+                // LDS operations of a wavefront end in order, and 16 of them (the column reads) follow the writes of P(t) and of
+                // the row values: with at most 14 in flight both writes are done.  (The counter has four bits: 15 is no wait.)
+                asm volatile("s_waitcnt lgkmcnt(14)" ::: "memory");
                 l4[0] = row_quad(row_lds[wrap(now + 1)][0], half, 0);
                 l4[1] = row_quad(row_lds[wrap(now + 1)][0], half, 1);
                 end_of_slot(t + kLead >= n_units);
