@@ -137,6 +137,20 @@ def test_backward_more_query_blocks_than_one_list_holds():
     run_backward(wl.with_overrides(wl.WORKLOADS["tiny"], name="bwd-many-blocks", head_dim=4, grid_h=132, grid_w=128, topk=2))
 
 
+def test_matrix_core_backward_with_more_query_blocks_than_one_list_holds():
+    """2 x 17 x 16 = 544 query blocks of 128 tokens: the key-side kernel lists them in two parts, and its ring of query units
+    starts anew on the accumulators of the first part (key blocks of the last tiles are kept by query blocks of both)."""
+    run_backward(wl.with_overrides(wl.WORKLOADS["small"], name="bwd-544-blocks", heads=1, grid_h=133, grid_w=250, q_frames=2,
+                                   cache_frames=2, radius=16, topk=3))
+
+
+@pytest.mark.parametrize("topk", [65, 130])
+def test_matrix_core_backward_with_more_than_64_kept_blocks(topk):
+    """16 frames of 9 blocks: the query-side kernel refills its chunk of 64 ids in both passes over the kept blocks, and goes
+    back to the first chunk in between; the key-side kernel looks its block up by binary search."""
+    run_backward(wl.with_overrides(wl.WORKLOADS["small"], name=f"bwd-topk{topk}", heads=1, q_frames=1, cache_frames=16, radius=-1, topk=topk))
+
+
 def test_backward_is_deterministic_and_rejects_bad_arguments():
     w = wl.with_overrides(wl.WORKLOADS["small"], name="bwd-det", heads=2, grid_h=16, grid_w=32, topk=4)
     a = run_backward(w)
