@@ -635,17 +635,19 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
             for (int t = 0, now = 0; t < n_units + 2; ++t, now = wrap(now + 1)) {
                 bf16x8 xa[8], wn[2];
                 float4 p4[4], d4[4];
-                const float *d_rows = row_lds[wrap(now + kStages - 1)][1];
+                // formed from the lane number on every trip: a base held across the loop was spilled, and its reload, for which the
+                // compiler waits with vmcnt(0), drained the copies that end_of_slot() keeps in flight
+                const float *d_rows = row_lds[wrap(now + kStages - 1)][1] + 8 * (fresh(lane) >> 5);
                 const int base = fresh(rows);
 #pragma unroll
-                for (int r4 = 0; r4 < 2; ++r4) { p4[r4] = p_lds[(t & 1) ^ 1][kg][r4][lane]; d4[r4] = row_quad(d_rows, half, r4); }
+                for (int r4 = 0; r4 < 2; ++r4) { p4[r4] = p_lds[(t & 1) ^ 1][kg][r4][lane]; d4[r4] = row_quad(d_rows, 0, r4); }
                 request_rows(t + kLead, wrap(now + kLead));
 #pragma unroll
                 for (int n = 0; n < 8; ++n) {
                     __builtin_amdgcn_sched_barrier(0);
                     acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
                     xa[n] = frag(img[now][1], base, n);
-                    if (n < 2) { p4[n + 2] = p_lds[(t & 1) ^ 1][kg][n + 2][lane]; d4[n + 2] = row_quad(d_rows, half, n + 2); }
+                    if (n < 2) { p4[n + 2] = p_lds[(t & 1) ^ 1][kg][n + 2][lane]; d4[n + 2] = row_quad(d_rows, 0, n + 2); }
 #pragma unroll
                     for (int e = 2 * n; e < 2 * n + 2; ++e)
                         wn[e >> 3][e & 7] = (__bf16)((&p4[e >> 2].x)[e & 3] * fmaf(x[e], scale, (&d4[e >> 2].x)[e & 3]));
