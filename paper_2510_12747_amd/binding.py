@@ -32,8 +32,12 @@ class lcsa_geom(ctypes.Structure):
         "radius_h", "radius_w", "window_mode", "topk", "dtype")]
 
 
+class _Struct:
+    __slots__ = ("_c",)      # beside a dataclass's __dict__: vars(), pickles and copies hold its fields only
+
+
 @dataclass(frozen=True)
-class Geom:
+class Geom(_Struct):
     heads: int
     head_dim: int
     grid_h: int
@@ -52,13 +56,14 @@ class Geom:
     def _ref(self):
         """The geometry as the library's calls take it.  Its fields cannot change, so the struct is made once: building it
         anew was 1.5 us of each call."""
-        c = self.__dict__.get("_c")
+        c = getattr(self, "_c", None)
         if c is None:
-            c = self.__dict__["_c"] = self.c()
+            c = self.c()
+            object.__setattr__(self, "_c", c)
         return ctypes.byref(c)
 
     def __getstate__(self):
-        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+        return self.__dict__
 
     def c(self) -> lcsa_geom:
         return lcsa_geom(self.heads, self.head_dim, self.grid_h, self.grid_w, self.tile_h, self.tile_w, self.tile_t,

@@ -1,7 +1,10 @@
 """CPU-only checks of the C ABI: the library loads, exports every declared symbol, and
 validates arguments on the host before touching the GPU."""
+import copy
 import ctypes
+import dataclasses
 import os
+import pickle
 import re
 
 import pytest
@@ -60,6 +63,15 @@ def test_cache_bytes_formula():
     assert paper288.nb == 66 and paper288.n_qb == 66
     assert B.lcsa_cache_device_bytes(paper288) == 2 * (12 * 3 * 66) * 128 * 128 * 2 + (12 * 3 * 66) * 128 * 4 \
         + eviction_state_bytes(12, 3, 66, 66)
+
+
+def test_a_geometry_that_was_used_holds_its_fields_only():
+    g = B.Geom(**PAPER)
+    g._ref()
+    assert B.Geom(**vars(g)) == g and hash(B.Geom(**vars(g))) == hash(g)
+    for other in (copy.copy(g), copy.deepcopy(g), pickle.loads(pickle.dumps(g)), dataclasses.replace(g)):
+        assert other == g and vars(other) == vars(g) and bytes(other._ref()._obj) == bytes(g.c())
+    assert dataclasses.replace(g, topk=7)._ref()._obj.topk == 7
 
 
 @pytest.mark.parametrize("field,value", [
