@@ -53,17 +53,22 @@ class Geom(_Struct):
     window_mode: int = WINDOW_TRUNCATED
     tile_t: int = 1          # frames per block; (tile_t, tile_h, tile_w) = (2, 8, 8) is the paper's partition
 
+    def __post_init__(self):
+        object.__setattr__(self, "_c", None)
+
     def _ref(self):
         """The geometry as the library's calls take it.  Its fields cannot change, so the struct is made once: building it
         anew was 1.5 us of each call."""
-        c = getattr(self, "_c", None)
-        if c is None:
-            c = self.c()
-            object.__setattr__(self, "_c", c)
-        return ctypes.byref(c)
+        if self._c is None:
+            object.__setattr__(self, "_c", self.c())
+        return ctypes.byref(self._c)
 
     def __getstate__(self):
         return self.__dict__
+
+    def __setstate__(self, state):
+        self.__dict__.update(state)
+        self.__post_init__()
 
     def c(self) -> lcsa_geom:
         return lcsa_geom(self.heads, self.head_dim, self.grid_h, self.grid_w, self.tile_h, self.tile_w, self.tile_t,
