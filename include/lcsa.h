@@ -244,7 +244,11 @@ int32_t lcsa_pool_select_blocks(const lcsa_geom *geom, const void *q, int64_t q_
  * formed from the stored element type with float accumulation and a float online
  * softmax; on the matrix-core path probabilities and V enter the second product as IEEE half
  * (range of V: see lcsa_kv_cache_append).
- * Rows with sel_cnt = 0 produce zeros (lse = -inf).  Counts outside [0, topk] and ids outside the
+ * On the matrix-core path the blocks of a row may be summed in two halves, each with a softmax of its own, merged at the
+ * end: where the number of rows of the call, the blocks a row keeps and the device's compute units make that faster.  The
+ * same call gives the same bits every time; the same row in a call of another size, or on a device with another number of
+ * units, may differ in the rounding of the result.
+ * Rows with sel_cnt = 0 produce zeros (lse = -inf); so do rows whose scores are all -inf.  Counts outside [0, topk] and ids outside the
  * visible blocks are clamped into range by the kernels (the row's result is then meaningless, but
  * nothing outside the cache is read).
  */
@@ -272,13 +276,14 @@ int32_t lcsa_sparse_attn_fwd(const lcsa_geom *geom,
  *               usually taken as d_o_i . o_i; it is formed from the kernel's own probabilities instead, because the
  *               forward's output rounded to bf16 would put a relative error of several 1e-3 into d_q and d_k
  * All results are written in full (zeros where no kept pair reaches).  scale <= 0 selects 1/sqrt(head_dim).
- * arithmetic = LCSA_BWD_AUTO: for bf16, head_dim 128 and 128-token blocks the products run on the matrix cores (bf16
- * operands, float accumulation; probabilities and their gradients are rounded to bf16 between the two levels of
- * products: results within a few 1e-3 of the largest gradient), every other shape in float products.
+ * arithmetic = LCSA_BWD_AUTO: for bf16, head_dim 128, 128-token blocks and at most 8192 query blocks per chunk the
+ * products run on the matrix cores (bf16 operands, float accumulation; probabilities and their gradients are rounded to
+ * bf16 between the two levels of products: results within a few 1e-3 of the largest gradient), every other shape in float
+ * products.
  * LCSA_BWD_FLOAT: float products for every shape (results within 2e-5 of the largest gradient; slower).
  * Either way the summation orders are fixed: results are reproducible bit for bit.
- * The float kernels return LCSA_EUNSUPPORTED if 2 * (tokens per block) * head_dim floats (a key block's
- * gradients) exceed 160 KB.
+ * The float path refuses (LCSA_EUNSUPPORTED) shapes with, for b tokens per block,
+ * (2 b head_dim + 8 b + 8 head_dim) * 4 + (query blocks per chunk) > 160 * 1024.
  */
 int32_t lcsa_sparse_attn_bwd(const lcsa_geom *geom,
                              const void *q, int64_t q_stride_tok, int64_t q_stride_head,

@@ -304,8 +304,8 @@ hipError_t launch(const KGeom &g, int kv_groups, const void *q, int64_t q_st, in
 
 } // namespace
 
-// Documented limit of these kernels (two float accumulator sets of a whole key block, per-wavefront rows and one flag per
-// query block within 160 KB): kept so that callers see the same shapes refused everywhere.
+// No resource limit of the kernels above, whose LDS does not depend on the block or on the number of query blocks: the shapes
+// whose key-block gradients, row values and query-block flags would exceed 160 KB have always been refused, and still are.
 bool attn_bwd_supported(const KGeom &g) {
     return ((size_t)2 * g.bt * g.d + 8 * g.bt + 8 * g.d) * sizeof(float) + (size_t)g.q_groups * g.nb <= 160 * 1024;
 }

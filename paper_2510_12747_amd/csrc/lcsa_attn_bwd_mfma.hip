@@ -45,7 +45,8 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int kTileBytes = 128 * 256;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxQueryBlocks = 8192;        // limit of these kernels; more query blocks go to the float kernels
+constexpr int kMaxQueryBlocks = 8192;        // more query blocks go to the float kernels.  No limit of the kernels below (they list any
+                                             // number, kListed at a time); it keeps the arithmetic that callers of such sizes have had
 constexpr int kListed = 512;                 // query blocks whose kept flags are turned into a list at a time
 
 #define LCSA_LDS __attribute__((address_space(3)))

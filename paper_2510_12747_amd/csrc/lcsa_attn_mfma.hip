@@ -1,9 +1,10 @@
 // Block-sparse flash attention on the gfx950 matrix cores (bf16, d = 128, 128-token blocks).
 //
 // Work item = one (head, query block): 128 query rows against its selected key blocks.
-// A workgroup has 8 wavefronts = two GROUPS of 4; each group owns one work item (the two
-// query blocks of the same spatial tile, which share their window), its own K and V tile
-// buffers in LDS, and wavefront w of a group owns query rows 32w .. 32w+31.
+// A workgroup has 8 wavefronts = two GROUPS of 4, each with its own K and V tile buffers in LDS;
+// wavefront w of a group owns query rows 32w .. 32w+31.  By the size of the launch (lcsa_attn_form.h)
+// each group owns one work item (the two query blocks of the same spatial tile, which share their
+// window), or both share one item's selected blocks, or one group owns the only item.
 //
 // Per selected key block a group runs
 //     QK   S^T = K Q^T        v_mfma_f32_32x32x16_bf16  (keys on the row axis, queries on lanes)

@@ -162,7 +162,8 @@ hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int6
 
 // Backward of the attention on the kept pairs (selection held fixed): d_q [q tokens][heads][d], d_k, d_v
 // [kv_groups*tt*H*W][heads][d], float, contiguous, written in full.  k, v: raster tensors of the visible frames,
-// oldest first; delta: float [q tokens][heads], receives D_i = sum_j p_ij (dO_i.v_j).  attn_bwd_supported: the key-block accumulators (2 * bt * d floats) must fit in LDS.
+// oldest first; delta: float [q tokens][heads], receives D_i = sum_j p_ij (dO_i.v_j).
+// attn_bwd_supported: (2 * bt * d + 8 * bt + 8 * d) * 4 + (query blocks) <= 160 * 1024, the shapes the float path accepts.
 bool attn_bwd_supported(const KGeom &g);
 hipError_t launch_attn_bwd(const KGeom &g, int kv_groups, const void *q, int64_t q_st, int64_t q_sh,
                            const void *k, const void *v, int64_t kv_st, int64_t kv_sh,
@@ -170,7 +171,8 @@ hipError_t launch_attn_bwd(const KGeom &g, int kv_groups, const void *q, int64_t
                            const void *d_o, int64_t o_st, int64_t o_sh, const float *lse,
                            float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream);
 
-// The same on the matrix cores (bf16, d = 128, 128-token blocks, at most 8192 query blocks per chunk): products in
+// The same on the matrix cores (bf16, d = 128, 128-token blocks; chunks of more than 8192 query blocks keep the float path's
+// arithmetic, see attn_bwd_mfma_supported): products in
 // bf16 with float accumulation, probabilities and their gradients rounded to bf16 between the two product levels.
 bool attn_bwd_mfma_supported(const KGeom &g);
 hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, int64_t q_st, int64_t q_sh,

@@ -134,7 +134,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
         // Keys of the row, PER_LANE in registers of each lane; PER_LANE = 0: read from LDS each time.  The search looks at every
         // key 32 times, one look waiting for the other: from LDS that is a round trip per 64 keys each time (a layer
         // call with 504 candidates a row: 329 us, 313 with 8 keys per lane; up to 128 candidates were in registers before).
-        // 512 candidates cover the windows in use; a row with more takes the LDS loop.
+        // 512 candidates cover, with 6 cached frames of 8 x 16-token tiles, windows of up to 85 tiles (9 x 9: radius 32 by 64);
+        // rows beyond that (12 cached frames and a 9 x 5 window: 540) take the LDS loop, as all beyond 128 did.
         uint32_t T = 0, below = 0;                       // k-th largest key; largest key < T (0 if none; keys of finite floats are > 0)
         int n_ge = 0;
         auto search = [&](auto per_lane) {

@@ -24,7 +24,7 @@ from paper_2510_12747_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-BARS = {"float": (2e-5, 2e-6),        # float FMA kernels, f32 and bf16 data alike
+BARS = {"float": (2e-5, 2e-6),        # kernels with float products, f32 and bf16 data alike
         "matrix": (6e-3, 6e-4)}       # matrix-core kernels: p and u enter the second-level products rounded to bf16
 
 
@@ -107,8 +107,7 @@ def test_backward_clipped_blocks_and_partly_filled_cache():
 
 
 def test_backward_each_tensor_with_strides_of_its_own():
-    """q token-major, dO head-major, K and V token-major: every tensor of the call is addressed through its own strides
-    (on the matrix cores the key-side kernel has a build of its own for Q and dO that do not share theirs)."""
+    """q token-major, dO head-major, K and V token-major: every tensor of the call is addressed through its own strides."""
     w = wl.with_overrides(wl.WORKLOADS["small"], name="bwd-strides", heads=2, grid_h=20, grid_w=40, radius=16, topk=6)
     run_backward(w, d_o_layout="htd")
 
