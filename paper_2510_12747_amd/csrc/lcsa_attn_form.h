@@ -11,21 +11,21 @@ enum AttnForm {
 };
 
 // A workgroup holds a compute unit to itself, so a launch takes rounds = ceil(workgroups / units), each as long as the blocks
-// of one workgroup plus a set-up and an epilogue that cost about 3.5 blocks: rounds_pairs * (k + 3.5) for pairs,
-// rounds_split * (ceil(k / 2) + 3.5) for split items (k: blocks of a full row).  Split only where that is less, i.e. for
-// items in (2 n, 2 n + 1] x units and k > 7 n.  Measured on 256 units, pairs / split in us (more in profiles/): 768 items
-// (3 rounds of split items for 2 of pairs) k = 4 47.8 / 50.7, k = 8 72.6 / 70.9, k = 32 219 / 194; 1080 items (5 for 3)
-// k = 6 90.8 / 97.8, k = 32 329 / 306; 2160 items (9 for 5) k = 16 335 / 348, k = 32 602 / 596.  From 11 rounds on the
-// workgroups have drifted apart and there is no last round to even out: 2816 items (11 for 6) k = 64 1540 / 1552, 3328
-// items (13 for 7) k = 64 1745 / 1780: pairs.
-// Up to one item per unit a split item always ends earlier than a pair; with one or two blocks there is nothing to share
-// out and the merge costs more than it saves: 256 items, alone / split, k = 1 10.2 / 11.0 us, k = 2 13.2 / 13.5, k = 3
-// 16.7 / 16.5, k = 16 50.8 / 39.8.
+// of one workgroup plus a set-up and an epilogue.  2 n + 1 rounds of split items against n + 1 of pairs save the last half
+// round and pay n more set-ups; with any other numbers of rounds splitting saves nothing.  Set-up and epilogue cost about
+// 2.5 blocks, which would make split items shorter for k > 5 n (k: blocks of a full row); the more rounds, the further the
+// workgroups have drifted apart and the less there is of a last round, hence k > n (9 + n) / 2, and pairs from n = 6 on.
+// Medians of split / pairs over 1900 launches of random geometry on 256 units (all of it in profiles/): n = 1, k = 4 1.04,
+// k = 6 0.985, k = 13 .. 20 0.87; n = 2, k = 9 .. 10 1.01, k = 11 .. 12 0.98; n = 3, k = 16 .. 18 1.00, k = 19 .. 21 0.99;
+// n = 4, k = 21 .. 24 1.01, k = 25 .. 28 1.00; n = 6, k = 43 .. 54 1.02, k = 55 .. 72 1.01.  Single geometries lie up to 10 % away,
+// most of them grids whose last row or column of tiles is a sliver.
+// Up to one item per unit a split item always ends earlier than a pair, and than an item on one group (k = 2 0.99, k = 4
+// 0.89), except that one block cannot be shared: k = 1 1.08.
 inline AttnForm attn_form(int items, int units, int k) {
     const int rounds_split = (items + units - 1) / units, rounds_pairs = ((items + 1) / 2 + units - 1) / units;
-    if (rounds_split <= 1) return k <= 2 ? kAttnAlone : kAttnSplit;
-    if (rounds_split > 9) return kAttnPairs;
-    return (long long)rounds_split * (2 * ((k + 1ll) / 2) + 7) < (long long)rounds_pairs * (2ll * k + 7) ? kAttnSplit : kAttnPairs;
+    if (rounds_split <= 1) return k <= 1 ? kAttnAlone : kAttnSplit;
+    const int n = rounds_pairs - 1;
+    return rounds_split == 2 * n + 1 && n <= 5 && k > n * (9 + n) / 2 ? kAttnSplit : kAttnPairs;
 }
 
 inline int attn_workgroups(AttnForm form, int items) { return form == kAttnPairs ? (items + 1) / 2 : items; }
