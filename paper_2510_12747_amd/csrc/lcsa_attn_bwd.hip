@@ -17,7 +17,7 @@
 // wavefront order.  K and V are read from the caller's raster tensors (the frames the cache held at the forward, oldest
 // first), token rows straight into registers.
 //
-// What bounds them: latency (2 heads, d = 32, fp32, 16-token blocks, k = 16 on a 24 x 44 grid: 19 + 18 us, of which
+// What bounds them: latency (2 heads, d = 32, fp32, 16-token blocks, k = 16 on a 24 x 44 grid: 20 + 19 us, of which
 // 2.4 us would be matrix work).  Token-per-wavefront dot products in vector FMA with the key block's accumulators in LDS
 // took 541 + 182 us there.
 #include "lcsa_fp32_mma.h"

@@ -16,8 +16,9 @@
 // columns (second level: over keys or queries), the fragment comes from two transposing reads (ds_read_b64_tr_b16:
 // 16 lanes fetch 4 rows x 16 columns and each receives 4 consecutive rows of one column), so no transposed copy of
 // a tile is ever built.  sw() spreads both kinds of read over the banks: 16 rows with distinct low bits map to 16
-// distinct chunk positions (the row reads are conflict free by the hardware counters), and 4 consecutive rows map to
-// 4 distinct 32-byte positions (the transposing reads still show about one conflict cycle in four).
+// distinct chunk positions (a kernel of row reads alone showed no conflicts), and 4 consecutive rows map to 4 distinct
+// 32-byte positions (the transposing reads are not free of them: conflict cycles are 0.17 of the LDS index cycles on the
+// query side, 0.24 on the key side).
 //
 // Operand reuse without LDS round trips: the rows fed to the matrix rows of a first-level product (S or S^T) are
 // permuted (bits 2 and 3 of the row index swapped), which makes the 8 accumulator registers 8s..8s+7 of a lane
@@ -31,7 +32,7 @@
 // Every matrix instruction takes one 1 KB operand fragment from LDS (the 64-bit transposing reads at less than half
 // the rate of the 128-bit row reads), and 64 KB of tiles per block pair come from L2 for each of the three passes.
 //
-// Paper scale (12 heads, 48 x 88 tokens, k = 32): 618 us + 640 us.  As three kernels, D and dQ apart and dK, dV with four
+// Paper scale (12 heads, 48 x 88 tokens, k = 32): 632 us + 668 us.  As three kernels, D and dQ apart and dK, dV with four
 // wavefronts, one per SIMD, they took 312 + 506 + 761 us: with one wavefront per SIMD nothing ran beside the exponentials,
 // and every copied row cost a 64-bit address computation.
 #include "lcsa_kernels.h"

@@ -7,10 +7,10 @@
 // split the key groups instead: each wavefront keeps a softmax of its own over every (4 / ways)-th stretch of GI groups,
 // and the partial results meet in LDS at the end.  No LDS and no barrier otherwise.
 //
-// What bounds it: at 8 heads, d = 64, bf16, 32-token blocks, k = 16 on a 24 x 44 grid 33 us, of which the float P V products
+// What bounds it: at 8 heads, d = 64, bf16, 32-token blocks, k = 16 on a 24 x 44 grid 34 us, of which the float P V products
 // are 9 us of matrix time and the rest is load latency (two wavefronts per SIMD).  A wavefront per query token with
 // lane-per-key dot products in vector FMA took 1429 us there (every query re-read all its keys) and 49 us where this
-// takes 7 us on the smallest case (1 head, d = 32, f32, 16-token blocks, k = 4).
+// takes 7.5 us on the smallest case (1 head, d = 32, f32, 16-token blocks, k = 4).
 #include "lcsa_fp32_mma.h"
 
 namespace lcsa {
