@@ -396,16 +396,17 @@ def test_rows_that_keep_fewer_blocks_than_a_split_launch_shares_out():
     masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse)
 
 
+@pytest.mark.parametrize("dtype,d,tile", [("bf16", 128, (8, 16)), ("fp32", 32, (4, 5))])
 @pytest.mark.parametrize("masked", [(0,), (1,), (1, 2), (0, 1, 2, 3, 4, 5)])
-def test_blocks_whose_scores_are_all_minus_infinity_weigh_nothing(masked):
+def test_blocks_whose_scores_are_all_minus_infinity_weigh_nothing(masked, dtype, d, tile):
     """Keys of whole blocks masked with -inf in a channel where every query is positive: such a block weighs nothing wherever it
     stands in a row's list (first of the row, first of the list's second half, all of them), and no NaN comes of it."""
     gen = torch.Generator(device="cuda").manual_seed(9)
-    h, w, frames, heads = 16, 48, 1, 2
-    g = B.Geom(heads, 128, h, w, 8, 16, 1, frames, -1, -1, 6, dtype=B.LCSA_BF16)
-    q, k, v = (torch.randn(h * w, heads, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    h, w, frames, heads = 2 * tile[0], 3 * tile[1], 1, 2
+    g = B.Geom(heads, d, h, w, *tile, 1, frames, -1, -1, 6, dtype=B.LCSA_F32 if dtype == "fp32" else B.LCSA_BF16)
+    q, k, v = (torch.randn(h * w, heads, d, generator=gen, device="cuda").to(g.torch_dtype) for _ in range(3))
     q[..., 0] = 1.0
-    block = (torch.arange(h, device="cuda")[:, None] // 8 * 3 + torch.arange(w, device="cuda")[None, :] // 16).reshape(-1)
+    block = (torch.arange(h, device="cuda")[:, None] // tile[0] * 3 + torch.arange(w, device="cuda")[None, :] // tile[1]).reshape(-1)
     hit = torch.isin(block, torch.tensor(masked, device="cuda"))
     k[hit, :, 0] = float("-inf")
     cache = B.lcsa_cache_init(g)
