@@ -276,8 +276,8 @@ int32_t lcsa_sparse_attn_fwd(const lcsa_geom *geom,
  *               usually taken as d_o_i . o_i; it is formed from the kernel's own probabilities instead, because the
  *               forward's output rounded to bf16 would put a relative error of several 1e-3 into d_q and d_k
  * All results are written in full (zeros where no kept pair reaches).  scale <= 0 selects 1/sqrt(head_dim).
- * arithmetic = LCSA_BWD_AUTO: for bf16, head_dim 128, 128-token blocks and at most 8192 query blocks per chunk the
- * products run on the matrix cores (bf16 operands, float accumulation; probabilities and their gradients are rounded to
+ * arithmetic = LCSA_BWD_AUTO: for bf16, head_dim 128, 128-token blocks, at most 8192 query blocks per chunk and blocks
+ * that span less than 4 GB of each tensor (first to last token, at the tensor's stride) the products run on the matrix cores (bf16 operands, float accumulation; probabilities and their gradients are rounded to
  * bf16 between the two levels of products: results within a few 1e-3 of the largest gradient), every other shape in float
  * products.
  * LCSA_BWD_FLOAT: float products for every shape (results within 2e-5 of the largest gradient; slower).

@@ -36,6 +36,7 @@
 // wavefronts, one per SIMD, they took 312 + 506 + 761 us: with one wavefront per SIMD nothing ran beside the exponentials,
 // and every copied row cost a 64-bit address computation.
 #include "lcsa_kernels.h"
+#include <utility>
 
 namespace lcsa {
 namespace {
@@ -74,7 +75,7 @@ __device__ inline int rel_token(const KGeom &g, const BlockTokens &bt, int i) {
 }
 
 // chunk position swizzle of a tile image and the byte offset of 16-byte chunk `chunk` of row `row`
-__device__ inline int sw(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
+__device__ inline int sw(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
 __device__ inline int img_off(int row, int chunk) { return row * 256 + ((chunk ^ sw(row)) << 4); }
 // matrix row m of a first-level product reads tile row swap23(m)
 __device__ inline int swap23(int m) { return (m & 0x13) | ((m & 4) << 1) | ((m & 8) >> 1); }
@@ -96,15 +97,22 @@ __device__ inline int column_base(int lane) {
     return img_off(row, chunk) + (i & 1) * 8;
 }
 __device__ inline bf16x8 frag_down(const unsigned char *unit, int base, int nt, int kk) {
-    const unsigned char *a = unit + 4096 * kk;               // rows + 4: four rows further, and bit 3 of sw() flips
+    const unsigned char *a = unit + 4096 * kk;               // rows + 4: four rows further, and bit 0 of sw() flips
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + (base ^ (nt << 6))));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + 1024 + (base ^ (nt << 6) ^ 128)));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + 1024 + (base ^ (nt << 6) ^ 16)));
     typedef __attribute__((ext_vector_type(8))) short i16x8;
     const i16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, both);
 }
 // Hides where a base came from, so that the XORs are formed where they are used instead of kept in registers.
 __device__ inline int fresh(int base) { asm volatile("" : "+v"(base)); return base; }
+
+// The lane's number, formed where it is used: two instructions instead of a register held across a loop.
+__device__ inline int lane_here() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
 
 // B-operand fragments of the 32 rows a wavefront owns, straight from the raster tensor: lane (n, half) holds
 // x[token(first + n)][16 ks + 8 half .. + 8] for ks = 0..7; rows beyond the block's valid tokens are zeros
@@ -122,28 +130,47 @@ __device__ inline void load_own_rows(const KGeom &g, const BlockRef &b, const __
 
 // ---- tile copies -------------------------------------------------------------------------------------------------
 // A wavefront copies 16 rows of a tile with 4 instructions; instruction i moves rows 16 wave + 4 i .. + 3, lane t
-// supplying row (t >> 4), chunk position (t & 15).  A CopyPlan holds, for the 4 rows of a lane, the byte distance of the
-// lane's 16 bytes from the block's first token: made once for the unclipped extent, so that a block costs one 64-bit
-// addition per row; clipped blocks make their own.  Rows beyond the block's valid tokens are copied from zero_row: their
-// probabilities are zero, and zero times an infinity of another row would not be.
+// supplying row (t >> 4), chunk position (t & 15).  A CopyPlan holds, for the 4 rows of a lane, the distance of the
+// lane's 16 bytes from the block's first token (the host sends blocks that reach 4 GB or more to the float kernels).  Made
+// once for the unclipped extent; clipped blocks make their own.  Rows beyond the block's valid tokens are copied as zeros:
+// their probabilities are zero, and zero times an infinity of another row would not be.
 constexpr int kWaves = 8;
-__device__ __attribute__((aligned(256))) const unsigned char zero_row[256] = {};
-struct CopyPlan { int64_t at[4]; };
+// byte offset of a block's i-th token from its first one
+constexpr uint32_t kNoRow = 0xfffffe00u;
+__device__ inline uint32_t row_offset(const KGeom &g, const BlockTokens &bt, int i, int64_t st) { return i < bt.n_valid ? (uint32_t)(rel_token(g, bt, i) * st * 2) : kNoRow; }
+struct CopyPlan { uint32_t at[4]; };
 __device__ inline CopyPlan copy_plan(const KGeom &g, int vh, int vw, int64_t st, int wave, int lane) {
     CopyPlan p;
     const BlockTokens bt(g, vh, vw);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = 4 * i + (lane >> 4);
-        p.at[i] = (rel_token(g, bt, 16 * wave + row) * st + ((lane & 15) ^ sw(row)) * 8) * 2;   // 16 wave does not enter sw()
+        p.at[i] = row_offset(g, bt, 16 * wave + row, st) + ((lane & 15) ^ sw(row)) * 16;        // 16 wave does not enter sw()
     }
     return p;
 }
-// One copy instruction: 64 lanes x 16 bytes from per-lane addresses to LDS bytes lds_rows + 16 lane.  The load
-// stays in flight (counted by vmcnt) until waited for; nothing else orders it.
-__device__ inline void copy_rows_to_lds(const void *src, uint32_t lds_rows) {
-    lds_rows = __builtin_amdgcn_readfirstlane(lds_rows);     // wavefront-uniform already; this pins it to a scalar register
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(lds_rows) : "memory", "m0");
+// One copy instruction: 64 lanes x 16 bytes from per-lane byte offsets of a scalar base to LDS bytes lds_rows + 16 lane; an
+// offset of kNoRow or more brings zeros.  The load stays in flight (counted by vmcnt) until waited for; nothing else orders it.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+__device__ inline u32x4 rows_from(const void *base) {
+    const uint64_t a = (uint64_t)base;
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), kNoRow, 0x00020000u};      // addresses have 48 bits: no stride above them
+}
+template <int AT> __device__ inline void copy_rows_to_lds(const u32x4 &from, uint32_t offset, uint32_t lds_rows) {      // to lds_rows + AT, scalar
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(offset), "s"(from), "s"(lds_rows), "i"(AT) : "memory", "m0", "scc");
+}
+// Piece i of a wavefront's copies of two tensors: rows 4 (i >> 1) .. + 3 of one or, SECOND bytes further on, the other.
+template <int SECOND> __device__ inline void copy_piece_to_lds(int piece, const u32x4 &first, const u32x4 &second, uint32_t offset, uint32_t lds_rows) {
+    switch (piece) {                                         // a constant where this is called
+    case 0: copy_rows_to_lds<0>(first, offset, lds_rows); break;
+    case 1: copy_rows_to_lds<SECOND>(second, offset, lds_rows); break;
+    case 2: copy_rows_to_lds<1024>(first, offset, lds_rows); break;
+    case 3: copy_rows_to_lds<SECOND + 1024>(second, offset, lds_rows); break;
+    case 4: copy_rows_to_lds<2048>(first, offset, lds_rows); break;
+    case 5: copy_rows_to_lds<SECOND + 2048>(second, offset, lds_rows); break;
+    case 6: copy_rows_to_lds<3072>(first, offset, lds_rows); break;
+    default: copy_rows_to_lds<SECOND + 3072>(second, offset, lds_rows); break;
+    }
 }
 __device__ inline uint32_t lds_address(const unsigned char *p) { return (uint32_t)(uintptr_t)((LCSA_LDS unsigned char *)p); }
 
@@ -155,36 +182,11 @@ __device__ inline Located locate(const KGeom &g, int block) {
 }
 __device__ inline int valid_tokens(const KGeom &g, const Located &b) { return g.tt * (b.extent & 0xffff) * (b.extent >> 16); }
 
-// This wavefront's rows of the tiles of block `b` of two tensors (K and V, or Q and dO), each with its plan.
-__device__ inline void copy_tiles(const KGeom &g, const Located &b, const CopyPlan &full0, const CopyPlan &full1, int wave, int lane,
-                                  const __bf16 *__restrict__ x0, int64_t st0, const __bf16 *__restrict__ x1, int64_t st1, uint32_t lds0) {
-    const char *b0 = (const char *)(x0 + b.origin * st0), *b1 = (const char *)(x1 + b.origin * st1);
-    const char *s0[4], *s1[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { s0[i] = b0 + full0.at[i]; s1[i] = b1 + full1.at[i]; }
-    if (b.extent != (g.th | g.tw << 16)) {                   // workgroup-uniform
-        const CopyPlan p0 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st0, wave, lane);
-        const CopyPlan p1 = copy_plan(g, b.extent & 0xffff, b.extent >> 16, st1, wave, lane);
-        const int n = valid_tokens(g, b);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool ok = 16 * wave + 4 * i + (lane >> 4) < n;
-            const char *none = (const char *)zero_row + (lane & 15) * 16;
-            s0[i] = ok ? b0 + p0.at[i] : none;
-            s1[i] = ok ? b1 + p1.at[i] : none;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t rows = (uint32_t)(16 * wave + 4 * i) * 256;
-        copy_rows_to_lds(s0[i], lds0 + rows);
-        copy_rows_to_lds(s1[i], lds0 + kTileBytes + rows);
-    }
-}
-
 // all of this wavefront's tile copies have landed; then a workgroup barrier: everybody's have, and everybody is
 // done with the buffer that the next copies will overwrite
 __device__ inline void tiles_ready() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// this wavefront's tile copies have landed
+__device__ inline void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // this wavefront's LDS writes so far are done
 __device__ inline void lds_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // a barrier for LDS traffic only: tile copies stay in flight
@@ -211,8 +213,9 @@ __device__ inline void zero(f32x16 &a) {
 // First-level products of the 32 rows mt of two tiles with two sets of register operands, operand fragments read kAhead
 // pairs ahead of the matrix instructions that use them.
 constexpr int kAhead = 3, kRing = kAhead + 1;
+template <class Also>
 __device__ inline void first_level(const unsigned char *x_unit, const unsigned char *y_unit, int base,
-                                   const bf16x8 (&xf)[8], const bf16x8 (&yf)[8], f32x16 &xs, f32x16 &ys) {
+                                   const bf16x8 (&xf)[8], const bf16x8 (&yf)[8], f32x16 &xs, f32x16 &ys, Also &&also) {
     bf16x8 xa[kRing], ya[kRing];
     base = fresh(base);
 #pragma unroll
@@ -221,6 +224,7 @@ __device__ inline void first_level(const unsigned char *x_unit, const unsigned c
     zero(xs); zero(ys);
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
+        also(ks);
         if (ks + kAhead < 8) {
             xa[(ks + kAhead) % kRing] = frag(x_unit, base, ks + kAhead);
             ya[(ks + kAhead) % kRing] = frag(y_unit, base, ks + kAhead);
@@ -242,12 +246,20 @@ __device__ inline void read_rows(const unsigned char *unit, int base, bf16x8 (&a
 __device__ inline void first_level(const unsigned char *x_unit, int base, const bf16x8 (&xf)[8], f32x16 &xs) {
     bf16x8 xa[8];
     read_rows(x_unit, base, xa);
-    zero(xs);
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) xs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[ks], xf[ks], xs, 0, 0, 0);
 }
-// Values of a unit's rows in the order of the accumulator registers: registers 4 r .. 4 r + 3
-__device__ inline float4 row_quad(const float *values, int half, int r) { return *(const float4 *)(values + 16 * (r >> 1) + 8 * half + 4 * (r & 1)); }
+// A value per row of a unit beside the accumulators of a first-level product: register 8 kk + j of a lane's accumulator is row
+// 16 kk + 8 half + j; lane (n, half) holds the value of row 16 (n >> 3 & 1) + 8 half + (n & 7), and register r takes it from
+// lane r of its row of 16 lanes (an addition with row_newbcast): one register and one LDS read of four bytes a lane, where
+// quads of the values took eight 16-byte reads a unit.
+template <int R> __device__ inline float row_value(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + R, 0xf, 0xf, true));
+}
+template <int R> __device__ inline float add_row(const f32x16 &x, float v) { return x[R] + row_value<R>(v); }
+// f(FIRST), f(FIRST + 1), ... with constants: what selects a register by row_value() needs them
+template <int FIRST, class F, int... R> __device__ inline void in_turn(F &&f, std::integer_sequence<int, R...>) { (f(std::integral_constant<int, FIRST + R>{}), ...); }
+template <int FIRST, int COUNT, class F> __device__ inline void in_turn(F &&f) { in_turn<FIRST>(f, std::make_integer_sequence<int, COUNT>{}); }
 // Column fragments of a unit (B operands of a second-level product: 4 channel groups x 2 k-steps)
 __device__ inline void read_columns(const unsigned char *unit, int base, bf16x8 (&b)[8]) {
     base = fresh(base);
@@ -295,14 +307,31 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
         // ids outside the visible blocks must not become wild addresses
         if (b0 + lane < cnt) chunk = locate(g, min(max(sel[b0 + lane], 0), kv_groups * g.nb - 1));
     };
-    auto request = [&](int b, int buf) {
+    // The copies of a block's K and V tiles: 8 instructions per wavefront.  Each holds the issuing wavefront while the memory
+    // pipeline accepts it, so they go along with the matrix instructions of the block before.
+    u32x4 k_from, v_from;
+    uint32_t copy_to = 0;
+    CopyPlan from;
+    auto locate_next = [&](int b, int buf) {
         if ((b & 63) == 0 && cnt > 64) refill(b);
         const Located kr = {__builtin_amdgcn_readlane(chunk.origin, b & 63), __builtin_amdgcn_readlane(chunk.extent, b & 63)};
-        copy_tiles(g, kr, plan, plan, wave, lane, k, kv_st, v, kv_st, lds_img + buf * 2 * kTileBytes);
+        k_from = rows_from(k + kr.origin * kv_st);
+        v_from = rows_from(v + kr.origin * kv_st);
+        copy_to = __builtin_amdgcn_readfirstlane(lds_img + buf * 2 * kTileBytes + wave * 4096);
+        from = plan;
+        if (kr.extent != (g.th | g.tw << 16)) from = copy_plan(g, kr.extent & 0xffff, kr.extent >> 16, kv_st, wave, lane);
         return valid_tokens(g, kr);
     };
+    auto copy_piece = [&](int piece) {
+        copy_piece_to_lds<kTileBytes>(piece, k_from, v_from, from.at[piece >> 1], copy_to);
+    };
     refill(0);
-    int n_next = cnt > 0 ? request(0, 0) : 0;
+    int n_next = 0;
+    if (cnt > 0) {
+        n_next = locate_next(0, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) copy_piece(i);
+    }
 
     // this wavefront's queries: Q and dO fragments (B operands), lse and the token to write to
     bf16x8 qf[8], gf[8];
@@ -335,22 +364,23 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
         for (int b = 0; b < cnt; ++b, ++step) {
             tiles_ready();                                   // block b is in buffer step & 1; nobody reads the other buffer any more
             const int n_keys = n_next;
-            if (b + 1 < cnt) n_next = request(b + 1, (step + 1) & 1);
-            else if (!last_pass) n_next = request(0, (step + 1) & 1);
-            if (wave_on) {
+            const bool more = b + 1 < cnt || !last_pass;
+            if (more) n_next = locate_next(b + 1 < cnt ? b + 1 : 0, (step + 1) & 1);
+            auto go_along = [&](int ks) { if (more) copy_piece(ks); };
+            auto no_copies = [](int) {};
+            if (wave_on && kh * 32 < n_keys) work(img[step & 1][0] + kh * 8192, img[step & 1][1] + kh * 8192, n_keys - kh * 32, go_along);
+            else
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int mt = kh + 2 * u;
-                    if (mt * 32 < n_keys) work(img[step & 1][0] + mt * 8192, img[step & 1][1] + mt * 8192, n_keys - mt * 32);
-                }
-            }
+                for (int i = 0; i < 8; ++i) go_along(i);
+            const int mt = kh + 2;
+            if (wave_on && mt * 32 < n_keys) work(img[step & 1][0] + mt * 8192, img[step & 1][1] + mt * 8192, n_keys - mt * 32, no_copies);
         }
     };
 
     float dsum = 0.f;
-    for_each_unit(false, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left) {
+    for_each_unit(false, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left, auto &&also) {
         f32x16 s, t;
-        first_level(k_unit, v_unit, rows, qf, gf, s, t);
+        first_level(k_unit, v_unit, rows, qf, gf, s, t, also);
         mask_keys(s, left);
 #pragma unroll
         for (int r = 0; r < 16; ++r) dsum = fmaf(prob(s[r]), t[r], dsum);
@@ -365,10 +395,10 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) zero(dq[nt]);
     const float d_scaled = D * scale;
-    for_each_unit(true, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left) {
+    for_each_unit(true, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left, auto &&also) {
         f32x16 s, t;
         bf16x8 kc[8], u[2];
-        first_level(k_unit, v_unit, rows, qf, gf, s, t);
+        first_level(k_unit, v_unit, rows, qf, gf, s, t, also);
         read_columns(k_unit, columns, kc);                   // arrives under the element-wise part
         mask_keys(s, left);
 #pragma unroll
@@ -404,39 +434,62 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
 // The query rows stream through LDS in units of 32 (Q and dO rows: 16 KB), kStages of them at a time, one unit per slot and
 // one barrier per slot; a role's element-wise work stands beside matrix work of its own that does not depend on it:
 //     slot t   w < 4:  exponentials of S(t), P(t) -> LDS  beside  dV += P(t - 1)^T dO;   then S(t + 1)
-//              w >= 4: U(t - 1) from T(t - 1), P(t - 1)   beside  dK += U(t - 2)^T Q;    then T(t)
+//              w >= 4: T(t - 1);   then U(t - 1) from T(t - 1), P(t - 1)  beside  dK += U(t - 2)^T Q
 // Slot t reads units t - 2 .. t + 1, and unit t + 4 is requested into the place of unit t - 3.
-constexpr int kStages = 7, kLead = kStages - 3, kStatLead = 3;
+// What bounds it is the number of instructions: a wavefront issues one every five cycles or so, and with 64-bit address
+// products, branches and a spilled operand in each slot (whose reload drained the copies in flight) a slot took 2640 cycles
+// for 1024 of matrix work; it takes 1890 now (paper scale 668 -> 470 us).
+constexpr int kStages = 7, kLead = kStages - 3;
 constexpr int kUnitBytes = 32 * 256;
 
-__global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
-    KGeom g, int kv_groups, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
-    const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
-    const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
+struct KeySideLds {
+    __attribute__((aligned(256))) unsigned char img[kStages][2][kUnitBytes];      // [stage][Q, dO]
+    float4 p[2][4][4][64];                                   // P on its way to the second role: [slot parity][key group][register quad][lane]
+    float rows[kStages][2][32];                              // [stage][-lse / scale, -D][query of the unit]
+    uint32_t row_at[3][4][128];                              // [tokens, bytes of Q, of dO][clipped rows, columns][token of the block]: see below
+    unsigned char kept_by[kListed];
+    uint16_t list[4 * kListed];                              // units: 4 * query block + unit of the block
+    int n_listed;
+};
+
+// Two paths of their own, loops over the lists included: with the roles side by side in one loop the compiler kept the
+// accumulators twice and reloaded spilled operands in every slot.
+template <bool P_ROLE>
+__device__ __forceinline__ void key_side(
+    KeySideLds &lds, int kb, int head, const KGeom &g, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
+    const __bf16 *__restrict__ kv, int64_t kv_st, int64_t kv_sh, const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse, const float *__restrict__ delta,
-    float *__restrict__ d_k, float *__restrict__ d_v, float scale, int per_xcd) {
-    __shared__ __attribute__((aligned(256))) unsigned char img[kStages][2][kUnitBytes];      // [stage][Q, dO]
-    __shared__ float4 p_lds[2][4][4][64];                    // [slot parity][key group][register quad][lane]
-    __shared__ __attribute__((aligned(16))) float row_lds[kStages][2][32];       // [stage][-lse log2(e), -scale D][query of the unit]
-    __shared__ unsigned char kept_by[kListed];
-    __shared__ uint16_t list[4 * kListed];                   // units: 4 * query block + unit of the block
-    __shared__ int n_listed;
-    int kb, head;
-    if (!work_item(g, kv_groups, per_xcd, head, kb)) return;
+    float *__restrict__ out, float scale) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave & 3;
-    const bool p_role = wave < 4;
     const int ql = lane & 31, half = lane >> 5;
     const int n_qb = g.q_groups * g.nb;
     const BlockRef kr = block_ref(g, kb);
     const float scale_log2 = scale * kLog2e;
-    const uint32_t lds_img = lds_address(&img[0][0][0]);
+    const uint32_t lds_img = lds_address(&lds.img[0][0][0]);
     q += (int64_t)head * q_sh;
     d_o += (int64_t)head * o_sh;
+    // How far token i of a block lies from its first one, for the four extents a block can have (whole; last column, last row
+    // or both clipped): formed once, because the divisions and 64-bit products of every unit took a third of the vector work.
+    {
+        const int e = tid >> 7;
+        const BlockTokens bt(g, e & 2 ? g.H - (g.ty - 1) * g.th : g.th, e & 1 ? g.W - (g.tx - 1) * g.tw : g.tw);
+        lds.row_at[0][e][tid & 127] = (uint32_t)rel_token(g, bt, tid & 127);
+        lds.row_at[1][e][tid & 127] = (uint32_t)(rel_token(g, bt, tid & 127) * q_st * 2);
+        lds.row_at[2][e][tid & 127] = row_offset(g, bt, tid & 127, o_st);
+    }
+    const uint32_t lane_chunk = ((lane & 15) ^ sw(8 * kg + (lane >> 4))) * 16;
+    const float *stat_from = (lane & 8 ? delta : lse) + head;
+    const float stat_factor = lane & 8 ? -1.f : -1.f / scale;
+    const int stat_row = lane & 8 ? -1 : 8 * kg + (lane & 7);                    // D of a padding query is that of another one, finite or not: p is zero
+    float *stat_to = &lds.rows[0][lane >> 3 & 1][8 * kg + (lane & 7)];
+    const float *stat_at = &lds.rows[0][0][2 * (lane & 8) + 8 * half + (lane & 7)];
+    float4 *p_to = &lds.p[0][kg][0][lane];
+    const uint32_t *own_rows = &lds.row_at[1][0][8 * kg + (lane >> 4)], *stat_row_at = &lds.row_at[0][0][8 * kg + (lane & 7)];
 
     // this wavefront's keys: K or V fragments (B operands of the first-level products)
     bf16x8 own[8];
-    load_own_rows(g, kr, p_role ? k : v, kv_st, kv_sh, head, 32 * kg, lane, own);
+    load_own_rows(g, kr, kv, kv_st, kv_sh, head, 32 * kg, lane, own);
     f32x16 acc[4];                                           // dV or dK
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) zero(acc[nt]);
@@ -446,7 +499,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
     for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
         // which query blocks kept this key block?  (ascending id lists)
         const int n_here = min(kListed, n_qb - qb0);
-        __syncthreads();                                     // the previous list and its units are no longer read
+        tiles_ready();                                       // the previous list and its units are no longer read, and no copy is in flight
         if (g.topk <= 64) {                                  // 16 lanes look at a row's ids at once
             for (int i = 4 * wave + (lane >> 4); i < ((n_here + 3) & ~3); i += 4 * kWaves) {
                 bool hit = false;
@@ -460,7 +513,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
                     for (int e = 0; e < 4; ++e) hit |= (lane & 15) + 16 * e < c && ids[e] == kb;
                 }
                 const uint64_t hits = __ballot(hit);
-                if ((lane & 15) == 0 && i < n_here) kept_by[i] = (hits >> (lane & 48) & 0xffff) != 0;
+                if ((lane & 15) == 0 && i < n_here) lds.kept_by[i] = (hits >> (lane & 48) & 0xffff) != 0;
             }
         } else {                                             // a binary search per row
             for (int i = tid; i < n_here; i += 64 * kWaves) {
@@ -469,7 +522,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
                 const int c = min(max(sel_cnt[row], 0), g.topk);
                 int lo = 0, hi = c;
                 while (lo < hi) { const int mid = (lo + hi) >> 1; if (sel[mid] < kb) lo = mid + 1; else hi = mid; }
-                kept_by[i] = lo < c && sel[lo] == kb;
+                lds.kept_by[i] = lo < c && sel[lo] == kb;
             }
         }
         __syncthreads();
@@ -477,90 +530,96 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
             int n = 0;
             for (int i0 = 0; i0 < n_here; i0 += 64) {
                 const int i = i0 + lane;
-                const bool kept = i < n_here && kept_by[i];
+                const bool kept = i < n_here && lds.kept_by[i];
                 const int units = kept ? (block_ref(g, qb0 + i).n_valid + 31) >> 5 : 0;
                 int before = units;                          // inclusive prefix sum
 #pragma unroll
                 for (int off = 1; off < 64; off <<= 1) { const int x = __shfl_up(before, off); before += lane >= off ? x : 0; }
-                for (int u = 0; u < units; ++u) list[n + before - units + u] = (uint16_t)(4 * i + u);
+                for (int u = 0; u < units; ++u) lds.list[n + before - units + u] = (uint16_t)(4 * i + u);
                 n += __shfl(before, 63);
             }
-            if (lane == 0) n_listed = n;
+            if (lane == 0) lds.n_listed = n;
         }
         __syncthreads();
-        const int n_units = __builtin_amdgcn_readfirstlane(n_listed);
+        const int n_units = __builtin_amdgcn_readfirstlane(lds.n_listed);
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0), where the compiler sees it (see the query-side kernel)
         if (n_units == 0) continue;
 
-        // Units 64 at a time, one per lane: raster token of the block's first token, vh | vw << 8 | unit of the block << 16,
-        // and the reciprocals that turn a token number into (frame, row, column).
-        int unit_origin = 0, unit_shape = 0, unit_mf = 0, unit_mr = 0;
+        // Units 64 at a time, one per lane: raster token of the block's first token, and where the unit's rows start in row_at |
+        // how many of them hold valid queries << 16.
+        int unit_origin = 0, unit_rows = 0;
         auto refill = [&](int t) {
             if ((t & 63) == 0 && t + lane < n_units) {
-                const int e = list[t + lane];
+                const int e = lds.list[t + lane];
                 const BlockRef b = block_ref(g, qb0 + (e >> 2));
-                const BlockTokens bt(g, b.vh, b.vw);
                 unit_origin = (int)block_origin(g, b);
-                unit_shape = b.vh | b.vw << 8 | (e & 3) << 16;
-                unit_mf = (int)bt.m_frame;
-                unit_mr = (int)bt.m_row;
+                unit_rows = ((b.vh < g.th) * 2 + (b.vw < g.tw)) * 128 + (e & 3) * 32 | min(b.n_valid - (e & 3) * 32, 32) << 16;
             }
-        };
-        auto unit_tokens = [&](int t, int &origin, int &first) {
-            const int shape = __builtin_amdgcn_readlane(unit_shape, t & 63);
-            origin = __builtin_amdgcn_readlane(unit_origin, t & 63);
-            first = (shape >> 16) * 32;
-            return BlockTokens(shape & 0xff, shape >> 8 & 0xff, g.tt, __builtin_amdgcn_readlane(unit_mf, t & 63), __builtin_amdgcn_readlane(unit_mr, t & 63));
         };
         // Unit t on its way into stage `stage`: 8 rows of Q and of dO per wavefront of the second role (lane t supplies row
-        // t >> 4 of four).  Rows beyond the block's valid queries repeat its first one in Q (an infinity there makes the
-        // gradients of the same keys NaN in any case) and are zeros in dO.
-        auto request_rows = [&](int t, int stage) {
-            if (t >= n_units) return;
-            refill(t);
-            int origin, first;
-            const BlockTokens bt = unit_tokens(t, origin, first);
-            const __bf16 *q_row = q + origin * q_st, *o_row = d_o + origin * o_st;
+        // t >> 4 of four), four instructions.  Rows beyond the block's valid queries repeat its first one in Q (an infinity
+        // there makes the gradients of the same keys NaN in any case) and are zeros in dO.
+        // A unit beyond the last one is the last one again: its stage is free, and the loop has no branch that would keep the
+        // scheduler from spreading a slot's work over its matrix instructions.
+        u32x4 q_from, o_from;
+        uint32_t row_off[4], copy_to = 0;
+        auto locate_rows = [&](int t, int stage) {           // refill(t) has been called
+            t = min(t, n_units - 1);
+            const int origin = __builtin_amdgcn_readlane(unit_origin, t & 63), rows_of = __builtin_amdgcn_readlane(unit_rows, t & 63);
+            q_from = rows_from((const char *)q + (uint64_t)(uint32_t)origin * (uint32_t)(q_st * 2));
+            o_from = rows_from((const char *)d_o + (uint64_t)(uint32_t)origin * (uint32_t)(o_st * 2));
+            copy_to = lds_img + stage * 2 * kUnitBytes + 8 * kg * 256;
+            const uint32_t *at = own_rows + (rows_of & 0xffff);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int l = fresh(lane), row = 8 * kg + 4 * i + (l >> 4);
-                const uint32_t chunk = ((l & 15) ^ sw(row)) * 16;
-                const uint32_t rel = rel_token(g, bt, first + row);
-                const uint32_t dst = lds_img + stage * 2 * kUnitBytes + (8 * kg + 4 * i) * 256;
-                copy_rows_to_lds((const char *)(q_row + rel * (uint64_t)q_st) + chunk, dst);
-                copy_rows_to_lds((first + row < bt.n_valid ? (const char *)(o_row + rel * (uint64_t)o_st) : (const char *)zero_row) + chunk, dst + kUnitBytes);
-            }
+            for (int i = 0; i < 2; ++i) { row_off[2 * i] = at[4 * i]; row_off[2 * i + 1] = at[512 + 4 * i]; }
+        };
+        auto copy_rows = [&](int piece) {                    // sw(8 kg + 4 i + row) = sw(8 kg + row) ^ i
+            copy_piece_to_lds<kUnitBytes>(piece, q_from, o_from, row_off[piece] + (lane_chunk ^ 16 * (piece >> 1)), copy_to);
+        };
+        auto request_rows = [&](int t, int stage) {
+            refill(t);
+            locate_rows(t, stage);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) copy_rows(i);
         };
         // lse (lanes 0..7) and D (lanes 8..15) of 8 rows per wavefront of the first role: an ordinary load, stored to the
-        // stage when it has arrived.  (As direct-to-LDS loads of single dwords these made every slot twice as long.)
-        // Stored as the kernel uses them, -lse log2(e) and -scale D; padding queries get an infinite lse: probability zero.
+        // stage a slot later.  (As direct-to-LDS loads of single dwords these made every slot twice as long.)  Stored as the
+        // kernel uses them, -lse / scale and -D; padding queries get an infinite lse: probability zero.
+        // Lanes 16.. repeat lanes 0..15.
         float stat = 0.f;
-        auto request_stats = [&](int t) {
-            if (t >= n_units) return;
-            refill(t);
-            int origin, first;
-            const BlockTokens bt = unit_tokens(t, origin, first);
-            const int i = first + 8 * kg + (lane & 7);
-            const int64_t tok = (int64_t)(origin + rel_token(g, bt, i)) * g.heads + head;
-            if (lane < 16) stat = (lane < 8 ? lse : delta)[tok] * (lane < 8 ? -kLog2e : -scale);
-            if (lane < 8 && i >= bt.n_valid) stat = -__builtin_inff();
+        int stat_rel = 0, stat_origin = 0, stat_rows = 0, rows_held = 0;
+        auto locate_stats = [&](int t) {                     // refill(t) has been called
+            t = min(t, n_units - 1);
+            stat_origin = __builtin_amdgcn_readlane(unit_origin, t & 63);
+            const int rows_of = __builtin_amdgcn_readlane(unit_rows, t & 63);
+            stat_rows = rows_of >> 16;
+            stat_rel = (int)stat_row_at[rows_of & 0xffff];
         };
-        auto store_stats = [&](int stage) {
-            if (lane < 16) row_lds[stage][lane >> 3][8 * kg + (lane & 7)] = stat;
+        auto request_stats = [&]() {                         // of the unit located last
+            stat = stat_from[(int64_t)(stat_origin + stat_rel) * g.heads];
+            rows_held = stat_rows;
         };
+        auto store_stats = [&](int stage) { stat_to[stage * 64] = stat_row >= rows_held ? -__builtin_inff() : stat * stat_factor; };
+        // what row_value() hands to this lane's accumulator registers
+        auto row_stat = [&](int stage, int which) { return stat_at[stage * 64 + which * 32]; };
         // The second role's copies of all units but the two requested last have landed, and every wavefront is done with the slot.
-        auto end_of_slot = [&](bool draining) {
-            if (p_role) asm volatile("s_barrier" ::: "memory");
-            else if (draining) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        auto end_of_slot = [&]() {
+            if constexpr (P_ROLE) asm volatile("s_barrier" ::: "memory");
             else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
         };
         auto wrap = [](int stage) { return stage >= kStages ? stage - kStages : stage; };
 
-        if (p_role)
-            { for (int t = 0; t < kStatLead; ++t) { request_stats(t); store_stats(t); } lds_done(); }
-        else
+        if constexpr (P_ROLE) {
+            refill(0);
+            for (int t = 0; t < 2; ++t) { locate_stats(t); request_stats(); store_stats(t); }
+            locate_stats(2); request_stats();
+            locate_stats(3);
+            for (int r = 0; r < 4; ++r) p_to[1024 + 64 * r] = make_float4(0.f, 0.f, 0.f, 0.f);      // P(-1)
+            lds_done();
+        } else {
             for (int t = 0; t < kLead; ++t) request_rows(t, t);
-        end_of_slot(n_units < kLead);                        // units 0 and 1 are in LDS
+        }
+        end_of_slot();                                       // units 0 and 1 are in LDS
 
         // The slots are alike; what a first or last one would take from a unit that does not exist is either multiplied by
         // the zeros p and u start with (dO rows: zeros too; Q rows: of unit 0 instead) or never used.
@@ -575,42 +634,42 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
         if (!wave_on) {
 #pragma unroll 1
             for (int t = 0, now = 0; t < n_units + 2; ++t, now = wrap(now + 1)) {
-                if (p_role) { request_stats(t + kStatLead); store_stats(wrap(now + kStatLead)); lds_done(); }
+                if constexpr (P_ROLE) { refill(t + 4); store_stats(wrap(now + 2)); request_stats(); locate_stats(t + 4); lds_done(); }
                 else request_rows(t + kLead, wrap(now + kLead));
-                end_of_slot(t + kLead >= n_units);
+                end_of_slot();
             }
-        } else if (p_role) {
-            first_level(img[0][0], rows, own, x);
+        } else if constexpr (P_ROLE) {
+            float l_now = row_stat(0, 0);
+            first_level(lds.img[0][0], rows, own, x);
             bf16x8 cols[8];                                  // of unit t - 1
-            float4 l4[4];                                    // of unit t, quads 0 and 1 read ahead
 #pragma unroll
             for (int n = 0; n < 8; ++n)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) cols[n][j] = (__bf16)0.f;
-            l4[0] = row_quad(row_lds[0][0], half, 0);
-            l4[1] = row_quad(row_lds[0][0], half, 1);
 #pragma unroll 1
             for (int t = 0, now = 0; t <= n_units; ++t, now = wrap(now + 1)) {
-                request_stats(t + kStatLead);
+                refill(t + 4);
                 bf16x8 xa[8], wn[2];
-                const unsigned char *next = img[wrap(now + 1)][0];
+                const unsigned char *next = lds.img[wrap(now + 1)][0];
                 const int base = fresh(rows);
-                l4[2] = row_quad(row_lds[now][0], half, 2);
-                l4[3] = row_quad(row_lds[now][0], half, 3);
-#pragma unroll
-                for (int n = 0; n < 8; ++n) {
+                float l_next;
+                in_turn<0, 8>([&](auto step) {
+                    constexpr int n = step;
                     __builtin_amdgcn_sched_barrier(0);
                     acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
                     xa[n] = frag(next, base, n);
-#pragma unroll
-                    for (int e = 2 * n; e < 2 * n + 2; ++e) {
-                        x[e] = __builtin_amdgcn_exp2f(fmaf(x[e], scale_log2, (&l4[e >> 2].x)[e & 3]));
+                    if (n == 0) l_next = row_stat(wrap(now + 1), 0);
+                    in_turn<2 * n, 2>([&](auto reg) {
+                        constexpr int e = reg;
+                        x[e] = __builtin_amdgcn_exp2f(add_row<e>(x, l_now) * scale_log2);
                         wn[e >> 3][e & 7] = (__bf16)x[e];
-                    }
-                    if (n & 1) p_lds[t & 1][kg][n >> 1][lane] = make_float4(x[2 * n - 2], x[2 * n - 1], x[2 * n], x[2 * n + 1]);
-                }
+                    });
+                    if (n & 1) p_to[t & 1 ? 1024 + 64 * (n >> 1) : 64 * (n >> 1)] = make_float4(x[2 * n - 2], x[2 * n - 1], x[2 * n], x[2 * n + 1]);
+                    if (n == 4) store_stats(wrap(now + 2));
+                    if (n == 5) request_stats();
+                    if (n == 6) locate_stats(t + 4);
+                });
                 pin(wn);
-                store_stats(wrap(now + kStatLead));
                 asm volatile("" ::: "memory");               // P(t) and the row values are written before the column reads below
                 const int col_base = fresh(columns);
                 zero(x);
@@ -618,60 +677,62 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
                 for (int n = 0; n < 8; ++n) {
                     __builtin_amdgcn_sched_barrier(0);
                     x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[n], own[n], x, 0, 0, 0);
-                    cols[n] = frag_down(img[now][1], col_base, n >> 1, n & 1);      // for the next slot: these need not wait for the barrier
+                    cols[n] = frag_down(lds.img[now][1], col_base, n >> 1, n & 1);      // for the next slot: these need not wait for the barrier
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 w[0] = wn[0]; w[1] = wn[1];
+                l_now = l_next;
                 // LDS operations of a wavefront end in order, and 16 of them (the column reads) follow the writes of P(t) and of
                 // the row values: with at most 14 in flight both writes are done.  (The counter has four bits: 15 is no wait.)
                 asm volatile("s_waitcnt lgkmcnt(14)" ::: "memory");
-                l4[0] = row_quad(row_lds[wrap(now + 1)][0], half, 0);
-                l4[1] = row_quad(row_lds[wrap(now + 1)][0], half, 1);
-                end_of_slot(t + kLead >= n_units);
+                end_of_slot();
             }
-            end_of_slot(true);
+            end_of_slot();
         } else {
-            bf16x8 cols[8];                                  // of unit t - 2
-            read_columns(img[0][0], columns, cols);
+            // T(t - 1) first, then U(t - 1) beside dK: while the first role's wavefront of the SIMD is at its exponentials this
+            // one has matrix work only, and the other way round.
+            bf16x8 cols[8], xa[8];                           // of unit t - 2, of unit t - 1
+            read_rows(lds.img[0][1], rows, xa);
+            request_rows(kLead, kLead);
+            end_of_slot();
 #pragma unroll 1
-            for (int t = 0, now = 0; t < n_units + 2; ++t, now = wrap(now + 1)) {
-                bf16x8 xa[8], wn[2];
-                float4 p4[4], d4[4];
-                // formed from the lane number on every trip: a base held across the loop was spilled, and its reload, for which the
-                // compiler waits with vmcnt(0), drained the copies that end_of_slot() keeps in flight
-                const float *d_rows = row_lds[wrap(now + kStages - 1)][1] + 8 * (fresh(lane) >> 5);
-                const int base = fresh(rows);
-#pragma unroll
-                for (int r4 = 0; r4 < 2; ++r4) { p4[r4] = p_lds[(t & 1) ^ 1][kg][r4][lane]; d4[r4] = row_quad(d_rows, 0, r4); }
-                request_rows(t + kLead, wrap(now + kLead));
-#pragma unroll
-                for (int n = 0; n < 8; ++n) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
-                    xa[n] = frag(img[now][1], base, n);
-                    if (n < 2) { p4[n + 2] = p_lds[(t & 1) ^ 1][kg][n + 2][lane]; d4[n + 2] = row_quad(d_rows, 0, n + 2); }
-#pragma unroll
-                    for (int e = 2 * n; e < 2 * n + 2; ++e)
-                        wn[e >> 3][e & 7] = (__bf16)((&p4[e >> 2].x)[e & 3] * fmaf(x[e], scale, (&d4[e >> 2].x)[e & 3]));
-                }
-                pin(wn);
-                const unsigned char *before = img[t == 0 ? 0 : wrap(now + kStages - 1)][0];
+            for (int t = 1, now = 1, last = 0, before = 0; t < n_units + 2; ++t, before = last, last = now, now = wrap(now + 1)) {
+                refill(t + kLead);
+                bf16x8 wn[2];
+                float4 p4[4];
+                float d_last;
+                const float4 *p_from = p_to + (t & 1 ? 0 : 1024);
                 const int col_base = fresh(columns);
                 zero(x);
-#pragma unroll
-                for (int n = 0; n < 8; ++n) {
+                in_turn<0, 8>([&](auto step) {
+                    constexpr int n = step;
                     __builtin_amdgcn_sched_barrier(0);
                     x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[n], own[n], x, 0, 0, 0);
-                    cols[n] = frag_down(before, col_base, n >> 1, n & 1);
-                }
+                    cols[n] = frag_down(lds.img[before][0], col_base, n >> 1, n & 1);
+                    if (n == 0) locate_rows(t + kLead, wrap(now + kLead));
+                    if constexpr (n >= 4) p4[n - 4] = p_from[64 * (n - 4)];
+                    if (n == 4) d_last = row_stat(last, 1);
+                    if (n == 3 || n == 6) copy_rows(n / 6);
+                });
+                const int base = fresh(rows);
+                in_turn<0, 8>([&](auto step) {
+                    constexpr int n = step;
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
+                    xa[n] = frag(lds.img[now][1], base, n);
+                    if constexpr (n >= 2 && n < 6)
+                        in_turn<4 * (n - 2), 4>([&](auto reg) { constexpr int e = reg; wn[e >> 3][e & 7] = (__bf16)((&p4[e >> 2].x)[e & 3] * add_row<e>(x, d_last)); });
+                    if (n == 1 || n == 6) copy_rows(2 + n / 6);
+                });
+                pin(wn);
                 __builtin_amdgcn_sched_barrier(0);
-                if (t > 0) { w[0] = wn[0]; w[1] = wn[1]; }
-                end_of_slot(t + kLead >= n_units);
+                w[0] = wn[0]; w[1] = wn[1];
+                end_of_slot();
             }
         }
     }
-    // tile nt: lane = channel nt*32 + ql, register r = key row 8 (r >> 2) + 4 half + (r & 3) of this wavefront
-    float *out = p_role ? d_v : d_k;
+    wait_copies();                                           // none may land after the workgroup has gone
+    const float factor = P_ROLE ? 1.f : scale;               // u enters dK without it
     const BlockTokens kt(g, kr.vh, kr.vw);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -679,14 +740,33 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
         if (ki < kr.n_valid) {
             const int64_t o = ((block_origin(g, kr) + rel_token(g, kt, ki)) * g.heads + head) * 128 + ql;
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) out[o + nt * 32] = acc[nt][r];
+            for (int nt = 0; nt < 4; ++nt) out[o + nt * 32] = acc[nt][r] * factor;
         }
     }
 }
 
+__global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
+    KGeom g, int kv_groups, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
+    const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
+    const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
+    const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse, const float *__restrict__ delta,
+    float *__restrict__ d_k, float *__restrict__ d_v, float scale, int per_xcd) {
+    __shared__ KeySideLds lds;
+    int kb, head;
+    if (!work_item(g, kv_groups, per_xcd, head, kb)) return;
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x) < 256)
+        key_side<true>(lds, kb, head, g, q, q_st, q_sh, k, kv_st, kv_sh, sel_idx, sel_cnt, d_o, o_st, o_sh, lse, delta, d_v, scale);
+    else
+        key_side<false>(lds, kb, head, g, q, q_st, q_sh, v, kv_st, kv_sh, sel_idx, sel_cnt, d_o, o_st, o_sh, lse, delta, d_k, scale);
+}
+
 } // namespace
 
-bool attn_bwd_mfma_supported(const KGeom &g) {
+bool attn_bwd_mfma_supported(const KGeom &g, int64_t q_st, int64_t kv_st, int64_t o_st) {
+    // byte offsets inside a block are 32-bit, up to kNoRow, and so is the distance of two tokens
+    const int64_t last = ((int64_t)(g.tt - 1) * g.H + min(g.th, g.H) - 1) * g.W + min(g.tw, g.W) - 1;
+    for (const int64_t st : {q_st, kv_st, o_st})
+        if (st > (1ll << 30) || last * st * 2 + 256 > (int64_t)kNoRow) return false;
     return g.bf16 && g.d == 128 && g.bt == 128 && g.q_groups * g.nb <= kMaxQueryBlocks;
 }
 

@@ -322,7 +322,7 @@ int32_t lcsa_sparse_attn_bwd(const lcsa_geom *geom, const void *q, int64_t q_str
     const int kv_groups = kv_frames / kg.tt;
     if ((int64_t)kv_frames * kg.H * kg.W > (1ll << 30) || (int64_t)kv_groups * kg.nb * kg.heads > (1ll << 30)) return LCSA_EINVAL;
     if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)kg.d);
-    if (arithmetic == LCSA_BWD_AUTO && attn_bwd_mfma_supported(kg))
+    if (arithmetic == LCSA_BWD_AUTO && attn_bwd_mfma_supported(kg, q_stride_tok, kv_stride_tok, o_stride_tok))
         return hip_status(launch_attn_bwd_mfma(kg, kv_groups, q, q_stride_tok, q_stride_head, k, v, kv_stride_tok, kv_stride_head,
                                                sel_idx, sel_cnt, d_o, o_stride_tok, o_stride_head, lse, d_q, d_k, d_v, delta, scale,
                                                (hipStream_t)stream));

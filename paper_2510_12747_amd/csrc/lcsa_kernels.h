@@ -172,9 +172,9 @@ hipError_t launch_attn_bwd(const KGeom &g, int kv_groups, const void *q, int64_t
                            float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream);
 
 // The same on the matrix cores (bf16, d = 128, 128-token blocks; chunks of more than 8192 query blocks keep the float path's
-// arithmetic, see attn_bwd_mfma_supported): products in
+// arithmetic, and so do blocks that span 4 GB of a tensor, see attn_bwd_mfma_supported): products in
 // bf16 with float accumulation, probabilities and their gradients rounded to bf16 between the two product levels.
-bool attn_bwd_mfma_supported(const KGeom &g);
+bool attn_bwd_mfma_supported(const KGeom &g, int64_t q_st, int64_t kv_st, int64_t o_st);
 hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, int64_t q_st, int64_t q_sh,
                                 const void *k, const void *v, int64_t kv_st, int64_t kv_sh,
                                 const int32_t *sel_idx, const int32_t *sel_cnt,
