@@ -7,34 +7,34 @@
 // orders, no atomics: results are reproducible bit for bit.
 //
 // Tiles.  A 128-token x 128-channel bf16 tile lives in LDS as 128 rows of 256 bytes, the 16-byte chunk j of row r
-// at chunk position j ^ sw(r), sw(r) = the low four bits of r rotated left by one.  It is copied there straight
+// at chunk position j ^ sw(r), sw(r) = the low four bits of r with their halves exchanged.  It is copied there straight
 // from the raster tensor by direct-to-LDS loads (a wavefront instruction moves 4 rows: lane t lands at byte 16 t of
-// them and fetches the chunk that belongs there), ahead of the computation: the query-side kernel copies a block's K and
-// V tiles into one of two buffers, the key-side kernel streams units of 32 rows of Q and dO through a ring.
+// them and fetches the chunk that belongs there), ahead of the computation: the query-side kernel copies a step's K and
+// V rows into one of two buffers, the key-side kernel streams units of 32 rows of Q and dO through a ring.
 // All products have the form C[m][n] = sum_k A[m][k] B[n][k].  Where the summed index runs along the rows of the
 // tile (first level: over channels), an operand fragment is one ds_read_b128 of a row; where it runs down the
 // columns (second level: over keys or queries), the fragment comes from two transposing reads (ds_read_b64_tr_b16:
 // 16 lanes fetch 4 rows x 16 columns and each receives 4 consecutive rows of one column), so no transposed copy of
 // a tile is ever built.  sw() spreads both kinds of read over the banks: 16 rows with distinct low bits map to 16
-// distinct chunk positions (a kernel of row reads alone showed no conflicts), and 4 consecutive rows map to 4 distinct
-// 32-byte positions (the transposing reads are not free of them: conflict cycles are 0.17 of the LDS index cycles on the
-// query side, 0.24 on the key side).
+// distinct chunk positions, and 4 consecutive rows map to 4 distinct 64-byte positions: 64 banks of 4 bytes serve half a
+// wavefront's transposing read at a time.  No conflicts of either kind (0.17 and 0.24 of the LDS index cycles with 32-byte
+// positions, which 16 lanes at a time would have been content with).
 //
 // Operand reuse without LDS round trips: the rows fed to the matrix rows of a first-level product (S or S^T) are
 // permuted (bits 2 and 3 of the row index swapped), which makes the 8 accumulator registers 8s..8s+7 of a lane
 // hold 8 consecutive indices of the summed dimension of the second-level product: the accumulator, rounded to
 // bf16, IS the A operand of that product.
 //
-//   bwd_dq_mfma_kernel    workgroup = (head, query block), two passes over the kept key blocks: D_i = sum_j p_ij t_ij (stored
-//                         in `delta`), formed from unrounded p and t in float; then u from D and dQ += u K.
+//   bwd_dq_mfma_kernel    workgroup = (head, query block) or half of one, two passes over the kept key blocks:
+//                         D_i = sum_j p_ij t_ij (stored in `delta`), formed from unrounded p and t in float; then u from D
+//                         and dQ += u K.
 //   bwd_dkv_mfma_kernel   workgroup = (head, key block).  Walks the query blocks that kept this block (ascending):
 //                         dV += P^T dO, dK += U^T Q.
-// Every matrix instruction takes one 1 KB operand fragment from LDS (the 64-bit transposing reads at less than half
-// the rate of the 128-bit row reads), and 64 KB of tiles per block pair come from L2 for each of the three passes.
+// Every matrix instruction takes one 1 KB operand fragment from LDS, and 64 KB of tiles per block pair come from L2 for each
+// of the three passes.
 //
-// Paper scale (12 heads, 48 x 88 tokens, k = 32): 632 us + 668 us.  As three kernels, D and dQ apart and dK, dV with four
-// wavefronts, one per SIMD, they took 312 + 506 + 761 us: with one wavefront per SIMD nothing ran beside the exponentials,
-// and every copied row cost a 64-bit address computation.
+// Paper scale (12 heads, 48 x 88 tokens, k = 32): 520 us + 460 us (632 + 668 before their copies and addresses were trimmed; as
+// three kernels, D and dQ apart and dK, dV with four wavefronts, one per SIMD, 312 + 506 + 761 us).
 #include "lcsa_kernels.h"
 #include <utility>
 
@@ -45,10 +45,10 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-constexpr int kTileBytes = 128 * 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kMaxQueryBlocks = 8192;        // more query blocks go to the float kernels.  No limit of the kernels below (they list any
                                              // number, kListed at a time); it keeps the arithmetic that callers of such sizes have had
+constexpr int kLast = 256;                   // flag beside a step's number of keys: a pass over the kept blocks ends with it
 constexpr int kListed = 512;                 // query blocks whose kept flags are turned into a list at a time
 
 #define LCSA_LDS __attribute__((address_space(3)))
@@ -88,7 +88,10 @@ __device__ inline int row_base(int lane) {
     const int row = swap23(lane & 31);
     return img_off(row, lane >> 5);
 }
-__device__ inline bf16x8 frag(const unsigned char *unit, int base, int ks) { return *(const bf16x8 *)(unit + (base ^ (ks << 5))); }
+// Units start at multiples of 256 bytes and the XORs reach bits 4 to 7: unit and base are added once, and
+// every fragment is one XOR further on.
+__device__ inline uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)((LCSA_LDS const unsigned char *)p); }
+__device__ inline bf16x8 frag(uint32_t at, int ks) { return *(LCSA_LDS const bf16x8 *)(uintptr_t)(at ^ (ks << 5)); }
 // Down a column: lane (n, half) receives column 32 nt + n, rows 16 kk + 8 half .. + 7.  A transposing read serves 16 lanes
 // at a time: lane i of the 16 points at 4 elements of row (first + i / 4), columns (c16 + 4 (i % 4) ..), and receives rows
 // first .. first + 3 of column c16 + i.
@@ -96,16 +99,16 @@ __device__ inline int column_base(int lane) {
     const int i = lane & 15, row = 8 * (lane >> 5) + (i >> 2), chunk = 2 * ((lane >> 4) & 1) + ((i >> 1) & 1);
     return img_off(row, chunk) + (i & 1) * 8;
 }
-__device__ inline bf16x8 frag_down(const unsigned char *unit, int base, int nt, int kk) {
-    const unsigned char *a = unit + 4096 * kk;               // rows + 4: four rows further, and bit 0 of sw() flips
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + (base ^ (nt << 6))));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(a + 1024 + (base ^ (nt << 6) ^ 16)));
+__device__ inline bf16x8 frag_down(uint32_t at, int nt, int kk) {
+    // rows + 4: four rows further, and bit 0 of sw() flips
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(uintptr_t)((at ^ (nt << 6)) + 4096 * kk));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LCSA_LDS i16x4 *)(uintptr_t)((at ^ (nt << 6) ^ 16) + 4096 * kk + 1024));
     typedef __attribute__((ext_vector_type(8))) short i16x8;
     const i16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, both);
 }
-// Hides where a base came from, so that the XORs are formed where they are used instead of kept in registers.
-__device__ inline int fresh(int base) { asm volatile("" : "+v"(base)); return base; }
+// The address in a unit; hides where it came from, so that the XORs are formed where they are used instead of kept in registers.
+__device__ inline uint32_t fresh(uint32_t unit, int base) { uint32_t a = unit + base; asm volatile("" : "+v"(a)); return a; }
 
 // The lane's number, formed where it is used: two instructions instead of a register held across a loop.
 __device__ inline int lane_here() {
@@ -129,23 +132,23 @@ __device__ inline void load_own_rows(const KGeom &g, const BlockRef &b, const __
 }
 
 // ---- tile copies -------------------------------------------------------------------------------------------------
-// A wavefront copies 16 rows of a tile with 4 instructions; instruction i moves rows 16 wave + 4 i .. + 3, lane t
-// supplying row (t >> 4), chunk position (t & 15).  A CopyPlan holds, for the 4 rows of a lane, the distance of the
-// lane's 16 bytes from the block's first token (the host sends blocks that reach 4 GB or more to the float kernels).  Made
-// once for the unclipped extent; clipped blocks make their own.  Rows beyond the block's valid tokens are copied as zeros:
-// their probabilities are zero, and zero times an infinity of another row would not be.
-constexpr int kWaves = 8;
+// In the query-side kernel a wavefront copies 16 rows of K and of V a step with 4 instructions per tensor; instruction i moves
+// rows first + 4 i .. + 3 of the block, lane t supplying row (t >> 4), chunk position (t & 15).
+// A CopyPlan holds, for the 4 rows of a lane, the distance of the lane's 16 bytes from the block's first token (the
+// host sends blocks that reach 4 GB or more to the float kernels).  Made once for the unclipped extent; clipped blocks make
+// their own.  Rows beyond the block's valid tokens are copied as zeros: their probabilities are zero, and zero times an
+// infinity of another row would not be.
 // byte offset of a block's i-th token from its first one
 constexpr uint32_t kNoRow = 0xfffffe00u;
 __device__ inline uint32_t row_offset(const KGeom &g, const BlockTokens &bt, int i, int64_t st) { return i < bt.n_valid ? (uint32_t)(rel_token(g, bt, i) * st * 2) : kNoRow; }
 struct CopyPlan { uint32_t at[4]; };
-__device__ inline CopyPlan copy_plan(const KGeom &g, int vh, int vw, int64_t st, int wave, int lane) {
+__device__ inline CopyPlan copy_plan(const KGeom &g, int vh, int vw, int64_t st, int first, int lane) {
     CopyPlan p;
     const BlockTokens bt(g, vh, vw);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int row = 4 * i + (lane >> 4);
-        p.at[i] = row_offset(g, bt, 16 * wave + row, st) + ((lane & 15) ^ sw(row)) * 16;        // 16 wave does not enter sw()
+        const int row = first + 4 * i + (lane >> 4);
+        p.at[i] = row_offset(g, bt, row, st) + ((lane & 15) ^ sw(row)) * 16;
     }
     return p;
 }
@@ -172,7 +175,6 @@ template <int SECOND> __device__ inline void copy_piece_to_lds(int piece, const 
     default: copy_rows_to_lds<SECOND + 3072>(second, offset, lds_rows); break;
     }
 }
-__device__ inline uint32_t lds_address(const unsigned char *p) { return (uint32_t)(uintptr_t)((LCSA_LDS unsigned char *)p); }
 
 // A block as the loops want it: raster token of its first token, and its clipped extent.
 struct Located { int origin, extent; };                      // extent = vh | vw << 16
@@ -195,9 +197,12 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // Launch order.  Workgroups are dealt to the 8 XCDs round-robin, each with an L2 of its own; workgroup ids are
 // mapped so that an XCD walks a contiguous run of (head, tile, frame group) items: neighbouring tiles of a head keep
 // (or are kept by) nearly the same blocks, whose tiles are then found in that XCD's L2.
-__device__ inline bool work_item(const KGeom &g, int groups, int per_xcd, int &head, int &block) {
-    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (item >= g.heads * groups * g.nb) return false;
+// `pieces` workgroups to an item follow one another.
+__device__ inline bool work_item(const KGeom &g, int groups, int pieces, int per_xcd, int &head, int &block, int &piece) {
+    int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (item >= g.heads * groups * g.nb * pieces) return false;
+    piece = item % pieces;
+    item /= pieces;
     head = item / (groups * g.nb);
     const int rem = item - head * groups * g.nb;
     const int tile = rem / groups, grp = rem - tile * groups;
@@ -210,40 +215,45 @@ __device__ inline void zero(f32x16 &a) {
     for (int i = 0; i < 16; ++i) a[i] = 0.f;
 }
 
+// f(FIRST), f(FIRST + 1), ... with constants: what selects a register by row_value() needs them
+template <int FIRST, class F, int... R> __device__ inline void in_turn(F &&f, std::integer_sequence<int, R...>) { (f(std::integral_constant<int, FIRST + R>{}), ...); }
+template <int FIRST, int COUNT, class F> __device__ inline void in_turn(F &&f) { in_turn<FIRST>(f, std::make_integer_sequence<int, COUNT>{}); }
+
 // First-level products of the 32 rows mt of two tiles with two sets of register operands, operand fragments read kAhead
 // pairs ahead of the matrix instructions that use them.
 constexpr int kAhead = 3, kRing = kAhead + 1;
-template <class Also>
-__device__ inline void first_level(const unsigned char *x_unit, const unsigned char *y_unit, int base,
-                                   const bf16x8 (&xf)[8], const bf16x8 (&yf)[8], f32x16 &xs, f32x16 &ys, Also &&also) {
+// also(ks), ks = 0 .. 7: what goes along with the matrix instructions.
+template <int SECOND, class Also>
+__device__ inline void first_level(uint32_t x_unit, int base, const bf16x8 (&xf)[8], const bf16x8 (&yf)[8], f32x16 &xs, f32x16 &ys, Also &&also) {
     bf16x8 xa[kRing], ya[kRing];
-    base = fresh(base);
+    const uint32_t x_at = fresh(x_unit, base);
+    auto frag_v = [](uint32_t at, int ks) { return *(LCSA_LDS const bf16x8 *)(uintptr_t)((at ^ (ks << 5)) + SECOND); };      // the same rows of the second tile
 #pragma unroll
-    for (int n = 0; n < kAhead; ++n) { xa[n] = frag(x_unit, base, n); ya[n] = frag(y_unit, base, n); }
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAhead, 0);
+    for (int n = 0; n < kAhead; ++n) { xa[n] = frag(x_at, n); ya[n] = frag_v(x_at, n); }
     zero(xs); zero(ys);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        also(ks);
-        if (ks + kAhead < 8) {
-            xa[(ks + kAhead) % kRing] = frag(x_unit, base, ks + kAhead);
-            ya[(ks + kAhead) % kRing] = frag(y_unit, base, ks + kAhead);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        }
+    in_turn<0, 8>([&](auto step) {
+        constexpr int ks = step;
+        __builtin_amdgcn_sched_barrier(0);
         xs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[ks % kRing], xf[ks], xs, 0, 0, 0);
+        if constexpr (ks + kAhead < 8) {
+            xa[(ks + kAhead) % kRing] = frag(x_at, ks + kAhead);
+            ya[(ks + kAhead) % kRing] = frag_v(x_at, ks + kAhead);
+        }
+        also(step);
+        __builtin_amdgcn_sched_barrier(0);
         ys = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ya[ks % kRing], yf[ks], ys, 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    }
+    });
+    __builtin_amdgcn_sched_barrier(0);
 }
 // Keeps the work that formed a value from moving past this point.
 __device__ inline void pin(bf16x8 (&v)[2]) { asm volatile("" : "+v"(v[0]), "+v"(v[1])); }
 // Row fragments of a unit
-__device__ inline void read_rows(const unsigned char *unit, int base, bf16x8 (&a)[8]) {
-    base = fresh(base);
+__device__ inline void read_rows(uint32_t unit, int base, bf16x8 (&a)[8]) {
+    const uint32_t at = fresh(unit, base);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) a[ks] = frag(unit, base, ks);
+    for (int ks = 0; ks < 8; ++ks) a[ks] = frag(at, ks);
 }
-__device__ inline void first_level(const unsigned char *x_unit, int base, const bf16x8 (&xf)[8], f32x16 &xs) {
+__device__ inline void first_level(uint32_t x_unit, int base, const bf16x8 (&xf)[8], f32x16 &xs) {
     bf16x8 xa[8];
     read_rows(x_unit, base, xa);
 #pragma unroll
@@ -257,14 +267,11 @@ template <int R> __device__ inline float row_value(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + R, 0xf, 0xf, true));
 }
 template <int R> __device__ inline float add_row(const f32x16 &x, float v) { return x[R] + row_value<R>(v); }
-// f(FIRST), f(FIRST + 1), ... with constants: what selects a register by row_value() needs them
-template <int FIRST, class F, int... R> __device__ inline void in_turn(F &&f, std::integer_sequence<int, R...>) { (f(std::integral_constant<int, FIRST + R>{}), ...); }
-template <int FIRST, int COUNT, class F> __device__ inline void in_turn(F &&f) { in_turn<FIRST>(f, std::make_integer_sequence<int, COUNT>{}); }
 // Column fragments of a unit (B operands of a second-level product: 4 channel groups x 2 k-steps)
-__device__ inline void read_columns(const unsigned char *unit, int base, bf16x8 (&b)[8]) {
-    base = fresh(base);
+__device__ inline void read_columns(uint32_t unit, int base, bf16x8 (&b)[8]) {
+    const uint32_t at = fresh(unit, base);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) b[i] = frag_down(unit, base, i >> 1, i & 1);
+    for (int i = 0; i < 8; ++i) b[i] = frag_down(at, i >> 1, i & 1);
 }
 __device__ inline void second_level(const bf16x8 (&a)[2], const bf16x8 (&b)[8], f32x16 (&acc)[4]) {
 #pragma unroll
@@ -274,21 +281,28 @@ __device__ inline void second_level(const bf16x8 (&a)[2], const bf16x8 (&b)[8], 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// D_i = sum_j p_ij t_ij over the kept key blocks, then once more over them for dQ += u K.  Eight wavefronts, two per SIMD:
-// wavefront w owns queries 32 (w & 3) .. + 31 and, of every kept key block, the 32-key units w >> 2 and (w >> 2) + 2; the
-// two partial results of a query meet in LDS.
-__global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
+// D_i = sum_j p_ij t_ij over the kept key blocks, then once more over them for dQ += u K.  A workgroup of QG x KH wavefronts
+// takes 32 QG queries of a block and walks the kept key blocks in steps of kKeys keys; wavefront w owns queries 32 (w / KH) ..
+// + 31 of them and, of every step, each KH-th 32-key unit; the KH partial results of a query meet in LDS.
+// Which of them when: bwd_query_form().  4 x 1 has 64 KB of tiles, so that two workgroups share a unit; 2 x 4 copies the keys
+// twice for a block's queries, where units would be idle otherwise (54 items, 16 blocks a row: 75 -> 60 us).
+// What bounds it: instructions, as on the key side (457 vector and 69 matrix instructions a wavefront and block before, of which
+// neither hid the other); paper scale 632 -> 520 us.  Tried without gain: the element-wise part of a unit beside the
+// products of the next one, more operands ahead, copies spread over both units.
+template <int QG, int KH>
+__global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     KGeom g, int kv_groups, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
     const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse,
     float *__restrict__ d_q, float *__restrict__ delta, float scale, int per_xcd) {
-    __shared__ __attribute__((aligned(256))) unsigned char img[2][2][kTileBytes];      // [buffer][K, V]
-    __shared__ float part[2][128];
-    int qb, head;
-    if (!work_item(g, g.q_groups, per_xcd, head, qb)) return;
+    constexpr int kKeys = 16 * QG * KH, kUnits = kKeys / 32 / KH, kStepBytes = kKeys * 256;
+    __shared__ __attribute__((aligned(256))) unsigned char img[2][2][kStepBytes];      // [buffer][K, V]
+    __shared__ float part[KH][32 * QG];
+    int qb, head, piece;
+    if (!work_item(g, g.q_groups, 4 / QG, per_xcd, head, qb, piece)) return;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qg = wave & 3, kh = wave >> 2;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qg = wave % QG, kh = wave / QG, first_query = 32 * (QG * piece + qg);
     const int ql = lane & 31, half = lane >> 5;
     const int n_qb = g.q_groups * g.nb;
     const BlockRef qr = block_ref(g, qb);
@@ -299,7 +313,9 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
     const uint32_t lds_img = lds_address(&img[0][0][0]);
     k += (int64_t)head * kv_sh;
     v += (int64_t)head * kv_sh;
-    const CopyPlan plan = copy_plan(g, g.th, g.tw, kv_st, wave, lane);
+    const CopyPlan plan = copy_plan(g, g.th, g.tw, kv_st, 16 * wave, lane);
+    // the second half of an unclipped block: 64 tokens on, which are whole rows or whole frames of the tile or half of its only row
+    const uint32_t half_block = row_offset(g, BlockTokens(g, g.th, g.tw), 64, kv_st);
 
     // kept blocks of this row, 64 at a time, one per lane
     Located chunk = {0, 0};
@@ -307,49 +323,57 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
         // ids outside the visible blocks must not become wild addresses
         if (b0 + lane < cnt) chunk = locate(g, min(max(sel[b0 + lane], 0), kv_groups * g.nb - 1));
     };
-    // The copies of a block's K and V tiles: 8 instructions per wavefront.  Each holds the issuing wavefront while the memory
-    // pipeline accepts it, so they go along with the matrix instructions of the block before.
+    // The steps follow one another through the two tile buffers, in both passes.  A step's copies, 8 instructions per
+    // wavefront, go along with the first unit's products of the step before: a copy holds the issuing wavefront while the
+    // memory pipeline accepts it, and all at once held everybody for 1000 to 2500 cycles a block.
+    // What they need is found out a step earlier still.  The requests simply go on behind the second pass.
     u32x4 k_from, v_from;
     uint32_t copy_to = 0;
     CopyPlan from;
-    auto locate_next = [&](int b, int buf) {
-        if ((b & 63) == 0 && cnt > 64) refill(b);
-        const Located kr = {__builtin_amdgcn_readlane(chunk.origin, b & 63), __builtin_amdgcn_readlane(chunk.extent, b & 63)};
-        k_from = rows_from(k + kr.origin * kv_st);
-        v_from = rows_from(v + kr.origin * kv_st);
-        copy_to = __builtin_amdgcn_readfirstlane(lds_img + buf * 2 * kTileBytes + wave * 4096);
+    int ask = 0, ask_half = 0, asked = 0;
+    auto locate_next = [&]() {                               // returns the valid keys of the step, + kLast if it ends a pass
+        if ((ask & 63) == 0 && ask_half == 0 && cnt > 64) refill(ask);
+        const Located kr = {__builtin_amdgcn_readlane(chunk.origin, ask & 63), __builtin_amdgcn_readlane(chunk.extent, ask & 63)};
+        const bool whole = kr.extent == (g.th | g.tw << 16);
         from = plan;
-        if (kr.extent != (g.th | g.tw << 16)) from = copy_plan(g, kr.extent & 0xffff, kr.extent >> 16, kv_st, wave, lane);
-        return valid_tokens(g, kr);
+        if (!whole) from = copy_plan(g, kr.extent & 0xffff, kr.extent >> 16, kv_st, 64 * ask_half + 16 * wave, lane);
+        const uint64_t at = (uint64_t)(uint32_t)kr.origin * (uint32_t)(kv_st * 2) + (whole && ask_half ? half_block : 0);
+        k_from = rows_from((const char *)k + at);
+        v_from = rows_from((const char *)v + at);
+        copy_to = __builtin_amdgcn_readfirstlane(lds_img + (asked & 1) * 2 * kStepBytes + wave * 4096);
+        ++asked;
+        int n = valid_tokens(g, kr) - 64 * ask_half;
+        ask_half = kKeys == 64 && ask_half == 0 && n > 64;
+        if (!ask_half && ++ask == cnt) { ask = 0; n += kLast; }
+        return n;
     };
-    auto copy_piece = [&](int piece) {
-        copy_piece_to_lds<kTileBytes>(piece, k_from, v_from, from.at[piece >> 1], copy_to);
-    };
+    auto copy_piece = [&](int piece) { copy_piece_to_lds<kStepBytes>(piece, k_from, v_from, from.at[piece >> 1], copy_to); };
     refill(0);
-    int n_next = 0;
+    int n_keys = 0, n_next = 0;                              // of the step at work and of the one behind it
     if (cnt > 0) {
-        n_next = locate_next(0, 0);
+        n_next = locate_next();
 #pragma unroll
         for (int i = 0; i < 8; ++i) copy_piece(i);
     }
 
     // this wavefront's queries: Q and dO fragments (B operands), lse and the token to write to
     bf16x8 qf[8], gf[8];
-    load_own_rows(g, qr, q, q_st, q_sh, head, 32 * qg, lane, qf);
-    load_own_rows(g, qr, d_o, o_st, o_sh, head, 32 * qg, lane, gf);
-    const bool q_ok = 32 * qg + ql < qr.n_valid;
+    load_own_rows(g, qr, q, q_st, q_sh, head, first_query, lane, qf);
+    load_own_rows(g, qr, d_o, o_st, o_sh, head, first_query, lane, gf);
+    const bool q_ok = first_query + ql < qr.n_valid;
     const BlockTokens qt(g, qr.vh, qr.vw);
-    const int64_t q_token = block_origin(g, qr) + rel_token(g, qt, 32 * qg + ql);
+    const int64_t q_token = block_origin(g, qr) + rel_token(g, qt, first_query + ql);
     // padding queries: an infinite reference makes every probability zero
     const float l2 = q_ok ? lse[q_token * g.heads + head] * kLog2e : __builtin_inff();
-    const bool wave_on = 32 * qg < qr.n_valid;               // else only copies and barriers
+    const bool wave_on = first_query < qr.n_valid;           // else only copies and barriers
     // All loads so far are waited for here, where the compiler sees it: left to itself it would wait at their first
     // use inside the loop, on every trip, and each such wait also drains the tile copies in flight (they share the counter).
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0)
     const int rows = row_base(lane), columns = column_base(lane);
+    int n_located = cnt > 0 ? locate_next() : 0;
 
-    // Lane = query ql; register 8 kk + j = key mt*32 + 16 kk + 8 half + j.  Keys beyond the block's valid ones must get
-    // probability zero; only a block's last unit can hold any.
+    // Lane = query ql; register 8 kk + j = key 16 kk + 8 half + j of a 32-key unit.  Of every step the wavefront takes units kh,
+    // kh + KH, .., the later ones only if there are that many keys.  Keys beyond the valid ones must get probability zero.
     auto mask_keys = [&](f32x16 &s, int left) {
         if (left < 32) {                                     // uniform
 #pragma unroll
@@ -359,70 +383,114 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
     };
     auto prob = [&](float s) { return __builtin_amdgcn_exp2f(fmaf(s, scale_log2, -l2)); };
 
-    int step = 0;                                            // tile buffers alternate over both passes
-    auto for_each_unit = [&](bool last_pass, auto &&work) {
-        for (int b = 0; b < cnt; ++b, ++step) {
-            tiles_ready();                                   // block b is in buffer step & 1; nobody reads the other buffer any more
-            const int n_keys = n_next;
-            const bool more = b + 1 < cnt || !last_pass;
-            if (more) n_next = locate_next(b + 1 < cnt ? b + 1 : 0, (step + 1) & 1);
-            auto go_along = [&](int ks) { if (more) copy_piece(ks); };
-            auto no_copies = [](int) {};
-            if (wave_on && kh * 32 < n_keys) work(img[step & 1][0] + kh * 8192, img[step & 1][1] + kh * 8192, n_keys - kh * 32, go_along);
-            else
+    uint32_t tiles = lds_img;
+    int step = 0;
+    bool last = false;
+    auto begin_step = [&]() {
+        tiles_ready();                                       // the step's tiles have landed; everybody is done with the other buffer
+        tiles = lds_img + (step & 1) * 2 * kStepBytes;
+        ++step;
+        n_keys = n_next & (kLast - 1);
+        last = n_next & kLast;
+        n_next = n_located;
+    };
+    // S and T of unit kh + KH * U; the first unit's products take the copies of the next step along
+    f32x16 s, t;
+    auto products = [&](auto U) {
+        __builtin_amdgcn_s_setprio(1);
+        first_level<kStepBytes>(tiles + (kh + KH * U) * 8192, rows, qf, gf, s, t, [&](auto ks) {
+            if constexpr (U == 0) copy_piece(ks);
+        });
+        __builtin_amdgcn_s_setprio(0);
+        mask_keys(s, n_keys - 32 * (kh + KH * U));
+    };
+    // One pass over the steps; work(U) is given S and T of a unit.
+    auto walk = [&](auto &&work) {
+        if (cnt == 0) return;
+        do {
+            begin_step();
+            if (wave_on) {
+                products(std::integral_constant<int, 0>{});
+                work(std::integral_constant<int, 0>{});
+            } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) go_along(i);
-            const int mt = kh + 2;
-            if (wave_on && mt * 32 < n_keys) work(img[step & 1][0] + mt * 8192, img[step & 1][1] + mt * 8192, n_keys - mt * 32, no_copies);
-        }
+                for (int i = 0; i < 8; ++i) copy_piece(i);
+            }
+            n_located = locate_next();
+            if constexpr (kUnits == 2)
+                if (wave_on && n_keys > 32 * KH) {
+                    products(std::integral_constant<int, 1>{});
+                    work(std::integral_constant<int, 1>{});
+                }
+        } while (!last);
     };
 
-    float dsum = 0.f;
-    for_each_unit(false, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left, auto &&also) {
-        f32x16 s, t;
-        first_level(k_unit, v_unit, rows, qf, gf, s, t, also);
-        mask_keys(s, left);
+    float dsum[2] = {0.f, 0.f};                              // KH = 1: one per unit, which makes the sums those of 4 x 2
+    walk([&](auto U) {
+        float &sum = dsum[KH == 1 ? U : 0];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) dsum = fmaf(prob(s[r]), t[r], dsum);
+        for (int r = 0; r < 16; ++r) sum = fmaf(prob(s[r]), t[r], sum);
     });
-    const float d_own = dsum + __shfl_xor(dsum, 32);         // the two half-waves hold the two halves of a unit's keys
-    if (half == 0) part[kh][32 * qg + ql] = d_own;
-    lds_barrier();
-    const float D = part[0][32 * qg + ql] + part[1][32 * qg + ql];
+    float D = dsum[0] + __shfl_xor(dsum[0], 32);             // the two half-waves hold the two halves of a unit's keys
+    if constexpr (KH == 1) D += dsum[1] + __shfl_xor(dsum[1], 32);
+    if constexpr (KH > 1) {
+        if (half == 0) part[kh][32 * qg + ql] = D;
+        lds_barrier();
+        D = part[0][32 * qg + ql];
+#pragma unroll
+        for (int i = 1; i < KH; ++i) D += part[i][32 * qg + ql];
+    }
     if (kh == 0 && half == 0 && q_ok) delta[q_token * g.heads + head] = D;
 
     f32x16 dq[4];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) zero(dq[nt]);
     const float d_scaled = D * scale;
-    for_each_unit(true, [&](const unsigned char *k_unit, const unsigned char *v_unit, int left, auto &&also) {
-        f32x16 s, t;
-        bf16x8 kc[8], u[2];
-        first_level(k_unit, v_unit, rows, qf, gf, s, t, also);
-        read_columns(k_unit, columns, kc);                   // arrives under the element-wise part
-        mask_keys(s, left);
+    walk([&](auto U) {
+        bf16x8 u[2], kc[kRing];
 #pragma unroll
         for (int r = 0; r < 16; ++r) u[r >> 3][r & 7] = (__bf16)(prob(s[r]) * fmaf(t[r], scale, -d_scaled));
-        second_level(u, kc, dq);
+        pin(u);
+        const uint32_t at_columns = fresh(tiles + (kh + KH * U) * 8192, columns);
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) kc[n] = frag_down(at_columns, n >> 1, n & 1);
+        in_turn<0, 8>([&](auto at) {
+            constexpr int n = at;
+            __builtin_amdgcn_sched_barrier(0);
+            dq[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u[n & 1], kc[n % kRing], dq[n >> 1], 0, 0, 0);
+            if constexpr (n + kAhead < 8) kc[(n + kAhead) % kRing] = frag_down(at_columns, (n + kAhead) >> 1, (n + kAhead) & 1);
+        });
+        __builtin_amdgcn_sched_barrier(0);
     });
 
-    // The two wavefronts of a query group exchange halves: wavefront kh finishes channel groups 2 kh, 2 kh + 1.
-    tiles_ready();                                           // nobody reads the tiles any more
-    float *x = (float *)&img[0][0][0] + wave * 2048;
+    tiles_ready();                                           // nobody reads the tiles any more, and no copy may land later
+    // The KH wavefronts of a query group: wavefront kh finishes channel groups kOut kh .. and gets the others' parts of them.
+    constexpr int kOut = 4 / KH;
+    float *x = (float *)&img[0][0][0];                       // [wavefront][channel group][register][lane]
+    if constexpr (KH > 1) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int nt = 0; nt < 4; ++nt)
+            if (nt / kOut != kh)                             // uniform
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 64 + lane] = kh ? dq[i][r] : dq[2 + i][r];
-    lds_barrier();
-    const float *y = (const float *)&img[0][0][0] + (wave ^ 4) * 2048;
+                for (int r = 0; r < 16; ++r) x[((wave * 4 + nt) * 16 + r) * 64 + lane] = dq[nt][r];
+        lds_barrier();
+    }
     // dq tile nt: lane = channel nt*32 + ql, register r = query row 8 (r >> 2) + 4 half + (r & 3) of this wavefront
+    const int64_t origin = block_origin(g, qr);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int qi = 32 * qg + 8 * (r >> 2) + 4 * half + (r & 3);
+        const int qi = first_query + 8 * (r >> 2) + 4 * half + (r & 3);
         if (qi < qr.n_valid) {
-            float *out = d_q + ((block_origin(g, qr) + rel_token(g, qt, qi)) * g.heads + head) * 128 + kh * 64 + ql;
+            float *out = d_q + ((origin + rel_token(g, qt, qi)) * g.heads + head) * 128 + ql;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) out[i * 32] = (kh ? dq[2 + i][r] : dq[i][r]) + y[(i * 16 + r) * 64 + lane];
+            for (int nt = 0; nt < 4; ++nt)
+                if (KH == 1 || nt / kOut == kh) {
+                    float sum = dq[nt][r];
+#pragma unroll
+                    for (int i = 0; i < KH; ++i)
+                        if (i != kh) sum += x[(((i * QG + qg) * 4 + nt) * 16 + r) * 64 + lane];
+                    out[nt * 32] = sum;
+                }
         }
     }
 }
@@ -438,9 +506,10 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_mfma_kernel(
 // Slot t reads units t - 2 .. t + 1, and unit t + 4 is requested into the place of unit t - 3.
 // What bounds it is the number of instructions: a wavefront issues one every five cycles or so, and with 64-bit address
 // products, branches and a spilled operand in each slot (whose reload drained the copies in flight) a slot took 2640 cycles
-// for 1024 of matrix work; it takes 1890 now (paper scale 668 -> 470 us).
+// for 1024 of matrix work; it takes 1840 now (paper scale 668 -> 460 us).
 constexpr int kStages = 7, kLead = kStages - 3;
 constexpr int kUnitBytes = 32 * 256;
+constexpr int kThreads = 512;
 
 struct KeySideLds {
     __attribute__((aligned(256))) unsigned char img[kStages][2][kUnitBytes];      // [stage][Q, dO]
@@ -467,6 +536,7 @@ __device__ __forceinline__ void key_side(
     const BlockRef kr = block_ref(g, kb);
     const float scale_log2 = scale * kLog2e;
     const uint32_t lds_img = lds_address(&lds.img[0][0][0]);
+    auto unit_at = [&](int stage, int which) { return lds_img + stage * 2 * kUnitBytes + which * kUnitBytes; };     // which: 0 = Q, 1 = dO
     q += (int64_t)head * q_sh;
     d_o += (int64_t)head * o_sh;
     // How far token i of a block lies from its first one, for the four extents a block can have (whole; last column, last row
@@ -499,27 +569,29 @@ __device__ __forceinline__ void key_side(
     for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
         // which query blocks kept this key block?  (ascending id lists)
         const int n_here = min(kListed, n_qb - qb0);
+        for (int i = tid; i < n_here; i += kThreads) lds.kept_by[i] = 0;
         tiles_ready();                                       // the previous list and its units are no longer read, and no copy is in flight
-        if (g.topk <= 64) {                                  // 16 lanes look at a row's ids at once
-            for (int i = 4 * wave + (lane >> 4); i < ((n_here + 3) & ~3); i += 4 * kWaves) {
-                bool hit = false;
-                if (i < n_here) {
-                    const int64_t row = (int64_t)head * n_qb + qb0 + i;
-                    const int c = min(max(sel_cnt[row], 0), g.topk);
-                    int ids[4];
+        const int64_t first_row = (int64_t)head * n_qb + qb0;
+        if (g.topk <= 128) {
+            // all ids, eight loads of a thread in flight: with 72 rows of 32 ids one latency instead of three (12 k cycles to
+            // the list, 7 k now); beyond 128 ids a row a search of the row reads less
+            const int32_t *ids = sel_idx + first_row * g.topk;
+            const int total = n_here * g.topk;
+            for (int base = tid; base < total; base += 8 * kThreads) {
+                int id[8];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ids[e] = (lane & 15) + 16 * e < g.topk ? sel_idx[row * g.topk + (lane & 15) + 16 * e] : -1;
+                for (int e = 0; e < 8; ++e) id[e] = base + e * kThreads < total ? ids[base + e * kThreads] : -1;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) hit |= (lane & 15) + 16 * e < c && ids[e] == kb;
-                }
-                const uint64_t hits = __ballot(hit);
-                if ((lane & 15) == 0 && i < n_here) lds.kept_by[i] = (hits >> (lane & 48) & 0xffff) != 0;
+                for (int e = 0; e < 8; ++e)
+                    if (id[e] == kb) {
+                        const int i = (base + e * kThreads) / g.topk;
+                        if (base + e * kThreads - i * g.topk < sel_cnt[first_row + i]) lds.kept_by[i] = 1;
+                    }
             }
         } else {                                             // a binary search per row
-            for (int i = tid; i < n_here; i += 64 * kWaves) {
-                const int64_t row = (int64_t)head * n_qb + qb0 + i;
-                const int32_t *sel = sel_idx + row * g.topk;
-                const int c = min(max(sel_cnt[row], 0), g.topk);
+            for (int i = tid; i < n_here; i += kThreads) {
+                const int32_t *sel = sel_idx + (first_row + i) * g.topk;
+                const int c = min(max(sel_cnt[first_row + i], 0), g.topk);
                 int lo = 0, hi = c;
                 while (lo < hi) { const int mid = (lo + hi) >> 1; if (sel[mid] < kb) lo = mid + 1; else hi = mid; }
                 lds.kept_by[i] = lo < c && sel[lo] == kb;
@@ -640,7 +712,7 @@ __device__ __forceinline__ void key_side(
             }
         } else if constexpr (P_ROLE) {
             float l_now = row_stat(0, 0);
-            first_level(lds.img[0][0], rows, own, x);
+            first_level(unit_at(0, 0), rows, own, x);
             bf16x8 cols[8];                                  // of unit t - 1
 #pragma unroll
             for (int n = 0; n < 8; ++n)
@@ -650,14 +722,13 @@ __device__ __forceinline__ void key_side(
             for (int t = 0, now = 0; t <= n_units; ++t, now = wrap(now + 1)) {
                 refill(t + 4);
                 bf16x8 xa[8], wn[2];
-                const unsigned char *next = lds.img[wrap(now + 1)][0];
-                const int base = fresh(rows);
+                const uint32_t next = fresh(unit_at(wrap(now + 1), 0), rows);
                 float l_next;
                 in_turn<0, 8>([&](auto step) {
                     constexpr int n = step;
                     __builtin_amdgcn_sched_barrier(0);
                     acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
-                    xa[n] = frag(next, base, n);
+                    xa[n] = frag(next, n);
                     if (n == 0) l_next = row_stat(wrap(now + 1), 0);
                     in_turn<2 * n, 2>([&](auto reg) {
                         constexpr int e = reg;
@@ -671,13 +742,13 @@ __device__ __forceinline__ void key_side(
                 });
                 pin(wn);
                 asm volatile("" ::: "memory");               // P(t) and the row values are written before the column reads below
-                const int col_base = fresh(columns);
+                const uint32_t down = fresh(unit_at(now, 1), columns);
                 zero(x);
 #pragma unroll
                 for (int n = 0; n < 8; ++n) {
                     __builtin_amdgcn_sched_barrier(0);
                     x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[n], own[n], x, 0, 0, 0);
-                    cols[n] = frag_down(lds.img[now][1], col_base, n >> 1, n & 1);      // for the next slot: these need not wait for the barrier
+                    cols[n] = frag_down(down, n >> 1, n & 1);      // for the next slot: these need not wait for the barrier
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 w[0] = wn[0]; w[1] = wn[1];
@@ -692,7 +763,7 @@ __device__ __forceinline__ void key_side(
             // T(t - 1) first, then U(t - 1) beside dK: while the first role's wavefront of the SIMD is at its exponentials this
             // one has matrix work only, and the other way round.
             bf16x8 cols[8], xa[8];                           // of unit t - 2, of unit t - 1
-            read_rows(lds.img[0][1], rows, xa);
+            read_rows(unit_at(0, 1), rows, xa);
             request_rows(kLead, kLead);
             end_of_slot();
 #pragma unroll 1
@@ -702,24 +773,24 @@ __device__ __forceinline__ void key_side(
                 float4 p4[4];
                 float d_last;
                 const float4 *p_from = p_to + (t & 1 ? 0 : 1024);
-                const int col_base = fresh(columns);
+                const uint32_t down = fresh(unit_at(before, 0), columns);
                 zero(x);
                 in_turn<0, 8>([&](auto step) {
                     constexpr int n = step;
                     __builtin_amdgcn_sched_barrier(0);
                     x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[n], own[n], x, 0, 0, 0);
-                    cols[n] = frag_down(lds.img[before][0], col_base, n >> 1, n & 1);
+                    cols[n] = frag_down(down, n >> 1, n & 1);
                     if (n == 0) locate_rows(t + kLead, wrap(now + kLead));
                     if constexpr (n >= 4) p4[n - 4] = p_from[64 * (n - 4)];
                     if (n == 4) d_last = row_stat(last, 1);
                     if (n == 3 || n == 6) copy_rows(n / 6);
                 });
-                const int base = fresh(rows);
+                const uint32_t across = fresh(unit_at(now, 1), rows);
                 in_turn<0, 8>([&](auto step) {
                     constexpr int n = step;
                     __builtin_amdgcn_sched_barrier(0);
                     acc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n & 1], cols[n], acc[n >> 1], 0, 0, 0);
-                    xa[n] = frag(lds.img[now][1], base, n);
+                    xa[n] = frag(across, n);
                     if constexpr (n >= 2 && n < 6)
                         in_turn<4 * (n - 2), 4>([&](auto reg) { constexpr int e = reg; wn[e >> 3][e & 7] = (__bf16)((&p4[e >> 2].x)[e & 3] * add_row<e>(x, d_last)); });
                     if (n == 1 || n == 6) copy_rows(2 + n / 6);
@@ -752,8 +823,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse, const float *__restrict__ delta,
     float *__restrict__ d_k, float *__restrict__ d_v, float scale, int per_xcd) {
     __shared__ KeySideLds lds;
-    int kb, head;
-    if (!work_item(g, kv_groups, per_xcd, head, kb)) return;
+    int kb, head, whole;
+    if (!work_item(g, kv_groups, 1, per_xcd, head, kb, whole)) return;
     if (__builtin_amdgcn_readfirstlane(threadIdx.x) < 256)
         key_side<true>(lds, kb, head, g, q, q_st, q_sh, k, kv_st, kv_sh, sel_idx, sel_cnt, d_o, o_st, o_sh, lse, delta, d_v, scale);
     else
@@ -775,9 +846,24 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
                                 const int32_t *sel_idx, const int32_t *sel_cnt,
                                 const void *d_o, int64_t o_st, int64_t o_sh, const float *lse,
                                 float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream) {
-    const int q_per_xcd = (g.q_groups * g.nb * g.heads + 7) / 8, k_per_xcd = (kv_groups * g.nb * g.heads + 7) / 8;
-    bwd_dq_mfma_kernel<<<dim3(q_per_xcd * 8), 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
-                                                                kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, d_q, delta, scale, q_per_xcd);
+    const int k_per_xcd = (kv_groups * g.nb * g.heads + 7) / 8;
+    int n_cu = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
+    const int items = g.q_groups * g.nb * g.heads;
+    auto query_side = [&](auto QG, auto KH) {
+        const int per_xcd = (items * (4 / QG) + 7) / 8;
+        bwd_dq_mfma_kernel<QG, KH><<<dim3(per_xcd * 8), 64 * QG * KH, 0, stream>>>(
+            g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v, kv_st, kv_sh, sel_idx, sel_cnt,
+            (const __bf16 *)d_o, o_st, o_sh, lse, d_q, delta, scale, per_xcd);
+    };
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 4> four{};
+    const BwdQueryForm form = bwd_query_form(items, n_cu);
+    if (form == kBwd4x1) query_side(four, one);
+    else if (form == kBwd4x2) query_side(four, two);
+    else query_side(two, four);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     bwd_dkv_mfma_kernel<<<dim3(k_per_xcd * 8), 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,

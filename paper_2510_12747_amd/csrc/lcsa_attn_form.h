@@ -1,4 +1,4 @@
-// How a launch of the matrix-core attention kernel deals its work items (one per (head, query block)) out to workgroups.
+// How launches of the matrix-core attention kernels deal their work items (one per (head, query block)) out to workgroups.
 // Host arithmetic only.
 #pragma once
 
@@ -29,5 +29,24 @@ inline AttnForm attn_form(int items, int units, int k) {
 }
 
 inline int attn_workgroups(AttnForm form, int items) { return form == kAttnPairs ? (items + 1) / 2 : items; }
+
+// Query-side backward: wavefronts of a workgroup = query groups of 32 x shares of the keys.
+enum BwdQueryForm {
+    kBwd4x1 = 0,         // a block's four query groups; two workgroups share a unit
+    kBwd4x2 = 1,         // the same with the keys shared by two wavefronts each: a workgroup has a unit to itself
+    kBwd2x4 = 2,         // half a block's queries, the keys shared by four
+};
+
+// Two workgroups of 4 x 1 on a unit take 1.86 times as long as one of 4 x 2 (they do not wait at each other's barriers), one
+// that has the unit to itself 1.4 times: with an odd number of rounds of 4 x 2 the last one would be such.  Whole backward,
+// 4 x 1 / 4 x 2 / 2 x 4 in us on 256 units: 72 items 231 / 188 / 170, 126 items 155 / 139 / 124, 144 items 158 / 142 / 164,
+// 252 items 189 / 181 / 207, 270 items 220 / 247 / 243, 288 items 381 / 418 / 427, 432 items 502 / 512 / 580, 576 items
+// 714 / 686 / 731, 864 items 959 / 991 / 1125, 960 items 1111 / 1143 / 1257, 1152 items 1305 / 1327 / 1469, 1680 items
+// 1118 / 1157 / 1294.
+inline BwdQueryForm bwd_query_form(int items, int units) {
+    const int rounds = (items + units - 1) / units;
+    if (rounds <= 1) return 2 * items <= units ? kBwd2x4 : kBwd4x2;
+    return rounds == 3 ? kBwd4x2 : kBwd4x1;
+}
 
 } // namespace lcsa

@@ -1,5 +1,6 @@
-"""CPU check of the rule that deals a launch's work items out to workgroups (csrc/lcsa_attn_form.h), against the measured
-times of the launch forms in profiles/: where the rule says so, the other form is not faster by more than the runs differ."""
+"""CPU check of the rules that deal a launch's work items out to workgroups (csrc/lcsa_attn_form.h), the forward's against the
+measured times of the launch forms in profiles/: where the rule says so, the other form is not faster by more than the runs
+differ."""
 import ctypes
 import os
 import subprocess
@@ -16,6 +17,7 @@ def rule(tmp_path_factory):
     src, lib = tmp / "form.cpp", tmp / "form.so"
     src.write_text('#include "lcsa_attn_form.h"\n'
                    'extern "C" int form(int items, int units, int k) { return lcsa::attn_form(items, units, k); }\n'
+                   'extern "C" int bwd_form(int items, int units) { return lcsa::bwd_query_form(items, units); }\n'
                    'extern "C" int workgroups(int form, int items) { return lcsa::attn_workgroups((lcsa::AttnForm)form, items); }\n')
     subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2510_12747_amd", "csrc"),
                     "-o", str(lib), str(src)], check=True)
@@ -59,3 +61,11 @@ def test_edges_of_the_rule(rule):
         assert rule.form((2 * n + 2) * 256, 256, 1 << 30) == PAIRS        # as many half rounds either way
     assert rule.form(13 * 256, 256, 1 << 30) == PAIRS
     assert [rule.workgroups(f, 7) for f in (PAIRS, SPLIT, ALONE)] == [4, 7, 7]
+
+
+def test_edges_of_the_query_side_backward_rule(rule):
+    four, eight, halves = 0, 1, 2
+    for units in (32, 256, 304):
+        assert [rule.bwd_form(n, units) for n in (1, units // 2, units // 2 + 1, units)] == [halves, halves, eight, eight]
+        assert [rule.bwd_form(n, units) for n in (units + 1, 2 * units, 2 * units + 1, 3 * units, 3 * units + 1)] == [four, four, eight, eight, four]
+        assert rule.bwd_form(1 << 30, units) == four

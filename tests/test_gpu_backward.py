@@ -150,6 +150,43 @@ def test_matrix_core_backward_with_more_than_64_kept_blocks(topk):
     run_backward(wl.with_overrides(wl.WORKLOADS["small"], name=f"bwd-topk{topk}", heads=1, q_frames=1, cache_frames=16, radius=-1, topk=topk))
 
 
+@pytest.mark.parametrize("heads,grid_h,grid_w,tile,topk", [
+    # rows of 80, 40 and 25 valid tokens: steps of 64 keys with a second half, with none, and units without keys
+    (7, 21, 37, (1, 8, 16), 3),        # 126 items: half a block's queries to a workgroup
+    (8, 21, 37, (1, 8, 16), 3),        # 144: the keys shared by two wavefronts
+    (15, 21, 37, (1, 8, 16), 3),       # 270: two workgroups on a unit
+    (8, 18, 18, (2, 8, 8), 5),         # 9 blocks a group: 72 items
+    (32, 18, 18, (2, 8, 8), 5),        # 288: the second half of a block is its second frame
+    (11, 9, 130, (1, 1, 128), 4),      # 396: the second half of a block is half of its only row, or two tokens
+    (33, 9, 9, (8, 4, 4), 3),          # 297: 8 frames of 16 tokens
+])
+def test_matrix_core_backward_forms_of_the_query_side(heads, grid_h, grid_w, tile, topk):
+    frames = max(2, tile[0])
+    run_backward(wl.with_overrides(wl.WORKLOADS["small"], name=f"bwd-form-{heads}-{tile}", heads=heads, grid_h=grid_h, grid_w=grid_w,
+                                   q_frames=frames, cache_frames=2 * frames, tile_h=tile[1], tile_w=tile[2], radius=16, topk=topk),
+                 chunks=2, tile_t=tile[0])
+
+
+def test_blocks_that_span_four_gigabytes_take_the_float_kernels():
+    """Two tokens further apart than the matrix-core kernels' 32-bit offsets allow, and just not: the results are those of the
+    same values stored densely, on the float and on the matrix-core path."""
+    g = B.Geom(1, 128, 1, 2, 8, 16, 1, 2, -1, -1, 2)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    q, k, v, d_o = (torch.randn(n, 1, 128, generator=gen, device="cuda").bfloat16() for n in (2, 4, 4, 2))
+    cache = B.lcsa_cache_init(g)
+    B.lcsa_kv_cache_append(cache, k, v, 2)
+    _, sel_idx, sel_cnt, _ = B.lcsa_pool_select_blocks(g, q, cache)
+    lse = torch.empty(2, 1, device="cuda")
+    B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
+    storage = torch.empty((1 << 30) + 8 + 128, dtype=torch.bfloat16, device="cuda")
+    for stride, float_path in ((1 << 30, False), ((1 << 30) + 8, True)):
+        wide = storage.as_strided((2, 1, 128), (stride, 128, 1))
+        wide.copy_(q)
+        for got, want in zip(B.lcsa_sparse_attn_bwd(g, wide, k, v, 2, sel_idx, sel_cnt, d_o, lse),
+                             B.lcsa_sparse_attn_bwd(g, q, k, v, 2, sel_idx, sel_cnt, d_o, lse, float_path=float_path)):
+            assert torch.equal(got, want)
+
+
 def test_backward_is_deterministic_and_rejects_bad_arguments():
     w = wl.with_overrides(wl.WORKLOADS["small"], name="bwd-det", heads=2, grid_h=16, grid_w=32, topk=4)
     a = run_backward(w)
