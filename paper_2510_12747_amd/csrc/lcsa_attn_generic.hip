@@ -25,7 +25,10 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
     KGeom g, KCache c, const T *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     T *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse, float scale_log2, int per_xcd) {
-    constexpr int GI = NT <= 4 ? 4 : NT <= 8 ? 2 : 1;
+    // Groups whose operands are loaded together.  Float rows take twice the registers of bf16 ones: with four groups there was one
+    // wavefront per SIMD at d = 64 (20.6 us for 2 heads of 20 x 40 tokens, 17.4 with two groups) and a walk of four groups, the
+    // smallest, left three of the four wavefronts without any (7.1 us, 5.6); bf16 gains from four (35.0 us with two, 33.1).
+    constexpr int GI = NT <= 4 ? (sizeof(T) == 4 ? 2 : 4) : NT <= 8 ? 2 : 1;
     __shared__ float part_ml[4][QS][2][16];                  // [wavefront][piece][max, sum][query]
     __shared__ f32x4 part_o[4][QS][NT][64];
     // XCD-aware order: an XCD (workgroup id mod 8) gets a contiguous run of (head, query block) items
