@@ -62,12 +62,18 @@ __global__ __launch_bounds__(kThreads) void importance_rows_kernel(KGeom g, KCac
                 const int t = (y0 + wy) * g.tx + x0 + (w - wy * wx);
                 const int slot = cache_slot(c, g, start, head, f);
                 const float4 *kr = (const float4 *)(c.pooled + (((int64_t)head * g.cap + slot) * g.nb + t) * g.d);
-                for (int e4 = part; e4 < n4; e4 += 4) {
-                    const float4 kk = kr[e4];
-                    s = fmaf(qs[4 * e4], kk.x, s);
-                    s = fmaf(qs[4 * e4 + 1], kk.y, s);
-                    s = fmaf(qs[4 * e4 + 2], kk.z, s);
-                    s = fmaf(qs[4 * e4 + 3], kk.w, s);
+                for (int e0 = part; e0 < n4; e0 += 4 * 16) {          // all loads of a lane issued first: 5.6 -> 4.9 us (108 rows of 36)
+                    float4 kk[16];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) kk[u] = e0 + 4 * u < n4 ? kr[e0 + 4 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) {
+                        const int e = (e0 + 4 * u < n4 ? e0 + 4 * u : 0) * 4;
+                        s = fmaf(qs[e], kk[u].x, s);
+                        s = fmaf(qs[e + 1], kk[u].y, s);
+                        s = fmaf(qs[e + 2], kk[u].z, s);
+                        s = fmaf(qs[e + 3], kk[u].w, s);
+                    }
                 }
             }
             s += __shfl_xor(s, 1);
