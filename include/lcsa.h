@@ -244,8 +244,8 @@ int32_t lcsa_pool_select_blocks(const lcsa_geom *geom, const void *q, int64_t q_
  * formed from the stored element type with float accumulation and a float online
  * softmax; on the matrix-core path probabilities and V enter the second product as IEEE half
  * (range of V: see lcsa_kv_cache_append).
- * On the matrix-core path the blocks of a row may be summed in two halves, each with a softmax of its own, merged at the
- * end: where the number of rows of the call, the blocks a row keeps and the device's compute units make that faster.  The
+ * On the matrix-core path the blocks of a row may be summed in two halves, or their keys in four quarters, each with a softmax
+ * of its own, merged at the end: where the number of rows of the call, the blocks a row keeps and the device's compute units make that faster.  The
  * same call gives the same bits every time; the same row in a call of another size, or on a device with another number of
  * units, may differ in the rounding of the result.
  * Rows with sel_cnt = 0 produce zeros (lse = -inf); so do rows whose scores are all -inf.  Counts outside [0, topk] and ids outside the

@@ -8,6 +8,7 @@ enum AttnForm {
     kAttnPairs = 0,      // two items per workgroup, one per group of four wavefronts
     kAttnSplit = 1,      // one item per workgroup, its blocks shared between the groups, the partial results merged
     kAttnAlone = 2,      // one item per workgroup on one group, the other only keeps the barriers company
+    kAttnFew = 3,        // two workgroups to an item, half its queries each (a kernel of its own)
 };
 
 // A workgroup holds a compute unit to itself, so a launch takes rounds = ceil(workgroups / units), each as long as the blocks
@@ -28,7 +29,13 @@ inline AttnForm attn_form(int items, int units, int k) {
     return rounds_split == 2 * n + 1 && n <= 5 && k > n * (9 + n) / 2 ? kAttnSplit : kAttnPairs;
 }
 
-inline int attn_workgroups(AttnForm form, int items) { return form == kAttnPairs ? (items + 1) / 2 : items; }
+// Before the rule above: where two workgroups an item still leave nobody waiting, an item is faster in two halves of its
+// queries than in two of its keys, which spares the second half of the blocks one after the other.  Whole / two halves, us on 256
+// units: 18 items of 16 blocks 28.0 / 21.8, 54 of 16 28.2 / 24.2, 108 of 16 29.6 / 24.4, 108 of 32 48.2 / 40.0, 126 of 16
+// 30.0 / 25.8, 72 of 64 84.7 / 67.3, 72 of 8 20.1 / 16.8, 9 of one, two and four 9.4 / 8.6, 11.5 / 9.5, 13.8 / 11.2.
+inline bool attn_few(int items, int units) { return items <= units / 2; }
+
+inline int attn_workgroups(AttnForm form, int items) { return form == kAttnPairs ? (items + 1) / 2 : form == kAttnFew ? 2 * items : items; }
 
 // Query-side backward: wavefronts of a workgroup = query groups of 32 x shares of the keys.
 enum BwdQueryForm {

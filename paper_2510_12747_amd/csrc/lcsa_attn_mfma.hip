@@ -4,7 +4,8 @@
 // A workgroup has 8 wavefronts = two GROUPS of 4, each with its own K and V tile buffers in LDS;
 // wavefront w of a group owns query rows 32w .. 32w+31.  By the size of the launch (lcsa_attn_form.h)
 // each group owns one work item (the two query blocks of the same spatial tile, which share their
-// window), or both share one item's selected blocks, or one group owns the only item.
+// window), or both share one item's selected blocks, or one group owns the only item.  Launches of
+// at most half an item per compute unit take a kernel of their own (attn_mfma_few_kernel).
 //
 // Per selected key block a group runs
 //     QK   S^T = K Q^T        v_mfma_f32_32x32x16_bf16  (keys on the row axis, queries on lanes)
@@ -537,6 +538,219 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     LCSA_STAMP(3)
 }
 
+// Few items: a workgroup takes 64 of a block's 128 queries, so that two workgroups work on an item.  Wavefront w owns queries
+// 32 (w >> 2) .. + 31 of them and, of every selected block, the 32 keys of unit w & 3, with a softmax of its own over the keys
+// it sees; the four partial results of a query meet in LDS at the end.  One barrier a block; the next block's copies go along
+// with the first product.
+// What bounds it: the arrival of the copies, 64 KB a block for half the queries, one block ahead (0.93 us a block; issued later,
+// or with the values waited for apart, it is 10 to 15 % slower); it is used only where units would be idle otherwise.
+__global__ __launch_bounds__(512, 2) void attn_mfma_few_kernel(
+    KGeom g, KCache c, const __bf16 *__restrict__ q, int64_t q_st, int64_t q_sh,
+    const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
+    __bf16 *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse,
+    float scale_log2, int total_items, int wg_per_xcd) {
+    __shared__ __attribute__((aligned(256))) unsigned char lds[2][2][kTileBytes];      // [stage][K, V]; at the end the partial results
+    __shared__ float2 softmax_all[4][64];                                              // [unit][query] reference and sum
+    const int wg = (blockIdx.x & 7) * wg_per_xcd + (blockIdx.x >> 3);
+    if (wg >= 2 * total_items) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qg = wave >> 2, unit = wave & 3;
+    const int ql = lane & 31, half = lane >> 5;
+    const int n_qb = g.q_groups * g.nb;
+    const int item = wg >> 1, head = item / n_qb, rem = item - head * n_qb;
+    const int tile = rem / g.q_groups, fq = rem - tile * g.q_groups, qb = fq * g.nb + tile;    // items ordered (head, tile, group)
+    const int by = tile / g.tx, bx = tile - by * g.tx;
+    const int qvh = min(g.th, g.H - by * g.th), qvw = min(g.tw, g.W - bx * g.tw);
+    const int first_query = 64 * (wg & 1);
+    if (first_query >= g.tt * qvh * qvw) return;             // a clipped block without a second half
+
+    const int64_t row = (int64_t)head * n_qb + qb;
+    const int32_t *sel = sel_idx + row * g.topk;
+    const int start = ring_start(c, g);
+    int cnt = sel_cnt[row];
+    const int32_t first_ids = lane < g.topk ? sel[lane] : -1;
+    const int tq = first_query + 32 * qg + ql;
+    int qft, qr, qc;
+    const bool q_valid = block_token(g, tq, qvh, qvw, qft, qr, qc);
+    const int64_t token = q_valid ? raster_token(g, fq, qft, by * g.th + qr, bx * g.tw + qc)
+                                  : raster_token(g, fq, 0, by * g.th, bx * g.tw);       // padding rows: the block's first token
+    bf16x8 bq[8];
+    {
+        const __bf16 *qp = q + token * q_st + (int64_t)head * q_sh + half * 8;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) bq[s] = *(const bf16x8 *)(qp + s * 16);
+    }
+    cnt = min(max(__builtin_amdgcn_readfirstlane(cnt), 0), g.topk);
+    const char *k_head = (const char *)c.k + (int64_t)head * g.cap * g.nb * kTileBytes;
+    const char *v_head = (const char *)c.v + (int64_t)head * g.cap * g.nb * kTileBytes;
+    const int ph = g.H - (g.ty - 1) * g.th, pw = g.W - (g.tx - 1) * g.tw;   // extent of clipped edge tiles
+    const uint32_t copy_voff = wave * 4096 + lane * 16;
+    const uint32_t lds_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)((LCSA_LDS unsigned char *)&lds[0][0][0]));
+    uint32_t blk_chunk = lane < cnt ? pack_block(g, c, start, head, first_ids, ph, pw) : 0u;
+    // piece of this wavefront's eighths of a block's K and V tiles
+    auto copy_piece = [&](uint32_t blk, int stage, int piece) {
+        const int64_t off = (int64_t)(blk & 0xffffffu) * kTileBytes;
+        const uint32_t dst = lds_at + stage * 2 * kTileBytes + wave * 4096;
+        if (piece < 4) copy_piece_to_lds(k_head + off, copy_voff, dst, piece);
+        else copy_piece_to_lds(v_head + off, copy_voff, dst + kTileBytes, piece - 4);
+    };
+    uint32_t blk = 0, blk_next = __builtin_amdgcn_readfirstlane(blk_chunk);
+    if (cnt > 0)
+#pragma unroll
+        for (int piece = 0; piece < 8; ++piece) copy_piece(blk_next, 0, piece);
+
+    // operand offsets as in the kernel above, for this wavefront's 32 keys
+    const int krow = (ql & 0x13) | ((ql & 4) << 1) | ((ql & 8) >> 1);
+    const int k_base = (32 * unit + krow) * 256 + (((half ^ krow) & 15) << 4);
+    const int v_base = kTileBytes + ql * 256 + (((4 * unit + half) ^ (ql & 15)) << 4);
+    f32x16 oacc[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+    float m_run = -__builtin_inff(), l_run = 0.f;
+    bool started = false;                                    // this wavefront has seen a key
+    __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), visible to the compiler
+
+    for (int it = 0; it < cnt; ++it) {
+        wait_vm0();                                          // the block's tiles have landed,
+        stage_barrier();                                     // everybody's, and everybody is done with the other stage
+        blk = blk_next;
+        if (((it + 1) & 63) == 0 && it + 1 < cnt)
+            blk_chunk = it + 1 + lane < cnt ? pack_block(g, c, start, head, sel[it + 1 + lane], ph, pw) : 0u;
+        blk_next = __builtin_amdgcn_readlane(blk_chunk, min(it + 1, cnt - 1) & 63);       // behind the last block itself again
+        const unsigned char *tiles = lds[it & 1][0];
+        const int nv = block_keys(blk) - 32 * unit;          // valid keys from this unit on
+        f32x16 sacc;
+        {
+            __builtin_amdgcn_s_setprio(2);
+            bf16x8 ka[kRing];
+#pragma unroll
+            for (int n = 0; n < kAhead; ++n) ka[n] = *(const bf16x8 *)(tiles + (k_base ^ (n << 5)));
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+#pragma unroll
+            for (int n = 0; n < 8; ++n) {
+                __builtin_amdgcn_sched_barrier(0);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[n % kRing], bq[n], sacc, 0, 0, 0);
+                if (n + kAhead < 8) ka[(n + kAhead) % kRing] = *(const bf16x8 *)(tiles + (k_base ^ ((n + kAhead) << 5)));
+                copy_piece(blk_next, (it + 1) & 1, n);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+        }
+        if (nv <= 0) continue;                               // uniform over the wavefront
+        if (nv < 32) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if ((i >> 3) * 16 + (i & 7) + 8 * half >= nv) sacc[i] = -__builtin_inff();
+        }
+        // reference as in the kernel above: exact for the first keys, kept finite, checked afterwards
+        auto row_max = [&]() {
+            float mx = sacc[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
+            return fmaxf(mx, __shfl_xor(mx, 32));
+        };
+        if (!started) { m_run = fmaxf(row_max() * scale_log2, -__FLT_MAX__); started = true; }
+        f16x8 pfrag[2];
+        const float l_before = l_run;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) softmax_fragment(sacc, 8 * ks, scale_log2, m_run, l_run, pfrag[ks]);
+        if (__ballot(!(l_run - l_before < 16384.f))) {
+            const float m_new = fmaxf(m_run, row_max() * scale_log2);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run = l_before * alpha;
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
+            m_run = m_new;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) softmax_fragment(sacc, 8 * ks, scale_log2, m_run, l_run, pfrag[ks]);
+        }
+        __builtin_amdgcn_s_setprio(2);
+        f16x8 va[kRing];
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) va[n] = *(const f16x8 *)(tiles + (n >> 1) * 8192 + (v_base ^ ((n & 1) << 5)));
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            __builtin_amdgcn_sched_barrier(0);
+            oacc[n >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[n % kRing], pfrag[n & 1], oacc[n >> 1], 0, 0, 0);
+            if (n + kAhead < 8) va[(n + kAhead) % kRing] = *(const f16x8 *)(tiles + ((n + kAhead) >> 1) * 8192 + (v_base ^ (((n + kAhead) & 1) << 5)));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+    }
+
+    // ---- epilogue: wavefront (qg, unit) finishes channels 32 unit .. + 31 of its queries from the four partial results
+    float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (half == 0) softmax_all[unit][32 * qg + ql] = make_float2(m_run, l_tot);
+    wait_vm0();
+    stage_barrier();                                         // nobody reads the tiles any more, and no copy may land later
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    f32x4 *part = (f32x4 *)&lds[0][0][0];                    // [wavefront][channel group][register quad][lane]
+    f32x16 out;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+        if (dt == unit) out = oacc[dt];                      // uniform
+        else
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4)
+                part[((wave * 4 + dt) * 4 + i4) * 64 + lane] = f32x4{oacc[dt][4 * i4], oacc[dt][4 * i4 + 1], oacc[dt][4 * i4 + 2], oacc[dt][4 * i4 + 3]};
+    }
+    stage_barrier();
+    float m_all = -__builtin_inff();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m_all = fmaxf(m_all, softmax_all[u][32 * qg + ql].x);
+    const float ref = m_all == -__builtin_inff() ? 0.f : m_all;      // no keys at all
+    l_tot = 0.f;
+    f32x16 sum;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const float2 ml = softmax_all[u][32 * qg + ql];
+        const float a = __builtin_amdgcn_exp2f(ml.x - ref);
+        l_tot = fmaf(ml.y, a, l_tot);
+        if (u == unit) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum[i] = fmaf(out[i], a, sum[i]);
+        } else {
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                const f32x4 x = part[(((4 * qg + u) * 4 + unit) * 4 + i4) * 64 + lane];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum[4 * i4 + j] = fmaf(x[j], a, sum[4 * i4 + j]);
+            }
+        }
+    }
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    if (lse && unit == 0 && half == 0 && q_valid)
+        lse[token * g.heads + head] = l_tot > 0.f ? (m_all + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
+    stage_barrier();                                         // the partial results have been read
+    // register i is channel 32 unit + (i >> 2) * 8 + half * 4 + (i & 3): rows of 256 bytes, 16-byte chunk j of row r at j ^ (r & 15)
+    unsigned char *rows = &lds[0][0][0];
+    const int r64 = 32 * qg + ql;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+        bf16x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = (__bf16)(sum[4 * i4 + j] * inv);
+        *(bf16x4 *)(rows + r64 * 256 + (((4 * unit + i4) ^ (r64 & 15)) << 4) + half * 8) = w;
+    }
+    stage_barrier();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = (tid >> 4) + 32 * i, j = tid & 15;
+        int ft, rr, cc;
+        if (block_token(g, first_query + r, qvh, qvw, ft, rr, cc)) {
+            const int64_t tok = raster_token(g, fq, ft, by * g.th + rr, bx * g.tw + cc);
+            *(uint4 *)(o + tok * o_st + (int64_t)head * o_sh + j * 8) = *(const uint4 *)(rows + r * 256 + ((j ^ (r & 15)) << 4));
+        }
+    }
+}
+
 } // namespace
 
 AttnLaunch attn_mfma_launch(const KGeom &g, const KCache &c) {
@@ -544,7 +758,10 @@ AttnLaunch attn_mfma_launch(const KGeom &g, const KCache &c) {
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
     const int total = g.heads * g.nb * g.q_groups, admissible = max_candidates(g, c.valid);
-    const AttnForm form = attn_form(total, n_cu, g.topk < admissible ? g.topk : admissible);
+    AttnForm form = attn_form(total, n_cu, g.topk < admissible ? g.topk : admissible);
+#ifndef LCSA_TIMERS                                          // the other forms are the ones with stamps
+    if (attn_few(total, n_cu)) form = kAttnFew;
+#endif
     return {form, total, (attn_workgroups(form, total) + 7) / 8};
 }
 
@@ -557,7 +774,10 @@ hipError_t launch_attn_mfma(const KGeom &g, const KCache &c, const void *q, int6
                                                                   (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e, total, per_xcd)
     if (form == kAttnPairs) LCSA_CALL(kAttnPairs);
     else if (form == kAttnSplit) LCSA_CALL(kAttnSplit);
-    else LCSA_CALL(kAttnAlone);
+    else if (form == kAttnAlone) LCSA_CALL(kAttnAlone);
+    else
+        attn_mfma_few_kernel<<<dim3(per_xcd * 8), 512, 0, stream>>>(g, c, (const __bf16 *)q, q_st, q_sh, sel_idx, sel_cnt,
+                                                                    (__bf16 *)o, o_st, o_sh, lse, scale * kLog2e, total, per_xcd);
 #undef LCSA_CALL
     return hipGetLastError();
 }

@@ -17,6 +17,7 @@ def rule(tmp_path_factory):
     src, lib = tmp / "form.cpp", tmp / "form.so"
     src.write_text('#include "lcsa_attn_form.h"\n'
                    'extern "C" int form(int items, int units, int k) { return lcsa::attn_form(items, units, k); }\n'
+                   'extern "C" int few(int items, int units) { return lcsa::attn_few(items, units); }\n'
                    'extern "C" int bwd_form(int items, int units) { return lcsa::bwd_query_form(items, units); }\n'
                    'extern "C" int workgroups(int form, int items) { return lcsa::attn_workgroups((lcsa::AttnForm)form, items); }\n')
     subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2510_12747_amd", "csrc"),
@@ -69,3 +70,8 @@ def test_edges_of_the_query_side_backward_rule(rule):
         assert [rule.bwd_form(n, units) for n in (1, units // 2, units // 2 + 1, units)] == [halves, halves, eight, eight]
         assert [rule.bwd_form(n, units) for n in (units + 1, 2 * units, 2 * units + 1, 3 * units, 3 * units + 1)] == [four, four, eight, eight, four]
         assert rule.bwd_form(1 << 30, units) == four
+
+
+def test_edges_of_the_rule_for_few_items(rule):
+    assert [rule.few(n, 256) & 1 for n in (1, 128, 129, 1 << 30)] == [1, 1, 0, 0]
+    assert rule.workgroups(3, 7) == 14

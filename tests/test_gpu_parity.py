@@ -364,6 +364,19 @@ def test_an_item_split_over_the_two_groups_of_a_workgroup(heads, topk, grid):
     run_primed(w, rows=None if heads < 3 else sample_rows(og, 40), check_lse=True)
 
 
+@pytest.mark.parametrize("heads,topk,grid", [
+    (8, 1, (24, 44)),          # 144 items, more than half of the compute units: one block, an item on one group
+    (8, 3, (21, 37)),          # split, two blocks against one; clipped query blocks
+    (3, 192, (64, 64)),        # 192 items, 96 blocks per group
+    (7, 3, (21, 37)),          # 126 items: two workgroups an item; query blocks without a second half
+    (2, 70, (64, 64)),         # the same, the id chunk refilled
+])
+def test_items_on_more_and_on_fewer_than_half_of_the_compute_units(heads, topk, grid):
+    w = wl.with_overrides(wl.WORKLOADS["small"], name=f"half-{heads}-{topk}", heads=heads, grid_h=grid[0], grid_w=grid[1], radius=-1, topk=topk)
+    _, og = geoms(w)
+    run_primed(w, rows=sample_rows(og, 40), check_lse=True)
+
+
 def masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse):
     """Checks o and lse of one frame against float64 on the blocks sel_idx[..., :sel_cnt]; keys of -inf weigh nothing."""
     for head in range(q.shape[1]):
@@ -413,6 +426,28 @@ def test_blocks_whose_scores_are_all_minus_infinity_weigh_nothing(masked, dtype,
     B.lcsa_kv_cache_append(cache, k, v, frames)
     sel_idx = torch.arange(6, dtype=torch.int32, device="cuda").repeat(heads, g.n_qb, 1)
     sel_cnt = torch.full((heads, g.n_qb), 6, dtype=torch.int32, device="cuda")
+    lse = torch.empty(h * w, heads, device="cuda")
+    o = B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
+    masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse)
+
+
+@pytest.mark.parametrize("masked", [(), (0,), (1,), (1, 2), (0, 1, 2, 3, 4, 5)])
+def test_short_rows_and_blocks_of_minus_infinity_in_a_launch_of_split_items(masked):
+    """The two tests above on 24 heads: 144 items, which are split over the two groups of a workgroup instead of dealt out
+    by halves.  Row counts 0 to 6 where nothing is masked, else all six blocks."""
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    h, w, heads = 16, 48, 24
+    g = B.Geom(heads, 128, h, w, 8, 16, 1, 1, -1, -1, 6, dtype=B.LCSA_BF16)
+    q, k, v = (torch.randn(h * w, heads, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    q[..., 0] = 1.0
+    block = (torch.arange(h, device="cuda")[:, None] // 8 * 3 + torch.arange(w, device="cuda")[None, :] // 16).reshape(-1)
+    k[torch.isin(block, torch.tensor(masked, device="cuda", dtype=torch.int64)), :, 0] = float("-inf")
+    cache = B.lcsa_cache_init(g)
+    B.lcsa_kv_cache_append(cache, k, v, 1)
+    sel_idx = torch.arange(6, dtype=torch.int32, device="cuda").repeat(heads, g.n_qb, 1)
+    sel_cnt = torch.full((heads, g.n_qb), 6, dtype=torch.int32, device="cuda")
+    if not masked:
+        sel_cnt = (torch.arange(heads * g.n_qb, device="cuda", dtype=torch.int32) % 7).reshape(heads, g.n_qb).contiguous()
     lse = torch.empty(h * w, heads, device="cuda")
     o = B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt, lse=lse)
     masked_attention(q, k, v, block, sel_idx, sel_cnt, o, lse)
