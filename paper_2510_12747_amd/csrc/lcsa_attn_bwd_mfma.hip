@@ -847,9 +847,6 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
                                 const void *d_o, int64_t o_st, int64_t o_sh, const float *lse,
                                 float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream) {
     const int k_per_xcd = (kv_groups * g.nb * g.heads + 7) / 8;
-    int n_cu = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
     const int items = g.q_groups * g.nb * g.heads;
     auto query_side = [&](auto QG, auto KH) {
         const int per_xcd = (items * (4 / QG) + 7) / 8;
@@ -860,7 +857,7 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
     constexpr std::integral_constant<int, 4> four{};
-    const BwdQueryForm form = bwd_query_form(items, n_cu);
+    const BwdQueryForm form = bwd_query_form(items, compute_units());
     if (form == kBwd4x1) query_side(four, one);
     else if (form == kBwd4x2) query_side(four, two);
     else query_side(two, four);

@@ -12,6 +12,7 @@
 // lane-per-key dot products in vector FMA took 1429 us there (every query re-read all its keys) and 49 us where this
 // takes 7.5 us on the smallest case (1 head, d = 32, f32, 16-token blocks, k = 4).
 #include "lcsa_fp32_mma.h"
+#include <type_traits>
 
 namespace lcsa {
 namespace {
@@ -20,15 +21,11 @@ using namespace fp32mma;
 
 constexpr int kThreads = 256;
 
-template <typename T, int NT, int QS>
+template <typename T, int NT, int QS, int GI>
 __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
     KGeom g, KCache c, const T *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     T *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse, float scale_log2, int per_xcd) {
-    // Groups whose operands are loaded together.  Float rows take twice the registers of bf16 ones: with four groups there was one
-    // wavefront per SIMD at d = 64 (20.6 us for 2 heads of 20 x 40 tokens, 17.4 with two groups) and a walk of four groups, the
-    // smallest, left three of the four wavefronts without any (7.1 us, 5.6); bf16 gains from four (35.0 us with two, 33.1).
-    constexpr int GI = NT <= 4 ? (sizeof(T) == 4 ? 2 : 4) : NT <= 8 ? 2 : 1;
     __shared__ float part_ml[4][QS][2][16];                  // [wavefront][piece][max, sum][query]
     __shared__ f32x4 part_o[4][QS][NT][64];
     // XCD-aware order: an XCD (workgroup id mod 8) gets a contiguous run of (head, query block) items
@@ -172,19 +169,39 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
     }
 }
 
-template <typename T>
+// Whether float rows are walked two groups at a time instead of four.  Four have their loads in flight together, which two make
+// up for where there are more workgroups than fit at four groups' registers (`resident` a unit: 1344 rows of 20 16-token blocks at
+// d = 64 50.7 us with four, 40.2 with two; 384 rows of 20 64-token blocks 157 / 131), or where the last stretch of four would be
+// half empty (5 groups a wavefront, 200 rows, 20.6 / 17.4; one group, 8 rows, 7.1 / 5.6; 10 groups 18.5 / 17.3).  Elsewhere two are
+// slower (28 groups 18.5 / 19.3, 40 groups 78.6 / 83.0).  bf16 rows take half the registers: 33.1 us with four, 35.0 with two.
+bool two_groups(const KGeom &g, const KCache &c, int rows_per_wave, int resident) {
+    const int admissible = max_candidates(g, c.valid), k = g.topk < admissible ? g.topk : admissible;
+    const int per_wave = (k * ((g.bt + 15) >> 4) + 4 / row_ways(g.bt, rows_per_wave) - 1) / (4 / row_ways(g.bt, rows_per_wave));
+    return g.q_groups * g.nb * g.heads > resident * compute_units() || (per_wave - 1) % 4 < 2;
+}
+
+template <typename T, int NT, int QS>
 void launch(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh, const int32_t *sel_idx, const int32_t *sel_cnt,
             void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
     const int per_xcd = (g.q_groups * g.nb * g.heads + 7) / 8;
+    constexpr int GI = NT <= 4 ? 4 : NT <= 8 ? 2 : 1;        // groups whose operands are loaded together
+    auto call = [&](auto gi) {
+        attn_generic_kernel<T, NT, QS, gi><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(
+            g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);
+    };
+    if constexpr (GI == 4 && sizeof(T) == 4)
+        if (two_groups(g, c, 16 * QS, NT == 2 ? (QS == 1 ? 4 : 2) : (QS == 1 ? 2 : 1))) return call(std::integral_constant<int, 2>{});
+    call(std::integral_constant<int, GI>{});
+}
+
+template <typename T>
+void launch(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh, const int32_t *sel_idx, const int32_t *sel_cnt,
+            void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
 #define LCSA_CALL(NT)                                                                                                       \
     {                                                                                                                       \
         constexpr int QS = NT <= 8 ? 2 : 1;      /* 32 query rows per wavefront share each operand fragment */             \
-        if (QS == 2 && g.bt > 16)                                                                                           \
-            attn_generic_kernel<T, NT, QS><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(                                     \
-                g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);        \
-        else                                                                                                                \
-            attn_generic_kernel<T, NT, 1><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(                                      \
-                g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);        \
+        if (QS == 2 && g.bt > 16) launch<T, NT, QS>(g, c, q, q_st, q_sh, sel_idx, sel_cnt, o, o_st, o_sh, lse, scale, stream); \
+        else launch<T, NT, 1>(g, c, q, q_st, q_sh, sel_idx, sel_cnt, o, o_st, o_sh, lse, scale, stream);                    \
     }
     LCSA_FOR_HEAD_DIM(g.d, LCSA_CALL)
 #undef LCSA_CALL

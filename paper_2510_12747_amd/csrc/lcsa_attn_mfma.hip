@@ -754,9 +754,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_few_kernel(
 } // namespace
 
 AttnLaunch attn_mfma_launch(const KGeom &g, const KCache &c) {
-    int n_cu = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 256;
+    const int n_cu = compute_units();
     const int total = g.heads * g.nb * g.q_groups, admissible = max_candidates(g, c.valid);
     AttnForm form = attn_form(total, n_cu, g.topk < admissible ? g.topk : admissible);
 #ifndef LCSA_TIMERS                                          // the other forms are the ones with stamps

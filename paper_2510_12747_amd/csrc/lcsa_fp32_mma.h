@@ -113,7 +113,7 @@ __device__ inline float column_max(float x) { x = fmaxf(x, __shfl_xor(x, 16)); r
 
 // How the four wavefronts of a workgroup share a block of n rows (n > 0) against a list of row groups: `ways` of them
 // take 16-row pieces (16 * S rows each) of the block, and 4 / ways share each piece's list.
-__device__ inline int row_ways(int n, int rows_per_wave) { return n > 2 * rows_per_wave ? 4 : n > rows_per_wave ? 2 : 1; }
+__host__ __device__ inline int row_ways(int n, int rows_per_wave) { return n > 2 * rows_per_wave ? 4 : n > rows_per_wave ? 2 : 1; }
 
 // head_dim -> number of 16-channel tiles the kernels are built for
 #define LCSA_FOR_HEAD_DIM(d, call)                                                                                    \

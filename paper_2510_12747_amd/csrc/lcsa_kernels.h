@@ -152,6 +152,12 @@ hipError_t launch_attn_generic(const KGeom &g, const KCache &c, const void *q, i
                                void *o, int64_t o_st, int64_t o_sh, float *lse, float scale,
                                hipStream_t stream);
 
+// Compute units of the current device.
+inline int compute_units() {
+    int n = 0, dev = 0;
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 256;
+}
+
 // How launch_attn_mfma launches: 8 * per_xcd workgroups, on the current device.
 struct AttnLaunch { AttnForm form; int items, per_xcd; };
 AttnLaunch attn_mfma_launch(const KGeom &g, const KCache &c);

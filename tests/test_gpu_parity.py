@@ -194,6 +194,21 @@ def test_general_path_head_dims_and_block_edges(dtype, d, tile_t, tile_h, tile_w
     say(f"{w.name}: max-abs {r.max_abs:.2e}, mean-abs {r.mean_abs:.2e}")
 
 
+@pytest.mark.parametrize("d,heads,grid,tile,topk", [
+    (32, 1, (6, 8), (4, 4), 8),          # two 16-key groups a wavefront: walked two at a time
+    (32, 1, (6, 8), (4, 4), 12),         # three: four at a time, the last one missing
+    (64, 2, (9, 17), (4, 8), 10),        # five a wavefront, 32-token blocks
+    (64, 2, (9, 17), (4, 8), 8),         # four
+    (64, 9, (28, 40), (4, 4), 12),       # 1260 rows, more than are resident: two at a time
+    (32, 15, (28, 36), (4, 8), 8),       # 1050 rows of 32-token blocks
+])
+def test_general_path_groups_walked_two_and_four_at_a_time(d, heads, grid, tile, topk):
+    w = wl.with_overrides(wl.WORKLOADS["tiny"], name=f"groups-{d}-{topk}", heads=heads, head_dim=d, grid_h=grid[0], grid_w=grid[1],
+                          tile_h=tile[0], tile_w=tile[1], radius=12, topk=topk)
+    _, og = geoms(w)
+    run_primed(w, rows=None if heads < 3 else sample_rows(og, 60), check_lse=True)
+
+
 def test_uneven_appends_wrap_the_ring():
     """Appends of 1, 2, 3 frames against a capacity of 4: a chunk straddles the eviction point."""
     w = wl.with_overrides(SMALL_MFMA, cache_frames=4, q_frames=1, heads=2)
