@@ -1,7 +1,7 @@
 // Block selection: coarse block-to-block scores (Sec. 3.2) restricted to the spatial local
 // window (Sec. 3.3, Fig. 3), then the per-row top-k with ties going to the lower key-block
 // id.  One workgroup owns one (head, query block) row: four lanes share each dot product
-// against an admissible key block, then one wavefront finds the k-th largest score by a 32-step
+// against an admissible key block, then one wavefront parts the k largest scores from the rest by a
 // bitwise search over order-preserving integer keys with ballot/popcount and emits the kept ids
 // in ascending order with ballot prefix counts.  No sort, no atomics, fully deterministic.
 #include "lcsa_kernels.h"
@@ -85,8 +85,11 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
     };
 
     // ---- scores: four lanes per candidate, each a quarter of the channels (interleaved float4s so
-    // that the four lanes read one contiguous 64-byte piece at a time); all loads of a lane are
-    // issued before the first FMA
+    // that the four lanes read one contiguous 64-byte piece at a time); up to eight loads of a lane,
+    // all of them at 128 channels, are issued before the first FMA.  Whole groups of 8, 4, 2 and 1: no lane
+    // does products beyond the channels (16 at a time with zeros in place of what was missing issued twice the FMAs
+    // and LDS reads at 128 channels, four times at 64: 28.7 -> 24.4 us for a layer call of 12 heads
+    // on a 90 x 160 grid, 2880 rows).
     {
         const int part = tid & 3, n4 = g.d / 4;
         for (int ci = tid >> 2; ci < ((n + 63) & ~63); ci += kSelThreads / 4) {
@@ -96,19 +99,27 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
                 const int t = tile_of(ci, f);
                 const int slot = cache_slot(c, g, start, head, f);
                 const float4 *kr = (const float4 *)(c.pooled + (((int64_t)head * g.cap + slot) * g.nb + t) * g.d);
-                for (int e0 = part; e0 < n4; e0 += 4 * 16) {
-                    float4 kk[16];
+                int e = part;
+                auto pieces = [&](auto count) {          // `count` pieces of the lane's quarter, loads first
+                    constexpr int N = decltype(count)::value;
+                    for (; e + 4 * (N - 1) < n4; e += 4 * N) {
+                        float4 kk[N];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) kk[u] = e0 + 4 * u < n4 ? kr[e0 + 4 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+                        for (int u = 0; u < N; ++u) kk[u] = kr[e + 4 * u];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        const int e = (e0 + 4 * u < n4 ? e0 + 4 * u : 0) * 4;
-                        s = fmaf(qs[e], kk[u].x, s);
-                        s = fmaf(qs[e + 1], kk[u].y, s);
-                        s = fmaf(qs[e + 2], kk[u].z, s);
-                        s = fmaf(qs[e + 3], kk[u].w, s);
+                        for (int u = 0; u < N; ++u) {
+                            const float4 qv = ((const float4 *)qs)[e + 4 * u];
+                            s = fmaf(qv.x, kk[u].x, s);
+                            s = fmaf(qv.y, kk[u].y, s);
+                            s = fmaf(qv.z, kk[u].z, s);
+                            s = fmaf(qv.w, kk[u].w, s);
+                        }
                     }
-                }
+                };
+                pieces(std::integral_constant<int, 8>{});
+                pieces(std::integral_constant<int, 4>{});
+                pieces(std::integral_constant<int, 2>{});
+                pieces(std::integral_constant<int, 1>{});
             }
             s += __shfl_xor(s, 1);
             s += __shfl_xor(s, 2);
@@ -132,11 +143,11 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
         written = n;
     } else {
         // Keys of the row, PER_LANE in registers of each lane; PER_LANE = 0: read from LDS each time.  The search looks at every
-        // key 32 times, one look waiting for the other: from LDS that is a round trip per 64 keys each time (a layer
+        // key up to 32 times, one look waiting for the other: from LDS that is a round trip per 64 keys each time (a layer
         // call with 504 candidates a row: 329 us, 313 with 8 keys per lane; up to 128 candidates were in registers before).
         // 512 candidates cover, with 6 cached frames of 8 x 16-token tiles, windows of up to 85 tiles (9 x 9: radius 32 by 64);
         // rows beyond that (12 cached frames and a 9 x 5 window: 540) take the LDS loop, as all beyond 128 did.
-        uint32_t T = 0, below = 0;                       // k-th largest key; largest key < T (0 if none; keys of finite floats are > 0)
+        uint32_t T = 0, below = 0, above = ~0u;          // bound of the kept keys; largest key < T (0 if none; keys of finite floats are > 0), least >= T
         int n_ge = 0;
         auto search = [&](auto per_lane) {
             constexpr int PER_LANE = decltype(per_lane)::value;
@@ -153,18 +164,24 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
 #pragma unroll
                 for (int i = 0; i < PER_LANE; ++i) held[i] = i * 64 + lane < n ? keys[i * 64 + lane] : 0u;
             }
-            // the largest value with at least k keys >= it (32-step bitwise search; trial > 0, so the zeros beyond n never count)
+            // A bound with exactly k keys >= it, or, if ties leave none, the k-th largest key: bitwise from the top, trial > 0, so
+            // the zeros beyond n never count.  It ends at the first bound that parts k keys from the rest (after
+            // about 9 + log2(n) bits instead of 32 for keys spread like a normal variable; 4 heads on 48 x 88 with 24 cached frames,
+            // most rows from LDS: 15.9 -> 14.8 us); unrolled, or what each step adds in scalar code costs short rows more than the steps left out give.
+#pragma unroll
             for (int bit = 31; bit >= 0; --bit) {
                 const uint32_t trial = T | (1u << bit);
                 int cnt = 0;
                 each([&](int, uint32_t key) { cnt += wave_count(key >= trial); });
                 if (cnt >= k) T = trial;
+                if (cnt == k) break;
             }
             int n_gt = 0;
             each([&](int ci, uint32_t key) {
                 n_gt += wave_count(ci < n && key > T);
                 n_ge += wave_count(ci < n && key >= T);
                 if (ci < n && key < T && key > below) below = key;
+                if (ci < n && key >= T && key < above) above = key;
             });
             const int need = k - n_gt;                   // how many of the blocks tied at T are kept (>= 1)
             int eq_seen = 0;
@@ -183,13 +200,15 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
         else if (n <= 512) search(std::integral_constant<int, 8>{});
         else search(std::integral_constant<int, 0>{});
         if (gap) {
-            if (n_ge > k) row_gap = 0.f;
+            if (n_ge > k) row_gap = 0.f;                 // the search went to the last bit: T is a key, and tied
             else {
                 for (int off = 32; off > 0; off >>= 1) {
                     const uint32_t o = __shfl_xor(below, off);
                     below = o > below ? o : below;
+                    const uint32_t a = __shfl_xor(above, off);
+                    above = a < above ? a : above;
                 }
-                row_gap = key_to_float(T) - key_to_float(below);
+                row_gap = key_to_float(above) - key_to_float(below);
             }
         }
     }

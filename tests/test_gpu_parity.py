@@ -825,3 +825,25 @@ def test_selection_at_the_numbers_of_candidates_where_its_search_changes(rows, c
     assert (sel_cnt == 7).all()
     assert torch.equal(sel_idx.cpu().long(), order.indices[..., :7].sort(dim=-1).values)
     assert torch.equal(gap.cpu(), order.values[..., 6] - order.values[..., 7])
+
+
+@pytest.mark.parametrize("d", [4, 12, 20, 36, 60, 128, 156, 252])
+@pytest.mark.parametrize("topk", [1, 13, 191])
+def test_selection_reads_every_channel_once_and_stops_where_k_blocks_part(d, topk):
+    """Head sizes on either side of what a lane loads at a time (8, 4, 2 and 1 pieces of 16 channels), and rows whose k-th
+    score differs from the next (the search stops early), is tied with it (it does not), or is less than zero.  192 candidates;
+    whole numbers whose sums are exact in any order: ids and gaps as a stable sort has them."""
+    g = B.Geom(2, d, 24, 32, 4, 4, 2, 4, -1, -1, topk, dtype=B.LCSA_F32)
+    gen = torch.Generator(device="cuda").manual_seed(d * 1000 + topk)
+    cache = B.lcsa_cache_init(g)
+    pk = torch.randint(-30, 31, (4, 6, 8, 2, d), generator=gen, device="cuda").float()
+    k = pk.repeat_interleave(4, 1).repeat_interleave(4, 2).reshape(-1, 2, d).contiguous()
+    B.lcsa_kv_cache_append(cache, k, k, 4)
+    pq = torch.randint(-30, 31, (2, g.n_qb, d), generator=gen, device="cuda").float()
+    pq[1, ::2] = pq[1, ::2].sign()
+    sel_idx, sel_cnt, gap = B.lcsa_select_blocks(g, pq, cache)
+    scores = pq.cpu() @ pk.reshape(-1, 2, d).permute(1, 2, 0).cpu().contiguous()
+    order = torch.sort(scores, dim=-1, descending=True, stable=True)
+    assert (sel_cnt == topk).all()
+    assert torch.equal(sel_idx.cpu().long(), order.indices[..., :topk].sort(dim=-1).values)
+    assert torch.equal(gap.cpu(), order.values[..., topk - 1] - order.values[..., topk])
