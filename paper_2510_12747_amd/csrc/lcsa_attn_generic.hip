@@ -7,10 +7,14 @@
 // split the key groups instead: each wavefront keeps a softmax of its own over every (4 / ways)-th stretch of GI groups,
 // and the partial results meet in LDS at the end.  No LDS and no barrier otherwise.
 //
-// What bounds it: at 8 heads, d = 64, bf16, 32-token blocks, k = 16 on a 24 x 44 grid 34 us, of which the float P V products
-// are 9 us of matrix time and the rest is load latency (two wavefronts per SIMD).  A wavefront per query token with
-// lane-per-key dot products in vector FMA took 1429 us there (every query re-read all its keys) and 49 us where this
-// takes 7.5 us on the smallest case (1 head, d = 32, f32, 16-token blocks, k = 4).
+// What bounds it: latency.  A row is a chain of ids -> keys -> scores -> values, and a wavefront of a short row goes through
+// it once or twice, so the kernel spends what it can on having loads in flight: ids are turned into tile addresses 64 at a time,
+// one per lane, before the walk, the keys of the next stretch are requested as soon as the scores of this one are formed, and
+// bf16 weights go through bf16 products (ColGroups), which leaves registers for three wavefronts a SIMD.  8 heads, d = 64, bf16,
+// 32-token blocks, k = 16 on a 24 x 44 grid (576 workgroups): 32.1 -> 17.1 us; of the 15 us saved, 10.5 are the prepared addresses,
+// early keys and bf16 products (21.6 us, 576 workgroups on 512 places), 4.4 the third wavefront (two groups a stretch instead of
+// four).  36 rows of 20 64-token blocks, float, d = 32 49.7 -> 34.8, d = 64 78.4 -> 57.6 us; rows of one stretch are where they were
+// (60 rows of 4 groups, d = 64: 8.6 -> 8.9).
 #include "lcsa_fp32_mma.h"
 #include <type_traits>
 
@@ -21,8 +25,11 @@ using namespace fp32mma;
 
 constexpr int kThreads = 256;
 
+// Wavefronts a SIMD, where the operands of GI groups leave room for more than one.
+template <typename T, int NT, int QS, int GI> constexpr int kWaves = sizeof(T) == 2 ? (NT * QS <= 12 ? 2 : 1) : (NT * QS == 2 ? 4 : NT < 16 && NT * QS * GI <= 16 ? 2 : 1);
+
 template <typename T, int NT, int QS, int GI>
-__global__ __launch_bounds__(kThreads) void attn_generic_kernel(
+__global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generic_kernel(
     KGeom g, KCache c, const T *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     T *__restrict__ o, int64_t o_st, int64_t o_sh, float *__restrict__ lse, float scale_log2, int per_xcd) {
@@ -41,25 +48,70 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
     const int qw = wave / splits, ks = wave - qw * splits;
 
     const int64_t row = (int64_t)head * n_qb + qb;
-    const int cnt = min(max(sel_cnt[row], 0), g.topk);       // a row holds at most topk ids
     const int32_t *sel = sel_idx + row * g.topk;
-    const int start = ring_start(c, g);
+    const int start = ring_start(c, g);                      // requested together with the count and the first ids
+    const int32_t first_id = lane < g.topk ? sel[lane] : 0;
+    const int cnt = min(max(sel_cnt[row], 0), g.topk);       // a row holds at most topk ids
     const int per_block = (g.bt + 15) >> 4, total = cnt * per_block;      // 16-key groups
-    const T *k_head = (const T *)c.k + (int64_t)head * g.cap * g.nb * g.bt * g.d;
-    const T *v_head = (const T *)c.v + (int64_t)head * g.cap * g.nb * g.bt * g.d;
+    // f / per_block: exact while f * per_block < 2^32 (8192 blocks of 64 groups reach 2^25)
+    const uint32_t m_block = per_block == 1 ? 0 : 0xffffffffu / (uint32_t)per_block + 1u;
+    const uint32_t row_bytes = g.d * sizeof(T);
+    const char *k_head = (const char *)c.k + (int64_t)head * g.cap * g.nb * g.bt * row_bytes;
+    const char *v_head = (const char *)c.v + (int64_t)head * g.cap * g.nb * g.bt * row_bytes;
+    const uint32_t k_lane = RowFrag<T, NT>::lane_offset(g4), v_lane = ColGroups<T, NT, GI>::lane_offset(m);
+
+    // Selected blocks of the row, 64 at a time, one per lane: tile index and valid keys.  The divisions take more
+    // instructions than the products of a group.
+    int chunk = 0, chunk_tile = 0, chunk_keys = 0;
+    auto take_chunk = [&](int32_t id) {
+        const int kb = min(max(id, 0), c.valid * g.nb - 1);  // ids outside the cache must not become wild addresses
+        const int grp = kb / g.nb, kt = kb - grp * g.nb, kby = kt / g.tx, kbx = kt - kby * g.tx;
+        chunk_tile = cache_slot(c, g, start, head, grp) * g.nb + kt;
+        chunk_keys = g.tt * min(g.th, g.H - kby * g.th) * min(g.tw, g.W - kbx * g.tw);
+    };
+    take_chunk(first_id);
+    auto block_of = [&](int f) { return per_block == 1 ? f : (int)__umulhi((uint32_t)f, m_block); };
 
     // more than one round only where four wavefronts do not cover the block, and then splits == 1
     for (int q0 = qw * 16 * QS; q0 < qt.n_valid || splits > 1; q0 += ways * 16 * QS) {
+        // Groups i0 .. i0 + GI - 1: their values are requested when their keys arrive, the keys of the next ones as soon as
+        // the products with the present ones are issued.
+        RowFrag<T, NT> kf[GI];
+        ColGroups<T, NT, GI> vf;
+        int64_t at[GI];                                      // of the group's first row in the head's tiles
+        int left[GI], present[GI];                           // valid keys of the group, rows of it that the tile has; <= 0: none
+        auto request_keys = [&](int i0) {
+            const int b_last = block_of(min(i0 + GI - 1, total - 1));
+            if (b_last >= chunk + 64) {                      // uniform
+                chunk = block_of(i0);
+                take_chunk(chunk + lane < cnt ? sel[chunk + lane] : 0);
+            }
+#pragma unroll
+            for (int i = 0; i < GI; ++i) {
+                const int f = min(i0 + i, total - 1), b = block_of(f), first = (f - b * per_block) * 16;
+                at[i] = ((int64_t)__builtin_amdgcn_readlane(chunk_tile, b - chunk) * g.bt + first) * row_bytes;
+                left[i] = i0 + i < total ? __builtin_amdgcn_readlane(chunk_keys, b - chunk) - first : 0;
+                present[i] = i0 + i < total ? g.bt - first : 0;
+                // rows beyond the block's bt (bt not a multiple of 16) repeat its last key, which is masked
+                kf[i].load_at(k_head + at[i], min(m * row_bytes, (g.bt - 1 - first) * row_bytes) + k_lane);
+            }
+        };
+        if (chunk != 0) { chunk = 0; take_chunk(sel[min(lane, g.topk - 1)]); }      // left by a round before this one
+        int i0 = ks * GI;
+        // four groups of float keys at d <= 32 and one set of queries: without the second set of operands four wavefronts fit a SIMD
+        constexpr bool AHEAD = !(sizeof(T) == 4 && GI == 4 && NT == 2 && QS == 1);
+        if (AHEAD && i0 < total) request_keys(i0);
+
         RowFrag<T, NT> qf[QS];
-        int64_t token[QS];
-        bool q_valid[QS];
+        int token[QS];                                       // ~: a padding row's
 #pragma unroll
         for (int s = 0; s < QS; ++s) {
             int ft, r, cc;
-            q_valid[s] = qt.at(q0 + 16 * s + m, ft, r, cc);
-            if (!q_valid[s]) ft = r = cc = 0;                // padding rows compute on the block's first token and store nothing
-            token[s] = raster_token(g, fq, ft, by * g.th + r, bx * g.tw + cc);
-            qf[s].load(q + token[s] * q_st + (int64_t)head * q_sh, g.d, g4);
+            const bool there = qt.at(q0 + 16 * s + m, ft, r, cc);
+            if (!there) ft = r = cc = 0;                     // padding rows compute on the block's first token and store nothing
+            const int64_t t = raster_token(g, fq, ft, by * g.th + r, bx * g.tw + cc);
+            token[s] = there ? (int)t : ~(int)t;
+            qf[s].load(q + t * q_st + (int64_t)head * q_sh, g.d, g4);
         }
         f32x4 oacc[QS][NT];
         float mx[QS], l[QS];
@@ -70,56 +122,57 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
 #pragma unroll
             for (int t = 0; t < NT; ++t) oacc[s][t] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        for (int i0 = ks * GI; i0 < total; i0 += splits * GI) {
-            RowFrag<T, NT> kf[GI];
-            ColFrag<T, NT> vf[GI];
-            int left[GI];                                    // valid keys of the group, <= 0: none
+        for (; i0 < total; i0 += splits * GI) {
+            if (!AHEAD) request_keys(i0);
+            f32x4 sc[QS][GI];
+            int rows[GI];
 #pragma unroll
             for (int i = 0; i < GI; ++i) {
-                const int f = min(i0 + i, total - 1), b = f / per_block, first = (f - b * per_block) * 16;
-                const int kb = min(max(sel[b], 0), c.valid * g.nb - 1);   // ids outside the cache must not become wild addresses
-                const int grp = kb / g.nb, kt = kb - grp * g.nb, kby = kt / g.tx, kbx = kt - kby * g.tx;
-                const int n = g.tt * min(g.th, g.H - kby * g.th) * min(g.tw, g.W - kbx * g.tw);
-                left[i] = i0 + i < total ? n - first : 0;
-                const int64_t base = ((int64_t)cache_slot(c, g, start, head, grp) * g.nb + kt) * g.bt;
-                // rows beyond the block's bt (bt not a multiple of 16) repeat its last key, which is masked, and have no value
-                kf[i].load(k_head + (base + min(first + m, g.bt - 1)) * g.d, g.d, g4);
+                rows[i] = present[i];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = first + 4 * g4 + r;
-                    vf[i].load(r, j < g.bt && i0 + i < total ? v_head + (base + j) * g.d : (const T *)zero_row, g.d, m);
+                for (int r = 0; r < 4; ++r)
+                    vf.load_at(i, r, v_head + at[i], min((4 * g4 + r) * row_bytes, max(present[i] - 1, 0) * row_bytes) + v_lane);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < GI; ++i) {
+                kf[i].clear_beyond(g.d, g4);
+#pragma unroll
+                for (int s = 0; s < QS; ++s) {
+                    sc[s][i] = RowFrag<T, NT>::mma(kf[i], qf[s], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sc[s][i][r] = 4 * g4 + r < left[i] ? sc[s][i][r] * scale_log2 : -__builtin_inff();
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
+            if (AHEAD && i0 + splits * GI < total) request_keys(i0 + splits * GI);
 #pragma unroll
             for (int s = 0; s < QS; ++s) {
-                f32x4 sc[GI];
                 float mnew = mx[s];
 #pragma unroll
-                for (int i = 0; i < GI; ++i) {
-                    sc[i] = RowFrag<T, NT>::mma(kf[i], qf[s], f32x4{0.f, 0.f, 0.f, 0.f});
+                for (int i = 0; i < GI; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        sc[i][r] = 4 * g4 + r < left[i] ? sc[i][r] * scale_log2 : -__builtin_inff();
-                        mnew = fmaxf(mnew, sc[i][r]);
-                    }
-                }
+                    for (int r = 0; r < 4; ++r) mnew = fmaxf(mnew, sc[s][i][r]);
                 mnew = column_max(mnew);
                 const float ref = mnew == -__builtin_inff() ? 0.f : mnew;     // nothing but padding so far
-                const float alpha = __builtin_amdgcn_exp2f(mx[s] - ref);
-                mx[s] = mnew;
-                l[s] *= alpha;
+                if (__ballot(mnew != mx[s])) {
+                    const float alpha = __builtin_amdgcn_exp2f(mx[s] - ref);
+                    l[s] *= alpha;
 #pragma unroll
-                for (int t = 0; t < NT; ++t) oacc[s][t] *= alpha;
+                    for (int t = 0; t < NT; ++t) oacc[s][t] *= alpha;
+                    mx[s] = mnew;
+                }
 #pragma unroll
-                for (int i = 0; i < GI; ++i) {
+                for (int i = 0; i < GI; ++i)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        sc[i][r] = __builtin_amdgcn_exp2f(sc[i][r] - ref);
-                        l[s] += sc[i][r];
+                        sc[s][i][r] = __builtin_amdgcn_exp2f(sc[s][i][r] - ref);
+                        l[s] += sc[s][i][r];
                     }
-                    ColFrag<T, NT>::mma(vf[i], sc[i], oacc[s]);
-                }
             }
+#pragma unroll
+            for (int i = 0; i < GI; ++i) vf.keep(i, rows[i], g4);
+            vf.mma(sc, oacc);
         }
 #pragma unroll
         for (int s = 0; s < QS; ++s) l[s] = column_sum(l[s]);
@@ -153,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
         }
 #pragma unroll
         for (int s = 0; s < QS; ++s) {
-            if (!q_valid[s]) continue;
+            if (token[s] < 0) continue;
             const float inv = l[s] > 0.f ? 1.f / l[s] : 0.f;
 #pragma unroll
             for (int p = 0; p < NT / 2; ++p) {
@@ -161,30 +214,31 @@ __global__ __launch_bounds__(kThreads) void attn_generic_kernel(
                 channels_of(oacc[s], p, x);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[i] *= inv;
-                store8(o + token[s] * o_st + (int64_t)head * o_sh, 32 * p + 8 * g4, g.d, x);
+                store8(o + (int64_t)token[s] * o_st + (int64_t)head * o_sh, 32 * p + 8 * g4, g.d, x);
             }
-            if (lse && g4 == 0) lse[token[s] * g.heads + head] = l[s] > 0.f ? (mx[s] + __builtin_amdgcn_logf(l[s])) * kLn2 : -__builtin_inff();
+            if (lse && g4 == 0) lse[(int64_t)token[s] * g.heads + head] = l[s] > 0.f ? (mx[s] + __builtin_amdgcn_logf(l[s])) * kLn2 : -__builtin_inff();
         }
         if (splits > 1) return;
     }
 }
 
-// Whether float rows are walked two groups at a time instead of four.  Four have their loads in flight together, which two make
-// up for where there are more workgroups than fit at four groups' registers (`resident` a unit: 1344 rows of 20 16-token blocks at
-// d = 64 50.7 us with four, 40.2 with two; 384 rows of 20 64-token blocks 157 / 131), or where the last stretch of four would be
-// half empty (5 groups a wavefront, 200 rows, 20.6 / 17.4; one group, 8 rows, 7.1 / 5.6; 10 groups 18.5 / 17.3).  Elsewhere two are
-// slower (28 groups 18.5 / 19.3, 40 groups 78.6 / 83.0).  bf16 rows take half the registers: 33.1 us with four, 35.0 with two.
+// Whether float rows are walked two groups at a time instead of four.  Four pay where few, long rows at d <= 32 leave a wavefront alone
+// with its loads (two / four, 36 rows of 64-token blocks, 7 to 40 groups a wavefront: 11.2 / 11.0 to 37.8 / 34.8 us; 110 rows of 16-token
+// blocks, 7 groups: 8.37 / 8.16).  Not where there are more workgroups than fit at four groups' registers (`resident` a unit: 1344 rows
+// of 7 groups, d = 64, 42.3 / 46.3; 384 rows of 64-token blocks, 40 groups, 100.6 / 135.3), not where the last stretch of four would be half
+// empty (10 groups 9.43 / 10.4), and not for the four groups of a short row, where it is the second request ahead of the first products
+// that helps (264 rows of 4: 7.72 / 8.41).  Between them, at d = 64 (7 groups, 60 rows), four cost up to a tenth: 17.3 / 19.3.
 bool two_groups(const KGeom &g, const KCache &c, int rows_per_wave, int resident) {
     const int admissible = max_candidates(g, c.valid), k = g.topk < admissible ? g.topk : admissible;
     const int per_wave = (k * ((g.bt + 15) >> 4) + 4 / row_ways(g.bt, rows_per_wave) - 1) / (4 / row_ways(g.bt, rows_per_wave));
-    return g.q_groups * g.nb * g.heads > resident * compute_units() || (per_wave - 1) % 4 < 2;
+    return per_wave <= 4 || g.q_groups * g.nb * g.heads > resident * compute_units() || (per_wave - 1) % 4 < 2;
 }
 
 template <typename T, int NT, int QS>
 void launch(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_t q_sh, const int32_t *sel_idx, const int32_t *sel_cnt,
             void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
     const int per_xcd = (g.q_groups * g.nb * g.heads + 7) / 8;
-    constexpr int GI = NT <= 4 ? 4 : NT <= 8 ? 2 : 1;        // groups whose operands are loaded together
+    constexpr int GI = sizeof(T) == 2 ? 2 : NT <= 4 ? 4 : NT <= 8 ? 2 : 1;        // groups whose operands are loaded together
     auto call = [&](auto gi) {
         attn_generic_kernel<T, NT, QS, gi><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(
             g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);

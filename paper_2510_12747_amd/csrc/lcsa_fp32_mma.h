@@ -41,6 +41,19 @@ template <int NT> struct RowFrag<float, NT> {
             v[j] = c < d ? *(const f32x4 *)(row + c) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
+    // a row of a tile image: `at` uniform, offset = this lane's byte offset from it, lane_offset(g) included
+    __device__ static uint32_t lane_offset(int g) { return 16 * g; }
+    __device__ void load_at(const char *at, uint32_t offset) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) v[j] = *(const f32x4 *)(at + offset + 64 * j);
+    }
+    // channels from d on: what followed the row's d
+    __device__ void clear_beyond(int d, int g) {
+        if (d == 16 * NT) return;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            if (16 * j + 4 * g >= d) v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     __device__ static f32x4 mma(const RowFrag &a, const RowFrag &b, f32x4 acc) {
 #pragma unroll
         for (int j = 0; j < NT; ++j)
@@ -58,6 +71,17 @@ template <int NT> struct RowFrag<__bf16, NT> {
             const uint4 u = c < d ? *(const uint4 *)(row + c) : make_uint4(0, 0, 0, 0);
             v[j] = __builtin_bit_cast(bf16x8, u);
         }
+    }
+    __device__ static uint32_t lane_offset(int g) { return 16 * g; }
+    __device__ void load_at(const char *at, uint32_t offset) {
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j) v[j] = __builtin_bit_cast(bf16x8, *(const uint4 *)(at + offset + 64 * j));
+    }
+    __device__ void clear_beyond(int d, int g) {
+        if (d == 16 * NT) return;
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j)
+            if (32 * j + 8 * g >= d) v[j] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
     }
     __device__ static f32x4 mma(const RowFrag &a, const RowFrag &b, f32x4 acc) {
 #pragma unroll
@@ -86,6 +110,132 @@ template <typename T, int NT> struct ColFrag {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)x.v[r][t >> 1][t & 1], w[r], acc[t], 0, 0, 0);
+    }
+};
+
+// Second-level products of GI 16-row groups with QS sets of columns: acc[s] += X^T w[s], X being the rows of the groups.
+//   load_at   row 4 g + r of group i, `at` uniform, offset = this lane's byte offset from it, lane_offset(m) included (channels
+//             from d on are what follows the row: they only reach channels of the result that are not stored)
+//   keep      only the first n rows of group i have a weight; the others become zeros, whatever was read
+template <typename T, int NT, int GI> struct ColGroups;
+template <int NT, int GI> struct ColGroups<float, NT, GI> {
+    f32x2 v[GI][4][NT / 2];                                  // [group][row 4 g + r][p]: channels 32 p + 2 m, + 1
+    __device__ static uint32_t lane_offset(int m) { return 8 * m; }
+    __device__ void load_at(int i, int r, const char *at, uint32_t offset) {
+#pragma unroll
+        for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const f32x2 *)(at + offset + 128 * p);
+    }
+    __device__ void keep(int i, int n, int g) {
+        if (n >= 16) return;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int p = 0; p < NT / 2; ++p)
+                if (4 * g + r >= n) v[i][r][p] = f32x2{0.f, 0.f};
+    }
+    template <int QS> __device__ void mma(const f32x4 (&w)[QS][GI], f32x4 (&acc)[QS][NT]) const {
+#pragma unroll
+        for (int i = 0; i < GI; ++i)
+#pragma unroll
+            for (int s = 0; s < QS; ++s)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i][r][t >> 1][t & 1], w[s][i][r], acc[s][t], 0, 0, 0);
+    }
+};
+// bf16 rows: a float weight is the sum of three bf16 values (8 bits of its 24 each, every remainder exact), and the products
+// of bf16 values are exact in v_mfma_f32_16x16x32_bf16, which takes two groups at a time: three instructions of 16 cycles in
+// place of eight of 32, and fewer roundings of the accumulator.  Zero and negative pieces of a weight must not meet an infinity:
+// infinities and NaN go through the float products by themselves, which leaves the bits of all other channels alone.
+template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
+    static_assert(GI % 2 == 0, "groups go in pairs");
+    uint32_t v[GI][4][NT / 2];
+    __device__ static uint32_t lane_offset(int m) { return 4 * m; }
+    __device__ void load_at(int i, int r, const char *at, uint32_t offset) {
+#pragma unroll
+        for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const uint32_t *)(at + offset + 64 * p);
+    }
+    __device__ void keep(int i, int n, int g) {
+        if (n >= 16) return;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int p = 0; p < NT / 2; ++p)
+                if (4 * g + r >= n) v[i][r][p] = 0;
+    }
+    __device__ bool finite() const {                         // wavefront-uniform
+        typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
+        u16x2 most = {0, 0};
+#pragma unroll
+        for (int i = 0; i < GI; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int p = 0; p < NT / 2; ++p)
+                    most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, v[i][r][p] & 0x7fff7fffu));
+        return __ballot(most[0] >= 0x7f80 || most[1] >= 0x7f80) == 0;
+    }
+    // the two weights of a word as bf16, and what they leave
+    __device__ static uint32_t piece(float &a, float &b) {
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+        const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+        a -= __uint_as_float(w << 16);
+        b -= __uint_as_float(w & 0xffff0000u);
+        return w;
+    }
+    template <int QS> __device__ void mma(const f32x4 (&w)[QS][GI], f32x4 (&acc)[QS][NT]) {
+        if (!finite())                                       // these by themselves, and zeros in their place below
+#pragma unroll
+            for (int i = 0; i < GI; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        uint32_t &u = v[i][r][t >> 1];
+                        const uint32_t half = t & 1 ? u & 0xffff0000u : u << 16;
+                        const bool odd = (half & 0x7f800000u) == 0x7f800000u;
+                        if (odd) u &= t & 1 ? 0xffffu : 0xffff0000u;
+#pragma unroll
+                        for (int s = 0; s < QS; ++s)
+                            acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? __uint_as_float(half) : 0.f, w[s][i][r], acc[s][t], 0, 0, 0);
+                    }
+#pragma unroll
+        for (int i = 0; i < GI; i += 2) {
+            bf16x8 pieces[QS][3];                            // largest first
+#pragma unroll
+            for (int s = 0; s < QS; ++s) {
+                uint32_t x[3][4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float a = w[s][i + (j >> 1)][2 * (j & 1)], b = w[s][i + (j >> 1)][2 * (j & 1) + 1];
+#pragma unroll
+                    for (int n = 0; n < 3; ++n) x[n][j] = piece(a, b);
+                }
+#pragma unroll
+                for (int n = 0; n < 3; ++n) pieces[s][n] = __builtin_bit_cast(bf16x8, make_uint4(x[n][0], x[n][1], x[n][2], x[n][3]));
+            }
+#pragma unroll
+            for (int p = 0; p < NT / 2; ++p) {
+                bf16x8 rows[2];                              // element j: row 4 g + (j & 3) of group i + (j >> 2), of channels 32 p + 2 m, + 1
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    uint32_t x[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        x[j] = __builtin_amdgcn_perm(v[i + (j >> 1)][2 * (j & 1) + 1][p], v[i + (j >> 1)][2 * (j & 1)][p], e ? 0x07060302u : 0x05040100u);
+                    rows[e] = __builtin_bit_cast(bf16x8, make_uint4(x[0], x[1], x[2], x[3]));
+                }
+#pragma unroll
+                for (int n = 2; n >= 0; --n)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int s = 0; s < QS; ++s)
+                            acc[s][2 * p + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows[e], pieces[s][n], acc[s][2 * p + e], 0, 0, 0);
+            }
+        }
     }
 };
 
