@@ -45,13 +45,13 @@ __device__ inline TileRef tile_ref(const KGeom &g, int block) {
 // Sum over the row-groups held in LDS and write the mean of the block.
 template <int VEC>
 __device__ inline void finish_pool(float *red, const float *acc, int rg, int j, int lpr, int rows_par,
-                                   bool active, int d, int count, float *out) {
+                                   bool active, int d, int count, float *out, int tid = threadIdx.x) {
     if (active) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) red[rg * d + j * VEC + e] = acc[e];
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < d; c += kThreads) {
+    for (int c = tid; c < d; c += kThreads) {
         float s = 0.f;
         for (int r = 0; r < rows_par; ++r) s += red[r * d + c];
         out[c] = s / (float)count;

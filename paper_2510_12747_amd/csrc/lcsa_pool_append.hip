@@ -7,6 +7,7 @@
 // pages they open busy.
 #include "lcsa_kernels.h"
 #include "lcsa_pool.h"
+#include <type_traits>
 
 namespace lcsa {
 namespace {
@@ -21,6 +22,14 @@ using namespace pooling;
 // A launch into an empty cache (fresh) reads nothing: it starts at slot 0 and initialises both words.
 struct RingPos { int head_slot, ticket; };
 
+// A return value is waited for where it is used only if the address may differ between lanes: adds to an address that the compiler
+// knows to be one and the same are gathered over the wavefront first, and what comes back is waited for and spread at once, before
+// the first load of the tile (2 heads of 14 x 30 tokens in 16-token blocks, float, d = 96: 4.47 -> 3.91 us without that).
+__device__ inline int draw_ticket(const KCache &c) {
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    return atomicAdd(&c.ring[1] + zero, 1);
+}
 // Called by every thread (holds a workgroup barrier unless the ring is not in use); word = one int of LDS.
 __device__ inline RingPos ring_enter(const KCache &c, bool fresh, int *word) {
     RingPos p = {0, -1};
@@ -28,7 +37,7 @@ __device__ inline RingPos ring_enter(const KCache &c, bool fresh, int *word) {
     if (threadIdx.x == 0) *word = c.ring[0];
     __syncthreads();
     p.head_slot = *word;
-    if (threadIdx.x == 0) p.ticket = atomicAdd(&c.ring[1], 1);
+    if (threadIdx.x == 0) p.ticket = draw_ticket(c);
     return p;
 }
 __device__ inline void ring_leave(const KCache &c, const KGeom &g, const RingPos &p, int n_groups, bool fresh) {
@@ -180,13 +189,18 @@ __global__ __launch_bounds__(kThreads) void rope_pool_kernel(KGeom g, const char
 
 // ---------------------------------------------------------------------------------------------
 // Cache append, generic tile image: K and V tiles row-major [bt][d], padded tokens zero;
-// pooled K written beside them.                                      grid n_groups*nb*heads
-template <int VEC>
-__global__ __launch_bounds__(kThreads) void append_generic_kernel(KGeom g, KCache c, const char *k, const char *v,
-                                                                  int64_t st, int64_t sh, int first, int n_groups, bool fresh) {
-    __shared__ float red[kThreads * VEC];
+// pooled K written beside them.                                      grid n_groups*nb*heads / SUB, rounded up
+// SUB parts of 256 threads, one (tile, head) each: what they share is the ticket.  Tickets are drawn one after the other, 10 ns each,
+// which is what bounds many small tiles; few are a chain of ring word -> rows -> means.
+template <int VEC, int SUB>
+__global__ __launch_bounds__(kThreads * SUB) void append_generic_kernel(KGeom g, KCache c, const char *k, const char *v,
+                                                                        int64_t st, int64_t sh, int first, int n_groups, bool fresh) {
+    __shared__ float red[SUB][kThreads * VEC];
     __shared__ int ring_word;
-    const int block = blockIdx.x / g.heads, head = blockIdx.x - block * g.heads;
+    const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x - sub * kThreads;
+    const int item = blockIdx.x * SUB + sub;
+    const bool there = SUB == 1 || item < n_groups * g.nb * g.heads;      // else only takes part in the barriers
+    const int block = there ? item / g.heads : 0, head = there ? item - block * g.heads : 0;
     const TileRef t = tile_ref(g, block);
     const RingPos ring = ring_enter(c, fresh, &ring_word);
     const int slot = c.order ? c.order[head * g.cap + first + t.group] : (ring.head_slot + t.group) % g.cap;
@@ -196,8 +210,8 @@ __global__ __launch_bounds__(kThreads) void append_generic_kernel(KGeom g, KCach
     char *kt = (char *)c.k + tile_index * g.bt * g.d * ELT;
     char *vt = (char *)c.v + tile_index * g.bt * g.d * ELT;
     const int lpr = g.d / VEC, rows_par = kThreads / lpr;
-    const int rg = threadIdx.x / lpr, j = threadIdx.x - rg * lpr;
-    const bool active = rg < rows_par;
+    const int rg = tid / lpr, j = tid - rg * lpr;
+    const bool active = there && rg < rows_par;
     float acc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
@@ -220,9 +234,8 @@ __global__ __launch_bounds__(kThreads) void append_generic_kernel(KGeom g, KCach
             *(uint4 *)(vt + ((int64_t)tok * g.d + j * VEC) * ELT) = uv;
         }
     }
-    finish_pool<VEC>(red, acc, rg, j, lpr, rows_par, active, g.d, g.tt * t.vh * t.vw,
-                     c.pooled + tile_index * g.d);
-    if (threadIdx.x == 0) c.v_clamped[tile_index] = 0;     // this layout stores V as given
+    finish_pool<VEC>(red[sub], acc, rg, j, lpr, rows_par, active, there ? g.d : 0, g.tt * t.vh * t.vw, c.pooled + tile_index * g.d, tid);
+    if (there && tid == 0) c.v_clamped[tile_index] = 0;     // this layout stores V as given
     ring_leave(c, g, ring, n_groups, fresh);
 }
 
@@ -289,7 +302,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(KGeom g, KCache c
     }
     __syncthreads();                                   // ring_word and n_clamped are set
     RingPos ring = {use_ring ? ring_word : 0, -1};
-    if (use_ring && threadIdx.x == 0) ring.ticket = atomicAdd(&c.ring[1], 1);      // looked at in ring_leave
+    if (use_ring && threadIdx.x == 0) ring.ticket = draw_ticket(c);      // looked at in ring_leave
     const int slot = c.order ? c.order[head * g.cap + first + t.group] : (ring.head_slot + t.group) % g.cap;
     const int tile = block - t.group * g.nb;
     const int64_t tile_index = ((int64_t)head * g.cap + slot) * g.nb + tile;
@@ -387,10 +400,22 @@ hipError_t launch_append(const KGeom &g, const KCache &c, const void *k, const v
     dim3 grid(n_groups * g.nb * g.heads);
     if (c.mfma_layout)
         append_mfma_kernel<<<grid, kThreads, 0, stream>>>(g, c, (const char *)k, (const char *)v, stride_tok, stride_head, first, n_groups, fresh);
-    else if (g.bf16)
-        append_generic_kernel<8><<<grid, kThreads, 0, stream>>>(g, c, (const char *)k, (const char *)v, stride_tok, stride_head, first, n_groups, fresh);
-    else
-        append_generic_kernel<4><<<grid, kThreads, 0, stream>>>(g, c, (const char *)k, (const char *)v, stride_tok, stride_head, first, n_groups, fresh);
+    else {
+        const int items = n_groups * g.nb * g.heads;
+        auto generic = [&](auto vec, auto sub) {
+            append_generic_kernel<vec, sub><<<dim3((items + sub - 1) / sub), kThreads * sub, 0, stream>>>(
+                g, c, (const char *)k, (const char *)v, stride_tok, stride_head, first, n_groups, fresh);
+        };
+        constexpr std::integral_constant<int, 4> four{};
+        constexpr std::integral_constant<int, 1> one{};
+        constexpr std::integral_constant<int, 8> eight{};
+        // One ticket for four tiles where the tickets would take longer than the tiles (one / four a workgroup, us: 576 tiles of 32
+        // tokens, bf16, d = 64, 10.4 / 6.1; 792 of 16 tokens, float, d = 32, 12.4 / 5.9; 256 of 16 tokens, float, d = 96, 6.1 / 4.9;
+        // 192 of 32, bf16, d = 32, 5.6 / 5.0), not where it leaves units idle (144 of 32, float, d = 96, 5.3 / 5.6; 36 of 64, d = 96, 4.2 / 5.2).
+        const bool share = !fresh && !c.order && items > 192;
+        if (g.bf16) share ? generic(eight, four) : generic(eight, one);
+        else share ? generic(four, four) : generic(four, one);
+    }
     return hipGetLastError();
 }
 

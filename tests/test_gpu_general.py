@@ -3,7 +3,7 @@ import pytest
 
 from lcsa_harness import geoms, sample_rows
 from paper_2510_12747_amd import workloads as wl
-from test_gpu_parity import run_primed
+from test_gpu_parity import F32_MAX, F32_MEAN, run_primed
 
 pytestmark = pytest.mark.gpu
 
@@ -22,3 +22,18 @@ def test_rows_of_more_than_64_blocks(dtype, d, grid, tile, topk):
                           tile_h=tile[0], tile_w=tile[1], radius=-1, topk=topk)
     _, og = geoms(w)
     run_primed(w, rows=sample_rows(og, 40), check_lse=True)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("heads,grid", [(3, (32, 32)), (3, (33, 32)), (7, (33, 33))])
+def test_appends_of_192_tiles_and_more(dtype, heads, grid):
+    """192 tiles a launch: a workgroup each; 216 and 1134: four to a workgroup, the last with two.  Three appends
+    fill the cache, a fourth goes round the ring; the step's selection and attention read every tile of it."""
+    w = wl.with_overrides(wl.WORKLOADS["tiny"], name=f"append-{dtype}-{heads}x{grid}", dtype=dtype, heads=heads, head_dim=64, grid_h=grid[0], grid_w=grid[1],
+                          tile_h=4, tile_w=8 if heads == 3 else 4, radius=-1, topk=9)
+    p, r = run_primed(w)
+    for _ in range(3):
+        q, qd = p.feed()
+    p.check_pooled_k()
+    tol = dict(max_abs=F32_MAX, mean_abs=F32_MEAN) if dtype == "fp32" else {}
+    p.step(q, qd, **tol)
