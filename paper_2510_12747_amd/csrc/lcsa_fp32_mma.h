@@ -26,10 +26,6 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// A row of zeros.  A row that is not there enters a second-level product with weight zero; it is loaded from here and not
-// from a neighbour, whose infinities would turn into NaN.
-static __device__ __attribute__((aligned(16))) float zero_row[256];      // not const: a select between two address spaces would load flat
-
 // A row of up to 16 NT channels, spread over the four lanes (m, g = 0..3); channels from d on are zero.
 template <typename T, int NT> struct RowFrag;
 template <int NT> struct RowFrag<float, NT> {
@@ -47,7 +43,16 @@ template <int NT> struct RowFrag<float, NT> {
 #pragma unroll
         for (int j = 0; j < NT; ++j) v[j] = *(const f32x4 *)(at + offset + 64 * j);
     }
-    // channels from d on: what followed the row's d
+    __device__ void clear() {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // a row of d channels anywhere: those from d on repeat others until clear_beyond()
+    __device__ void load_row(const float *row, int d, int g) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) v[j] = *(const f32x4 *)(row + min(16 * j + 4 * g, d - 4));
+    }
+    // channels from d on: zeros instead of what was read
     __device__ void clear_beyond(int d, int g) {
         if (d == 16 * NT) return;
 #pragma unroll
@@ -72,6 +77,14 @@ template <int NT> struct RowFrag<__bf16, NT> {
             v[j] = __builtin_bit_cast(bf16x8, u);
         }
     }
+    __device__ void clear() {
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j) v[j] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+    }
+    __device__ void load_row(const __bf16 *row, int d, int g) {
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j) v[j] = __builtin_bit_cast(bf16x8, *(const uint4 *)(row + min(32 * j + 8 * g, d - 8)));
+    }
     __device__ static uint32_t lane_offset(int g) { return 16 * g; }
     __device__ void load_at(const char *at, uint32_t offset) {
 #pragma unroll
@@ -90,32 +103,10 @@ template <int NT> struct RowFrag<__bf16, NT> {
     }
 };
 
-// Channels of four rows: what a lane feeds the second-level products of one 16-row group.
-template <typename T, int NT> struct ColFrag {
-    T v[4][NT / 2][2];                                       // [row 4 g + r][p]: channels 32 p + 2 m, + 1
-    __device__ void load(int r, const T *row, int d, int m) {
-        typedef __attribute__((ext_vector_type(2))) T T2;
-#pragma unroll
-        for (int p = 0; p < NT / 2; ++p) {
-            const int c = 32 * p + 2 * m;
-            const T2 u = c < d ? *(const T2 *)(row + c) : T2{(T)0.f, (T)0.f};
-            v[r][p][0] = u[0];
-            v[r][p][1] = u[1];
-        }
-    }
-    // acc[t] += X^T w: w = this lane's column of the first-level result
-    __device__ static void mma(const ColFrag &x, const f32x4 &w, f32x4 (&acc)[NT]) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)x.v[r][t >> 1][t & 1], w[r], acc[t], 0, 0, 0);
-    }
-};
-
 // Second-level products of GI 16-row groups with QS sets of columns: acc[s] += X^T w[s], X being the rows of the groups.
 //   load_at   row 4 g + r of group i, `at` uniform, offset = this lane's byte offset from it, lane_offset(m) included (channels
 //             from d on are what follows the row: they only reach channels of the result that are not stored)
+//   load_row  the same from a row of d channels anywhere
 //   keep      only the first n rows of group i have a weight; the others become zeros, whatever was read
 template <typename T, int NT, int GI> struct ColGroups;
 template <int NT, int GI> struct ColGroups<float, NT, GI> {
@@ -124,6 +115,10 @@ template <int NT, int GI> struct ColGroups<float, NT, GI> {
     __device__ void load_at(int i, int r, const char *at, uint32_t offset) {
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const f32x2 *)(at + offset + 128 * p);
+    }
+    __device__ void load_row(int i, int r, const float *row, int d, int m) {
+#pragma unroll
+        for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const f32x2 *)(row + min(32 * p + 2 * m, d - 2));
     }
     __device__ void keep(int i, int n, int g) {
         if (n >= 16) return;
@@ -156,6 +151,10 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
     __device__ void load_at(int i, int r, const char *at, uint32_t offset) {
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const uint32_t *)(at + offset + 64 * p);
+    }
+    __device__ void load_row(int i, int r, const __bf16 *row, int d, int m) {
+#pragma unroll
+        for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const uint32_t *)(row + min(32 * p + 2 * m, d - 2));
     }
     __device__ void keep(int i, int n, int g) {
         if (n >= 16) return;
@@ -236,6 +235,32 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
                             acc[s][2 * p + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows[e], pieces[s][n], acc[s][2 * p + e], 0, 0, 0);
             }
         }
+    }
+};
+
+// One group by itself: half of a bf16 instruction's sum would be empty, and taking weights apart takes as long as the float products.
+template <int NT> struct ColGroups<__bf16, NT, 1> {
+    uint32_t v[4][NT / 2];
+    __device__ void load_row(int, int r, const __bf16 *row, int d, int m) {
+#pragma unroll
+        for (int p = 0; p < NT / 2; ++p) v[r][p] = *(const uint32_t *)(row + min(32 * p + 2 * m, d - 2));
+    }
+    __device__ void keep(int, int n, int g) {
+        if (n >= 16) return;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int p = 0; p < NT / 2; ++p)
+                if (4 * g + r >= n) v[r][p] = 0;
+    }
+    template <int QS> __device__ void mma(const f32x4 (&w)[QS][1], f32x4 (&acc)[QS][NT]) const {
+#pragma unroll
+        for (int s = 0; s < QS; ++s)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(t & 1 ? v[r][t >> 1] & 0xffff0000u : v[r][t >> 1] << 16), w[s][0][r], acc[s][t], 0, 0, 0);
     }
 };
 

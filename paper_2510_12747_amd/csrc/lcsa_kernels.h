@@ -84,6 +84,8 @@ struct BlockTokens {
         m_frame = 0xFFFFFFFFu / (uint32_t)per_frame + 1u;
         m_row = 0xFFFFFFFFu / (uint32_t)vw + 1u;
     }
+    __device__ BlockTokens(int frames, int vh, int vw_, uint32_t m_frame_, uint32_t m_row_)
+        : m_frame(m_frame_), m_row(m_row_), per_frame(vh * vw_), vw(vw_), n_valid(frames * vh * vw_) {}
     __device__ bool at(int i, int &ft, int &r, int &c) const {
         ft = per_frame == 1 ? i : (int)__umulhi((uint32_t)i, m_frame);
         const int rem = i - ft * per_frame;

@@ -1,8 +1,9 @@
-"""General forward: how a row's list of blocks is walked (chunks of 64 ids, stretches of 16-key groups)."""
+"""General kernels: how a row's list of blocks is walked (chunks of 64 ids, stretches of 16-key groups), appends of many tiles."""
 import pytest
 
 from lcsa_harness import geoms, sample_rows
 from paper_2510_12747_amd import workloads as wl
+from test_gpu_backward import run_backward
 from test_gpu_parity import F32_MAX, F32_MEAN, run_primed
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +38,19 @@ def test_appends_of_192_tiles_and_more(dtype, heads, grid):
     p.check_pooled_k()
     tol = dict(max_abs=F32_MAX, mean_abs=F32_MEAN) if dtype == "fp32" else {}
     p.step(q, qd, **tol)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("heads,d,grid,tile,topk", [
+    (1, 32, (10, 14), (4, 4), 8),        # two groups a wavefront: one stretch held
+    (2, 32, (10, 14), (4, 4), 9),        # three, of which the others have two: two stretches
+    (1, 32, (10, 14), (4, 4), 17),       # five: walked twice
+    (5, 24, (37, 61), (4, 4), 16),       # held rows, but 1600 of them: walked twice
+    (1, 64, (16, 24), (2, 8), 80),       # more than 64 ids, pieces that are whole rows of unclipped tiles
+    (2, 64, (17, 23), (5, 7), 11),       # 35 tokens: pieces that are not, every extent
+    (1, 96, (16, 24), (4, 8), 33),       # key side: ids searched, not listed
+])
+def test_backward_rows_and_pieces(dtype, heads, d, grid, tile, topk):
+    w = wl.with_overrides(wl.WORKLOADS["tiny"], name=f"bwd-{dtype}-{d}-{topk}", dtype=dtype, heads=heads, head_dim=d, grid_h=grid[0], grid_w=grid[1],
+                          tile_h=tile[0], tile_w=tile[1], radius=-1, topk=topk)
+    run_backward(w)
