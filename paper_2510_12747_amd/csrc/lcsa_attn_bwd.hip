@@ -37,9 +37,9 @@ constexpr int kListed = 1024;            // query blocks whose kept flags are tu
 struct BlockRef { int group, by, bx, vh, vw, n_valid; };
 __device__ inline BlockRef block_ref(const KGeom &g, int block) {
     BlockRef b;
-    b.group = block / g.nb;
+    b.group = g.by_nb(block);
     const int tile = block - b.group * g.nb;
-    b.by = tile / g.tx;
+    b.by = g.by_tx(tile);
     b.bx = tile - b.by * g.tx;
     b.vh = min(g.th, g.H - b.by * g.th);
     b.vw = min(g.tw, g.W - b.bx * g.tw);
@@ -52,30 +52,9 @@ __device__ inline Located locate(const KGeom &g, int block) {
     const BlockRef b = block_ref(g, block);
     return {(int)raster_token(g, b.group, 0, b.by * g.th, b.bx * g.tw), (b.vh < g.th ? 1 : 0) | (b.vw < g.tw ? 2 : 0)};
 }
-// How tokens lie in blocks of the four extents there are: the divisions of BlockTokens once, instead of once per 16 rows (an
-// eighth of the time on grids with many clipped blocks).
-struct Extents {
-    uint32_t vh[2], vw[2], m_frame[2][2], m_row[2];          // [rows clipped][columns clipped]
-    static __device__ uint32_t reciprocal(uint32_t n) { return __builtin_amdgcn_readfirstlane(0xFFFFFFFFu / n + 1u); }
-    __device__ explicit Extents(const KGeom &g) {
-        vh[0] = g.th; vh[1] = g.H - (g.ty - 1) * g.th;
-        vw[0] = g.tw; vw[1] = g.W - (g.tx - 1) * g.tw;
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            m_row[w] = reciprocal(vw[w]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) m_frame[h][w] = reciprocal(vh[h] * vw[w]);
-        }
-    }
-    // by arithmetic: a choice between members becomes one between their addresses, and the struct goes to memory for it
-    static __device__ uint32_t pick(const uint32_t (&x)[2], uint32_t second) { return x[0] ^ ((x[0] ^ x[1]) & (0u - second)); }
-    // clip is wavefront-uniform
-    __device__ BlockTokens tokens(const KGeom &g, int clip) const {
-        const uint32_t h = clip & 1, w = clip >> 1;
-        const uint32_t m[2] = {pick(m_frame[0], w), pick(m_frame[1], w)};
-        return BlockTokens(g.tt, pick(vh, h), pick(vw, w), pick(m, h), pick(m_row, w));
-    }
-};
+__device__ inline BlockTokens tokens_of(const KGeom &g, int clip) {
+    return BlockTokens(g, clip & 1 ? g.H - (g.ty - 1) * g.th : g.th, clip & 2 ? g.W - (g.tx - 1) * g.tw : g.tw);
+}
 // Raster token of block token i, from the block's first one; rows beyond the valid ones repeat that one (their probability is
 // zero, and what it multiplies is cleared).
 __device__ inline int rel_token(const KGeom &g, const BlockTokens &bt, int i) {
@@ -127,7 +106,7 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
     float *__restrict__ d_q, float *__restrict__ delta, float scale) {
     __shared__ float part_d[4][16];
     __shared__ f32x4 part_q[4][NT][64];
-    const int qb = blockIdx.x / g.heads, head = blockIdx.x - qb * g.heads;
+    const int qb = g.by_heads(blockIdx.x), head = blockIdx.x - qb * g.heads;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g4 = lane >> 4;
     const int n_qb = g.q_groups * g.nb;
@@ -136,8 +115,7 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
     const int32_t first_id = sel[min(lane, g.topk - 1)];     // requested together with the count
     const int cnt = min(max(sel_cnt[row], 0), g.topk);
     const Located own = locate(g, qb);
-    const Extents extents(g);
-    const BlockTokens qt = extents.tokens(g, own.clip);
+    const BlockTokens qt = tokens_of(g, own.clip);
     const int ways = row_ways(qt.n_valid, 16), splits = 4 / ways;
     const int qw = wave / splits, ks = wave - qw * splits;
     const int per_block = (g.bt + 15) >> 4, total = cnt * per_block;      // 16-key groups
@@ -152,8 +130,8 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
     // ids outside the visible blocks must not become wild addresses
     auto take_chunk = [&](int32_t id) { held = locate(g, min(max(id, 0), kv_groups * g.nb - 1)); };
     take_chunk(first_id);
-    const bool simple = whole_rows(g);
-    const PieceRows unclipped(g, extents.tokens(g, 0), 0, m, g4);
+    const bool simple = NT <= 6 && whole_rows(g);            // the offsets stay in registers throughout
+    const PieceRows unclipped(g, tokens_of(g, 0), 0, m, g4);
 
     // more than one round only where four wavefronts do not cover the block, and then splits == 1
     for (int q0 = qw * 16; q0 < qt.n_valid || splits > 1; q0 += ways * 16) {
@@ -191,7 +169,7 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 if (clip == 0 && simple) {                   // uniform
                     with(i, unclipped, (int64_t)(origin + piece_distance(g, first)) * kv_st, there ? g.bt - first : 0);
                 } else {
-                    const BlockTokens kt = extents.tokens(g, clip);
+                    const BlockTokens kt = tokens_of(g, clip);
                     with(i, PieceRows(g, kt, first, m, g4), (int64_t)origin * kv_st, there ? kt.n_valid - first : 0);
                 }
             }
@@ -328,13 +306,12 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
     __shared__ unsigned char kept_by[kListed], list_clip[kListed];
     __shared__ int list_origin[kListed];
     __shared__ int n_listed;
-    const int kb = blockIdx.x / g.heads, head = blockIdx.x - kb * g.heads;
+    const int kb = g.by_heads(blockIdx.x), head = blockIdx.x - kb * g.heads;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g4 = lane >> 4;
     const int n_qb = g.q_groups * g.nb;
     const Located own = locate(g, kb);
-    const Extents extents(g);
-    const BlockTokens kt = extents.tokens(g, own.clip);
+    const BlockTokens kt = tokens_of(g, own.clip);
     const int ways = row_ways(kt.n_valid, 16), splits = 4 / ways;
     const int kw = wave / splits, ks = wave - kw * splits;
     const int per_block = (g.bt + 15) >> 4;
@@ -343,8 +320,8 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
     q += (int64_t)head * q_sh;
     d_o += (int64_t)head * o_sh;
 
-    const bool simple = whole_rows(g);
-    const PieceRows unclipped(g, extents.tokens(g, 0), 0, m, g4);
+    const bool simple = NT <= 6 && whole_rows(g);            // the offsets stay in registers throughout
+    const PieceRows unclipped(g, tokens_of(g, 0), 0, m, g4);
 
     // rounds over the block's key rows: every wavefront takes part in every round (the lists are made together)
     for (int base = 0; base < kt.n_valid; base += ways * 16) {
@@ -365,7 +342,7 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
             const int n_here = min(kListed, n_qb - qb0);
             const int64_t first_row = (int64_t)head * n_qb + qb0;
             __syncthreads();                                 // the previous list is no longer read
-            if (g.topk <= 32) {                              // all ids, eight loads of a thread in flight; longer rows: a search reads less
+            if (NT <= 8 && g.topk <= 32) {                   // all ids, eight loads of a thread in flight; longer rows: a search reads less
                 for (int i = tid; i < n_here; i += kThreads) kept_by[i] = 0;
                 __syncthreads();
                 const int32_t *ids = sel_idx + first_row * g.topk;
@@ -413,7 +390,18 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
                 ColGroups<T, NT, GI> qc, gc;
                 float l2[GI][4], D[GI][4];
                 int valid[GI];
-                int origin[GI], at[GI][4];                   // first token, and rows 4 g4 + r from it
+                int origin[GI], own_at[GI], at[GI][4];       // first token, and rows m and 4 g4 + r from it
+                auto request_stats = [&]() {
+#pragma unroll
+                    for (int i = 0; i < GI; ++i) {
+                        const float *lse_from = lse + (int64_t)origin[i] * g.heads + head, *d_from = delta + (int64_t)origin[i] * g.heads + head;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            l2[i][r] = lse_from[(int64_t)at[i][r] * g.heads] * kLog2e;
+                            D[i][r] = d_from[(int64_t)at[i][r] * g.heads];           // written by bwd_dq_kernel, earlier on the stream
+                        }
+                    }
+                };
                 auto request_columns = [&](ColGroups<T, NT, GI> &cols, const T *x, int64_t st) {
 #pragma unroll
                     for (int i = 0; i < GI; ++i)
@@ -428,34 +416,36 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
                     const bool there = f0 + i * splits < total;
                     auto request_rows = [&](const PieceRows &rows) {
                         qf[i].load_row(q + (int64_t)origin[i] * q_st + rows.own * q_st, g.d, g4);
-                        gf[i].load_row(d_o + (int64_t)origin[i] * o_st + rows.own * o_st, g.d, g4);
-                        const float *lse_from = lse + (int64_t)origin[i] * g.heads + head, *d_from = delta + (int64_t)origin[i] * g.heads + head;
+                        own_at[i] = rows.own;
+                        if (NT <= 8) gf[i].load_row(d_o + (int64_t)origin[i] * o_st + rows.own * o_st, g.d, g4);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            at[i][r] = rows.col[r];
-                            l2[i][r] = lse_from[(int64_t)rows.col[r] * g.heads] * kLog2e;
-                            D[i][r] = d_from[(int64_t)rows.col[r] * g.heads];        // written by bwd_dq_kernel, earlier on the stream
-                        }
+                        for (int r = 0; r < 4; ++r) at[i][r] = rows.col[r];
                     };
                     if (clip == 0 && simple) {               // uniform
                         origin[i] += piece_distance(g, first);
                         valid[i] = there ? g.bt - first : 0;
                         request_rows(unclipped);
                     } else {
-                        const BlockTokens qt = extents.tokens(g, clip);
+                        const BlockTokens qt = tokens_of(g, clip);
                         valid[i] = there ? qt.n_valid - first : 0;
                         request_rows(PieceRows(g, qt, first, m, g4));
                     }
                 }
                 constexpr bool COLUMNS = NT <= 2 || (NT <= 4 && WAVES == 2);         // registers for these beside the rows
+                if (NT <= 8) request_stats();
                 if (COLUMNS) { request_columns(gc, d_o, o_st); request_columns(qc, q, q_st); }
                 f32x4 p[1][GI], u[1][GI];
 #pragma unroll
                 for (int i = 0; i < GI; ++i) {
                     qf[i].clear_beyond(g.d, g4);
-                    gf[i].clear_beyond(g.d, g4);
                     p[0][i] = RowFrag<T, NT>::mma(qf[i], kf, f32x4{0.f, 0.f, 0.f, 0.f});
+                    if (NT > 8) { __builtin_amdgcn_sched_barrier(0); gf[i].load_row(d_o + (int64_t)origin[i] * o_st + own_at[i] * o_st, g.d, g4); }
+                    gf[i].clear_beyond(g.d, g4);
                     u[0][i] = RowFrag<T, NT>::mma(gf[i], vf, f32x4{0.f, 0.f, 0.f, 0.f});
+                }
+                if (NT > 8) { __builtin_amdgcn_sched_barrier(0); request_stats(); }
+#pragma unroll
+                for (int i = 0; i < GI; ++i) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const bool ok = 4 * g4 + r < valid[i];               // padding queries: probability zero
@@ -528,7 +518,7 @@ hipError_t launch(const KGeom &g, int kv_groups, const void *q, int64_t q_st, in
     // bf16 groups in pairs where blocks have pairs of them (8 heads, d = 64, 32-token blocks, k = 14: 60.7 / 40.7 us, of which the bf16
     // products are the larger part); 16-token blocks leave a wavefront one or two groups, and pairs half empty (1 head, d = 64, k = 5,
     // in pairs 18.2 us, 15.5 one by one; 2 heads, k = 9, 25.4 / 22.1).
-    const bool pairs = sizeof(T) == 2 && g.bt > 16;
+    const bool pairs = sizeof(T) == 2 && g.bt > 16 && g.d <= 128;        // beyond that registers spill
     // Rows short enough to be held (d <= 32), where the registers for it leave room for all workgroups, two a unit: 264 rows of 4
     // groups a wavefront 32.9 / 30.2 us; more workgroups than that would take turns.
     const int admissible = max_candidates(g, kv_groups), kept = g.topk < admissible ? g.topk : admissible, splits = 4 / row_ways(g.bt, 16);
@@ -540,13 +530,15 @@ hipError_t launch(const KGeom &g, int kv_groups, const void *q, int64_t q_st, in
             else if (held == 2) query_side(nt, two, two);
         }
         if (nt != 2 || held == 0) {
-            if constexpr (sizeof(T) == 2) { if (pairs) query_side(nt, two, none); }
+            if constexpr (sizeof(T) == 2 && nt <= 8) { if (pairs) query_side(nt, two, none); }
             if (!pairs) query_side(nt, one, none);
         }
         const hipError_t launched = hipGetLastError();
         if (launched != hipSuccess) return launched;
+        // as many wavefronts a SIMD as fit without spilled registers: a spill of half an address to an accumulation register and half
+        // to scratch memory has come back without its first half here, an address beyond all memory (tests look for spills)
         constexpr std::integral_constant<int, nt <= 2 ? 4 : nt <= 4 ? 2 : 1> waves{};
-        if constexpr (sizeof(T) == 2) { if (pairs) key_side(nt, two, waves); }
+        if constexpr (sizeof(T) == 2 && nt <= 8) { if (pairs) key_side(nt, two, std::integral_constant<int, nt <= 2 ? 3 : nt <= 4 ? 2 : 1>{}); }
         // Three workgroups a unit and the column operands requested late, where two a unit with all of them in flight would take turns
         // (1584 key blocks, d = 64, float: 50.8 / 45.7 us; 440 the other way round, 22.1 / 23.4).
         if constexpr (sizeof(T) == 4 && nt == 4) { if ((int)grid_k.x > 2 * compute_units()) { key_side(nt, one, three); return hipGetLastError(); } }

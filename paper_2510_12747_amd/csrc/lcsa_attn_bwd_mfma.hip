@@ -56,9 +56,9 @@ constexpr int kListed = 512;                 // query blocks whose kept flags ar
 struct BlockRef { int group, by, bx, vh, vw, n_valid; };
 __device__ inline BlockRef block_ref(const KGeom &g, int block) {
     BlockRef b;
-    b.group = block / g.nb;
+    b.group = g.by_nb(block);
     const int tile = block - b.group * g.nb;
-    b.by = tile / g.tx;
+    b.by = g.by_tx(tile);
     b.bx = tile - b.by * g.tx;
     b.vh = min(g.th, g.H - b.by * g.th);
     b.vw = min(g.tw, g.W - b.bx * g.tw);
@@ -190,15 +190,19 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // Launch order.  Workgroups are dealt to the 8 XCDs round-robin, each with an L2 of its own; workgroup ids are
 // mapped so that an XCD walks a contiguous run of (head, tile, frame group) items: neighbouring tiles of a head keep
 // (or are kept by) nearly the same blocks, whose tiles are then found in that XCD's L2.
-// `pieces` workgroups to an item follow one another.
-__device__ inline bool work_item(const KGeom &g, int groups, int pieces, int per_xcd, int &head, int &block, int &piece) {
-    int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (item >= g.heads * groups * g.nb * pieces) return false;
-    piece = item % pieces;
-    item /= pieces;
-    head = item / (groups * g.nb);
-    const int rem = item - head * groups * g.nb;
-    const int tile = rem / groups, grp = rem - tile * groups;
+// `pieces` workgroups to an item, one or two, follow one another.
+struct Deal { int groups, per_xcd; Quotient by_blocks, by_groups; };         // blocks = groups*nb
+Deal deal(const KGeom &g, int groups, int pieces) {
+    return {groups, (groups * g.nb * g.heads * pieces + 7) / 8, quotient_by(groups * g.nb), quotient_by(groups)};
+}
+__device__ inline bool work_item(const KGeom &g, const Deal &d, int pieces, int &head, int &block, int &piece) {
+    int item = (blockIdx.x & 7) * d.per_xcd + (blockIdx.x >> 3);
+    if (item >= g.heads * d.groups * g.nb * pieces) return false;
+    piece = item & (pieces - 1);
+    item >>= pieces - 1;
+    head = d.by_blocks(item);
+    const int rem = item - head * d.groups * g.nb;
+    const int tile = d.by_groups(rem), grp = rem - tile * d.groups;
     block = grp * g.nb + tile;
     return true;
 }
@@ -277,12 +281,12 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse,
-    float *__restrict__ d_q, float *__restrict__ delta, float scale, int per_xcd) {
+    float *__restrict__ d_q, float *__restrict__ delta, float scale, Deal items) {
     constexpr int kKeys = 16 * QG * KH, kUnits = kKeys / 32 / KH, kStepBytes = kKeys * 256;
     __shared__ __attribute__((aligned(256))) unsigned char img[2][2][kStepBytes];      // [buffer][K, V]
     __shared__ float part[KH][32 * QG];
     int qb, head, piece;
-    if (!work_item(g, g.q_groups, 4 / QG, per_xcd, head, qb, piece)) return;
+    if (!work_item(g, items, 4 / QG, head, qb, piece)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qg = wave % QG, kh = wave / QG, first_query = 32 * (QG * piece + qg);
     const int ql = lane & 31, half = lane >> 5;
@@ -804,10 +808,10 @@ __global__ __launch_bounds__(512, 2) void bwd_dkv_mfma_kernel(
     const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, int64_t kv_st, int64_t kv_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const __bf16 *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse, const float *__restrict__ delta,
-    float *__restrict__ d_k, float *__restrict__ d_v, float scale, int per_xcd) {
+    float *__restrict__ d_k, float *__restrict__ d_v, float scale, Deal items) {
     __shared__ KeySideLds lds;
     int kb, head, whole;
-    if (!work_item(g, kv_groups, 1, per_xcd, head, kb, whole)) return;
+    if (!work_item(g, items, 1, head, kb, whole)) return;
     if (__builtin_amdgcn_readfirstlane(threadIdx.x) < 256)
         key_side<true>(lds, kb, head, g, q, q_st, q_sh, k, kv_st, kv_sh, sel_idx, sel_cnt, d_o, o_st, o_sh, lse, delta, d_v, scale);
     else
@@ -829,13 +833,13 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
                                 const int32_t *sel_idx, const int32_t *sel_cnt,
                                 const void *d_o, int64_t o_st, int64_t o_sh, const float *lse,
                                 float *d_q, float *d_k, float *d_v, float *delta, float scale, hipStream_t stream) {
-    const int k_per_xcd = (kv_groups * g.nb * g.heads + 7) / 8;
+    const Deal keys = deal(g, kv_groups, 1);
     const int items = g.q_groups * g.nb * g.heads;
     auto query_side = [&](auto QG, auto KH) {
-        const int per_xcd = (items * (4 / QG) + 7) / 8;
-        bwd_dq_mfma_kernel<QG, KH><<<dim3(per_xcd * 8), 64 * QG * KH, 0, stream>>>(
+        const Deal to = deal(g, g.q_groups, 4 / QG);
+        bwd_dq_mfma_kernel<QG, KH><<<dim3(to.per_xcd * 8), 64 * QG * KH, 0, stream>>>(
             g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v, kv_st, kv_sh, sel_idx, sel_cnt,
-            (const __bf16 *)d_o, o_st, o_sh, lse, d_q, delta, scale, per_xcd);
+            (const __bf16 *)d_o, o_st, o_sh, lse, d_q, delta, scale, to);
     };
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
@@ -847,9 +851,9 @@ hipError_t launch_attn_bwd_mfma(const KGeom &g, int kv_groups, const void *q, in
     else query_side(two, four);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    bwd_dkv_mfma_kernel<<<dim3(k_per_xcd * 8), 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
+    bwd_dkv_mfma_kernel<<<dim3(keys.per_xcd * 8), 512, 0, stream>>>(g, kv_groups, (const __bf16 *)q, q_st, q_sh, (const __bf16 *)k, (const __bf16 *)v,
                                                                  kv_st, kv_sh, sel_idx, sel_cnt, (const __bf16 *)d_o, o_st, o_sh, lse, delta,
-                                                                 d_k, d_v, scale, k_per_xcd);
+                                                                 d_k, d_v, scale, keys);
     return hipGetLastError();
 }
 

@@ -39,10 +39,10 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
     const int n_qb = g.q_groups * g.nb;
     const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (item >= n_qb * g.heads) return;
-    const int head = item / n_qb, qb = item - head * n_qb;
+    const int head = g.by_n_qb(item), qb = item - head * n_qb;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g4 = lane >> 4;
-    const int fq = qb / g.nb, tile = qb - fq * g.nb, by = tile / g.tx, bx = tile - by * g.tx;
+    const int fq = g.by_nb(qb), tile = qb - fq * g.nb, by = g.by_tx(tile), bx = tile - by * g.tx;
     const BlockTokens qt(g, min(g.th, g.H - by * g.th), min(g.tw, g.W - bx * g.tw));
     const int ways = row_ways(qt.n_valid, 16 * QS), splits = 4 / ways;
     const int qw = wave / splits, ks = wave - qw * splits;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
     int chunk = 0, chunk_tile = 0, chunk_keys = 0;
     auto take_chunk = [&](int32_t id) {
         const int kb = min(max(id, 0), c.valid * g.nb - 1);  // ids outside the cache must not become wild addresses
-        const int grp = kb / g.nb, kt = kb - grp * g.nb, kby = kt / g.tx, kbx = kt - kby * g.tx;
+        const int grp = g.by_nb(kb), kt = kb - grp * g.nb, kby = g.by_tx(kt), kbx = kt - kby * g.tx;
         chunk_tile = cache_slot(c, g, start, head, grp) * g.nb + kt;
         chunk_keys = g.tt * min(g.th, g.H - kby * g.th) * min(g.tw, g.W - kbx * g.tw);
     };

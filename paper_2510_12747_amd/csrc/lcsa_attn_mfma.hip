@@ -142,8 +142,8 @@ __device__ inline float block_row_max(const f32x16 (&sc)[4], int nf) {
 //   bits 0..23 tile index (slot*nb + tile), bits 24..30 valid keys - 1
 __device__ inline uint32_t pack_block(const KGeom &g, const KCache &c, int start, int head, int kb, int ph, int pw) {
     kb = min(max(kb, 0), c.valid * g.nb - 1);          // ids outside the cache (corrupt input) must not become wild addresses
-    const int f = kb / g.nb, kt = kb - f * g.nb;
-    const int kby = kt / g.tx, kbx = kt - kby * g.tx;
+    const int f = g.by_nb(kb), kt = kb - f * g.nb;
+    const int kby = g.by_tx(kt), kbx = kt - kby * g.tx;
     const int vh = kby == g.ty - 1 ? ph : g.th, vw = kbx == g.tx - 1 ? pw : g.tw;
     return (uint32_t)(cache_slot(c, g, start, head, f) * g.nb + kt) | (uint32_t)(g.tt * vh * vw - 1) << 24;
 }
@@ -180,9 +180,9 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
 
     // this group's item, and how many blocks the other group has (the stage clock is shared)
     auto item_row = [&](int item, int &head, int &qb) {
-        head = item / n_qb;
+        head = g.by_n_qb(item);
         const int rem = item - head * n_qb;
-        const int tile = rem / g.q_groups, fq = rem - tile * g.q_groups;   // items ordered (head, tile, group)
+        const int tile = g.by_q_groups(rem), fq = rem - tile * g.q_groups;   // items ordered (head, tile, group)
         qb = fq * g.nb + tile;
     };
     const int item = SPLIT ? wg : ALONE ? (grp8 == 0 ? wg : total_items) : 2 * wg + grp8;
@@ -199,15 +199,16 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
         if (listed(lane) < g.topk) first_ids = sel_idx[((int64_t)head * n_qb + qb) * g.topk + listed(lane)];
     }
     if (!SPLIT && other < total_items) { int h2, q2; item_row(other, h2, q2); other_cnt = sel_cnt[(int64_t)h2 * n_qb + q2]; }
-    const int fq = qb / g.nb, tile = qb - fq * g.nb;
-    const int by = tile / g.tx, bx = tile - by * g.tx;
+    const int fq = g.by_nb(qb), tile = qb - fq * g.nb;
+    const int by = g.by_tx(tile), bx = tile - by * g.tx;
     const int qvh = min(g.th, g.H - by * g.th), qvw = min(g.tw, g.W - bx * g.tw);
 
     // ---- Q fragments (B operand of S^T = K Q^T), requested before the counts are waited for:
     // lane holds query ql of this wavefront, channels 16s+8*half..+8
     const int tq = wave * 32 + ql;
     int qft, qr, qc;
-    const bool q_valid = block_token(g, tq, qvh, qvw, qft, qr, qc) && active;
+    const BlockTokens q_tokens(g, qvh, qvw);
+    const bool q_valid = q_tokens.at(tq, qft, qr, qc) && active;
     const int64_t token = q_valid ? raster_token(g, fq, qft, by * g.th + qr, bx * g.tw + qc)
                                   : raster_token(g, fq, 0, by * g.th, bx * g.tw);       // clamp padding rows
     // a wavefront whose 32 query rows are all padding only takes part in the copies and barriers
@@ -530,7 +531,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
         for (int itr = 0; itr < 32 / kRows; ++itr) {
             const int t = wave * 32 + rg + kRows * itr;
             int ft, r, cc;
-            if (block_token(g, t, qvh, qvw, ft, r, cc)) {
+            if (q_tokens.at(t, ft, r, cc)) {
                 const int64_t tok = raster_token(g, fq, ft, by * g.th + r, bx * g.tw + cc);
                 const uint4 u = *(const uint4 *)(k_lds + t * 256 + ((j ^ (t & 15)) << 4));
                 *(uint4 *)(o + tok * o_st + (int64_t)head * o_sh + first_dt * 32 + j * 8) = u;
@@ -559,9 +560,9 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_few_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qg = wave >> 2, unit = wave & 3;
     const int ql = lane & 31, half = lane >> 5;
     const int n_qb = g.q_groups * g.nb;
-    const int item = wg >> 1, head = item / n_qb, rem = item - head * n_qb;
-    const int tile = rem / g.q_groups, fq = rem - tile * g.q_groups, qb = fq * g.nb + tile;    // items ordered (head, tile, group)
-    const int by = tile / g.tx, bx = tile - by * g.tx;
+    const int item = wg >> 1, head = g.by_n_qb(item), rem = item - head * n_qb;
+    const int tile = g.by_q_groups(rem), fq = rem - tile * g.q_groups, qb = fq * g.nb + tile;    // items ordered (head, tile, group)
+    const int by = g.by_tx(tile), bx = tile - by * g.tx;
     const int qvh = min(g.th, g.H - by * g.th), qvw = min(g.tw, g.W - bx * g.tw);
     const int first_query = 64 * (wg & 1);
     if (first_query >= g.tt * qvh * qvw) return;             // a clipped block without a second half
@@ -573,7 +574,8 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_few_kernel(
     const int32_t first_ids = lane < g.topk ? sel[lane] : -1;
     const int tq = first_query + 32 * qg + ql;
     int qft, qr, qc;
-    const bool q_valid = block_token(g, tq, qvh, qvw, qft, qr, qc);
+    const BlockTokens q_tokens(g, qvh, qvw);
+    const bool q_valid = q_tokens.at(tq, qft, qr, qc);
     const int64_t token = q_valid ? raster_token(g, fq, qft, by * g.th + qr, bx * g.tw + qc)
                                   : raster_token(g, fq, 0, by * g.th, bx * g.tw);       // padding rows: the block's first token
     bf16x8 bq[8];
@@ -746,7 +748,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_few_kernel(
     for (int i = 0; i < 2; ++i) {
         const int r = (tid >> 4) + 32 * i, j = tid & 15;
         int ft, rr, cc;
-        if (block_token(g, first_query + r, qvh, qvw, ft, rr, cc)) {
+        if (q_tokens.at(first_query + r, ft, rr, cc)) {
             const int64_t tok = raster_token(g, fq, ft, by * g.th + rr, bx * g.tw + cc);
             *(uint4 *)(o + tok * o_st + (int64_t)head * o_sh + j * 8) = *(const uint4 *)(rows + r * 256 + ((j ^ (r & 15)) << 4));
         }

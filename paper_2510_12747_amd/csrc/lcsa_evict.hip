@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kThreads) void importance_rows_kernel(KGeom g, KCac
     float *sc = red + 4;                    // [n] scaled scores, then exponentials
     const int qb = blockIdx.x, head = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_qb = g.q_groups * g.nb;
-    const int tile = qb % g.nb, by = tile / g.tx, bx = tile - by * g.tx;
+    const int tile = qb - g.by_nb(qb) * g.nb, by = g.by_tx(tile), bx = tile - by * g.tx;
     int y0, y1, x0, x1;
     axis_window(by, g.th, g.ty, g.rh, g.wmode, &y0, &y1);
     axis_window(bx, g.tw, g.tx, g.rw, g.wmode, &x0, &x1);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "lcsa_attn_form.h"
+#include "lcsa_quotient.h"
 
 namespace lcsa {
 
@@ -17,6 +18,9 @@ struct KGeom {
     int rh, rw, wmode;
     int topk;
     int bf16;          // element type of Q,K,V,O and cache: 1 = bf16, 0 = f32
+    // what the kernels divide by
+    Quotient by_heads, by_nb, by_tx, by_q_groups, by_n_qb;       // n_qb = q_groups*nb
+    uint32_t m_frame, m_frame_w, m_frame_h, m_frame_hw, m_row, m_row_w;      // BlockTokens; _h, _w: last row, last column of tiles
 };
 
 // Ring cache as the kernels see it.
@@ -74,18 +78,20 @@ __host__ __device__ inline bool block_token(const KGeom &g, int i, int vh, int v
     c = rem - r * vw;
     return i < g.tt * per_frame;
 }
-// block_token for many tokens of one block: the two divisions become multiplications by reciprocals prepared once
-// per block.  q = (i * ceil(2^32 / d)) >> 32 equals i / d for i < 65536 and 2 <= d <= 32768 (a block has at most
+// block_token for the tokens of one block: the two divisions become multiplications by reciprocals, which the host prepares for the
+// four extents that blocks have.  q = (i * ceil(2^32 / d)) >> 32 equals i / d for i < 65536 and 2 <= d <= 32768 (a block has at most
 // 1024 tokens); d = 1 is passed through.
 struct BlockTokens {
     uint32_t m_frame, m_row;
     int per_frame, vw, n_valid;
+    // b, else a; by arithmetic: a choice between members becomes one between their addresses, and the struct goes to memory for it
+    static __device__ uint32_t pick(bool second, uint32_t a, uint32_t b) { return a ^ ((a ^ b) & (0u - (uint32_t)second)); }
+    // vh, vw: the tile's extent, or that of the last row or column of tiles
     __device__ BlockTokens(const KGeom &g, int vh, int vw_) : per_frame(vh * vw_), vw(vw_), n_valid(g.tt * vh * vw_) {
-        m_frame = 0xFFFFFFFFu / (uint32_t)per_frame + 1u;
-        m_row = 0xFFFFFFFFu / (uint32_t)vw + 1u;
+        const bool h = vh != g.th, w = vw_ != g.tw;
+        m_frame = pick(h, pick(w, g.m_frame, g.m_frame_w), pick(w, g.m_frame_h, g.m_frame_hw));
+        m_row = pick(w, g.m_row, g.m_row_w);
     }
-    __device__ BlockTokens(int frames, int vh, int vw_, uint32_t m_frame_, uint32_t m_row_)
-        : m_frame(m_frame_), m_row(m_row_), per_frame(vh * vw_), vw(vw_), n_valid(frames * vh * vw_) {}
     __device__ bool at(int i, int &ft, int &r, int &c) const {
         ft = per_frame == 1 ? i : (int)__umulhi((uint32_t)i, m_frame);
         const int rem = i - ft * per_frame;

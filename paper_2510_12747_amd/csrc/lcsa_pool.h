@@ -33,9 +33,9 @@ struct TileRef {
 
 __device__ inline TileRef tile_ref(const KGeom &g, int block) {
     TileRef t;
-    t.group = block / g.nb;
+    t.group = g.by_nb(block);
     int tile = block - t.group * g.nb;
-    t.by = tile / g.tx;
+    t.by = g.by_tx(tile);
     t.bx = tile - t.by * g.tx;
     t.vh = min(g.th, g.H - t.by * g.th);
     t.vw = min(g.tw, g.W - t.bx * g.tw);

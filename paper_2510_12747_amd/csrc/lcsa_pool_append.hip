@@ -42,7 +42,7 @@ __device__ inline RingPos ring_enter(const KCache &c, bool fresh, int *word) {
 }
 __device__ inline void ring_leave(const KCache &c, const KGeom &g, const RingPos &p, int n_groups, bool fresh) {
     if (c.order || threadIdx.x != 0) return;
-    const int next = (p.head_slot + n_groups) % g.cap;
+    const int next = slot_of_frame(p.head_slot, g.cap, n_groups);      // n_groups <= cap
     if (fresh) {
         if (blockIdx.x == 0) { c.ring[0] = next; c.ring[1] = 0; }
     } else if (p.ticket == (int)gridDim.x - 1) {
@@ -57,7 +57,7 @@ template <int VEC>
 __global__ __launch_bounds__(kThreads) void pool_kernel(KGeom g, const char *x, int64_t st, int64_t sh,
                                                         int n_blocks, float *pooled) {
     __shared__ float red[kThreads * VEC];
-    const int block = blockIdx.x / g.heads, head = blockIdx.x - block * g.heads;
+    const int block = g.by_heads(blockIdx.x), head = blockIdx.x - block * g.heads;
     const TileRef t = tile_ref(g, block);
     const int lpr = g.d / VEC;                 // lanes per token row
     const int rows_par = kThreads / lpr;       // token rows in flight
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreads) void rope_pool_kernel(KGeom g, const char
                                                              RopeParams rp, char *x_rot, int64_t rot_st, int64_t rot_sh, float *pooled) {
     __shared__ float red[kThreads * VEC];
     extern __shared__ float2 rope_table[];
-    const int block = blockIdx.x / g.heads, head = blockIdx.x - block * g.heads;
+    const int block = g.by_heads(blockIdx.x), head = blockIdx.x - block * g.heads;
     const TileRef t = tile_ref(g, block);
     const int lpr = g.d / VEC, rows_par = kThreads / lpr;
     const int rg = threadIdx.x / lpr, j = threadIdx.x - rg * lpr;
@@ -200,10 +200,10 @@ __global__ __launch_bounds__(kThreads * SUB) void append_generic_kernel(KGeom g,
     const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x - sub * kThreads;
     const int item = blockIdx.x * SUB + sub;
     const bool there = SUB == 1 || item < n_groups * g.nb * g.heads;      // else only takes part in the barriers
-    const int block = there ? item / g.heads : 0, head = there ? item - block * g.heads : 0;
+    const int block = there ? g.by_heads(item) : 0, head = there ? item - block * g.heads : 0;
     const TileRef t = tile_ref(g, block);
     const RingPos ring = ring_enter(c, fresh, &ring_word);
-    const int slot = c.order ? c.order[head * g.cap + first + t.group] : (ring.head_slot + t.group) % g.cap;
+    const int slot = c.order ? c.order[head * g.cap + first + t.group] : slot_of_frame(ring.head_slot, g.cap, t.group);
     const int tile = block - t.group * g.nb;
     constexpr int ELT = 16 / VEC;
     const int64_t tile_index = ((int64_t)head * g.cap + slot) * g.nb + tile;
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(KGeom g, KCache c
                                                                int64_t st, int64_t sh, int first, int n_groups, bool fresh) {
     __shared__ float red[16 * 128];
     __shared__ int n_clamped, ring_word;
-    const int block = blockIdx.x / g.heads, head = blockIdx.x - block * g.heads;
+    const int block = g.by_heads(blockIdx.x), head = blockIdx.x - block * g.heads;
     const TileRef t = tile_ref(g, block);
     const int rg = threadIdx.x >> 4, j = threadIdx.x & 15;     // K: 16 token rows in flight, 16 chunks per row
     const int vc = threadIdx.x & 15, vj = threadIdx.x >> 4;    // V: tokens 8vc..8vc+7, channels 8vj..8vj+7
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kThreads) void append_mfma_kernel(KGeom g, KCache c
     __syncthreads();                                   // ring_word and n_clamped are set
     RingPos ring = {use_ring ? ring_word : 0, -1};
     if (use_ring && threadIdx.x == 0) ring.ticket = draw_ticket(c);      // looked at in ring_leave
-    const int slot = c.order ? c.order[head * g.cap + first + t.group] : (ring.head_slot + t.group) % g.cap;
+    const int slot = c.order ? c.order[head * g.cap + first + t.group] : slot_of_frame(ring.head_slot, g.cap, t.group);
     const int tile = block - t.group * g.nb;
     const int64_t tile_index = ((int64_t)head * g.cap + slot) * g.nb + tile;
     char *kt = (char *)c.k + tile_index * (128 * 256);

@@ -38,10 +38,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(KGeom g, KCache c, 
     extern __shared__ __align__(16) float smem[];
     float *qs = smem;                                  // [d] pooled query of this row
     uint32_t *keys = (uint32_t *)(smem + g.d);         // [n] ordered keys of the admissible blocks (after pooling's partial sums)
-    const int qb = blockIdx.x / g.heads, head = blockIdx.x - qb * g.heads;     // head-fastest, like the pooling kernels
+    const int qb = g.by_heads(blockIdx.x), head = blockIdx.x - qb * g.heads;     // head-fastest, like the pooling kernels
     const int tid = threadIdx.x, lane = tid & 63;
     const int n_qb = g.q_groups * g.nb;
-    const int tile = qb % g.nb, by = tile / g.tx, bx = tile - by * g.tx;
+    const int tile = qb - g.by_nb(qb) * g.nb, by = g.by_tx(tile), bx = tile - by * g.tx;
     int y0, y1, x0, x1;
     axis_window(by, g.th, g.ty, g.rh, g.wmode, &y0, &y1);
     axis_window(bx, g.tw, g.tx, g.rw, g.wmode, &x0, &x1);
