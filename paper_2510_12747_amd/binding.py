@@ -1,4 +1,5 @@
-"""ctypes binding of liblcsa.so: argument marshalling only.
+"""ctypes binding of liblcsa.so: argument marshalling only (of a layer's three calls in native code, _marshal.so, where the arguments
+are plain tensors that pass the checks below).
 
 Function names and argument order follow include/lcsa.h.  Tensors are torch CUDA
 (ROCm) tensors used purely as device memory; every step of the path runs in the
@@ -33,7 +34,7 @@ class lcsa_geom(ctypes.Structure):
 
 
 class _Struct:
-    __slots__ = ("_c",)      # beside a dataclass's __dict__: vars(), pickles and copies hold its fields only
+    __slots__ = ("_c", "_n")      # beside a dataclass's __dict__: vars(), pickles and copies hold its fields only
 
 
 @dataclass(frozen=True)
@@ -55,6 +56,15 @@ class Geom(_Struct):
 
     def __post_init__(self):
         object.__setattr__(self, "_c", None)
+        object.__setattr__(self, "_n", None)
+
+    def _plan(self):
+        """What the native marshalling needs of the geometry, made once as the struct is."""
+        if self._n is None:
+            self._ref()
+            object.__setattr__(self, "_n", (ctypes.addressof(self._c), self.heads, self.n_qb, self.head_dim, self.topk, self.tokens_per_frame,
+                                            self.q_frames, 1 if self.dtype == LCSA_BF16 else 0))
+        return self._n
 
     def _ref(self):
         """The geometry as the library's calls take it.  Its fields cannot change, so the struct is made once: building it
@@ -94,6 +104,7 @@ class Geom(_Struct):
 
 
 _lib = None
+_marshal = None
 _vp, _i32, _i64, _f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
 _gp = ctypes.POINTER(lcsa_geom)
 
@@ -141,8 +152,20 @@ def lib():
                   "lcsa_pool_select_blocks", "lcsa_cache_set_eviction", "lcsa_cache_eviction", "lcsa_block_importance", "lcsa_sparse_attn_bwd", "lcsa_rope_pool_blocks",
                   "lcsa_block_importance_static"):
             getattr(L, f).restype = _i32
+        _bind(L)
         _lib = L
     return _lib
+
+
+def _bind(L) -> None:
+    """Hands the entry points of the loaded library to the native marshalling."""
+    global _marshal
+    try:
+        from . import _marshal as native
+    except ImportError as e:
+        raise LcsaError(f"_marshal.so not found or not loadable ({e}): build it with `python -m paper_2510_12747_amd.build`") from e
+    native.bind(*(_vp.from_buffer(f).value for f in (L.lcsa_kv_cache_append, L.lcsa_pool_select_blocks, L.lcsa_sparse_attn_fwd)))
+    _marshal = native
 
 
 def _check(status: int, what: str) -> None:
@@ -284,6 +307,10 @@ def lcsa_cache_v_clamped(cache: Cache) -> torch.Tensor:
 
 
 def lcsa_kv_cache_append(cache: Cache, k: torch.Tensor, v: torch.Tensor, n_frames: int, stream=None) -> None:
+    # the cache was made by the library, so it is loaded
+    status = _marshal.append(cache.geom._plan(), cache.handle.value, k, v, n_frames, _stream(stream))
+    if status is not None:
+        return _check(status, "lcsa_kv_cache_append")
     kp, st, sh = _tok(k)
     vp, vst, vsh = _tok(v)
     if (st, sh) != (vst, vsh) or k.dtype != cache.geom.torch_dtype or v.dtype != k.dtype:
@@ -346,6 +373,10 @@ def lcsa_select_blocks(geom: Geom, pooled_q: torch.Tensor, cache: Cache, sel_idx
 def lcsa_pool_select_blocks(geom: Geom, q: torch.Tensor, cache: Cache, pooled_q=None, sel_idx=None, sel_cnt=None, gap=None,
                             want_gap: bool = True, stream=None):
     """lcsa_pool_blocks + lcsa_select_blocks in one launch; returns (pooled_q, sel_idx, sel_cnt, gap)."""
+    if pooled_q is None and sel_idx is None and sel_cnt is None and gap is None:
+        out = _marshal.pool_select(geom._plan(), q, cache.handle.value, want_gap, _stream(stream))
+        if out is not None:
+            return out if type(out) is tuple else _check(out, "lcsa_pool_select_blocks")
     n_qb = geom.n_qb
     qp, qst, qsh = _tok(q)
     if q.dtype != geom.torch_dtype or q.shape != (geom.q_frames * geom.tokens_per_frame, geom.heads, geom.head_dim):
@@ -371,6 +402,9 @@ def lcsa_pool_select_blocks(geom: Geom, q: torch.Tensor, cache: Cache, pooled_q=
 def lcsa_sparse_attn_fwd(geom: Geom, q: torch.Tensor, cache: Cache, sel_idx: torch.Tensor, sel_cnt: torch.Tensor,
                          o: torch.Tensor | None = None, lse: torch.Tensor | None = None, scale: float = 0.0,
                          stream=None):
+    out = _marshal.forward(geom._plan(), q, cache.handle.value, sel_idx, sel_cnt, o, lse, scale, _stream(stream))
+    if out is not None:
+        return out if type(out) is not int else _check(out, "lcsa_sparse_attn_fwd")
     qp, qst, qsh = _tok(q)
     if q.dtype != geom.torch_dtype or q.shape != (geom.q_frames * geom.tokens_per_frame, geom.heads, geom.head_dim):
         raise LcsaError("lcsa_sparse_attn_fwd: q shape/dtype mismatch")

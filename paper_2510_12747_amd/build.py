@@ -8,6 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblcsa.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["lcsa_host.hip", "lcsa_pool_append.hip", "lcsa_select.hip", "lcsa_attn_generic.hip", "lcsa_attn_mfma.hip",
            "lcsa_evict.hip", "lcsa_attn_bwd.hip", "lcsa_attn_bwd_mfma.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -31,6 +32,23 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_marshal(verbose: bool = False) -> str:
+    """_marshal.so: the binding's native argument marshalling, host code against the installed torch."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-I{os.path.join(root, 'include', *sub)}" for sub in ((), ("torch", "csrc", "api", "include"))],
+           f"-I{sysconfig.get_paths()['include']}", "-o", MARSHAL, os.path.join(CSRC, "lcsa_marshal.cpp"),
+           f"-L{os.path.join(root, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stderr)
+    return MARSHAL
+
+
 def build_bench_aids(verbose: bool = False) -> str:
     """bench.py's measurement aids (matrix-instruction loops, the attention kernel with time stamps), a shared
     object of their own."""
@@ -50,4 +68,5 @@ def build_bench_aids(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_marshal(verbose=True))
     print(build_bench_aids(verbose=True))

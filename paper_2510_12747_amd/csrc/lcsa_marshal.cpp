@@ -1,0 +1,172 @@
+// Argument marshalling of the three calls of a layer in native code: checks, output tensors, pointers and strides, the library call.
+// In Python (binding.py) they cost 9 us a call, more than the kernels of the smallest layer: 26 us for three calls, 14 of them kernels.
+//
+// Nothing is decided here.  Each function takes the ordinary case, plain torch.Tensor arguments that pass every check, and returns
+// None for anything else, and where torch throws: the Python function then goes on as if this module were not there, and raises what
+// it raises.  The library's entry points are handed over as addresses by bind(), from the one copy of the library that binding.py loaded.
+#define PY_SSIZE_T_CLEAN
+#include <ATen/ATen.h>
+#include <Python.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+namespace {
+
+using AppendFn = int32_t (*)(void *, const void *, const void *, int64_t, int64_t, int32_t, void *);
+using PoolSelectFn = int32_t (*)(const void *, const void *, int64_t, int64_t, const void *, float *, int32_t *, int32_t *, float *, void *);
+using ForwardFn = int32_t (*)(const void *, const void *, int64_t, int64_t, const void *, const int32_t *, const int32_t *, void *, int64_t, int64_t,
+                              float *, float, void *);
+AppendFn append_fn = nullptr;
+PoolSelectFn pool_select_fn = nullptr;
+ForwardFn forward_fn = nullptr;
+
+// Geom._plan(): address of its C struct, heads, query blocks, head_dim, topk, tokens a frame, query frames, bf16
+struct Plan {
+    const void *geom;
+    int64_t heads, n_qb, d, topk, frame, q_frames;
+    at::ScalarType type;
+    bool take(PyObject *t) {
+        if (!PyTuple_CheckExact(t) || PyTuple_GET_SIZE(t) != 8) return false;
+        int64_t v[8];
+        for (int i = 0; i < 8; ++i) {
+            v[i] = PyLong_AsLongLong(PyTuple_GET_ITEM(t, i));
+            if (v[i] == -1 && PyErr_Occurred()) { PyErr_Clear(); return false; }
+        }
+        geom = (const void *)v[0];
+        heads = v[1]; n_qb = v[2]; d = v[3]; topk = v[4]; frame = v[5]; q_frames = v[6];
+        type = v[7] ? at::kBFloat16 : at::kFloat;
+        return true;
+    }
+};
+
+bool plain(PyObject *x) { return THPVariable_CheckExact(x); }
+// [frames * frame][heads][d] of the element type on the GPU, d contiguous
+bool tokens(const at::Tensor &x, const Plan &p, int64_t frames) {
+    return x.is_cuda() && x.layout() == at::kStrided && x.dim() == 3 && x.stride(2) == 1 && x.scalar_type() == p.type &&
+           x.size(0) == frames * p.frame && x.size(1) == p.heads && x.size(2) == p.d;
+}
+bool whole(const at::Tensor &x, at::ScalarType type, int64_t numel) {
+    return x.is_cuda() && x.layout() == at::kStrided && x.scalar_type() == type && x.is_contiguous() && x.numel() == numel;
+}
+bool address(PyObject *x, void *&out) {
+    out = PyLong_AsVoidPtr(x);
+    if (!out && PyErr_Occurred()) { PyErr_Clear(); return false; }
+    return true;
+}
+
+// append(plan, cache, k, v, n_frames, stream) -> status
+PyObject *append(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    Plan p;
+    void *cache, *stream;
+    if (n != 6 || !p.take(a[0]) || !address(a[1], cache) || !plain(a[2]) || !plain(a[3]) || !PyLong_CheckExact(a[4]) || !address(a[5], stream)) Py_RETURN_NONE;
+    const int64_t frames = PyLong_AsLongLong(a[4]);
+    if (frames < 1 || frames > (1 << 30)) { PyErr_Clear(); Py_RETURN_NONE; }
+    int32_t status;
+    try {
+        const at::Tensor &k = THPVariable_Unpack(a[2]), &v = THPVariable_Unpack(a[3]);
+        if (!tokens(k, p, frames) || !tokens(v, p, frames) || k.stride(0) != v.stride(0) || k.stride(1) != v.stride(1)) Py_RETURN_NONE;
+        const void *kp = k.data_ptr(), *vp = v.data_ptr();
+        const int64_t st = k.stride(0), sh = k.stride(1);
+        Py_BEGIN_ALLOW_THREADS
+        status = append_fn(cache, kp, vp, st, sh, (int32_t)frames, stream);
+        Py_END_ALLOW_THREADS
+    } catch (...) { Py_RETURN_NONE; }
+    return PyLong_FromLong(status);
+}
+
+// pool_select(plan, q, cache, want_gap, stream) -> (pooled_q, sel_idx, sel_cnt, gap) or status
+PyObject *pool_select(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    Plan p;
+    void *cache, *stream;
+    if (n != 5 || !p.take(a[0]) || !plain(a[1]) || !address(a[2], cache) || !PyBool_Check(a[3]) || !address(a[4], stream)) Py_RETURN_NONE;
+    int32_t status;
+    at::Tensor pooled, idx, cnt, gap;
+    try {
+        const at::Tensor &q = THPVariable_Unpack(a[1]);
+        if (!tokens(q, p, p.q_frames)) Py_RETURN_NONE;
+        const auto on = at::TensorOptions().device(q.device());
+        pooled = at::empty({p.heads, p.n_qb, p.d}, on.dtype(at::kFloat));
+        idx = at::empty({p.heads, p.n_qb, p.topk}, on.dtype(at::kInt));
+        cnt = at::empty({p.heads, p.n_qb}, on.dtype(at::kInt));
+        if (a[3] == Py_True) gap = at::empty({p.heads, p.n_qb}, on.dtype(at::kFloat));
+        const void *qp = q.data_ptr();
+        float *pp = (float *)pooled.data_ptr(), *gp = gap.defined() ? (float *)gap.data_ptr() : nullptr;
+        int32_t *ip = (int32_t *)idx.data_ptr(), *cp = (int32_t *)cnt.data_ptr();
+        const int64_t st = q.stride(0), sh = q.stride(1);
+        Py_BEGIN_ALLOW_THREADS
+        status = pool_select_fn(p.geom, qp, st, sh, cache, pp, ip, cp, gp, stream);
+        Py_END_ALLOW_THREADS
+    } catch (...) { Py_RETURN_NONE; }
+    if (status != 0) return PyLong_FromLong(status);
+    PyObject *out = PyTuple_New(4);
+    if (!out) return nullptr;
+    PyTuple_SET_ITEM(out, 0, THPVariable_Wrap(std::move(pooled)));
+    PyTuple_SET_ITEM(out, 1, THPVariable_Wrap(std::move(idx)));
+    PyTuple_SET_ITEM(out, 2, THPVariable_Wrap(std::move(cnt)));
+    PyObject *last = Py_None;
+    if (gap.defined()) last = THPVariable_Wrap(std::move(gap));
+    else Py_INCREF(Py_None);
+    PyTuple_SET_ITEM(out, 3, last);
+    return out;
+}
+
+// forward(plan, q, cache, sel_idx, sel_cnt, o or None, lse or None, scale, stream) -> o or status
+PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    Plan p;
+    void *cache, *stream;
+    if (n != 9 || !p.take(a[0]) || !plain(a[1]) || !address(a[2], cache) || !plain(a[3]) || !plain(a[4]) || !(a[5] == Py_None || plain(a[5])) ||
+        !(a[6] == Py_None || plain(a[6])) || !PyFloat_CheckExact(a[7]) || !address(a[8], stream))
+        Py_RETURN_NONE;
+    const float scale = (float)PyFloat_AS_DOUBLE(a[7]);
+    int32_t status;
+    at::Tensor o;
+    try {
+        const at::Tensor &q = THPVariable_Unpack(a[1]), &idx = THPVariable_Unpack(a[3]), &cnt = THPVariable_Unpack(a[4]);
+        // sel_cnt's number of values is not checked by the Python function either
+        if (!tokens(q, p, p.q_frames) || !whole(idx, at::kInt, p.heads * p.n_qb * p.topk) || !whole(cnt, at::kInt, cnt.numel())) Py_RETURN_NONE;
+        float *lse = nullptr;
+        if (a[6] != Py_None) {
+            const at::Tensor &l = THPVariable_Unpack(a[6]);
+            if (!whole(l, at::kFloat, q.size(0) * p.heads) || l.dim() != 2 || l.size(0) != q.size(0)) Py_RETURN_NONE;
+            lse = (float *)l.data_ptr();
+        }
+        if (a[5] == Py_None) o = at::empty({q.size(0), q.size(1), q.size(2)}, at::TensorOptions().device(q.device()).dtype(q.scalar_type()));
+        else {
+            o = THPVariable_Unpack(a[5]);
+            if (!tokens(o, p, p.q_frames)) Py_RETURN_NONE;
+        }
+        const void *qp = q.data_ptr();
+        const int32_t *ip = (const int32_t *)idx.data_ptr(), *cp = (const int32_t *)cnt.data_ptr();
+        void *op = o.data_ptr();
+        const int64_t st = q.stride(0), sh = q.stride(1), ost = o.stride(0), osh = o.stride(1);
+        Py_BEGIN_ALLOW_THREADS
+        status = forward_fn(p.geom, qp, st, sh, cache, ip, cp, op, ost, osh, lse, scale, stream);
+        Py_END_ALLOW_THREADS
+    } catch (...) { Py_RETURN_NONE; }
+    if (status != 0) return PyLong_FromLong(status);
+    if (a[5] != Py_None) { Py_INCREF(a[5]); return a[5]; }
+    return THPVariable_Wrap(std::move(o));
+}
+
+// bind(addresses of lcsa_kv_cache_append, lcsa_pool_select_blocks, lcsa_sparse_attn_fwd)
+PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    void *f[3];
+    if (n != 3) { PyErr_SetString(PyExc_TypeError, "bind: three addresses"); return nullptr; }
+    for (int i = 0; i < 3; ++i)
+        if (!address(a[i], f[i]) || !f[i]) { PyErr_SetString(PyExc_TypeError, "bind: three addresses"); return nullptr; }
+    append_fn = (AppendFn)f[0];
+    pool_select_fn = (PoolSelectFn)f[1];
+    forward_fn = (ForwardFn)f[2];
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {
+    {"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr},
+    {"append", (PyCFunction)(void (*)(void))append, METH_FASTCALL, nullptr},
+    {"pool_select", (PyCFunction)(void (*)(void))pool_select, METH_FASTCALL, nullptr},
+    {"forward", (PyCFunction)(void (*)(void))forward, METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+} // namespace
+
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal() { return PyModule_Create(&module); }

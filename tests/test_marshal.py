@@ -1,0 +1,87 @@
+"""The native argument marshalling (csrc/lcsa_marshal.cpp) against the Python functions it stands in for: the same results, and for
+whatever it does not take, the same errors."""
+import types
+
+import pytest
+import torch
+
+from paper_2510_12747_amd import binding as B
+
+NOTHING = types.SimpleNamespace(append=lambda *a: None, pool_select=lambda *a: None, forward=lambda *a: None)
+
+
+def test_it_takes_only_plain_device_tensors():
+    B.lib()
+    g = B.Geom(1, 32, 6, 8, 4, 4, 2, 4, 4, 4, 4, dtype=B.LCSA_F32)
+    x = torch.zeros(96, 1, 32)                               # on the CPU
+    i, n = torch.zeros(1, 8, 4, dtype=torch.int32), torch.zeros(1, 8, dtype=torch.int32)
+    for plan in (g._plan(), g._plan()[:7], list(g._plan()), (1 << 70,) * 8, None):
+        assert B._marshal.append(plan, 0, x, x, 2, 0) is None
+        assert B._marshal.pool_select(plan, x, 0, True, 0) is None
+        assert B._marshal.forward(plan, x, 0, i, n, None, None, 0.0, 0) is None
+    for bad in (None, 3, [x], "x"):
+        assert B._marshal.append(g._plan(), 0, bad, x, 2, 0) is None
+        assert B._marshal.pool_select(g._plan(), bad, 0, True, 0) is None
+        assert B._marshal.forward(g._plan(), x, 0, bad, n, None, None, 0.0, 0) is None
+    assert B._marshal.append(g._plan(), 0, x, x, 1 << 40, 0) is None and B._marshal.append(g._plan()) is None
+    with pytest.raises(TypeError):
+        B._marshal.bind(1, 2)
+    assert B.Geom(**vars(g))._plan()[1:] == g._plan()[1:]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d,tile", [("fp32", 32, (4, 4)), ("bf16", 64, (4, 8)), ("bf16", 128, (8, 16))])
+def test_results_and_errors_are_those_of_the_python_functions(monkeypatch, dtype, d, tile):
+    h, w, heads, dt = 3 * tile[0] - 1, 2 * tile[1] + 3, 3, torch.float32 if dtype == "fp32" else torch.bfloat16
+    g = B.Geom(heads, d, h, w, *tile, 2, 4, 16, 16, 5, dtype=B.LCSA_F32 if dtype == "fp32" else B.LCSA_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(0)
+    make = lambda frames: torch.randn(frames * h * w, heads, d, generator=gen, device="cuda").to(dt)
+    q, k, v = make(2), make(2), make(2)
+    head_major = lambda x: x.transpose(0, 1).contiguous().transpose(0, 1)
+
+    class Sub(torch.Tensor):
+        pass
+
+    def steps(q, k, v, **kw):
+        cache = B.lcsa_cache_init(g)
+        for _ in range(2):
+            B.lcsa_kv_cache_append(cache, k, v, 2)
+        pooled, idx, cnt, gap = B.lcsa_pool_select_blocks(g, q, cache, want_gap=kw.get("want_gap", True))
+        lse = torch.empty(q.shape[0], heads, device="cuda") if kw.get("lse") else None
+        o = torch.empty_like(q) if kw.get("o") else None
+        got = B.lcsa_sparse_attn_fwd(g, q, cache, idx, cnt, o=o, lse=lse, scale=kw.get("scale", 0.0))
+        assert o is None or got is o
+        assert got.is_contiguous() or o is not None
+        return [cache.storage[:0], B.lcsa_cache_pooled_k(cache).clone(), pooled, idx, cnt, gap, lse, got]
+
+    forms = [((q, k, v), {}), ((head_major(q), head_major(k), head_major(v)), dict(lse=True)), ((q, head_major(k), head_major(v)), dict(o=True, want_gap=False)),
+             ((torch.nn.Parameter(q, requires_grad=False), k, v), dict(scale=0.3)), ((q.as_subclass(Sub), k, v), dict(scale=1))]
+    for (a, b, c), kw in forms:
+        native = steps(a, b, c, **kw)
+        with monkeypatch.context() as m:
+            m.setattr(B, "_marshal", NOTHING)
+            python = steps(a, b, c, **kw)
+        for x, y in zip(native, python):
+            assert (x is None) == (y is None)
+            if x is not None:
+                assert x.shape == y.shape and x.dtype == y.dtype and x.stride() == y.stride() and torch.equal(x, y)
+
+    cache = B.lcsa_cache_init(g)
+    B.lcsa_kv_cache_append(cache, k, v, 2)
+    idx, cnt = torch.zeros(heads, g.n_qb, 5, dtype=torch.int32, device="cuda"), torch.zeros(heads, g.n_qb, dtype=torch.int32, device="cuda")
+    other = torch.float32 if dt == torch.bfloat16 else torch.bfloat16
+    wrong = [lambda: B.lcsa_kv_cache_append(cache, k[:-1], v[:-1], 2), lambda: B.lcsa_kv_cache_append(cache, k, head_major(v), 2),
+             lambda: B.lcsa_kv_cache_append(cache, k.to(other), v.to(other), 2), lambda: B.lcsa_kv_cache_append(cache, k.cpu(), v.cpu(), 2),
+             lambda: B.lcsa_pool_select_blocks(g, q[:-1], cache), lambda: B.lcsa_pool_select_blocks(g, q.to(other), cache),
+             lambda: B.lcsa_sparse_attn_fwd(g, q, cache, idx[:, :, :4], cnt), lambda: B.lcsa_sparse_attn_fwd(g, q, cache, idx.long(), cnt),
+             lambda: B.lcsa_sparse_attn_fwd(g, q, cache, idx, cnt, lse=torch.empty(heads, q.shape[0], device="cuda")),
+             lambda: B.lcsa_sparse_attn_fwd(g, q, cache, idx, cnt, o=torch.empty(q.shape[0], heads, d, 2, device="cuda", dtype=dt)[..., 0]),
+             lambda: B.lcsa_pool_select_blocks(B.Geom(**{**vars(g), "q_frames": 4, "cache_frames": 8}), make(4), cache)]      # another geometry: the library refuses
+    for call in wrong:
+        with pytest.raises((B.LcsaError, AssertionError)) as native:
+            call()
+        with monkeypatch.context() as m:
+            m.setattr(B, "_marshal", NOTHING)
+            with pytest.raises((B.LcsaError, AssertionError)) as python:
+                call()
+        assert type(native.value) is type(python.value) and str(native.value) == str(python.value)
