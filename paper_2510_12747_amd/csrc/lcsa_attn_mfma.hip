@@ -182,8 +182,8 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(
     auto item_row = [&](int item, int &head, int &qb) {
         head = g.by_n_qb(item);
         const int rem = item - head * n_qb;
-        const int tile = g.by_q_groups(rem), fq = rem - tile * g.q_groups;   // items ordered (head, tile, group)
-        qb = fq * g.nb + tile;
+        const int t = g.by_q_groups(rem), fq = rem - t * g.q_groups;   // items ordered (head, tile, group)
+        qb = fq * g.nb + dealt_tile(g, t);
     };
     const int item = SPLIT ? wg : ALONE ? (grp8 == 0 ? wg : total_items) : 2 * wg + grp8;
     const int other = SPLIT ? wg : ALONE ? (grp8 == 0 ? total_items : wg) : 2 * wg + (grp8 ^ 1);

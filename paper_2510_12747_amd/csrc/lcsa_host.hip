@@ -61,7 +61,7 @@ KGeom derive(const lcsa_geom &g) {
     k.rh = g.radius_h; k.rw = g.radius_w; k.wmode = g.window_mode;
     k.topk = g.topk;
     k.bf16 = g.dtype == LCSA_BF16;
-    k.by_heads = quotient_by(k.heads); k.by_nb = quotient_by(k.nb); k.by_tx = quotient_by(k.tx);
+    k.by_heads = quotient_by(k.heads); k.by_nb = quotient_by(k.nb); k.by_tx = quotient_by(k.tx); k.by_ty = quotient_by(k.ty);
     k.by_q_groups = quotient_by(k.q_groups); k.by_n_qb = quotient_by(k.q_groups * k.nb);
     const int last_h = k.H - (k.ty - 1) * k.th, last_w = k.W - (k.tx - 1) * k.tw;
     auto reciprocal = [](int n) { return 0xFFFFFFFFu / (uint32_t)n + 1u; };
