@@ -285,7 +285,8 @@ int32_t lcsa_sparse_attn_fwd(const lcsa_geom *geom,
  * LCSA_BWD_FLOAT: float products for every shape (results within 2e-5 of the largest gradient; slower).
  * Either way the summation orders are fixed: the same call gives the same bits every time.  On the matrix cores d_q and delta
  * (and through delta d_k) are sums of one, two or four parts by the number of rows of the call and the device's compute
- * units: the same row in a call of another size, or on another device, may differ in their rounding.
+ * units: the same row in a call of another size, or on another device, may differ in their rounding.  So may d_q in float
+ * products of bf16 tensors with head_dim <= 32 and blocks of at most 16 tokens (float products, or exact bf16 pieces of them).
  * The float path refuses (LCSA_EUNSUPPORTED) shapes with, for b tokens per block,
  * (2 b head_dim + 8 b + 8 head_dim) * 4 + (query blocks per chunk) > 160 * 1024.
  */
