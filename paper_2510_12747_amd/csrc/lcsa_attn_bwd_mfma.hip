@@ -127,24 +127,13 @@ __device__ inline void load_own_rows(const KGeom &g, const BlockRef &b, const __
 // ---- tile copies -------------------------------------------------------------------------------------------------
 // In the query-side kernel a wavefront copies 16 rows of K and of V a step with 4 instructions per tensor; instruction i moves
 // rows first + 4 i .. + 3 of the block, lane t supplying row (t >> 4), chunk position (t & 15).
-// A CopyPlan holds, for the 4 rows of a lane, the distance of the lane's 16 bytes from the block's first token (the
-// host sends blocks that reach 4 GB or more to the float kernels).  Made once for the unclipped extent; clipped blocks make
-// their own.  Rows beyond the block's valid tokens are copied as zeros: their probabilities are zero, and zero times an
-// infinity of another row would not be.
+// plan[] holds, for the 4 rows of a lane, the distance of the lane's 16 bytes from a whole block's first token (the
+// host sends blocks that reach 4 GB or more to the float kernels); clipped blocks take theirs from a table in LDS.  Rows
+// beyond the block's valid tokens are copied as zeros: their probabilities are zero, and zero times an infinity of another row
+// would not be.
 // byte offset of a block's i-th token from its first one
 constexpr uint32_t kNoRow = 0xfffffe00u;
 __device__ inline uint32_t row_offset(const KGeom &g, const BlockTokens &bt, int i, int64_t st) { return i < bt.n_valid ? (uint32_t)(rel_token(g, bt, i) * st * 2) : kNoRow; }
-struct CopyPlan { uint32_t at[4]; };
-__device__ inline CopyPlan copy_plan(const KGeom &g, int vh, int vw, int64_t st, int first, int lane) {
-    CopyPlan p;
-    const BlockTokens bt(g, vh, vw);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = first + 4 * i + (lane >> 4);
-        p.at[i] = row_offset(g, bt, row, st) + ((lane & 15) ^ sw(row)) * 16;
-    }
-    return p;
-}
 // One copy instruction: 64 lanes x 16 bytes from per-lane byte offsets of a scalar base to LDS bytes lds_rows + 16 lane; an
 // offset of kNoRow or more brings zeros.  The load stays in flight (counted by vmcnt) until waited for; nothing else orders it.
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -169,13 +158,15 @@ template <int SECOND> __device__ inline void copy_piece_to_lds(int piece, const 
     }
 }
 
-// A block as the loops want it: raster token of its first token, and its clipped extent.
-struct Located { int origin, extent; };                      // extent = vh | vw << 16
+// A block as the loops want it: raster token of its first token, its valid tokens and how it is clipped.
+// A block has one of four extents: whole, last column, last row or both clipped (0 to 3).
+__device__ inline BlockTokens tokens_of_extent(const KGeom &g, int e) { return BlockTokens(g, e & 2 ? g.H - (g.ty - 1) * g.th : g.th, e & 1 ? g.W - (g.tx - 1) * g.tw : g.tw); }
+__device__ inline int extent_of(const KGeom &g, const BlockRef &b) { return (b.vh < g.th) * 2 + (b.vw < g.tw); }
+struct Located { int origin, valid; };                       // valid tokens | extent << 8
 __device__ inline Located locate(const KGeom &g, int block) {
     const BlockRef b = block_ref(g, block);
-    return {(int)block_origin(g, b), b.vh | b.vw << 16};
+    return {(int)block_origin(g, b), b.n_valid | extent_of(g, b) << 8};
 }
-__device__ inline int valid_tokens(const KGeom &g, const Located &b) { return g.tt * (b.extent & 0xffff) * (b.extent >> 16); }
 
 // all of this wavefront's tile copies have landed; then a workgroup barrier: everybody's have, and everybody is
 // done with the buffer that the next copies will overwrite
@@ -270,7 +261,9 @@ template <int R> __device__ inline float add_row(const f32x16 &x, float v) { ret
 // takes 32 QG queries of a block and walks the kept key blocks in steps of kKeys keys; wavefront w owns queries 32 (w / KH) ..
 // + 31 of them and, of every step, each KH-th 32-key unit; the KH partial results of a query meet in LDS.
 // Which of them when: bwd_query_form().  4 x 1 has 64 KB of tiles, so that two workgroups share a unit; 2 x 4 copies the keys
-// twice for a block's queries, where units would be idle otherwise (54 items, 16 blocks a row: 75 -> 60 us).
+// twice for a block's queries, where units would be idle otherwise (54 items, 16 blocks a row: 75 -> 60 us).  Four wavefronts for 32 queries,
+// four workgroups a block, did no better with the units that still are (0.96 at rows of up to 4 blocks, 1.00 from 16 on): a step
+// is as long as one wavefront's chain of reads, products and exponentials, with or without its copies (0.97 in a timing-only build).
 // What bounds it: instructions, as on the key side (457 vector and 69 matrix instructions a wavefront and block before, of which
 // neither hid the other; 4.2 vector, 2.2 scalar and 1.2 LDS instructions beside each matrix one now, one issued every 7.6 cycles a
 // SIMD, matrix pipe busy 0.49); paper scale 632 -> 483 us.  Tried without gain: the element-wise part of a unit beside the
@@ -285,6 +278,7 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     constexpr int kKeys = 16 * QG * KH, kUnits = kKeys / 32 / KH, kStepBytes = kKeys * 256;
     __shared__ __attribute__((aligned(256))) unsigned char img[2][2][kStepBytes];      // [buffer][K, V]
     __shared__ float part[KH][32 * QG];
+    __shared__ uint32_t row_at[4][128];                      // byte offsets of a key block's tokens from its first one, by extent
     int qb, head, piece;
     if (!work_item(g, items, 4 / QG, head, qb, piece)) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -300,9 +294,21 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     const uint32_t lds_img = lds_address(&img[0][0][0]);
     k += (int64_t)head * kv_sh;
     v += (int64_t)head * kv_sh;
-    const CopyPlan plan = copy_plan(g, g.th, g.tw, kv_st, 16 * wave, lane);
+    // Formed once: divisions and products anew for every clipped block were a quarter of its step, 900 cycles.  Backward of 3 heads on
+    // 21 x 37 tokens in (1, 8, 16) blocks, 16 kept: 84.5 -> 78.0 us, and 75.8 with the units that hold no key left out; 16 heads on
+    // 21 x 45 142 -> 139, whole blocks within 0.3 % (one more barrier).
+    for (int i = tid; i < 512; i += 64 * QG * KH) row_at[i >> 7][i & 127] = row_offset(g, tokens_of_extent(g, i >> 7), i & 127, kv_st);
+    // this lane's rows of a whole block's step, and where they stand in row_at; its chunk of each
+    const int own_row = 16 * wave + (lane >> 4);
+    const BlockTokens whole_block(g, g.th, g.tw);
+    uint32_t plan[4], from[4], lane_chunk[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        lane_chunk[i] = ((lane & 15) ^ sw(own_row + 4 * i)) * 16;
+        plan[i] = row_offset(g, whole_block, own_row + 4 * i, kv_st) + lane_chunk[i];
+    }
     // the second half of an unclipped block: 64 tokens on, which are whole rows or whole frames of the tile or half of its only row
-    const uint32_t half_block = row_offset(g, BlockTokens(g, g.th, g.tw), 64, kv_st);
+    const uint32_t half_block = __builtin_amdgcn_readfirstlane(row_offset(g, whole_block, 64, kv_st));
 
     // kept blocks of this row, 64 at a time, one per lane
     Located chunk = {0, 0};
@@ -316,26 +322,31 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     // What they need is found out a step earlier still.  The requests simply go on behind the second pass.
     u32x4 k_from, v_from;
     uint32_t copy_to = 0;
-    CopyPlan from;
     int ask = 0, ask_half = 0, asked = 0;
     auto locate_next = [&]() {                               // returns the valid keys of the step, + kLast if it ends a pass
         if ((ask & 63) == 0 && ask_half == 0 && cnt > 64) refill(ask);
-        const Located kr = {__builtin_amdgcn_readlane(chunk.origin, ask & 63), __builtin_amdgcn_readlane(chunk.extent, ask & 63)};
-        const bool whole = kr.extent == (g.th | g.tw << 16);
-        from = plan;
-        if (!whole) from = copy_plan(g, kr.extent & 0xffff, kr.extent >> 16, kv_st, 64 * ask_half + 16 * wave, lane);
+        const Located kr = {__builtin_amdgcn_readlane(chunk.origin, ask & 63), __builtin_amdgcn_readlane(chunk.valid, ask & 63)};
+        const int extent = kr.valid >> 8;
+        const bool whole = extent == 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) from[i] = plan[i];
+        if (!whole) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) from[i] = row_at[extent][own_row + 64 * ask_half + 4 * i] + lane_chunk[i];
+        }
         const uint64_t at = (uint64_t)(uint32_t)kr.origin * (uint32_t)(kv_st * 2) + (whole && ask_half ? half_block : 0);
         k_from = rows_from((const char *)k + at);
         v_from = rows_from((const char *)v + at);
         copy_to = __builtin_amdgcn_readfirstlane(lds_img + (asked & 1) * 2 * kStepBytes + wave * 4096);
         ++asked;
-        int n = valid_tokens(g, kr) - 64 * ask_half;
+        int n = (kr.valid & 255) - 64 * ask_half;
         ask_half = kKeys == 64 && ask_half == 0 && n > 64;
         if (!ask_half && ++ask == cnt) { ask = 0; n += kLast; }
         return n;
     };
-    auto copy_piece = [&](int piece) { copy_piece_to_lds<kStepBytes>(piece, k_from, v_from, from.at[piece >> 1], copy_to); };
+    auto copy_piece = [&](int piece) { copy_piece_to_lds<kStepBytes>(piece, k_from, v_from, from[piece >> 1], copy_to); };
     refill(0);
+    lds_barrier();                                           // row_at is there
     int n_keys = 0, n_next = 0;                              // of the step at work and of the one behind it
     if (cnt > 0) {
         n_next = locate_next();
@@ -396,7 +407,7 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
         if (cnt == 0) return;
         do {
             begin_step();
-            if (wave_on) {
+            if (wave_on && n_keys > 32 * kh) {               // unit kh of a clipped block may hold no key
                 products(std::integral_constant<int, 0>{});
                 work(std::integral_constant<int, 0>{});
             } else {
@@ -531,7 +542,7 @@ __device__ __forceinline__ void key_side(
     // or both clipped): formed once, because the divisions and 64-bit products of every unit took a third of the vector work.
     {
         const int e = tid >> 7;
-        const BlockTokens bt(g, e & 2 ? g.H - (g.ty - 1) * g.th : g.th, e & 1 ? g.W - (g.tx - 1) * g.tw : g.tw);
+        const BlockTokens bt = tokens_of_extent(g, e);
         lds.row_at[0][e][tid & 127] = (uint32_t)rel_token(g, bt, tid & 127);
         lds.row_at[1][e][tid & 127] = (uint32_t)(rel_token(g, bt, tid & 127) * q_st * 2);
         lds.row_at[2][e][tid & 127] = row_offset(g, bt, tid & 127, o_st);
@@ -613,7 +624,7 @@ __device__ __forceinline__ void key_side(
                 const int e = lds.list[t + lane];
                 const BlockRef b = block_ref(g, qb0 + (e >> 2));
                 unit_origin = (int)block_origin(g, b);
-                unit_rows = ((b.vh < g.th) * 2 + (b.vw < g.tw)) * 128 + (e & 3) * 32 | min(b.n_valid - (e & 3) * 32, 32) << 16;
+                unit_rows = extent_of(g, b) * 128 + (e & 3) * 32 | min(b.n_valid - (e & 3) * 32, 32) << 16;
             }
         };
         // Unit t on its way into stage `stage`: 8 rows of Q and of dO per wavefront of the second role (lane t supplies row
