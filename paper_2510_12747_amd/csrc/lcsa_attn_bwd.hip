@@ -20,7 +20,7 @@
 // What bounds them: latency, and address arithmetic (64-bit products and divisions run at a quarter of the rate).  Ids are turned
 // into block positions 64 at a time, one per lane, a list of query blocks when it is made; row offsets are formed once for all
 // unclipped blocks; several groups' operands are requested together; a short row's p and t stay in registers for the second pass.
-// 2 heads, d = 32, fp32, 16-token blocks, k = 16 on a 24 x 44 grid: 19.4 + 18.7 -> 13.9 + 16.5 us (36.0 -> 30.1 us back to back), of which
+// 2 heads, d = 32, fp32, 16-token blocks, k = 16 on a 24 x 44 grid: 19.4 + 18.7 -> 13.5 + 17.5 us in whole passes (36.0 -> 28.7 us back to back), of which
 // 2.4 us are matrix work; 30 random geometries 0.84 of the time, 0.67 to 1.03.  Token-per-wavefront dot products in vector FMA with the
 // key block's accumulators in LDS took 541 + 182 us there.
 #include "lcsa_fp32_mma.h"

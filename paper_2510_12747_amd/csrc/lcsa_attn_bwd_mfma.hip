@@ -33,7 +33,7 @@
 // Every matrix instruction takes one 1 KB operand fragment from LDS, and 64 KB of tiles per block pair come from L2 for each
 // of the three passes.
 //
-// Paper scale (12 heads, 48 x 88 tokens, k = 32): 483 us + 464 us (632 + 668 before their copies and addresses were trimmed; as
+// Paper scale (12 heads, 48 x 88 tokens, k = 32): 483 to 509 us + 464 to 482 us, by the card (632 + 668 before their copies and addresses were trimmed; as
 // three kernels, D and dQ apart and dK, dV with four wavefronts, one per SIMD, 312 + 506 + 761 us).
 #include "lcsa_kernels.h"
 #include <utility>
@@ -265,7 +265,7 @@ template <int R> __device__ inline float add_row(const f32x16 &x, float v) { ret
 // four workgroups a block, did no better with the units that still are (0.96 at rows of up to 4 blocks, 1.00 from 16 on): a step
 // is as long as one wavefront's chain of reads, products and exponentials, with or without its copies (0.97 in a timing-only build).
 // What bounds it: instructions, as on the key side (457 vector and 69 matrix instructions a wavefront and block before, of which
-// neither hid the other; 4.2 vector, 2.2 scalar and 1.2 LDS instructions beside each matrix one now, one issued every 7.6 cycles a
+// neither hid the other; 4.0 vector, 2.0 scalar and 1.2 LDS instructions beside each matrix one now, one issued every 7.6 cycles a
 // SIMD, matrix pipe busy 0.49); paper scale 632 -> 483 us.  Tried without gain: the element-wise part of a unit beside the
 // products of the next one, more operands ahead, copies spread over both units.
 template <int QG, int KH>
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
 // Slot t reads units t - 2 .. t + 1, and unit t + 4 is requested into the place of unit t - 3.
 // What bounds it is the number of instructions: a wavefront issues one every five cycles or so, and with 64-bit address
 // products, branches and a spilled operand in each slot (whose reload drained the copies in flight) a slot took 2640 cycles
-// for 1024 of matrix work; it took 1840 without them (paper scale 668 -> 464 us; 6.7 vector, 2.6 scalar and 2.0
+// for 1024 of matrix work; it took 1840 without them (paper scale 668 -> 464 us; 6.6 vector, 2.5 scalar and 2.0
 // LDS instructions beside each matrix one, one issued every 6.6 cycles a SIMD, matrix pipe busy 0.39).
 constexpr int kStages = 7, kLead = kStages - 3;
 constexpr int kUnitBytes = 32 * 256;
