@@ -33,6 +33,10 @@ class lcsa_geom(ctypes.Structure):
         "radius_h", "radius_w", "window_mode", "topk", "dtype")]
 
 
+class _Address(int):
+    """Address of `struct`, which lives as long as the address does."""
+
+
 class _Struct:
     __slots__ = ("_c", "_n")      # beside a dataclass's __dict__: vars(), pickles and copies hold its fields only
 
@@ -59,10 +63,13 @@ class Geom(_Struct):
         object.__setattr__(self, "_n", None)
 
     def _plan(self):
-        """What the native marshalling needs of the geometry, made once as the struct is."""
+        """What the native marshalling needs of the geometry, made once as the struct is.  It has a struct of its own: threads that
+        meet in the first calls may each make one, and no address may outlive its struct."""
         if self._n is None:
-            self._ref()
-            object.__setattr__(self, "_n", (ctypes.addressof(self._c), self.heads, self.n_qb, self.head_dim, self.topk, self.tokens_per_frame,
+            struct = self.c()
+            address = _Address(ctypes.addressof(struct))
+            address.struct = struct
+            object.__setattr__(self, "_n", (address, self.heads, self.n_qb, self.head_dim, self.topk, self.tokens_per_frame,
                                             self.q_frames, 1 if self.dtype == LCSA_BF16 else 0))
         return self._n
 

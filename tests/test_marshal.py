@@ -1,6 +1,10 @@
 """The native argument marshalling (csrc/lcsa_marshal.cpp) against the Python functions it stands in for: the same results, and for
 whatever it does not take, the same errors."""
+import ctypes
+import sys
+import threading
 import types
+import weakref
 
 import pytest
 import torch
@@ -27,6 +31,52 @@ def test_it_takes_only_plain_device_tensors():
     with pytest.raises(TypeError):
         B._marshal.bind(1, 2)
     assert B.Geom(**vars(g))._plan()[1:] == g._plan()[1:]
+
+
+def test_a_plan_keeps_the_struct_whose_address_it_holds(monkeypatch):
+    """Two first uses of one geometry at a time, from two threads: every interleaving leaves an address of a living struct."""
+    fields = (1, 32, 6, 8, 4, 4, 2, 4, 4, 4, 4, B.LCSA_F32)
+    made, build = [], B.Geom.c
+
+    def interrupted(self):
+        """Another thread's whole first use, between the first look at the geometry and the struct that follows from it."""
+        monkeypatch.setattr(B.Geom, "c", recorded)
+        self._plan()
+        return recorded(self)
+
+    def recorded(self):
+        struct = build(self)
+        made.append(weakref.ref(struct))
+        return struct
+
+    alive = lambda address: any(w() is not None and ctypes.addressof(w()) == address for w in made)
+    for first in (B.Geom._ref, B.Geom._plan):
+        g = B.Geom(*fields)
+        monkeypatch.setattr(B.Geom, "c", interrupted)
+        first(g)
+        assert alive(g._plan()[0])
+        plan, seen = g._plan(), bytes(build(g))
+        del g
+        assert alive(plan[0]) and ctypes.string_at(plan[0], len(seen)) == seen
+
+    monkeypatch.setattr(B.Geom, "c", build)
+    geoms, interval, start = [B.Geom(*fields) for _ in range(4000)], sys.getswitchinterval(), threading.Barrier(4)
+
+    def use():
+        start.wait()
+        for g in geoms:
+            g._ref()
+            g._plan()
+
+    threads = [threading.Thread(target=use) for _ in range(4)]
+    sys.setswitchinterval(1e-7)
+    try:
+        for t in threads: t.start()
+        for t in threads: t.join()
+    finally:
+        sys.setswitchinterval(interval)
+    want = bytes(geoms[0].c())
+    assert all(g._plan()[0] == ctypes.addressof(g._plan()[0].struct) and bytes(g._plan()[0].struct) == want for g in geoms)
 
 
 @pytest.mark.gpu
