@@ -32,21 +32,21 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
-def build_marshal(verbose: bool = False) -> str:
+def build_marshal(verbose: bool = False, source: str = os.path.join(CSRC, "lcsa_marshal.cpp"), out: str = MARSHAL) -> str:
     """_marshal.so: the binding's native argument marshalling, host code against the installed torch."""
     import sysconfig
     import torch
     root = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[f"-I{os.path.join(root, 'include', *sub)}" for sub in ((), ("torch", "csrc", "api", "include"))],
-           f"-I{sysconfig.get_paths()['include']}", "-o", MARSHAL, os.path.join(CSRC, "lcsa_marshal.cpp"),
+           f"-I{sysconfig.get_paths()['include']}", "-o", out, source,
            f"-L{os.path.join(root, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ failed:\n" + res.stderr)
-    return MARSHAL
+    return out
 
 
 def build_bench_aids(verbose: bool = False) -> str:

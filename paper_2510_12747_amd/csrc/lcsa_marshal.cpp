@@ -2,11 +2,14 @@
 // In Python (binding.py) they cost 9 us a call, more than the kernels of the smallest layer: 26 us for three calls, 14 of them kernels.
 //
 // Nothing is decided here.  Each function takes the ordinary case, plain torch.Tensor arguments that pass every check, and returns
-// None for anything else, and where torch throws: the Python function then goes on as if this module were not there, and raises what
-// it raises.  The library's entry points are handed over as addresses by bind(), from the one copy of the library that binding.py loaded.
+// None for anything else, and where torch throws before the launch: the Python function then goes on as if this module were not there,
+// and raises what it raises.  After the launch nothing returns None, which would launch again.
+// The library's entry points are handed over as addresses by bind(), from the one copy of the library that binding.py loaded.
 #define PY_SSIZE_T_CLEAN
 #include <ATen/ATen.h>
 #include <Python.h>
+#include <cxxabi.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 namespace {
@@ -53,6 +56,24 @@ bool address(PyObject *x, void *&out) {
     return true;
 }
 
+// What torch throws becomes None.  A thread that asks for the interpreter lock while the interpreter shuts down is ended by unwinding its
+// stack, which must not be held up: the process would abort.  Hence, too, no handler around the lock given up and taken back.
+#define LCSA_OR_NONE catch (abi::__forced_unwind &) { throw; } catch (...) { PyErr_Clear(); Py_RETURN_NONE; }
+
+// The result as a Python object, or null with a Python error set.
+PyObject *wrapped(at::Tensor &&x) {
+    try {
+        return THPVariable_Wrap(std::move(x));
+    } catch (abi::__forced_unwind &) {
+        throw;
+    } catch (python_error &e) {
+        e.restore();
+    } catch (...) {
+        PyErr_SetString(PyExc_RuntimeError, "a result could not be handed to Python");
+    }
+    return nullptr;
+}
+
 // append(plan, cache, k, v, n_frames, stream) -> status
 PyObject *append(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Plan p;
@@ -60,16 +81,18 @@ PyObject *append(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (n != 6 || !p.take(a[0]) || !address(a[1], cache) || !plain(a[2]) || !plain(a[3]) || !PyLong_CheckExact(a[4]) || !address(a[5], stream)) Py_RETURN_NONE;
     const int64_t frames = PyLong_AsLongLong(a[4]);
     if (frames < 1 || frames > (1 << 30)) { PyErr_Clear(); Py_RETURN_NONE; }
-    int32_t status;
+    const void *kp, *vp;
+    int64_t st, sh;
     try {
         const at::Tensor &k = THPVariable_Unpack(a[2]), &v = THPVariable_Unpack(a[3]);
         if (!tokens(k, p, frames) || !tokens(v, p, frames) || k.stride(0) != v.stride(0) || k.stride(1) != v.stride(1)) Py_RETURN_NONE;
-        const void *kp = k.data_ptr(), *vp = v.data_ptr();
-        const int64_t st = k.stride(0), sh = k.stride(1);
-        Py_BEGIN_ALLOW_THREADS
-        status = append_fn(cache, kp, vp, st, sh, (int32_t)frames, stream);
-        Py_END_ALLOW_THREADS
-    } catch (...) { Py_RETURN_NONE; }
+        kp = k.data_ptr(); vp = v.data_ptr();
+        st = k.stride(0); sh = k.stride(1);
+    } LCSA_OR_NONE
+    int32_t status;
+    Py_BEGIN_ALLOW_THREADS
+    status = append_fn(cache, kp, vp, st, sh, (int32_t)frames, stream);
+    Py_END_ALLOW_THREADS
     return PyLong_FromLong(status);
 }
 
@@ -78,8 +101,11 @@ PyObject *pool_select(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Plan p;
     void *cache, *stream;
     if (n != 5 || !p.take(a[0]) || !plain(a[1]) || !address(a[2], cache) || !PyBool_Check(a[3]) || !address(a[4], stream)) Py_RETURN_NONE;
-    int32_t status;
     at::Tensor pooled, idx, cnt, gap;
+    const void *qp;
+    float *pp, *gp;
+    int32_t *ip, *cp;
+    int64_t st, sh;
     try {
         const at::Tensor &q = THPVariable_Unpack(a[1]);
         if (!tokens(q, p, p.q_frames)) Py_RETURN_NONE;
@@ -88,24 +114,26 @@ PyObject *pool_select(PyObject *, PyObject *const *a, Py_ssize_t n) {
         idx = at::empty({p.heads, p.n_qb, p.topk}, on.dtype(at::kInt));
         cnt = at::empty({p.heads, p.n_qb}, on.dtype(at::kInt));
         if (a[3] == Py_True) gap = at::empty({p.heads, p.n_qb}, on.dtype(at::kFloat));
-        const void *qp = q.data_ptr();
-        float *pp = (float *)pooled.data_ptr(), *gp = gap.defined() ? (float *)gap.data_ptr() : nullptr;
-        int32_t *ip = (int32_t *)idx.data_ptr(), *cp = (int32_t *)cnt.data_ptr();
-        const int64_t st = q.stride(0), sh = q.stride(1);
-        Py_BEGIN_ALLOW_THREADS
-        status = pool_select_fn(p.geom, qp, st, sh, cache, pp, ip, cp, gp, stream);
-        Py_END_ALLOW_THREADS
-    } catch (...) { Py_RETURN_NONE; }
+        qp = q.data_ptr();
+        pp = (float *)pooled.data_ptr(); gp = gap.defined() ? (float *)gap.data_ptr() : nullptr;
+        ip = (int32_t *)idx.data_ptr(); cp = (int32_t *)cnt.data_ptr();
+        st = q.stride(0); sh = q.stride(1);
+    } LCSA_OR_NONE
+    int32_t status;
+    Py_BEGIN_ALLOW_THREADS
+    status = pool_select_fn(p.geom, qp, st, sh, cache, pp, ip, cp, gp, stream);
+    Py_END_ALLOW_THREADS
     if (status != 0) return PyLong_FromLong(status);
     PyObject *out = PyTuple_New(4);
     if (!out) return nullptr;
-    PyTuple_SET_ITEM(out, 0, THPVariable_Wrap(std::move(pooled)));
-    PyTuple_SET_ITEM(out, 1, THPVariable_Wrap(std::move(idx)));
-    PyTuple_SET_ITEM(out, 2, THPVariable_Wrap(std::move(cnt)));
-    PyObject *last = Py_None;
-    if (gap.defined()) last = THPVariable_Wrap(std::move(gap));
-    else Py_INCREF(Py_None);
-    PyTuple_SET_ITEM(out, 3, last);
+    at::Tensor *results[4] = {&pooled, &idx, &cnt, &gap};
+    for (int i = 0; i < 4; ++i) {
+        PyObject *x = Py_None;
+        if (results[i]->defined()) x = wrapped(std::move(*results[i]));
+        else Py_INCREF(Py_None);
+        if (!x) { Py_DECREF(out); return nullptr; }
+        PyTuple_SET_ITEM(out, i, x);
+    }
     return out;
 }
 
@@ -117,13 +145,16 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
         !(a[6] == Py_None || plain(a[6])) || !PyFloat_CheckExact(a[7]) || !address(a[8], stream))
         Py_RETURN_NONE;
     const float scale = (float)PyFloat_AS_DOUBLE(a[7]);
-    int32_t status;
     at::Tensor o;
+    const void *qp;
+    const int32_t *ip, *cp;
+    void *op;
+    float *lse = nullptr;
+    int64_t st, sh, ost, osh;
     try {
         const at::Tensor &q = THPVariable_Unpack(a[1]), &idx = THPVariable_Unpack(a[3]), &cnt = THPVariable_Unpack(a[4]);
         // sel_cnt's number of values is not checked by the Python function either
         if (!tokens(q, p, p.q_frames) || !whole(idx, at::kInt, p.heads * p.n_qb * p.topk) || !whole(cnt, at::kInt, cnt.numel())) Py_RETURN_NONE;
-        float *lse = nullptr;
         if (a[6] != Py_None) {
             const at::Tensor &l = THPVariable_Unpack(a[6]);
             if (!whole(l, at::kFloat, q.size(0) * p.heads) || l.dim() != 2 || l.size(0) != q.size(0)) Py_RETURN_NONE;
@@ -134,17 +165,18 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
             o = THPVariable_Unpack(a[5]);
             if (!tokens(o, p, p.q_frames)) Py_RETURN_NONE;
         }
-        const void *qp = q.data_ptr();
-        const int32_t *ip = (const int32_t *)idx.data_ptr(), *cp = (const int32_t *)cnt.data_ptr();
-        void *op = o.data_ptr();
-        const int64_t st = q.stride(0), sh = q.stride(1), ost = o.stride(0), osh = o.stride(1);
-        Py_BEGIN_ALLOW_THREADS
-        status = forward_fn(p.geom, qp, st, sh, cache, ip, cp, op, ost, osh, lse, scale, stream);
-        Py_END_ALLOW_THREADS
-    } catch (...) { Py_RETURN_NONE; }
+        qp = q.data_ptr();
+        ip = (const int32_t *)idx.data_ptr(); cp = (const int32_t *)cnt.data_ptr();
+        op = o.data_ptr();
+        st = q.stride(0); sh = q.stride(1); ost = o.stride(0); osh = o.stride(1);
+    } LCSA_OR_NONE
+    int32_t status;
+    Py_BEGIN_ALLOW_THREADS
+    status = forward_fn(p.geom, qp, st, sh, cache, ip, cp, op, ost, osh, lse, scale, stream);
+    Py_END_ALLOW_THREADS
     if (status != 0) return PyLong_FromLong(status);
     if (a[5] != Py_None) { Py_INCREF(a[5]); return a[5]; }
-    return THPVariable_Wrap(std::move(o));
+    return wrapped(std::move(o));
 }
 
 // bind(addresses of lcsa_kv_cache_append, lcsa_pool_select_blocks, lcsa_sparse_attn_fwd)

@@ -1,6 +1,9 @@
 """The native argument marshalling (csrc/lcsa_marshal.cpp) against the Python functions it stands in for: the same results, and for
 whatever it does not take, the same errors."""
 import ctypes
+import importlib.util
+import os
+import subprocess
 import sys
 import threading
 import types
@@ -10,8 +13,115 @@ import pytest
 import torch
 
 from paper_2510_12747_amd import binding as B
+from paper_2510_12747_amd import build
 
 NOTHING = types.SimpleNamespace(append=lambda *a: None, pool_select=lambda *a: None, forward=lambda *a: None)
+
+
+PROBES = """
+#include <ATen/ATen.h>
+#include <Python.h>
+#include <torch/csrc/autograd/python_variable.h>
+extern "C" {
+__attribute__((visibility("default"))) int fail_wraps = 0;
+}
+static PyObject *probed_wrap(at::Tensor x) {
+    if (fail_wraps && --fail_wraps == 0) throw 1;
+    return THPVariable_Wrap(std::move(x));
+}
+"""
+LIBRARY = """
+#include <stdint.h>
+#include <stdlib.h>
+#include <unistd.h>
+int calls, status, delay_us;
+int64_t seen[12];
+int append(void *c, const void *k, const void *v, int64_t st, int64_t sh, int32_t n, void *s) {
+    int64_t a[] = {(int64_t)c, (int64_t)k, (int64_t)v, st, sh, n, (int64_t)s};
+    for (int i = 0; i < 7; ++i) seen[i] = a[i];
+    usleep(delay_us); ++calls; return status;
+}
+int pool_select(const void *g, const void *q, int64_t st, int64_t sh, const void *c, float *p, int32_t *i_, int32_t *n, float *gap, void *s) {
+    int64_t a[] = {(int64_t)g, (int64_t)q, st, sh, (int64_t)c, (int64_t)p, (int64_t)i_, (int64_t)n, (int64_t)gap, (int64_t)s};
+    for (int i = 0; i < 10; ++i) seen[i] = a[i];
+    usleep(delay_us); ++calls; return status;
+}
+int forward(const void *g, const void *q, int64_t st, int64_t sh, const void *c, const int32_t *i_, const int32_t *n, void *o, int64_t ost, int64_t osh,
+            float *l, float scale, void *s) {
+    int64_t a[] = {(int64_t)g, (int64_t)q, st, sh, (int64_t)c, (int64_t)i_, (int64_t)n, (int64_t)o, ost, osh, (int64_t)l, (int64_t)s};
+    for (int i = 0; i < 12; ++i) seen[i] = a[i];
+    usleep(delay_us); ++calls; return status;
+}
+static void linger(void) { usleep(1000000); }
+void linger_at_exit(void) { atexit(linger); }
+"""
+
+
+def load_on_cpu(folder):
+    """The marshalling's source built for CPU tensors in front of a library that only notes its arguments."""
+    spec = importlib.util.spec_from_file_location("_marshal", os.path.join(folder, "_marshal.so"))
+    native = importlib.util.module_from_spec(spec)
+    library = ctypes.CDLL(os.path.join(folder, "library.so"))
+    native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (library.append, library.pool_select, library.forward)))
+    return native, library
+
+
+@pytest.fixture(scope="module")
+def on_cpu(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("marshal")
+    with open(os.path.join(build.CSRC, "lcsa_marshal.cpp")) as f:
+        source = f.read()
+    for old, new in (("is_cuda()", "is_cpu()"), ("THPVariable_Wrap(", "probed_wrap(")):
+        assert old in source
+        source = source.replace(old, new)
+    (folder / "marshal.cpp").write_text(PROBES + source)
+    (folder / "library.c").write_text(LIBRARY)
+    build.build_marshal(source=str(folder / "marshal.cpp"), out=str(folder / "_marshal.so"))
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(folder / "library.so"), str(folder / "library.c")], check=True)
+    return (str(folder), *load_on_cpu(folder))
+
+
+GEOM = (2, 32, 6, 8, 4, 4, 2, 4, 4, 4, 4, B.LCSA_F32)
+
+
+def arguments():
+    """Of a layer's three calls, without their streams."""
+    g = B.Geom(*GEOM)
+    x = torch.zeros(96, 2, 32)
+    i, n = torch.zeros(2, 8, 4, dtype=torch.int32), torch.zeros(2, 8, dtype=torch.int32)
+    return (g._plan(), 5, x, x, 2), (g._plan(), x, 5, True), (g._plan(), x, 5, i, n, None, None, 0.0)
+
+
+def test_a_thread_that_the_interpreter_ends_in_a_call_ends_quietly(on_cpu):
+    """The interpreter shuts down while daemon threads are in the library: they are ended when they come back, not the process."""
+    folder = on_cpu[0]
+    script = f"""
+import ctypes, sys, threading, time
+sys.path[:0] = {[os.path.dirname(__file__), os.path.dirname(build.HERE)]!r}
+import test_marshal as t
+native, library = t.load_on_cpu({folder!r})
+append, pool_select, forward = t.arguments()
+ctypes.c_int.in_dll(library, "delay_us").value = 500000
+for f, a in ((native.append, append), (native.pool_select, pool_select), (native.forward, forward)):
+    threading.Thread(target=f, args=(*a, 7), daemon=True).start()
+time.sleep(0.2)
+library.linger_at_exit()
+print("leaving", flush=True)
+"""
+    done = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=120)
+    assert done.stdout == "leaving\n" and done.returncode == 0, (done.returncode, done.stderr)
+
+
+def test_a_result_that_python_cannot_take_is_an_error_and_not_a_second_launch(on_cpu):
+    _, native, library = on_cpu
+    calls, fail = ctypes.c_int.in_dll(library, "calls"), ctypes.c_int.in_dll(ctypes.CDLL(native.__file__), "fail_wraps")
+    _, pool_select, forward = arguments()
+    for f, a, results in ((native.pool_select, pool_select, 4), (native.forward, forward, 1)):
+        for nth in range(1, results + 1):
+            calls.value, fail.value = 0, nth
+            with pytest.raises(RuntimeError):
+                f(*a, 7)
+            assert calls.value == 1 and fail.value == 0
 
 
 def test_it_takes_only_plain_device_tensors():
