@@ -60,6 +60,18 @@ bool address(PyObject *x, void *&out) {
 // stack, which must not be held up: the process would abort.  Hence, too, no handler around the lock given up and taken back.
 #define LCSA_OR_NONE catch (abi::__forced_unwind &) { throw; } catch (...) { PyErr_Clear(); Py_RETURN_NONE; }
 
+// Outputs are allocated without the interpreter lock, as torch.empty does it: a first allocation takes long.  False where torch throws.
+template <typename F> bool allocated(F &&outputs) {
+    try {
+        outputs();
+        return true;
+    } catch (abi::__forced_unwind &) {
+        throw;
+    } catch (...) {
+        return false;
+    }
+}
+
 // The result as a Python object, or null with a Python error set.
 PyObject *wrapped(at::Tensor &&x) {
     try {
@@ -101,28 +113,34 @@ PyObject *pool_select(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Plan p;
     void *cache, *stream;
     if (n != 5 || !p.take(a[0]) || !plain(a[1]) || !address(a[2], cache) || !PyBool_Check(a[3]) || !address(a[4], stream)) Py_RETURN_NONE;
+    const bool want_gap = a[3] == Py_True;
     at::Tensor pooled, idx, cnt, gap;
+    at::TensorOptions on;
     const void *qp;
-    float *pp, *gp;
-    int32_t *ip, *cp;
     int64_t st, sh;
     try {
         const at::Tensor &q = THPVariable_Unpack(a[1]);
         if (!tokens(q, p, p.q_frames)) Py_RETURN_NONE;
-        const auto on = at::TensorOptions().device(q.device());
-        pooled = at::empty({p.heads, p.n_qb, p.d}, on.dtype(at::kFloat));
-        idx = at::empty({p.heads, p.n_qb, p.topk}, on.dtype(at::kInt));
-        cnt = at::empty({p.heads, p.n_qb}, on.dtype(at::kInt));
-        if (a[3] == Py_True) gap = at::empty({p.heads, p.n_qb}, on.dtype(at::kFloat));
+        on = on.device(q.device());
         qp = q.data_ptr();
-        pp = (float *)pooled.data_ptr(); gp = gap.defined() ? (float *)gap.data_ptr() : nullptr;
-        ip = (int32_t *)idx.data_ptr(); cp = (int32_t *)cnt.data_ptr();
         st = q.stride(0); sh = q.stride(1);
     } LCSA_OR_NONE
     int32_t status;
+    bool launched;
     Py_BEGIN_ALLOW_THREADS
-    status = pool_select_fn(p.geom, qp, st, sh, cache, pp, ip, cp, gp, stream);
+    float *pp, *gp = nullptr;
+    int32_t *ip, *cp;
+    launched = allocated([&] {
+        pooled = at::empty({p.heads, p.n_qb, p.d}, on.dtype(at::kFloat));
+        idx = at::empty({p.heads, p.n_qb, p.topk}, on.dtype(at::kInt));
+        cnt = at::empty({p.heads, p.n_qb}, on.dtype(at::kInt));
+        if (want_gap) gap = at::empty({p.heads, p.n_qb}, on.dtype(at::kFloat));
+        pp = (float *)pooled.data_ptr(); ip = (int32_t *)idx.data_ptr(); cp = (int32_t *)cnt.data_ptr();
+        if (want_gap) gp = (float *)gap.data_ptr();
+    });
+    if (launched) status = pool_select_fn(p.geom, qp, st, sh, cache, pp, ip, cp, gp, stream);
     Py_END_ALLOW_THREADS
+    if (!launched) { PyErr_Clear(); Py_RETURN_NONE; }
     if (status != 0) return PyLong_FromLong(status);
     PyObject *out = PyTuple_New(4);
     if (!out) return nullptr;
@@ -145,12 +163,13 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
         !(a[6] == Py_None || plain(a[6])) || !PyFloat_CheckExact(a[7]) || !address(a[8], stream))
         Py_RETURN_NONE;
     const float scale = (float)PyFloat_AS_DOUBLE(a[7]);
+    const bool own_o = a[5] == Py_None;
     at::Tensor o;
+    at::TensorOptions as_q;
     const void *qp;
     const int32_t *ip, *cp;
-    void *op;
     float *lse = nullptr;
-    int64_t st, sh, ost, osh;
+    int64_t rows, st, sh;
     try {
         const at::Tensor &q = THPVariable_Unpack(a[1]), &idx = THPVariable_Unpack(a[3]), &cnt = THPVariable_Unpack(a[4]);
         // sel_cnt's number of values is not checked by the Python function either
@@ -160,22 +179,29 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n) {
             if (!whole(l, at::kFloat, q.size(0) * p.heads) || l.dim() != 2 || l.size(0) != q.size(0)) Py_RETURN_NONE;
             lse = (float *)l.data_ptr();
         }
-        if (a[5] == Py_None) o = at::empty({q.size(0), q.size(1), q.size(2)}, at::TensorOptions().device(q.device()).dtype(q.scalar_type()));
-        else {
+        if (!own_o) {
             o = THPVariable_Unpack(a[5]);
             if (!tokens(o, p, p.q_frames)) Py_RETURN_NONE;
         }
+        as_q = as_q.device(q.device()).dtype(q.scalar_type());
+        rows = q.size(0);
         qp = q.data_ptr();
         ip = (const int32_t *)idx.data_ptr(); cp = (const int32_t *)cnt.data_ptr();
-        op = o.data_ptr();
-        st = q.stride(0); sh = q.stride(1); ost = o.stride(0); osh = o.stride(1);
+        st = q.stride(0); sh = q.stride(1);
     } LCSA_OR_NONE
     int32_t status;
+    bool launched;
     Py_BEGIN_ALLOW_THREADS
-    status = forward_fn(p.geom, qp, st, sh, cache, ip, cp, op, ost, osh, lse, scale, stream);
+    void *op;
+    launched = allocated([&] {
+        if (own_o) o = at::empty({rows, p.heads, p.d}, as_q);
+        op = o.data_ptr();
+    });
+    if (launched) status = forward_fn(p.geom, qp, st, sh, cache, ip, cp, op, o.stride(0), o.stride(1), lse, scale, stream);
     Py_END_ALLOW_THREADS
+    if (!launched) { PyErr_Clear(); Py_RETURN_NONE; }
     if (status != 0) return PyLong_FromLong(status);
-    if (a[5] != Py_None) { Py_INCREF(a[5]); return a[5]; }
+    if (!own_o) { Py_INCREF(a[5]); return a[5]; }
     return wrapped(std::move(o));
 }
 

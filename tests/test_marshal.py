@@ -23,7 +23,13 @@ PROBES = """
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
 extern "C" {
-__attribute__((visibility("default"))) int fail_wraps = 0;
+__attribute__((visibility("default"))) int fail_wraps = 0, fail_allocations = 0, locked_allocations = 0, allocations = 0;
+}
+static at::Tensor probed_empty(at::IntArrayRef sizes, at::TensorOptions options) {
+    ++allocations;
+    locked_allocations += PyGILState_Check();
+    if (fail_allocations && --fail_allocations == 0) throw 1;
+    return at::empty(sizes, options);
 }
 static PyObject *probed_wrap(at::Tensor x) {
     if (fail_wraps && --fail_wraps == 0) throw 1;
@@ -71,7 +77,7 @@ def on_cpu(tmp_path_factory):
     folder = tmp_path_factory.mktemp("marshal")
     with open(os.path.join(build.CSRC, "lcsa_marshal.cpp")) as f:
         source = f.read()
-    for old, new in (("is_cuda()", "is_cpu()"), ("THPVariable_Wrap(", "probed_wrap(")):
+    for old, new in (("is_cuda()", "is_cpu()"), ("THPVariable_Wrap(", "probed_wrap("), ("at::empty(", "probed_empty(")):
         assert old in source
         source = source.replace(old, new)
     (folder / "marshal.cpp").write_text(PROBES + source)
@@ -122,6 +128,20 @@ def test_a_result_that_python_cannot_take_is_an_error_and_not_a_second_launch(on
             with pytest.raises(RuntimeError):
                 f(*a, 7)
             assert calls.value == 1 and fail.value == 0
+
+
+def test_outputs_are_allocated_without_the_interpreter_lock(on_cpu):
+    """As torch.empty allocates; and where an allocation throws, the Python function is to go on."""
+    _, native, library = on_cpu
+    probes = ctypes.CDLL(native.__file__)
+    calls, fail, made, locked = ctypes.c_int.in_dll(library, "calls"), *(ctypes.c_int.in_dll(probes, p) for p in ("fail_allocations", "allocations", "locked_allocations"))
+    _, pool_select, forward = arguments()
+    for f, a, outputs in ((native.pool_select, pool_select, 4), (native.forward, forward, 1)):
+        calls.value = made.value = locked.value = 0
+        assert f(*a, 7) is not None and [calls.value, made.value, locked.value] == [1, outputs, 0]
+        for nth in range(1, outputs + 1):
+            fail.value = nth
+            assert f(*a, 7) is None and calls.value == 1 and fail.value == 0
 
 
 def test_it_takes_only_plain_device_tensors():
