@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch  # imported first so that the HIP runtime torch ships is the one the library binds to
@@ -110,8 +111,14 @@ class Geom(_Struct):
         return torch.bfloat16 if self.dtype == LCSA_BF16 else torch.float32
 
 
+class _InPython:
+    """Stands for _marshal.so where that is not there: takes nothing, so that the Python functions do all of it."""
+
+    append = pool_select = forward = staticmethod(lambda *a: None)
+
+
 _lib = None
-_marshal = None
+_marshal = _InPython
 _vp, _i32, _i64, _f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
 _gp = ctypes.POINTER(lcsa_geom)
 
@@ -165,12 +172,17 @@ def lib():
 
 
 def _bind(L) -> None:
-    """Hands the entry points of the loaded library to the native marshalling."""
+    """Hands the entry points of the loaded library to the native marshalling, which only spares time: without it every call works."""
     global _marshal
     try:
         from . import _marshal as native
+        if native.torch_version != torch.__version__.split("+")[0]:
+            raise ImportError(f"built for torch {native.torch_version}, this is {torch.__version__}")
     except ImportError as e:
-        raise LcsaError(f"_marshal.so not found or not loadable ({e}): build it with `python -m paper_2510_12747_amd.build`") from e
+        warnings.warn(f"_marshal.so not loaded ({e}): a layer's calls take some 9 us each on the host instead of 5; build it with "
+                      "`python -m paper_2510_12747_amd.build`", RuntimeWarning, stacklevel=3)
+        _marshal = _InPython
+        return
     native.bind(*(_vp.from_buffer(f).value for f in (L.lcsa_kv_cache_append, L.lcsa_pool_select_blocks, L.lcsa_sparse_attn_fwd)))
     _marshal = native
 

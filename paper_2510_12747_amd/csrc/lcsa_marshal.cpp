@@ -11,6 +11,7 @@
 #include <cxxabi.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 namespace {
 
@@ -227,4 +228,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 } // namespace
 
-extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal() { return PyModule_Create(&module); }
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal() {
+    PyObject *m = PyModule_Create(&module);
+    // of the headers it was built with: tensors are read by their layout there
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) != 0) { Py_DECREF(m); return nullptr; }
+    return m;
+}

@@ -98,6 +98,28 @@ def arguments():
     return (g._plan(), 5, x, x, 2), (g._plan(), x, 5, True), (g._plan(), x, 5, i, n, None, None, 0.0)
 
 
+@pytest.mark.parametrize("how", ["absent", "unloadable", "another torch"])
+def test_the_library_loads_without_it(monkeypatch, tmp_path, how):
+    """Callers that need none of its functions, and those that do: the Python functions are all there."""
+    B.lib()
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_marshal", B._marshal)
+    if how == "another torch":
+        monkeypatch.setattr(B._marshal, "torch_version", "1.0.0")
+    else:
+        if how == "unloadable":
+            (tmp_path / "_marshal.so").write_bytes(b"no object file")
+        monkeypatch.setattr(sys.modules[B.__package__], "__path__", [str(tmp_path)])
+        monkeypatch.delattr(sys.modules[B.__package__], "_marshal", raising=False)
+        monkeypatch.delitem(sys.modules, B.__package__ + "._marshal", raising=False)
+    with pytest.warns(RuntimeWarning, match="_marshal.so not loaded"):
+        assert B.lcsa_cache_device_bytes(B.Geom(*GEOM)) > 0
+    (plan, *a), (_, *b), (_, *c) = arguments()
+    assert B._marshal.append(plan, *a, 7) is B._marshal.pool_select(plan, *b, 7) is B._marshal.forward(plan, *c, 7) is None
+    with pytest.raises(B.LcsaError, match="device tensor"):
+        B._tok(a[1])
+
+
 def test_a_thread_that_the_interpreter_ends_in_a_call_ends_quietly(on_cpu):
     """The interpreter shuts down while daemon threads are in the library: they are ended when they come back, not the process."""
     folder = on_cpu[0]
