@@ -1,5 +1,5 @@
-// How launches of the matrix-core attention kernels deal their work items (one per (head, query block)) out to workgroups.
-// Host arithmetic only.
+// How launches of the matrix-core attention kernels deal their work items (one per (head, query block)) out to workgroups, and
+// the general append its tiles.  Host arithmetic only.
 #pragma once
 #include <stdint.h>
 
@@ -63,6 +63,22 @@ inline BwdQueryForm bwd_query_form(int items, int units, int k) {
     const int rounds = (items + units - 1) / units;
     if (rounds <= 1) return 2 * items <= units ? kBwd2x4 : kBwd4x2;
     return rounds == 3 && k > 16 ? kBwd4x2 : kBwd4x1;
+}
+
+// General append into the ring: whether four tiles share a workgroup of 1024 threads.  What they share is a ticket, 10 ns each and one
+// after the other; what it costs is that a tile's threads move together with three others', in fewer workgroups.  So by the bytes of a tile
+// (each of K and V; the shape does not matter) and by how evenly the units are filled.  One / four a workgroup, us on 256 units (all of it in
+// profiles/):
+//   to 16 KB     the tickets are most of it: 200 tiles of 16 KB 7.0 / 6.8, of 4 KB 5.4 / 4.5; 576 of 4 KB 10.4 / 6.1; 2400 of 16 KB 53 / 39
+//   to 32 KB     once units have a tile each: 200 tiles of 32 KB 9.2 / 9.7, 224 9.8 / 9.8, 256 10.4 / 10.2, 1152 44.8 / 42.3, 2400 83 / 71
+//   more         where four to a workgroup fill more than half of the units, all of them at once, and the single ones take turns: 576 to
+//                1024 tiles of 48 KB 31.4 / 30.0 to 52.7 / 44.4, of 256 KB 137 / 136 to 231 / 226; not 512 (26.3 / 27.9, 120 / 138) or
+//                1152 (61.1 / 61.5, 266 / 308); 224 tiles of 64 KB would take 1.13 and of 256 KB 1.6 times as long.  Beyond five tiles a unit
+//                the unevenness fades: 64 KB 1408 91.6 / 87.4, 2048 127 / 113; from 128 KB on it does not pay for itself (1408 169 / 170).
+inline bool append_shares(int items, int units, int64_t tile_bytes) {
+    if (tile_bytes <= 16384) return items > units * 3 / 4;
+    if (tile_bytes <= 32768) return items >= units;
+    return (items > 2 * units && items <= 4 * units) || (tile_bytes <= 65536 && items > 5 * units);
 }
 
 } // namespace lcsa

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void rope_pool_kernel(KGeom g, const char
 // Cache append, generic tile image: K and V tiles row-major [bt][d], padded tokens zero;
 // pooled K written beside them.                                      grid n_groups*nb*heads / SUB, rounded up
 // SUB parts of 256 threads, one (tile, head) each: what they share is the ticket.  Tickets are drawn one after the other, 10 ns each,
-// which is what bounds many small tiles; few are a chain of ring word -> rows -> means.
+// which is what bounds many small tiles; few are a chain of ring word -> rows -> means.  Which SUB when: append_shares().
 template <int VEC, int SUB>
 __global__ __launch_bounds__(kThreads * SUB) void append_generic_kernel(KGeom g, KCache c, const char *k, const char *v,
                                                                         int64_t st, int64_t sh, int first, int n_groups, bool fresh) {
@@ -409,10 +409,7 @@ hipError_t launch_append(const KGeom &g, const KCache &c, const void *k, const v
         constexpr std::integral_constant<int, 4> four{};
         constexpr std::integral_constant<int, 1> one{};
         constexpr std::integral_constant<int, 8> eight{};
-        // One ticket for four tiles where the tickets would take longer than the tiles (one / four a workgroup, us: 576 tiles of 32
-        // tokens, bf16, d = 64, 10.4 / 6.1; 792 of 16 tokens, float, d = 32, 12.4 / 5.9; 256 of 16 tokens, float, d = 96, 6.1 / 4.9;
-        // 192 of 32, bf16, d = 32, 5.6 / 5.0), not where it leaves units idle (144 of 32, float, d = 96, 5.3 / 5.6; 36 of 64, d = 96, 4.2 / 5.2).
-        const bool share = !fresh && !c.order && items > 192;
+        const bool share = !fresh && !c.order && append_shares(items, compute_units(), (int64_t)g.bt * g.d * (g.bf16 ? 2 : 4));
         if (g.bf16) share ? generic(eight, four) : generic(eight, one);
         else share ? generic(four, four) : generic(four, one);
     }

@@ -18,6 +18,7 @@ def rule(tmp_path_factory):
                    'extern "C" int form(int items, int units, int k) { return lcsa::attn_form(items, units, k); }\n'
                    'extern "C" int few(int items, int units, long long tokens, int blocks) { return lcsa::attn_few(items, units, tokens, blocks); }\n'
                    'extern "C" int bwd_form(int items, int units, int k) { return lcsa::bwd_query_form(items, units, k); }\n'
+                   'extern "C" int shares(int items, int units, long long bytes) { return lcsa::append_shares(items, units, bytes); }\n'
                    'extern "C" int workgroups(int form, int items) { return lcsa::attn_workgroups((lcsa::AttnForm)form, items); }\n')
     subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2510_12747_amd", "csrc"),
                     "-o", str(lib), str(src)], check=True)
@@ -115,3 +116,25 @@ def test_edges_of_the_rule_for_few_items(rule):
     for tokens, blocks, few in ((80, 10, 0), (208, 7, 0), (192, 3, 0), (193, 3, 1), (216, 3, 1), (777, 9, 1), (1 << 30, 1 << 24, 0), ((1 << 30) + 1, 1 << 24, 1)):
         assert rule.few(8, 256, ctypes.c_longlong(tokens), blocks) & 1 == few, (tokens, blocks)
     assert rule.workgroups(3, 7) == 14
+
+
+def test_tiles_share_a_workgroup_of_the_append_where_that_was_measured_faster(rule):
+    """Never slower than a tile each by more than the runs differ; means of the ratio to the better form: the rule 1.002, a tile
+    each 1.21, four always 1.08."""
+    path = os.path.join(ROOT, "profiles", "append_general_tiles_a_workgroup.txt")
+    rows, picked, single, four_always = [[float(x) for x in line.split()] for line in open(path) if not line.startswith("#")], 1.0, 1.0, 1.0
+    assert len(rows) == 545
+    for size, items, _, _, _, one, four in rows:
+        us = four if rule.shares(int(items), 256, ctypes.c_longlong(int(size))) & 1 else one
+        assert us <= 1.02 * one and (us <= 1.08 * four or size == 49152 or items <= 192), (size, items)
+        picked, single, four_always = picked * us / min(one, four), single * one / min(one, four), four_always * four / min(one, four)
+    assert picked ** (1 / len(rows)) < 1.003 < 1.05 < four_always ** (1 / len(rows)) < single ** (1 / len(rows))
+
+
+def test_edges_of_the_sharing_rule(rule):
+    kb = lambda n, items: rule.shares(items, 256, ctypes.c_longlong(int(n * 1024))) & 1
+    for size, first in ((1, 193), (16, 193), (16.5, 256), (32, 256)):
+        assert [kb(size, n) for n in (1, first - 1, first, 1 << 30)] == [0, 0, 1, 1]
+    for size, many in ((33, 1), (64, 1), (65, 0), (1024, 0)):
+        assert [kb(size, n) for n in (193, 216, 512, 513, 1024, 1025, 1280, 1281, 1 << 30)] == [0, 0, 0, 1, 1, 0, 0, many, many]
+    assert [rule.shares(n, 32, ctypes.c_longlong(4096)) & 1 for n in (24, 25)] == [0, 1]
