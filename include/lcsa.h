@@ -287,6 +287,7 @@ int32_t lcsa_sparse_attn_fwd(const lcsa_geom *geom,
  * (and through delta d_k) are sums of one, two or four parts by the number of rows of the call and the device's compute
  * units: the same row in a call of another size, or on another device, may differ in their rounding.  So may d_q in float
  * products of bf16 tensors with head_dim <= 32 and blocks of at most 16 tokens (float products, or exact bf16 pieces of them).
+ * Infinite, NaN, very large and very small weights and values give what products of floats give, whichever form they take.
  * The float path refuses (LCSA_EUNSUPPORTED) shapes with, for b tokens per block,
  * (2 b head_dim + 8 b + 8 head_dim) * 4 + (query blocks per chunk) > 160 * 1024.
  */

@@ -104,6 +104,7 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const T *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse,
     float *__restrict__ d_q, float *__restrict__ delta, float scale) {
+    constexpr bool PIECES = sizeof(T) == 2 && GI > 1;
     __shared__ float part_d[4][16];
     __shared__ f32x4 part_q[4][NT][64];
     const int qb = g.by_heads(blockIdx.x), head = blockIdx.x - qb * g.heads;
@@ -221,9 +222,7 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
             if (q_valid && g4 == 0 && ks == 0) delta[token * g.heads + head] = D;
         };
         f32x4 dq[1][NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) dq[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto add_to_dq = [&](const f32x4 (&p)[GI], const f32x4 (&t)[GI], ColGroups<T, NT, GI> &kc, const int (&valid)[GI]) {
+        auto add_to_dq = [&](const f32x4 (&p)[GI], const f32x4 (&t)[GI], ColGroups<T, NT, GI> &kc, const int (&valid)[GI], auto in_float) {
             f32x4 u[1][GI];
 #pragma unroll
             for (int i = 0; i < GI; ++i) {
@@ -231,7 +230,19 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 for (int r = 0; r < 4; ++r) u[0][i][r] = p[i][r] * ((t[i][r] - D) * scale);
                 kc.keep(i, valid[i], g4);
             }
-            kc.template mma<1>(u, dq);
+            kc.template mma<1, in_float>(u, dq);
+        };
+        // dq = what pass(in_float) adds up; once more in float products alone where the sums of pieces are doubtful
+        auto sum = [&](auto &&pass) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) dq[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            pass(std::bool_constant<!PIECES>{});
+            if constexpr (PIECES) {
+                if (!ColGroups<T, NT, GI>::doubtful(dq[0])) return;      // uniform over the wavefront
+#pragma unroll
+                for (int t = 0; t < NT; ++t) dq[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                pass(std::true_type{});
+            }
         };
         const int mine = total > ks ? (total - ks + splits - 1) / splits : 0;      // groups of this wavefront
         if (HELD && total <= HELD * GI * splits) {           // uniform over the workgroup
@@ -250,10 +261,15 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 if (HELD > 1) { products(keys_b, p_b, t_b); add_to_d(p_b, t_b); }
             }
             finish_d();
-            if (total > 0) {
-                add_to_dq(p_a, t_a, kc_a, valid_a);
-                if (HELD > 1) add_to_dq(p_b, t_b, kc_b, valid_b);
-            }
+            sum([&](auto in_float) {
+                if (total == 0) return;
+                if (PIECES && in_float) {                    // the first time took the large values out
+                    request_columns(0, kc_a, valid_a);
+                    if (HELD > 1) request_columns(GI, kc_b, valid_b);
+                }
+                add_to_dq(p_a, t_a, kc_a, valid_a, in_float);
+                if (HELD > 1) add_to_dq(p_b, t_b, kc_b, valid_b, in_float);
+            });
         } else {
             Keys keys;
             f32x4 p[GI], t[GI];
@@ -263,14 +279,16 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 add_to_d(p, t);
             }
             finish_d();
-            for (int i0 = 0; i0 < mine; i0 += GI) {
-                ColGroups<T, NT, GI> kc;
-                int valid[GI];
-                request(i0, keys);
-                request_columns(i0, kc, valid);
-                products(keys, p, t);
-                add_to_dq(p, t, kc, valid);
-            }
+            sum([&](auto in_float) {
+                for (int i0 = 0; i0 < mine; i0 += GI) {
+                    ColGroups<T, NT, GI> kc;
+                    int valid[GI];
+                    request(i0, keys);
+                    request_columns(i0, kc, valid);
+                    products(keys, p, t);
+                    add_to_dq(p, t, kc, valid, in_float);
+                }
+            });
         }
         if (splits > 1) {
             if (ks != 0)
@@ -301,11 +319,13 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
     const T *__restrict__ d_o, int64_t o_st, int64_t o_sh, const float *__restrict__ lse, const float *__restrict__ delta,
     float *__restrict__ d_k, float *__restrict__ d_v, float scale) {
+    using Cols = ColGroups<T, NT, GI>;
+    constexpr bool PIECES = sizeof(T) == 2 && GI > 1;
     constexpr int kParts = NT <= 4 ? 2 : 1;
     __shared__ f32x4 part[kParts][4][NT][64];
     __shared__ unsigned char kept_by[kListed], list_clip[kListed];
     __shared__ int list_origin[kListed];
-    __shared__ int n_listed;
+    __shared__ int n_listed, again;
     const int kb = g.by_heads(blockIdx.x), head = blockIdx.x - kb * g.heads;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g4 = lane >> 4;
@@ -323,6 +343,7 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
     const bool simple = NT <= 6 && whole_rows(g);            // the offsets stay in registers throughout
     const PieceRows unclipped(g, tokens_of(g, 0), 0, m, g4);
 
+    if (tid == 0) again = -1;
     // rounds over the block's key rows: every wavefront takes part in every round (the lists are made together)
     for (int base = 0; base < kt.n_valid; base += ways * 16) {
         const int k0 = base + kw * 16;
@@ -334,134 +355,141 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
         kf.clear_beyond(g.d, g4);
         vf.clear_beyond(g.d, g4);
         f32x4 dk[1][NT], dv[1][NT];
+        auto walk = [&](auto in_float) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) dk[0][t] = dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-        for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
-            // which query blocks kept this key block?  (ascending id lists)
-            const int n_here = min(kListed, n_qb - qb0);
-            const int64_t first_row = (int64_t)head * n_qb + qb0;
-            __syncthreads();                                 // the previous list is no longer read
-            if (NT <= 8 && g.topk <= 32) {                   // all ids, eight loads of a thread in flight; longer rows: a search reads less
-                for (int i = tid; i < n_here; i += kThreads) kept_by[i] = 0;
-                __syncthreads();
-                const int32_t *ids = sel_idx + first_row * g.topk;
-                const int n_ids = n_here * g.topk;
-                for (int at = tid; at < n_ids; at += 8 * kThreads) {
-                    int id[8];
+            for (int t = 0; t < NT; ++t) dk[0][t] = dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
+                // which query blocks kept this key block?  (ascending id lists)
+                const int n_here = min(kListed, n_qb - qb0);
+                const int64_t first_row = (int64_t)head * n_qb + qb0;
+                __syncthreads();                                 // the previous list is no longer read
+                if (NT <= 8 && g.topk <= 32) {                   // all ids, eight loads of a thread in flight; longer rows: a search reads less
+                    for (int i = tid; i < n_here; i += kThreads) kept_by[i] = 0;
+                    __syncthreads();
+                    const int32_t *ids = sel_idx + first_row * g.topk;
+                    const int n_ids = n_here * g.topk;
+                    for (int at = tid; at < n_ids; at += 8 * kThreads) {
+                        int id[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) id[e] = at + e * kThreads < n_ids ? ids[at + e * kThreads] : -1;
+                        for (int e = 0; e < 8; ++e) id[e] = at + e * kThreads < n_ids ? ids[at + e * kThreads] : -1;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (id[e] == kb) {
-                            const int i = (at + e * kThreads) / g.topk;
-                            if (at + e * kThreads - i * g.topk < sel_cnt[first_row + i]) kept_by[i] = 1;
-                        }
-                }
-            } else {
-                for (int i = tid; i < n_here; i += kThreads) {
-                    const int32_t *sel = sel_idx + (first_row + i) * g.topk;
-                    const int c = min(max(sel_cnt[first_row + i], 0), g.topk);
-                    int lo = 0, hi = c;
-                    while (lo < hi) { const int mid = (lo + hi) >> 1; if (sel[mid] < kb) lo = mid + 1; else hi = mid; }
-                    kept_by[i] = lo < c && sel[lo] == kb;
-                }
-            }
-            __syncthreads();
-            if (wave == 0) {
-                int n = 0;
-                for (int i0 = 0; i0 < n_here; i0 += 64) {
-                    const bool kept = i0 + lane < n_here && kept_by[i0 + lane];
-                    const uint64_t mask = __ballot(kept);
-                    if (kept) {
-                        const int at = n + __popcll(mask & ((1ull << lane) - 1ull));
-                        const Located b = locate(g, qb0 + i0 + lane);
-                        list_origin[at] = b.origin;
-                        list_clip[at] = (unsigned char)b.clip;
+                        for (int e = 0; e < 8; ++e)
+                            if (id[e] == kb) {
+                                const int i = (at + e * kThreads) / g.topk;
+                                if (at + e * kThreads - i * g.topk < sel_cnt[first_row + i]) kept_by[i] = 1;
+                            }
                     }
-                    n += __popcll(mask);
+                } else {
+                    for (int i = tid; i < n_here; i += kThreads) {
+                        const int32_t *sel = sel_idx + (first_row + i) * g.topk;
+                        const int c = min(max(sel_cnt[first_row + i], 0), g.topk);
+                        int lo = 0, hi = c;
+                        while (lo < hi) { const int mid = (lo + hi) >> 1; if (sel[mid] < kb) lo = mid + 1; else hi = mid; }
+                        kept_by[i] = lo < c && sel[lo] == kb;
+                    }
                 }
-                if (lane == 0) n_listed = n;
-            }
-            __syncthreads();
-            const int total = __builtin_amdgcn_readfirstlane(n_listed) * per_block;          // 16-query groups
-            for (int f0 = ks; f0 < total; f0 += GI * splits) {
-                RowFrag<T, NT> qf[GI], gf[GI];
-                ColGroups<T, NT, GI> qc, gc;
-                float l2[GI][4], D[GI][4];
-                int valid[GI];
-                int origin[GI], own_at[GI], at[GI][4];       // first token, and rows m and 4 g4 + r from it
-                auto request_stats = [&]() {
+                __syncthreads();
+                if (wave == 0) {
+                    int n = 0;
+                    for (int i0 = 0; i0 < n_here; i0 += 64) {
+                        const bool kept = i0 + lane < n_here && kept_by[i0 + lane];
+                        const uint64_t mask = __ballot(kept);
+                        if (kept) {
+                            const int at = n + __popcll(mask & ((1ull << lane) - 1ull));
+                            const Located b = locate(g, qb0 + i0 + lane);
+                            list_origin[at] = b.origin;
+                            list_clip[at] = (unsigned char)b.clip;
+                        }
+                        n += __popcll(mask);
+                    }
+                    if (lane == 0) n_listed = n;
+                }
+                __syncthreads();
+                const int total = __builtin_amdgcn_readfirstlane(n_listed) * per_block;          // 16-query groups
+                for (int f0 = ks; f0 < total; f0 += GI * splits) {
+                    RowFrag<T, NT> qf[GI], gf[GI];
+                    ColGroups<T, NT, GI> qc, gc;
+                    float l2[GI][4], D[GI][4];
+                    int valid[GI];
+                    int origin[GI], own_at[GI], at[GI][4];       // first token, and rows m and 4 g4 + r from it
+                    auto request_stats = [&]() {
+#pragma unroll
+                        for (int i = 0; i < GI; ++i) {
+                            const float *lse_from = lse + (int64_t)origin[i] * g.heads + head, *d_from = delta + (int64_t)origin[i] * g.heads + head;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                l2[i][r] = lse_from[(int64_t)at[i][r] * g.heads] * kLog2e;
+                                D[i][r] = d_from[(int64_t)at[i][r] * g.heads];           // written by bwd_dq_kernel, earlier on the stream
+                            }
+                        }
+                    };
+                    auto request_columns = [&](ColGroups<T, NT, GI> &cols, const T *x, int64_t st) {
+#pragma unroll
+                        for (int i = 0; i < GI; ++i)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) cols.load_row(i, r, x + (int64_t)origin[i] * st + at[i][r] * st, g.d, m);
+                    };
 #pragma unroll
                     for (int i = 0; i < GI; ++i) {
-                        const float *lse_from = lse + (int64_t)origin[i] * g.heads + head, *d_from = delta + (int64_t)origin[i] * g.heads + head;
+                        const int f = min(f0 + i * splits, total - 1), b = by_block(f), first = (f - b * per_block) * 16;
+                        origin[i] = __builtin_amdgcn_readfirstlane(list_origin[b]);
+                        const int clip = __builtin_amdgcn_readfirstlane(list_clip[b]);
+                        const bool there = f0 + i * splits < total;
+                        auto request_rows = [&](const PieceRows &rows) {
+                            qf[i].load_row(q + (int64_t)origin[i] * q_st + rows.own * q_st, g.d, g4);
+                            own_at[i] = rows.own;
+                            if (NT <= 8) gf[i].load_row(d_o + (int64_t)origin[i] * o_st + rows.own * o_st, g.d, g4);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            l2[i][r] = lse_from[(int64_t)at[i][r] * g.heads] * kLog2e;
-                            D[i][r] = d_from[(int64_t)at[i][r] * g.heads];           // written by bwd_dq_kernel, earlier on the stream
+                            for (int r = 0; r < 4; ++r) at[i][r] = rows.col[r];
+                        };
+                        if (clip == 0 && simple) {               // uniform
+                            origin[i] += piece_distance(g, first);
+                            valid[i] = there ? g.bt - first : 0;
+                            request_rows(unclipped);
+                        } else {
+                            const BlockTokens qt = tokens_of(g, clip);
+                            valid[i] = there ? qt.n_valid - first : 0;
+                            request_rows(PieceRows(g, qt, first, m, g4));
                         }
                     }
-                };
-                auto request_columns = [&](ColGroups<T, NT, GI> &cols, const T *x, int64_t st) {
+                    constexpr bool COLUMNS = NT <= 2 || (NT <= 4 && WAVES == 2);         // registers for these beside the rows
+                    if (NT <= 8) request_stats();
+                    if (COLUMNS) { request_columns(gc, d_o, o_st); request_columns(qc, q, q_st); }
+                    f32x4 p[1][GI], u[1][GI];
 #pragma unroll
-                    for (int i = 0; i < GI; ++i)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) cols.load_row(i, r, x + (int64_t)origin[i] * st + at[i][r] * st, g.d, m);
-                };
-#pragma unroll
-                for (int i = 0; i < GI; ++i) {
-                    const int f = min(f0 + i * splits, total - 1), b = by_block(f), first = (f - b * per_block) * 16;
-                    origin[i] = __builtin_amdgcn_readfirstlane(list_origin[b]);
-                    const int clip = __builtin_amdgcn_readfirstlane(list_clip[b]);
-                    const bool there = f0 + i * splits < total;
-                    auto request_rows = [&](const PieceRows &rows) {
-                        qf[i].load_row(q + (int64_t)origin[i] * q_st + rows.own * q_st, g.d, g4);
-                        own_at[i] = rows.own;
-                        if (NT <= 8) gf[i].load_row(d_o + (int64_t)origin[i] * o_st + rows.own * o_st, g.d, g4);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) at[i][r] = rows.col[r];
-                    };
-                    if (clip == 0 && simple) {               // uniform
-                        origin[i] += piece_distance(g, first);
-                        valid[i] = there ? g.bt - first : 0;
-                        request_rows(unclipped);
-                    } else {
-                        const BlockTokens qt = tokens_of(g, clip);
-                        valid[i] = there ? qt.n_valid - first : 0;
-                        request_rows(PieceRows(g, qt, first, m, g4));
+                    for (int i = 0; i < GI; ++i) {
+                        qf[i].clear_beyond(g.d, g4);
+                        p[0][i] = RowFrag<T, NT>::mma(qf[i], kf, f32x4{0.f, 0.f, 0.f, 0.f});
+                        if (NT > 8) { __builtin_amdgcn_sched_barrier(0); gf[i].load_row(d_o + (int64_t)origin[i] * o_st + own_at[i] * o_st, g.d, g4); }
+                        gf[i].clear_beyond(g.d, g4);
+                        u[0][i] = RowFrag<T, NT>::mma(gf[i], vf, f32x4{0.f, 0.f, 0.f, 0.f});
                     }
-                }
-                constexpr bool COLUMNS = NT <= 2 || (NT <= 4 && WAVES == 2);         // registers for these beside the rows
-                if (NT <= 8) request_stats();
-                if (COLUMNS) { request_columns(gc, d_o, o_st); request_columns(qc, q, q_st); }
-                f32x4 p[1][GI], u[1][GI];
+                    if (NT > 8) { __builtin_amdgcn_sched_barrier(0); request_stats(); }
 #pragma unroll
-                for (int i = 0; i < GI; ++i) {
-                    qf[i].clear_beyond(g.d, g4);
-                    p[0][i] = RowFrag<T, NT>::mma(qf[i], kf, f32x4{0.f, 0.f, 0.f, 0.f});
-                    if (NT > 8) { __builtin_amdgcn_sched_barrier(0); gf[i].load_row(d_o + (int64_t)origin[i] * o_st + own_at[i] * o_st, g.d, g4); }
-                    gf[i].clear_beyond(g.d, g4);
-                    u[0][i] = RowFrag<T, NT>::mma(gf[i], vf, f32x4{0.f, 0.f, 0.f, 0.f});
-                }
-                if (NT > 8) { __builtin_amdgcn_sched_barrier(0); request_stats(); }
+                    for (int i = 0; i < GI; ++i) {
 #pragma unroll
-                for (int i = 0; i < GI; ++i) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const bool ok = 4 * g4 + r < valid[i];               // padding queries: probability zero
-                        p[0][i][r] = ok ? __builtin_amdgcn_exp2f(fmaf(p[0][i][r], scale_log2, -l2[i][r])) : 0.f;
-                        u[0][i][r] = ok ? p[0][i][r] * ((u[0][i][r] - D[i][r]) * scale) : 0.f;
+                        for (int r = 0; r < 4; ++r) {
+                            const bool ok = 4 * g4 + r < valid[i];               // padding queries: probability zero
+                            p[0][i][r] = ok ? __builtin_amdgcn_exp2f(fmaf(p[0][i][r], scale_log2, -l2[i][r])) : 0.f;
+                            u[0][i][r] = ok ? p[0][i][r] * ((u[0][i][r] - D[i][r]) * scale) : 0.f;
+                        }
                     }
+                    if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(gc, d_o, o_st); }
+#pragma unroll
+                    for (int i = 0; i < GI; ++i) gc.keep(i, valid[i], g4);
+                    gc.template mma<1, in_float>(p, dv);
+                    if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(qc, q, q_st); }
+#pragma unroll
+                    for (int i = 0; i < GI; ++i) qc.keep(i, valid[i], g4);
+                    qc.template mma<1, in_float>(u, dk);
                 }
-                if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(gc, d_o, o_st); }
-#pragma unroll
-                for (int i = 0; i < GI; ++i) gc.keep(i, valid[i], g4);
-                gc.template mma<1>(p, dv);
-                if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(qc, q, q_st); }
-#pragma unroll
-                for (int i = 0; i < GI; ++i) qc.keep(i, valid[i], g4);
-                qc.template mma<1>(u, dk);
             }
+        };
+        walk(std::bool_constant<!PIECES>{});
+        if constexpr (PIECES) {                              // once more in float products alone where a wavefront's sums of pieces are doubtful
+            if (Cols::doubtful(dk[0]) || Cols::doubtful(dv[0])) again = base;
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(again) == base) walk(std::true_type{});       // set anew only behind the next barriers
         }
         if (splits > 1) {                                    // uniform over the workgroup
 #pragma unroll

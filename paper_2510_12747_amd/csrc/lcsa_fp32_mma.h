@@ -108,6 +108,8 @@ template <int NT> struct RowFrag<__bf16, NT> {
 //             from d on are what follows the row: they only reach channels of the result that are not stored)
 //   load_row  the same from a row of d channels anywhere
 //   keep      only the first n rows of group i have a weight; the others become zeros, whatever was read
+//   mma       weights between 0 and 1, or NaN; sums of others have to be looked at when they are complete, and made again in
+//             mma<QS, true> where they are doubtful()
 template <typename T, int NT, int GI> struct ColGroups;
 template <int NT, int GI> struct ColGroups<float, NT, GI> {
     f32x2 v[GI][4][NT / 2];                                  // [group][row 4 g + r][p]: channels 32 p + 2 m, + 1
@@ -128,7 +130,8 @@ template <int NT, int GI> struct ColGroups<float, NT, GI> {
             for (int p = 0; p < NT / 2; ++p)
                 if (4 * g + r >= n) v[i][r][p] = f32x2{0.f, 0.f};
     }
-    template <int QS> __device__ void mma(const f32x4 (&w)[QS][GI], f32x4 (&acc)[QS][NT]) const {
+    __device__ static bool doubtful(const f32x4 (&)[NT]) { return false; }
+    template <int QS, bool FLOAT = true> __device__ void mma(const f32x4 (&w)[QS][GI], f32x4 (&acc)[QS][NT]) const {
 #pragma unroll
         for (int i = 0; i < GI; ++i)
 #pragma unroll
@@ -143,7 +146,12 @@ template <int NT, int GI> struct ColGroups<float, NT, GI> {
 // bf16 rows: a float weight is the sum of three bf16 values (8 bits of its 24 each, every remainder exact), and the products
 // of bf16 values are exact in v_mfma_f32_16x16x32_bf16, which takes two groups at a time: three instructions of 16 cycles in
 // place of eight of 32, and fewer roundings of the accumulator.  Zero and negative pieces of a weight must not meet an infinity:
-// infinities and NaN go through the float products by themselves, which leaves the bits of all other channels alone.
+// infinities and NaN go through the float products by themselves, which leaves the bits of all other channels alone.  So do values from
+// 2^16 on, because the last pieces of weights below 2^-110 fall among bf16's subnormals, which count for nothing: 2^-126 of a value is lost.
+// Weights that may be anything: an infinite one leaves inf - inf behind its first piece, one close to the largest float rounds to an infinity,
+// and tiny ones may all lose their last pieces.  The sums tell (doubtful()): they are infinite or NaN, or a lane's are all below 2^-76, where
+// the 2^13 terms' losses are no longer below 2^-20 of them.  In the backward that costs 0 to 2 % (8 heads, d = 64, 32-token blocks, k = 16 on a
+// 24 x 44 grid 108.3 / 109.9 us); looking at the weights instead, group by group, or one loop for both kinds of product, 1 to 8 %.
 template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
     static_assert(GI % 2 == 0, "groups go in pairs");
     uint32_t v[GI][4][NT / 2];
@@ -164,7 +172,8 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
             for (int p = 0; p < NT / 2; ++p)
                 if (4 * g + r >= n) v[i][r][p] = 0;
     }
-    __device__ bool finite() const {                         // wavefront-uniform
+    static constexpr uint32_t kLarge = 0x4780;               // bf16 of 2^16
+    __device__ bool large() const {                          // wavefront-uniform
         typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
         u16x2 most = {0, 0};
 #pragma unroll
@@ -174,7 +183,15 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
 #pragma unroll
                 for (int p = 0; p < NT / 2; ++p)
                     most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, v[i][r][p] & 0x7fff7fffu));
-        return __ballot(most[0] >= 0x7f80 || most[1] >= 0x7f80) == 0;
+        return __ballot(most[0] >= kLarge || most[1] >= kLarge) != 0;
+    }
+    __device__ static bool doubtful(const f32x4 (&acc)[NT]) {      // wavefront-uniform
+        uint32_t most = 0;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) most = max(most, __float_as_uint(acc[t][r]) & 0x7fffffffu);
+        return __ballot(most >= 0x7f800000u || (most != 0 && most < 0x19800000u)) != 0;
     }
     // the two weights of a word as bf16, and what they leave
     __device__ static uint32_t piece(float &a, float &b) {
@@ -184,8 +201,8 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
         b -= __uint_as_float(w & 0xffff0000u);
         return w;
     }
-    template <int QS> __device__ void mma(const f32x4 (&w)[QS][GI], f32x4 (&acc)[QS][NT]) {
-        if (!finite())                                       // these by themselves, and zeros in their place below
+    template <int QS, bool FLOAT = false> __device__ void mma(const f32x4 (&w)[QS][GI], f32x4 (&acc)[QS][NT]) {
+        if (FLOAT || large())                                // these by themselves, and zeros in their place below
 #pragma unroll
             for (int i = 0; i < GI; ++i)
 #pragma unroll
@@ -194,12 +211,13 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
                     for (int t = 0; t < NT; ++t) {
                         uint32_t &u = v[i][r][t >> 1];
                         const uint32_t half = t & 1 ? u & 0xffff0000u : u << 16;
-                        const bool odd = (half & 0x7f800000u) == 0x7f800000u;
+                        const bool odd = FLOAT || (half & 0x7fffffffu) >= kLarge << 16;
                         if (odd) u &= t & 1 ? 0xffffu : 0xffff0000u;
 #pragma unroll
                         for (int s = 0; s < QS; ++s)
                             acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? __uint_as_float(half) : 0.f, w[s][i][r], acc[s][t], 0, 0, 0);
                     }
+        if constexpr (FLOAT) return;
 #pragma unroll
         for (int i = 0; i < GI; i += 2) {
             bf16x8 pieces[QS][3];                            // largest first
@@ -253,7 +271,8 @@ template <int NT> struct ColGroups<__bf16, NT, 1> {
             for (int p = 0; p < NT / 2; ++p)
                 if (4 * g + r >= n) v[r][p] = 0;
     }
-    template <int QS> __device__ void mma(const f32x4 (&w)[QS][1], f32x4 (&acc)[QS][NT]) const {
+    __device__ static bool doubtful(const f32x4 (&)[NT]) { return false; }
+    template <int QS, bool FLOAT = true> __device__ void mma(const f32x4 (&w)[QS][1], f32x4 (&acc)[QS][NT]) const {
 #pragma unroll
         for (int s = 0; s < QS; ++s)
 #pragma unroll
