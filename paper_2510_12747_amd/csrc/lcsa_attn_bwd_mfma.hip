@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     k += (int64_t)head * kv_sh;
     v += (int64_t)head * kv_sh;
     // Formed once: divisions and products anew for every clipped block were a quarter of its step, 900 cycles.  Backward of 3 heads on
-    // 21 x 37 tokens in (1, 8, 16) blocks, 16 kept: 84.5 -> 78.0 us, and 75.8 with the units that hold no key left out; 16 heads on
+    // 21 x 37 tokens in (1, 8, 16) blocks, 16 kept: 84.5 -> 78.0 us, and 75.8 with a wavefront's first unit left out where it holds no key; 16 heads on
     // 21 x 45 142 -> 139, whole blocks within 0.3 % (one more barrier).
     for (int i = tid; i < 512; i += 64 * QG * KH) row_at[i >> 7][i & 127] = row_offset(g, tokens_of_extent(g, i >> 7), i & 127, kv_st);
     // this lane's rows of a whole block's step, and where they stand in row_at; its chunk of each
@@ -370,8 +370,8 @@ __global__ __launch_bounds__(64 * QG * KH, 2) void bwd_dq_mfma_kernel(
     const int rows = row_base(lane), columns = column_base(lane);
     int n_located = cnt > 0 ? locate_next() : 0;
 
-    // Lane = query ql; register 8 kk + j = key 16 kk + 8 half + j of a 32-key unit.  Of every step the wavefront takes units kh,
-    // kh + KH, .., the later ones only if there are that many keys.  Keys beyond the valid ones must get probability zero.
+    // Lane = query ql; register 8 kk + j = key 16 kk + 8 half + j of a 32-key unit.  Of every step the wavefront takes unit kh if
+    // that holds a key, and kh + KH if the first of the later units does.  Keys beyond the valid ones must get probability zero.
     auto mask_keys = [&](f32x16 &s, int left) {
         if (left < 32) {                                     // uniform
 #pragma unroll

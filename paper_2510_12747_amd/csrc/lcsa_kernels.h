@@ -79,15 +79,7 @@ __device__ inline int cache_slot(const KCache &c, const KGeom &g, int start, int
 // Block token i -> (frame within the group, row, col inside the tile) of a tile clipped to vh x vw.
 // The valid tokens of a block come first, in (frame, row, col) order over the clipped extent;
 // positions tt*vh*vw .. bt-1 are padding (false is returned for them).
-__host__ __device__ inline bool block_token(const KGeom &g, int i, int vh, int vw, int &ft, int &r, int &c) {
-    const int per_frame = vh * vw;
-    ft = i / per_frame;
-    const int rem = i - ft * per_frame;
-    r = rem / vw;
-    c = rem - r * vw;
-    return i < g.tt * per_frame;
-}
-// block_token for the tokens of one block: the two divisions become multiplications by reciprocals, which the host prepares for the
+// The two divisions are multiplications by reciprocals, which the host prepares for the
 // four extents that blocks have.  q = (i * ceil(2^32 / d)) >> 32 equals i / d for i < 65536 and 2 <= d <= 32768 (a block has at most
 // 1024 tokens); d = 1 is passed through.
 struct BlockTokens {
