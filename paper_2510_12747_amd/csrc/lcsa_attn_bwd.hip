@@ -355,9 +355,14 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
         kf.clear_beyond(g.d, g4);
         vf.clear_beyond(g.d, g4);
         f32x4 dk[1][NT], dv[1][NT];
+        bool sum_k = true, sum_v = true;                     // uniform over the wavefront; false for a sum that a second walk leaves alone
         auto walk = [&](auto in_float) {
+            constexpr bool SECOND = PIECES && in_float;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) dk[0][t] = dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < NT; ++t) {
+                if (!SECOND || sum_k) dk[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (!SECOND || sum_v) dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
             for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
                 // which query blocks kept this key block?  (ascending id lists)
                 const int n_here = min(kListed, n_qb - qb0);
@@ -477,17 +482,19 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
                     if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(gc, d_o, o_st); }
 #pragma unroll
                     for (int i = 0; i < GI; ++i) gc.keep(i, valid[i], g4);
-                    gc.template mma<1, in_float>(p, dv);
+                    if (!SECOND || sum_v) gc.template mma<1, in_float>(p, dv);
                     if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(qc, q, q_st); }
 #pragma unroll
                     for (int i = 0; i < GI; ++i) qc.keep(i, valid[i], g4);
-                    qc.template mma<1, in_float>(u, dk);
+                    if (!SECOND || sum_k) qc.template mma<1, in_float>(u, dk);
                 }
             }
         };
         walk(std::bool_constant<!PIECES>{});
         if constexpr (PIECES) {                              // once more in float products alone where a wavefront's sums of pieces are doubtful
-            if (Cols::doubtful(dk[0]) || Cols::doubtful(dv[0])) again = base;
+            sum_k = Cols::doubtful(dk[0]);
+            sum_v = Cols::doubtful(dv[0]);
+            if (sum_k || sum_v) again = base;
             __syncthreads();
             if (__builtin_amdgcn_readfirstlane(again) == base) walk(std::true_type{});       // set anew only behind the next barriers
         }

@@ -149,8 +149,8 @@ template <int NT, int GI> struct ColGroups<float, NT, GI> {
 // infinities and NaN go through the float products by themselves, which leaves the bits of all other channels alone.  So do values from
 // 2^16 on, because the last pieces of weights below 2^-110 fall among bf16's subnormals, which count for nothing: 2^-126 of a value is lost.
 // Weights that may be anything: an infinite one leaves inf - inf behind its first piece, one close to the largest float rounds to an infinity,
-// and tiny ones may all lose their last pieces.  The sums tell (doubtful()): they are infinite or NaN, or a lane's are all below 2^-76, where
-// the 2^13 terms' losses are no longer below 2^-20 of them.  In the backward that costs 0 to 2 % (8 heads, d = 64, 32-token blocks, k = 16 on a
+// and tiny ones may all lose their last pieces.  The sums tell (doubtful()): all channels of a column are infinite or NaN, or all are below
+// 2^-76, where the 2^13 terms' losses are no longer below 2^-20 of them.  In the backward that costs 0 to 2 % (8 heads, d = 64, 32-token blocks, k = 16 on a
 // 24 x 44 grid 108.3 / 109.9 us); looking at the weights instead, group by group, or one loop for both kinds of product, 1 to 8 %.
 template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
     static_assert(GI % 2 == 0, "groups go in pairs");
@@ -186,12 +186,19 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
         return __ballot(most[0] >= kLarge || most[1] >= kLarge) != 0;
     }
     __device__ static bool doubtful(const f32x4 (&acc)[NT]) {      // wavefront-uniform
-        uint32_t most = 0;
+        uint32_t most = 0, least = 0x7fffffffu;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) most = max(most, __float_as_uint(acc[t][r]) & 0x7fffffffu);
-        return __ballot(most >= 0x7f800000u || (most != 0 && most < 0x19800000u)) != 0;
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t bits = __float_as_uint(acc[t][r]) & 0x7fffffffu;
+                most = max(most, bits);
+                least = min(least, bits);
+            }
+        // a column's channels lie in lanes m, m + 16, m + 32, m + 48
+        auto all_four = [](uint64_t lanes) { lanes &= lanes >> 32; return lanes & lanes >> 16 & 0xffffu; };
+        return all_four(__ballot(least >= 0x7f800000u)) != 0 ||
+               (all_four(__ballot(most < 0x19800000u)) & ~all_four(__ballot(most == 0))) != 0;
     }
     // the two weights of a word as bf16, and what they leave
     __device__ static uint32_t piece(float &a, float &b) {

@@ -54,6 +54,9 @@ def test_appends_of_192_tiles_and_more(dtype, heads, grid):
     (1, 64, (16, 24), (2, 8), 80),       # more than 64 ids, pieces that are whole rows of unclipped tiles
     (2, 64, (17, 23), (5, 7), 11),       # 35 tokens: pieces that are not, every extent
     (1, 96, (16, 24), (4, 8), 33),       # key side: ids searched, not listed
+    (1, 136, (10, 20), (4, 9), 7),       # beyond 128 channels, where rows and columns are loaded in turn: 36 tokens, three pieces
+    (2, 200, (9, 17), (4, 8), 5),        # two, all four extents
+    (1, 256, (8, 24), (8, 8), 6),        # four, all channels
 ])
 def test_backward_rows_and_pieces(dtype, heads, d, grid, tile, topk):
     w = wl.with_overrides(wl.WORKLOADS["tiny"], name=f"bwd-{dtype}-{d}-{topk}", dtype=dtype, heads=heads, head_dim=d, grid_h=grid[0], grid_w=grid[1],
@@ -133,3 +136,48 @@ def test_forward_small_weights_of_large_values(d, tile):
     want = (p @ v.double().permute(1, 0, 2).contiguous()).permute(1, 0, 2)
     half_unit = 2.0 ** (want.abs().log2().floor() - 8)       # of bf16; and the exponent's float rounding, 124 x 2^-24 with that of the scale
     assert ((o - want).abs() <= half_unit + 2e-5 * want.abs()).all(), float(((o - want).abs() / half_unit).max())
+
+
+@pytest.mark.parametrize("d,tile", [(32, (2, 8)), (64, (4, 8)), (96, (5, 7))])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_values_that_are_not_finite(d, tile, value):
+    """One of them in an even or an odd channel (either half of a word) of V, dO, K or Q of bf16 tensors: what the float kernels make of
+    the same numbers, and where it is V's or dO's, no other channel of o or d_v changes."""
+    n = 2 * 2 * tile[0] * 2 * tile[1]
+    normal = [torch.randn(n, 1, d, generator=torch.Generator().manual_seed(20 + s)).bfloat16().float() for s in range(4)]
+    plain = backward_in(torch.bfloat16, d, tile, *normal)
+    for which in (2, 3, 1, 0):                               # of q, k, v, d_o
+        for channel in (6, 9):
+            inputs = [x.clone() for x in normal]
+            inputs[which][17, 0, channel] = value
+            got, want = (backward_in(dtype, d, tile, *inputs) for dtype in (torch.bfloat16, torch.float32))
+            assert not all(x.isfinite().all() for x in want)
+            same(got, want, 2e-6)
+            if which == 3:
+                others = [c for c in range(d) if c != channel]
+                assert torch.equal(got[2][..., others], plain[2][..., others]) and not got[2][..., channel].isfinite().any()
+
+
+@pytest.mark.parametrize("d,tile", [(32, (4, 4)), (64, (4, 8)), (96, (5, 7)), (128, (8, 8))])
+def test_forward_values_that_are_not_finite(d, tile):
+    n = 2 * 2 * tile[0] * 2 * tile[1]
+    g = B.Geom(1, d, 2 * tile[0], 2 * tile[1], *tile, 2, 2, -1, -1, 8)
+    q, k, v = (torch.randn(n, 1, d, generator=torch.Generator().manual_seed(30 + s)).to("cuda", torch.bfloat16) for s in range(3))
+
+    def forward(v):
+        cache = B.lcsa_cache_init(g)
+        B.lcsa_kv_cache_append(cache, k, v, 2)
+        _, sel_idx, sel_cnt, _ = B.lcsa_pool_select_blocks(g, q, cache)
+        assert (sel_cnt == 8).all()
+        return B.lcsa_sparse_attn_fwd(g, q, cache, sel_idx, sel_cnt)
+
+    plain, planted = forward(v), v.clone()
+    values = {6: float("inf"), 9: float("inf"), 10: float("-inf"), 13: float("-inf"), 16: float("nan"), 21: float("nan")}
+    for i, (channel, value) in enumerate(values.items()):
+        planted[5 + 7 * i, 0, channel] = value
+    planted[3, 0, 24], planted[50, 0, 24] = float("inf"), float("-inf")      # of both signs: NaN
+    got = forward(planted)
+    for channel, value in {**values, 24: float("nan")}.items():
+        assert (got[..., channel].isnan() if value != value else got[..., channel] == value).all(), channel
+    others = [c for c in range(d) if c not in values and c != 24]
+    assert torch.equal(got[..., others], plain[..., others])
