@@ -166,6 +166,49 @@ def test_outputs_are_allocated_without_the_interpreter_lock(on_cpu):
             assert f(*a, 7) is None and calls.value == 1 and fail.value == 0
 
 
+def test_what_it_takes_reaches_the_library(on_cpu):
+    _, native, library = on_cpu
+    calls, status, seen = (t.in_dll(library, n) for t, n in ((ctypes.c_int, "calls"), (ctypes.c_int, "status"), (ctypes.c_int64 * 12, "seen")))
+    head_major = lambda x: x.transpose(0, 1).contiguous().transpose(0, 1)
+    g = B.Geom(*GEOM)
+    plan, at = g._plan(), g._plan()[0]
+    i, n = torch.zeros(2, 8, 4, dtype=torch.int32), torch.zeros(2, 8, dtype=torch.int32)
+    for x in (torch.zeros(96, 2, 32), head_major(torch.zeros(96, 2, 32)), torch.zeros(96, 4, 64)[:, ::2, :32], torch.nn.Parameter(torch.zeros(96, 2, 32))):
+        y = x.detach().clone(memory_format=torch.preserve_format) if x.is_contiguous() else x
+        st, sh = x.stride()[:2]
+        assert native.append(plan, 5, x, y, 2, 7) == 0 and list(seen[:7]) == [5, x.data_ptr(), y.data_ptr(), st, sh, 2, 7]
+        for want_gap in (True, False):
+            pooled, idx, cnt, gap = native.pool_select(plan, x, 5, want_gap, 7)
+            assert (gap is not None) == want_gap
+            assert list(seen[:10]) == [at, x.data_ptr(), st, sh, 5, pooled.data_ptr(), idx.data_ptr(), cnt.data_ptr(), gap.data_ptr() if want_gap else 0, 7]
+            assert [(tuple(t.shape), t.dtype) for t in (pooled, idx, cnt)] == [((2, 8, 32), torch.float32), ((2, 8, 4), torch.int32), ((2, 8), torch.int32)]
+            assert not want_gap or (tuple(gap.shape), gap.dtype) == ((2, 8), torch.float32)
+        for o, lse in ((None, None), (torch.zeros(96, 2, 32), torch.zeros(96, 2)), (head_major(torch.zeros(96, 2, 32)), None)):
+            got = native.forward(plan, x, 5, i, n, o, lse, 0.0, 7)
+            assert got is o or (o is None and tuple(got.shape) == (96, 2, 32) and got.is_contiguous())
+            assert list(seen) == [at, x.data_ptr(), st, sh, 5, i.data_ptr(), n.data_ptr(), got.data_ptr(), *got.stride()[:2], lse.data_ptr() if lse is not None else 0, 7]
+    x = torch.zeros(96, 2, 32)
+    status.value = -2
+    assert native.append(plan, 5, x, x, 2, 7) == native.pool_select(plan, x, 5, True, 7) == native.forward(plan, x, 5, i, n, None, None, 0.0, 7) == -2
+    status.value = calls.value = 0
+    # what it leaves to the Python functions: each by itself, everything else being in order
+    wrong = [x[:-1], x[:, :1], x[..., :16], x.double(), x.bfloat16(), x[..., ::2], x.reshape(-1), x.to_sparse(), torch.zeros(96, 32, 2).transpose(1, 2),
+             x.as_subclass(type("Sub", (torch.Tensor,), {}))]
+    for bad in wrong:
+        assert native.append(plan, 5, bad, x, 2, 7) is native.append(plan, 5, x, bad, 2, 7) is native.pool_select(plan, bad, 5, True, 7) is None
+        assert native.forward(plan, bad, 5, i, n, None, None, 0.0, 7) is native.forward(plan, x, 5, i, n, bad, None, 0.0, 7) is None
+    assert native.append(plan, 5, x, head_major(x), 2, 7) is native.append(plan, 5, x, x, 1, 7) is native.append(plan, 5, x, x, True, 7) is None
+    assert native.pool_select(plan, x, 5, 1, 7) is native.pool_select(plan, x, None, True, 7) is native.pool_select(plan, x, 5, True, None) is None
+    for bad_i, bad_n in ((i.long(), n), (i[:, :, :3], n), (i[:1], n), (i, n.long()), (i, torch.zeros(2, 16, dtype=torch.int32)[:, ::2])):
+        assert native.forward(plan, x, 5, bad_i, bad_n, None, None, 0.0, 7) is None
+    for bad in (torch.zeros(2, 96), torch.zeros(96, 2, dtype=torch.float64), torch.zeros(192), torch.zeros(96, 4)[:, ::2]):
+        assert native.forward(plan, x, 5, i, n, None, bad, 0.0, 7) is None
+    assert native.forward(plan, x, 5, i, n, None, None, 0, 7) is None
+    for bad in (plan[:7], (*plan, 0), list(plan), (1 << 70,) * 8, (None,) * 8, None):
+        assert native.append(bad, 5, x, x, 2, 7) is native.pool_select(bad, x, 5, True, 7) is native.forward(bad, x, 5, i, n, None, None, 0.0, 7) is None
+    assert calls.value == 0
+
+
 def test_it_takes_only_plain_device_tensors():
     B.lib()
     g = B.Geom(1, 32, 6, 8, 4, 4, 2, 4, 4, 4, 4, dtype=B.LCSA_F32)
@@ -258,8 +301,19 @@ def test_results_and_errors_are_those_of_the_python_functions(monkeypatch, dtype
 
     forms = [((q, k, v), {}), ((head_major(q), head_major(k), head_major(v)), dict(lse=True)), ((q, head_major(k), head_major(v)), dict(o=True, want_gap=False)),
              ((torch.nn.Parameter(q, requires_grad=False), k, v), dict(scale=0.3)), ((q.as_subclass(Sub), k, v), dict(scale=1))]
+    assert B._marshal is not B._InPython
+    answers = []
+    note = types.SimpleNamespace(**{f: (lambda *a, f=f, real=getattr(B._marshal, f): answers.append((f, real(*a))) or answers[-1][1])
+                                    for f in ("append", "pool_select", "forward")})
     for (a, b, c), kw in forms:
-        native = steps(a, b, c, **kw)
+        answers.clear()
+        with monkeypatch.context() as m:
+            m.setattr(B, "_marshal", note)
+            native = steps(a, b, c, **kw)
+        # k and v are plain in every form; the last form's q is not, and its scale no float
+        assert [f for f, _ in answers] == ["append", "append", "pool_select", "forward"]
+        taken = not isinstance(a, Sub)
+        assert [x is not None for _, x in answers] == [True, True, taken, taken]
         with monkeypatch.context() as m:
             m.setattr(B, "_marshal", NOTHING)
             python = steps(a, b, c, **kw)
