@@ -227,7 +227,9 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
 // blocks, 7 groups: 8.37 / 8.16).  Not where there are more workgroups than fit at four groups' registers (`resident` a unit: 1344 rows
 // of 7 groups, d = 64, 42.3 / 46.3; 384 rows of 64-token blocks, 40 groups, 100.6 / 135.3), not where the last stretch of four would be half
 // empty (10 groups 9.43 / 10.4), and not for the four groups of a short row, where it is the second request ahead of the first products
-// that helps (264 rows of 4: 7.72 / 8.41).  Between them, at d = 64 (7 groups, 60 rows), four cost up to a tenth: 17.3 / 19.3.
+// that helps (264 rows of 4: 7.72 / 8.41).  Over 300 random geometries (in profiles/) the rule is 1.005 of the better form at d <= 32 (two 1.017,
+// four 1.066).  At 32 < d <= 64 it is 1.008 where two alone would be 1.001: what four still take there are rows of 128-token blocks (up to
+// 0.97), and rows of 7 groups in 32-token blocks for up to 1.07 of the time (60 rows, d = 64: 17.3 / 19.3).
 bool two_groups(const KGeom &g, const KCache &c, int rows_per_wave, int resident) {
     const int admissible = max_candidates(g, c.valid), k = g.topk < admissible ? g.topk : admissible;
     const int per_wave = (k * ((g.bt + 15) >> 4) + 4 / row_ways(g.bt, rows_per_wave) - 1) / (4 / row_ways(g.bt, rows_per_wave));
