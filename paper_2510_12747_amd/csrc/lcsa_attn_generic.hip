@@ -172,6 +172,7 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
             }
 #pragma unroll
             for (int i = 0; i < GI; ++i) vf.keep(i, rows[i], g4);
+            vf.clear_beyond(g.d, m);
             vf.mma(sc, oacc);
         }
 #pragma unroll

@@ -118,6 +118,7 @@ template <int NT, int GI> struct ColGroups<float, NT, GI> {
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const f32x2 *)(at + offset + 128 * p);
     }
+    __device__ void clear_beyond(int, int) {}
     __device__ void load_row(int i, int r, const float *row, int d, int m) {
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) v[i][r][p] = *(const f32x2 *)(row + min(32 * p + 2 * m, d - 2));
@@ -171,6 +172,21 @@ template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
 #pragma unroll
             for (int p = 0; p < NT / 2; ++p)
                 if (4 * g + r >= n) v[i][r][p] = 0;
+    }
+    // After load_at(): zeros in the channels from d on.  What follows the last row of all, means in float, would look like large values:
+    // d = 200, 400 rows of 16-token blocks, k = 4, 20 us for 16.5, the one workgroup's time that meets them.
+    __device__ void clear_beyond(int d, int m) {
+        if (d == 16 * NT) return;
+        constexpr int first = NT == 16 ? 4 : NT / 2 - 1;     // LCSA_FOR_HEAD_DIM: all channels of the words before it exist
+#pragma unroll
+        for (int p = first; p < NT / 2; ++p) {
+            const bool beyond = 32 * p + 2 * m >= d;
+#pragma unroll
+            for (int i = 0; i < GI; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (beyond) v[i][r][p] = 0;
+        }
     }
     static constexpr uint32_t kLarge = 0x4780;               // bf16 of 2^16
     __device__ bool large() const {                          // wavefront-uniform
