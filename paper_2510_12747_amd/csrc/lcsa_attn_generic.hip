@@ -9,12 +9,11 @@
 //
 // What bounds it: latency.  A row is a chain of ids -> keys -> scores -> values, and a wavefront of a short row goes through
 // it once or twice, so the kernel spends what it can on having loads in flight: ids are turned into tile addresses 64 at a time,
-// one per lane, before the walk, the keys of the next stretch are requested as soon as the scores of this one are formed, and
-// bf16 weights go through bf16 products (ColGroups), which leaves registers for three wavefronts a SIMD.  8 heads, d = 64, bf16,
-// 32-token blocks, k = 16 on a 24 x 44 grid (576 workgroups): 32.1 -> 17.1 us; of the 15 us saved, 10.5 are the prepared addresses,
-// early keys and bf16 products (21.6 us, 576 workgroups on 512 places), 4.4 the third wavefront (two groups a stretch instead of
-// four).  36 rows of 20 64-token blocks, float, d = 32 49.7 -> 34.8, d = 64 78.4 -> 57.6 us; rows of one stretch are where they were
-// (60 rows of 4 groups, d = 64: 8.6 -> 8.9).
+// one per lane, before the walk, the keys of the next stretch are requested as soon as the scores of this one are formed where that
+// pays (launch()), and bf16 weights go through bf16 products (ColGroups), which leaves registers for three wavefronts a SIMD.  8 heads,
+// d = 64, bf16, 32-token blocks, k = 16 on a 24 x 44 grid (576 workgroups): 32.1 -> 16.2 us.  36 rows of 20 64-token blocks, float, d = 32
+// 49.7 -> 34.8, d = 64 78.4 -> 57.6 us; rows of one stretch, d = 64: 60 of 4 groups, 32-token blocks, 8.3 -> 8.1,
+// 560 of 7 groups, 16-token blocks, 10.7 -> 10.0.
 #include "lcsa_fp32_mma.h"
 #include <type_traits>
 
@@ -28,7 +27,8 @@ constexpr int kThreads = 256;
 // Wavefronts a SIMD, where the operands of GI groups leave room for more than one.
 template <typename T, int NT, int QS, int GI> constexpr int kWaves = sizeof(T) == 2 ? (NT * QS <= 12 ? 2 : 1) : (NT * QS == 2 ? 4 : NT < 16 && NT * QS * GI <= 16 ? 2 : 1);
 
-template <typename T, int NT, int QS, int GI>
+// AHEAD: the keys of the next stretch are requested before the weights of this one are formed, else when their turn comes.
+template <typename T, int NT, int QS, int GI, bool AHEAD>
 __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generic_kernel(
     KGeom g, KCache c, const T *__restrict__ q, int64_t q_st, int64_t q_sh,
     const int32_t *__restrict__ sel_idx, const int32_t *__restrict__ sel_cnt,
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
 
     // more than one round only where four wavefronts do not cover the block, and then splits == 1
     for (int q0 = qw * 16 * QS; q0 < qt.n_valid || splits > 1; q0 += ways * 16 * QS) {
-        // Groups i0 .. i0 + GI - 1: their values are requested when their keys arrive, the keys of the next ones as soon as
-        // the products with the present ones are issued.
+        // Groups i0 .. i0 + GI - 1: values requested beside their keys, or, AHEAD, when these arrive, and then the keys of the next ones as
+        // soon as the products with the present ones are issued.
         RowFrag<T, NT> kf[GI];
         ColGroups<T, NT, GI> vf;
         int64_t at[GI];                                      // of the group's first row in the head's tiles
@@ -98,8 +98,6 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
         };
         if (chunk != 0) { chunk = 0; take_chunk(sel[min(lane, g.topk - 1)]); }      // left by a round before this one
         int i0 = ks * GI;
-        // four groups of float keys at d <= 32 and one set of queries: without the second set of operands four wavefronts fit a SIMD
-        constexpr bool AHEAD = !(sizeof(T) == 4 && GI == 4 && NT == 2 && QS == 1);
         if (AHEAD && i0 < total) request_keys(i0);
 
         RowFrag<T, NT> qf[QS];
@@ -223,17 +221,20 @@ __global__ __launch_bounds__(kThreads, (kWaves<T, NT, QS, GI>)) void attn_generi
     }
 }
 
+// 16-key groups of a full row that a wavefront of rows_per_wave queries walks
+int groups_per_wave(const KGeom &g, const KCache &c, int rows_per_wave) {
+    const int admissible = max_candidates(g, c.valid), k = g.topk < admissible ? g.topk : admissible, splits = 4 / row_ways(g.bt, rows_per_wave);
+    return (k * ((g.bt + 15) >> 4) + splits - 1) / splits;
+}
+
 // Whether float rows are walked two groups at a time instead of four.  Four pay where few, long rows at d <= 32 leave a wavefront alone
-// with its loads (two / four, 36 rows of 64-token blocks, 7 to 40 groups a wavefront: 11.2 / 11.0 to 37.8 / 34.8 us; 110 rows of 16-token
-// blocks, 7 groups: 8.37 / 8.16).  Not where there are more workgroups than fit at four groups' registers (`resident` a unit: 1344 rows
-// of 7 groups, d = 64, 42.3 / 46.3; 384 rows of 64-token blocks, 40 groups, 100.6 / 135.3), not where the last stretch of four would be half
-// empty (10 groups 9.43 / 10.4), and not for the four groups of a short row, where it is the second request ahead of the first products
-// that helps (264 rows of 4: 7.72 / 8.41).  Over 300 random geometries (in profiles/) the rule is 1.005 of the better form at d <= 32 (two 1.017,
-// four 1.066).  At 32 < d <= 64 it is 1.008 where two alone would be 1.001: what four still take there are rows of 128-token blocks (up to
-// 0.97), and rows of 7 groups in 32-token blocks for up to 1.07 of the time (60 rows, d = 64: 17.3 / 19.3).
-bool two_groups(const KGeom &g, const KCache &c, int rows_per_wave, int resident) {
-    const int admissible = max_candidates(g, c.valid), k = g.topk < admissible ? g.topk : admissible;
-    const int per_wave = (k * ((g.bt + 15) >> 4) + 4 / row_ways(g.bt, rows_per_wave) - 1) / (4 / row_ways(g.bt, rows_per_wave));
+// with its loads (two / four, 36 rows of 64-token blocks, 40 and 80 groups a wavefront: 36.8 / 35.2, 68.6 / 65.0 us; 110 rows of 16-token
+// blocks, 7 groups: 8.12 / 7.95).  Not where there are more workgroups than fit at four groups' registers (`resident` a unit: 1344 rows
+// of 7 groups, d = 64, 39.9 / 45.8; 672 in 32-token blocks 40.8 / 56.0), not where the last stretch of four would be half empty (10 groups
+// 9.05 / 9.81), and not for the four groups of a short row (264 rows of 4: 7.24 / 7.69).  Over 300 random geometries (in profiles/) the rule
+// is the better form at d <= 32 (two 1.009, four 1.101 of it).  At 32 < d <= 64 it is 1.004 where two alone would be 1.001: four still takes
+// rows of 128-token blocks (0.98), and rows of 7 groups in 32-token blocks for up to 1.07 of the time (60 rows, d = 64: 17.1 / 18.1).
+bool two_groups(const KGeom &g, int per_wave, int resident) {
     return per_wave <= 4 || g.q_groups * g.nb * g.heads > resident * compute_units() || (per_wave - 1) % 4 < 2;
 }
 
@@ -242,12 +243,29 @@ void launch(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_
             void *o, int64_t o_st, int64_t o_sh, float *lse, float scale, hipStream_t stream) {
     const int per_xcd = (g.q_groups * g.nb * g.heads + 7) / 8;
     constexpr int GI = sizeof(T) == 2 ? 2 : NT <= 4 ? 4 : NT <= 8 ? 2 : 1;        // groups whose operands are loaded together
-    auto call = [&](auto gi) {
-        attn_generic_kernel<T, NT, QS, gi><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(
+    const int per_wave = groups_per_wave(g, c, 16 * QS);
+    auto start = [&](auto gi, auto ahead) {
+        attn_generic_kernel<T, NT, QS, gi, ahead><<<dim3(per_xcd * 8), kThreads, 0, stream>>>(
             g, c, (const T *)q, q_st, q_sh, sel_idx, sel_cnt, (T *)o, o_st, o_sh, lse, scale * kLog2e, per_xcd);
     };
+    // Whether to request keys a stretch ahead.  It costs registers, and a row of one stretch its order of requests; it pays where a wavefront is
+    // alone with its loads, rows are long and a stretch's products long enough to cover a request.  In turn / ahead, us (groups a wavefront,
+    // 16-token blocks unless stated; all of it in profiles/): float, d = 64, 256 rows of 2 groups 6.1 / 6.6, of 6 9.7 / 9.5, of 16 22.2 / 17.8,
+    // 512 rows of 4 12.4 / 11.9, of 7 (by four) 19.3 / 21.6; d = 96, 256 rows of 4 11.6 / 10.7, 512 of them 17.9 / 19.7, but in 32-token blocks
+    // 35.2 / 32.4; d = 200 always (256 rows of 4 24.2 / 21.8); d = 32 not (256 rows of 2 4.6 / 5.2), except, for 1.06 of the time, by four in blocks
+    // of more than 16 tokens, of which two_groups() counts two workgroups a unit.  bf16: not up to d = 96 (d = 64, 256 rows of 2 4.8 / 5.0, of 4
+    // 5.9 / 6.0), beyond in blocks of more than 16 tokens (d = 128, 32-token blocks, 256 rows of 6 15.6 / 14.6).
+    const int items = g.q_groups * g.nb * g.heads, units = compute_units();
+    auto call = [&](auto gi) {
+        constexpr bool ALWAYS = NT == 16 || NT * QS * gi == 16 && NT == 2, SOMETIMES = !ALWAYS && (sizeof(T) == 4 ? NT >= 4 : NT * QS == 16);
+        if constexpr (SOMETIMES) {
+            const int most = NT * QS >= 12 || (NT == 8 && per_wave >= 6) ? items : NT * QS * gi == 8 ? 2 * units : units;
+            if (per_wave >= (sizeof(T) == 4 && NT * QS >= 12 ? 3 : 4) && items <= most) return start(gi, std::true_type{});
+        }
+        start(gi, std::bool_constant<ALWAYS>{});
+    };
     if constexpr (GI == 4 && sizeof(T) == 4)
-        if (two_groups(g, c, 16 * QS, NT == 2 ? (QS == 1 ? 4 : 2) : (QS == 1 ? 2 : 1))) return call(std::integral_constant<int, 2>{});
+        if (two_groups(g, per_wave, NT == 2 ? (QS == 1 ? 4 : 2) : (QS == 1 ? 2 : 1))) return call(std::integral_constant<int, 2>{});
     call(std::integral_constant<int, GI>{});
 }
 

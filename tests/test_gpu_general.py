@@ -21,6 +21,9 @@ pytestmark = pytest.mark.gpu
     (40, (21, 35), (4, 4), 150),         # three chunks, channels that end inside a 16- and a 32-channel piece
     (96, (21, 35), (2, 17), 70),         # 34 tokens: three groups a block, the last with two rows; stretches straddle chunks
     (200, (21, 35), (3, 5), 67),         # 15 tokens: one group, a row short
+    (64, (39, 61), (4, 4), 70),          # 640 rows, more than two a unit: keys requested in their turn, in float
+    (96, (27, 45), (4, 4), 66),          # 336 rows, more than one a unit: the same
+    (128, (21, 35), (4, 8), 66),         # 32-token blocks: a stretch ahead, in bf16 too
     (32, (39, 60), (9, 16), 70),         # 144 tokens: more queries than four wavefronts take at a time, the chunks once more for the rest
 ])
 def test_rows_of_more_than_64_blocks(dtype, d, grid, tile, topk):
