@@ -222,7 +222,9 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
             if (q_valid && g4 == 0 && ks == 0) delta[token * g.heads + head] = D;
         };
         f32x4 dq[1][NT];
-        auto add_to_dq = [&](const f32x4 (&p)[GI], const f32x4 (&t)[GI], ColGroups<T, NT, GI> &kc, const int (&valid)[GI], auto in_float) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) dq[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto add_to_dq = [&](const f32x4 (&p)[GI], const f32x4 (&t)[GI], ColGroups<T, NT, GI> &kc, const int (&valid)[GI], int pass) {
             f32x4 u[1][GI];
 #pragma unroll
             for (int i = 0; i < GI; ++i) {
@@ -230,19 +232,16 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 for (int r = 0; r < 4; ++r) u[0][i][r] = p[i][r] * ((t[i][r] - D) * scale);
                 kc.keep(i, valid[i], g4);
             }
-            kc.template mma<1, in_float>(u, dq);
+            if (pass == 0) kc.template mma<1>(u, dq);
+            else kc.template mma<1, true>(u, dq);
         };
-        // dq = what pass(in_float) adds up; once more in float products alone where the sums of pieces are doubtful
-        auto sum = [&](auto &&pass) {
+        // Sums of pieces that are doubtful are made once more in float products alone; each pass ends here, true if it was the last.
+        constexpr int PASSES = PIECES ? 2 : 1;
+        auto last_pass = [&](int pass) {
+            if (!PIECES || pass == 1 || !ColGroups<T, NT, GI>::doubtful(dq[0])) return true;      // uniform over the wavefront
 #pragma unroll
             for (int t = 0; t < NT; ++t) dq[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            pass(std::bool_constant<!PIECES>{});
-            if constexpr (PIECES) {
-                if (!ColGroups<T, NT, GI>::doubtful(dq[0])) return;      // uniform over the wavefront
-#pragma unroll
-                for (int t = 0; t < NT; ++t) dq[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-                pass(std::true_type{});
-            }
+            return false;
         };
         const int mine = total > ks ? (total - ks + splits - 1) / splits : 0;      // groups of this wavefront
         if (HELD && total <= HELD * GI * splits) {           // uniform over the workgroup
@@ -261,15 +260,18 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 if (HELD > 1) { products(keys_b, p_b, t_b); add_to_d(p_b, t_b); }
             }
             finish_d();
-            sum([&](auto in_float) {
-                if (total == 0) return;
-                if (PIECES && in_float) {                    // the first time took the large values out
-                    request_columns(0, kc_a, valid_a);
-                    if (HELD > 1) request_columns(GI, kc_b, valid_b);
+#pragma unroll
+            for (int pass = 0; pass < PASSES; ++pass) {
+                if (total > 0) {
+                    if (pass == 1) {                         // the first took the large values out
+                        request_columns(0, kc_a, valid_a);
+                        if (HELD > 1) request_columns(GI, kc_b, valid_b);
+                    }
+                    add_to_dq(p_a, t_a, kc_a, valid_a, pass);
+                    if (HELD > 1) add_to_dq(p_b, t_b, kc_b, valid_b, pass);
                 }
-                add_to_dq(p_a, t_a, kc_a, valid_a, in_float);
-                if (HELD > 1) add_to_dq(p_b, t_b, kc_b, valid_b, in_float);
-            });
+                if (last_pass(pass)) break;
+            }
         } else {
             Keys keys;
             f32x4 p[GI], t[GI];
@@ -279,16 +281,18 @@ __global__ __launch_bounds__(kThreads, (HELD ? 2 : NT <= 2 ? 4 : NT <= 4 ? 3 : N
                 add_to_d(p, t);
             }
             finish_d();
-            sum([&](auto in_float) {
+#pragma unroll
+            for (int pass = 0; pass < PASSES; ++pass) {
                 for (int i0 = 0; i0 < mine; i0 += GI) {
                     ColGroups<T, NT, GI> kc;
                     int valid[GI];
                     request(i0, keys);
                     request_columns(i0, kc, valid);
                     products(keys, p, t);
-                    add_to_dq(p, t, kc, valid, in_float);
+                    add_to_dq(p, t, kc, valid, pass);
                 }
-            });
+                if (last_pass(pass)) break;
+            }
         }
         if (splits > 1) {
             if (ks != 0)
@@ -343,7 +347,7 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
     const bool simple = NT <= 6 && whole_rows(g);            // the offsets stay in registers throughout
     const PieceRows unclipped(g, tokens_of(g, 0), 0, m, g4);
 
-    if (tid == 0) again = -1;
+    if (PIECES && tid == 0) again = -1;
     // rounds over the block's key rows: every wavefront takes part in every round (the lists are made together)
     for (int base = 0; base < kt.n_valid; base += ways * 16) {
         const int k0 = base + kw * 16;
@@ -355,13 +359,17 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
         kf.clear_beyond(g.d, g4);
         vf.clear_beyond(g.d, g4);
         f32x4 dk[1][NT], dv[1][NT];
-        bool sum_k = true, sum_v = true;                     // uniform over the wavefront; false for a sum that a second walk leaves alone
-        auto walk = [&](auto in_float) {
-            constexpr bool SECOND = PIECES && in_float;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                if (!SECOND || sum_k) dk[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (!SECOND || sum_v) dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) dk[0][t] = dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bool again_k = true, again_v = true;                 // uniform over the wavefront
+#pragma unroll
+        for (int pass = 0; pass < (PIECES ? 2 : 1); ++pass) {      // the second in float products alone, for sums of pieces that are doubtful
+            if (pass == 1) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    if (again_k) dk[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (again_v) dv[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
             }
             for (int qb0 = 0; qb0 < n_qb; qb0 += kListed) {
                 // which query blocks kept this key block?  (ascending id lists)
@@ -482,21 +490,22 @@ __global__ __launch_bounds__(kThreads, WAVES) void bwd_dkv_kernel(
                     if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(gc, d_o, o_st); }
 #pragma unroll
                     for (int i = 0; i < GI; ++i) gc.keep(i, valid[i], g4);
-                    if (!SECOND || sum_v) gc.template mma<1, in_float>(p, dv);
+                    if (pass == 0) gc.template mma<1>(p, dv);
+                    else if (again_v) gc.template mma<1, true>(p, dv);
                     if (!COLUMNS) { __builtin_amdgcn_sched_barrier(0); request_columns(qc, q, q_st); }
 #pragma unroll
                     for (int i = 0; i < GI; ++i) qc.keep(i, valid[i], g4);
-                    if (!SECOND || sum_k) qc.template mma<1, in_float>(u, dk);
+                    if (pass == 0) qc.template mma<1>(u, dk);
+                    else if (again_k) qc.template mma<1, true>(u, dk);
                 }
             }
-        };
-        walk(std::bool_constant<!PIECES>{});
-        if constexpr (PIECES) {                              // once more in float products alone where a wavefront's sums of pieces are doubtful
-            sum_k = Cols::doubtful(dk[0]);
-            sum_v = Cols::doubtful(dv[0]);
-            if (sum_k || sum_v) again = base;
-            __syncthreads();
-            if (__builtin_amdgcn_readfirstlane(again) == base) walk(std::true_type{});       // set anew only behind the next barriers
+            if (PIECES && pass == 0) {
+                again_k = Cols::doubtful(dk[0]);
+                again_v = Cols::doubtful(dv[0]);
+                if (again_k || again_v) again = base;
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(again) != base) break;      // set anew only behind the next barriers
+            }
         }
         if (splits > 1) {                                    // uniform over the workgroup
 #pragma unroll

@@ -151,8 +151,8 @@ template <int NT, int GI> struct ColGroups<float, NT, GI> {
 // 2^16 on, because the last pieces of weights below 2^-110 fall among bf16's subnormals, which count for nothing: 2^-126 of a value is lost.
 // Weights that may be anything: an infinite one leaves inf - inf behind its first piece, one close to the largest float rounds to an infinity,
 // and tiny ones may all lose their last pieces.  The sums tell (doubtful()): all channels of a column are infinite or NaN, or all are below
-// 2^-76, where the 2^13 terms' losses are no longer below 2^-20 of them.  In the backward that costs 0 to 2 % (8 heads, d = 64, 32-token blocks, k = 16 on a
-// 24 x 44 grid 108.3 / 109.9 us); looking at the weights instead, group by group, or one loop for both kinds of product, 1 to 8 %.
+// 2^-76, where the 2^13 terms' losses are no longer below 2^-20 of them.  In the backward that costs 0 to 3 % (8 heads, d = 64, 32-token blocks, k = 16 on a
+// 24 x 44 grid 107.8 / 110.2 us); looking at the weights instead, group by group, or one loop for both kinds of product, 1 to 8 %.
 template <int NT, int GI> struct ColGroups<__bf16, NT, GI> {
     static_assert(GI % 2 == 0, "groups go in pairs");
     uint32_t v[GI][4][NT / 2];
