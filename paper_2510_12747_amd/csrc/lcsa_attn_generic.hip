@@ -255,13 +255,12 @@ void launch(const KGeom &g, const KCache &c, const void *q, int64_t q_st, int64_
     // 35.2 / 32.4; d = 200 always (256 rows of 4 24.2 / 21.8); d = 32 not (256 rows of 2 4.6 / 5.2), except, for 1.06 of the time, by four in blocks
     // of more than 16 tokens, of which two_groups() counts two workgroups a unit.  bf16: not up to d = 96 (d = 64, 256 rows of 2 4.8 / 5.0, of 4
     // 5.9 / 6.0), beyond in blocks of more than 16 tokens (d = 128, 32-token blocks, 256 rows of 6 15.6 / 14.6).
-    const int items = g.q_groups * g.nb * g.heads, units = compute_units();
     auto call = [&](auto gi) {
         constexpr bool ALWAYS = NT == 16 || NT * QS * gi == 16 && NT == 2, SOMETIMES = !ALWAYS && (sizeof(T) == 4 ? NT >= 4 : NT * QS == 16);
-        if constexpr (SOMETIMES) {
-            const int most = NT * QS >= 12 || (NT == 8 && per_wave >= 6) ? items : NT * QS * gi == 8 ? 2 * units : units;
-            if (per_wave >= (sizeof(T) == 4 && NT * QS >= 12 ? 3 : 4) && items <= most) return start(gi, std::true_type{});
-        }
+        if constexpr (SOMETIMES)
+            if (per_wave >= (sizeof(T) == 4 && NT * QS >= 12 ? 3 : 4) &&
+                (NT * QS >= 12 || (NT == 8 && per_wave >= 6) || g.q_groups * g.nb * g.heads <= (NT * QS * gi == 8 ? 2 : 1) * compute_units()))
+                return start(gi, std::true_type{});
         start(gi, std::bool_constant<ALWAYS>{});
     };
     if constexpr (GI == 4 && sizeof(T) == 4)

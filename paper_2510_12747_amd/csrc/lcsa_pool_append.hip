@@ -409,7 +409,8 @@ hipError_t launch_append(const KGeom &g, const KCache &c, const void *k, const v
         constexpr std::integral_constant<int, 4> four{};
         constexpr std::integral_constant<int, 1> one{};
         constexpr std::integral_constant<int, 8> eight{};
-        const bool share = !fresh && !c.order && append_shares(items, compute_units(), (int64_t)g.bt * g.d * (g.bf16 ? 2 : 4));
+        // up to 24 tiles never share, whatever part of the device this is (32 units at least): asking for its units takes 0.2 us
+        const bool share = !fresh && !c.order && items > 24 && append_shares(items, compute_units(), (int64_t)g.bt * g.d * (g.bf16 ? 2 : 4));
         if (g.bf16) share ? generic(eight, four) : generic(eight, one);
         else share ? generic(four, four) : generic(four, one);
     }
