@@ -176,8 +176,9 @@ def _bind(L) -> None:
     global _marshal
     try:
         from . import _marshal as native
-        if native.torch_version != torch.__version__.split("+")[0]:
-            raise ImportError(f"built for torch {native.torch_version}, this is {torch.__version__}")
+        built_for = getattr(native, "torch_version", "an unknown version")
+        if built_for != torch.__version__.split("+")[0]:
+            raise ImportError(f"built for torch {built_for}, this is {torch.__version__}")
     except ImportError as e:
         warnings.warn(f"_marshal.so not loaded ({e}): a layer's calls take some 9 us each on the host instead of 5; build it with "
                       "`python -m paper_2510_12747_amd.build`", RuntimeWarning, stacklevel=3)

@@ -98,7 +98,7 @@ def arguments():
     return (g._plan(), 5, x, x, 2), (g._plan(), x, 5, True), (g._plan(), x, 5, i, n, None, None, 0.0)
 
 
-@pytest.mark.parametrize("how", ["absent", "unloadable", "another torch"])
+@pytest.mark.parametrize("how", ["absent", "unloadable", "another torch", "of before it told"])
 def test_the_library_loads_without_it(monkeypatch, tmp_path, how):
     """Callers that need none of its functions, and those that do: the Python functions are all there."""
     B.lib()
@@ -106,6 +106,8 @@ def test_the_library_loads_without_it(monkeypatch, tmp_path, how):
     monkeypatch.setattr(B, "_marshal", B._marshal)
     if how == "another torch":
         monkeypatch.setattr(B._marshal, "torch_version", "1.0.0")
+    elif how == "of before it told":
+        monkeypatch.delattr(B._marshal, "torch_version")
     else:
         if how == "unloadable":
             (tmp_path / "_marshal.so").write_bytes(b"no object file")
